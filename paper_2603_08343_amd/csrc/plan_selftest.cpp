@@ -23,8 +23,7 @@
 using namespace wht;
 
 typedef unsigned (*PhysFn)(unsigned);
-static unsigned phys_pad2(unsigned i) { return lds_phys_pad(i, 2); }
-static unsigned phys_pad3(unsigned i) { return lds_phys_pad(i, 3); }
+static unsigned phys_plain(unsigned i) { return lds_phys_plain(i); }
 static unsigned phys_rot(unsigned i) { return lds_phys_rot(i); }
 
 static unsigned thread_elem(const PhaseDesc& p, int n, int e, unsigned t) {
@@ -85,6 +84,31 @@ static bool check(const char* kind, const PlanDesc& pl, PhysFn phys, unsigned wo
         for (int p = 0; p < pl.nphase; ++p)
             for (int k = 0; k < 6; ++k) if (pl.ph[p].tb[k] != 3 + k) ok = false;
     }
+    if (pl.lane_bits) {
+        // wave schedule: lane positions 0..5 carry element bits v.. in the first layout, positions 0..3
+        // in every layout; position k's DPP partner differs in element bit v+k and in no other
+        const int L = n - e < 6 ? n - e : 6;
+        for (int k = 0; k < L; ++k) if (pl.ph[0].tb[k] != v + k) ok = false;
+        for (int p = 0; p < pl.nphase; ++p)
+            for (int k = 0; k < L && k < 4; ++k) if (pl.ph[p].tb[k] != v + k) ok = false;
+        const unsigned partner[4] = {1, 2, 7, 8};
+        for (int k = 0; k < L && k < 4; ++k) {
+            if (!((pl.lane_bits >> (v + k)) & 1u)) ok = false;
+            for (unsigned l = 0; l < 64; ++l)
+                if ((wave_lane_to_bits(l, L) ^ wave_lane_to_bits(l ^ partner[k], L)) != (1u << k)) ok = false;
+        }
+        // the second layout is the first with lane positions 4 (5) and register bits e-1 (e-2) exchanged;
+        // the third with wave positions and register bits v, v+1 exchanged: nothing else moves
+        for (int p = 1; p < pl.nphase; ++p) {
+            PhaseDesc x = pl.ph[p - 1];
+            if (p == 1)
+                for (int k = 4; k < L; ++k) { const int b = x.tb[k]; x.tb[k] = x.rb[e - 1 - (k - 4)]; x.rb[e - 1 - (k - 4)] = b; }
+            else
+                for (int k = 0; k < n - e - 6; ++k) { const int b = x.tb[6 + k]; x.tb[6 + k] = x.rb[v + k]; x.rb[v + k] = b; }
+            for (int q = 0; q < e; ++q) if (x.rb[q] != pl.ph[p].rb[q]) ok = false;
+            for (int k = 0; k < n - e; ++k) if (x.tb[k] != pl.ph[p].tb[k]) ok = false;
+        }
+    }
     // emulate on the CPU for small d
     if (n <= 12) {
         for (int reverse = 0; reverse < 2; ++reverse) {
@@ -100,7 +124,7 @@ static bool check(const char* kind, const PlanDesc& pl, PhysFn phys, unsigned wo
                 }
             }
             // the matrix-core rounds come first going forward (on the data as loaded) ...
-            if (!reverse) butterfly_bits(x, pl.mfma_bits);
+            if (!reverse) butterfly_bits(x, pl.mfma_bits | pl.lane_bits);
             std::vector<std::vector<double>> reg(T, std::vector<double>(E));
             for (int s = 0; s < pl.nphase; ++s) {
                 const int p = reverse ? pl.nphase - 1 - s : s;
@@ -130,7 +154,7 @@ static bool check(const char* kind, const PlanDesc& pl, PhysFn phys, unsigned wo
             std::vector<double> got(D);
             for (unsigned j = 0; j < D; ++j) got[j] = lds[phys(j)];
             // ... and last in reverse (on the registers of the first layout)
-            if (reverse) butterfly_bits(got, pl.mfma_bits);
+            if (reverse) butterfly_bits(got, pl.mfma_bits | pl.lane_bits);
             double worst = 0, big = 0;
             for (unsigned j = 0; j < D; ++j) {
                 worst = std::fmax(worst, std::fabs(got[j] - want[j]));
@@ -224,8 +248,8 @@ int main(int argc, char** argv) {
     for (int n = 10; n <= 14; ++n) ok = check_twelve(n) && ok;
     for (int v : {2, 3})
         for (int n = 5; n <= (v == 2 ? 13 : 14); ++n) {
-            const PlanDesc pl = make_plan(n, log_e_for(n, v), v);
-            ok = check("butterfly", pl, v == 2 ? phys_pad2 : phys_pad3, lds_words_pad(1u << n, v), verbose) && ok;
+            const PlanDesc pl = make_wave_plan(n, wave_log_e(n, v), v);
+            ok = check("wave", pl, phys_plain, 1u << n, verbose) && ok;
         }
     for (int n = 10; n <= 14; ++n)
         for (int backward = 0; backward < 2; ++backward) {

@@ -41,15 +41,19 @@ static int forward_cluster(int64_t N, int grid, bool resid) {
 
 // Few tokens (decoding, short prefills): one token group per workgroup and no token loop.  Measured
 // under HIP-graph replay, bfloat16: 2.1 against 3.2 us per call for one token of 4096 elements.  The
-// persistent kernel takes over where the two break even: 2^22 elements per call at d >= 4096 (and for
-// the butterfly schedule), 2^24 for the matrix-core schedule at d = 1024 and 2048 (16384 tokens of
-// 1024 elements: 12.0 against 13.3 us), 2^21 for rows of 12 * 2^m elements.  Both kernels do the same
-// arithmetic on a token in the same order, so the switch is invisible in y (the norm statistic is
-// summed in the order of the launch shape: its last bits may differ between the two).
+// persistent kernel takes over where the two break even:
+//   matrix-core schedule: 2^24 elements per call at d = 1024 and 2048 (16384 tokens of 1024 elements:
+//     12.0 against 13.3 us), 2^22 above, 2^21 for rows of 12 * 2^m elements;
+//   wave schedule: bfloat16 2^24 (65536 tokens of 256 elements: 12.7 against 13.3 us; twice that: 26.9
+//     against 23.9), float32 2^23 up to d = 2048 (8192 tokens of 1024: 11.7 against 12.8; twice that:
+//     25.3 against 23.3) and 2^21 above (1024 tokens of 4096: 8.4 against 7.6).
+// Both kernels do the same arithmetic on a token in the same order, so the switch is invisible in y
+// (the norm statistic is summed in the order of the launch shape: its last bits may differ).
 template <class C>
 static bool few_tokens(int64_t N) {
-    const int64_t limit = C::kTwelve ? (1 << 21) : ((C::kMfma && C::n <= 11) ? (1 << 24) : (1 << 22));
-    return N * C::kRow <= limit;
+    constexpr int limit = C::kTwelve ? 21 : C::kMfma ? (C::n <= 11 ? 24 : 22)
+                                          : C::v == 3 ? 24 : (C::n <= 11 ? 23 : 21);
+    return N * C::kRow <= (int64_t(1) << limit);
 }
 
 template <class C>
@@ -100,7 +104,18 @@ static int launch_backward(const void* dy, const void* x, const float* alpha, vo
     const bool grads = dalpha != nullptr;
     const int grid = grid_for<C>(N, grads);      // dx alone streams like a forward pass
 
-    if (grads && dx) {
+    if constexpr (C::kWave) {
+        const T *dyp = static_cast<const T*>(dy), *xp = static_cast<const T*>(x);
+        if (grads && dx)
+            hipLaunchKernelGGL((backward_wave_kernel<C, true, true>), dim3(grid), dim3(C::BT), 0, stream, dyp, xp, alpha,
+                               static_cast<T*>(dx), static_cast<float*>(workspace), N);
+        else if (grads)
+            hipLaunchKernelGGL((backward_wave_kernel<C, true, false>), dim3(grid), dim3(C::BT), 0, stream, dyp, xp, alpha,
+                               static_cast<T*>(nullptr), static_cast<float*>(workspace), N);
+        else
+            hipLaunchKernelGGL((backward_wave_kernel<C, false, true>), dim3(grid), dim3(C::BT), 0, stream, dyp,
+                               static_cast<const T*>(nullptr), alpha, static_cast<T*>(dx), static_cast<float*>(nullptr), N);
+    } else if (grads && dx) {
         if constexpr (C::kBwdTeams)
             hipLaunchKernelGGL((backward_teams_kernel<C>), dim3(grid), dim3(3 * C::BT), 0, stream,
                                static_cast<const T*>(dy), static_cast<const T*>(x), alpha, static_cast<T*>(dx),
@@ -156,8 +171,8 @@ static int run(Op op, Args& a) {
 }
 
 // Schedule choice: bfloat16 tokens of 1024 elements or more take the matrix-core schedule, the
-// rest the butterfly schedule.  WHT_AFFINE_SCHEDULE=butterfly in the environment (read once per
-// process; the library's only environment variable) forces the butterfly schedule for those too:
+// rest the wave schedule, in which every stage is additions.  WHT_AFFINE_SCHEDULE=butterfly in the environment (read once per
+// process; the library's only environment variable) forces the wave schedule for those too:
 // it exists so that both schedules of one build can be tested and profiled against each other.
 static bool use_mfma() {
     static const bool on = [] {
@@ -174,7 +189,7 @@ static int run_d(Op op, Args& a) {
             return run<MfmaCfg<LOGD, mfma_log_tiles(LOGD, false)>, MfmaCfg<LOGD, mfma_log_tiles(LOGD, true)>,
                        MfmaCfg<LOGD, mfma_log_tiles_few(LOGD)>>(op, a);
     }
-    return run<Cfg<LOGD, log_e_for(LOGD, Io::kLogVec), Io>>(op, a);
+    return run<WaveCfg<LOGD, wave_log_e(LOGD, Io::kLogVec), Io>>(op, a);
 }
 
 // The debug build that poisons LDS after every read (WHT_POISON_LDS, libwht_affine_poison.so, loaded

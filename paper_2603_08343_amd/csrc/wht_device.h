@@ -2,8 +2,9 @@
 // Eq. 1) for gfx950: the per-token transform H_raw x (Fig. 2's butterfly stages, scheduled by
 // wht_plan.h), the fused affine epilogue, the backward pass with z recomputed, and the fixed-order
 // reduction of dalpha / dbeta.  1/sqrt(d) is folded into alpha.  Two schedules share the kernels:
-//   - butterfly schedule (float32 I/O, and bfloat16 below d = 1024): every stage is adds/subtracts
-//     on register pairs; the token is re-dealt through LDS between groups of stages;
+//   - wave schedule (float32 I/O, and bfloat16 below d = 1024): every stage is additions, in registers
+//     or between the lanes of one wave; float32 tokens above 2048 elements take two or four waves and
+//     one LDS exchange;
 //   - matrix-core schedule (bfloat16 I/O, d >= 1024): ten of the log2(d) stages run as two rounds
 //     of 32x32 +-1 products on the MFMA unit (exact products, float32 accumulation), the rest as
 //     register butterflies plus one LDS exchange across the waves of a token.
@@ -86,41 +87,6 @@ struct IoBF16 {
 // ------------------------------------------------------------------------------------------------
 // per-(d, dtype) configuration
 
-// Butterfly schedule.
-template <int LOGD, int LOGE, class Io>
-struct Cfg {
-    using io = Io;
-    static constexpr bool kMfma = false;
-    static constexpr int n = LOGD, e = LOGE, v = Io::kLogVec;
-    static_assert(v <= e && e <= n && e <= kMaxRegBits, "bad tile");
-    static constexpr PlanDesc plan = make_plan(n, e, v);
-    static_assert(plan_is_complete(plan), "every butterfly stage must run exactly once");
-    static constexpr int P = plan.nphase;
-    static constexpr int D = 1 << n;
-    static constexpr int E = 1 << e;            // values per thread
-    static constexpr int V = 1 << v;            // elements per 16-byte vector
-    static constexpr int NV = E / V;            // 16-byte vectors per thread
-    static constexpr int TPT = 1 << (n - e);    // threads per token
-    static constexpr int BT = TPT > 256 ? TPT : 256;   // threads per workgroup
-    static constexpr int G = BT / TPT;          // tokens per workgroup pass
-    static constexpr bool kTwelve = false;
-    // persistent-grid size in workgroups per CU (measured optima, N = 16384..32768 tokens)
-    static constexpr int kFwdGroupsPerCU = v == 2 ? (n >= 13 ? 8 : 4) : (n <= 9 ? 2 : 8);
-    static constexpr int kBwdGroupsPerCU = v == 2 ? 1 : 2;
-    static constexpr int kFwdCluster = 0, kFwdClusterResid = 0;     // see MfmaCfg
-    static constexpr bool kBwdTeams = false;    // see MfmaCfg
-    static constexpr int kRow = D;              // elements per row in memory
-    static constexpr unsigned real(unsigned i) { return i; }
-    static constexpr bool valid(unsigned) { return true; }
-    static constexpr unsigned phys(unsigned i) { return lds_phys_pad(i, v); }
-    static constexpr unsigned kTokenWords = lds_words_pad(D, v);
-    static constexpr unsigned kExchangeBytes = (P > 1 || G > 1) ? G * kTokenWords * 4u : 16u;
-    static constexpr unsigned kStageBytes = BT * NV * 16u;          // one tensor's token group, as stored
-    static constexpr unsigned kLdsBytes = kExchangeBytes + kStageBytes;              // forward
-    static constexpr unsigned kLdsBytesBackward = kExchangeBytes + 2u * kStageBytes; // x and dy
-    static_assert(kLdsBytesBackward <= 160u * 1024u, "token group does not fit LDS");
-};
-
 // Matrix-core schedule (bfloat16 I/O, d >= 1024): 2^LOGT MFMA tiles of 1024 elements per wave.
 //
 // TWELVE: the row in memory has 12 * 2^m elements (m = LOGD - 4) and the schedule runs on 2^LOGD
@@ -135,7 +101,7 @@ struct Cfg {
 template <int LOGD, int LOGT, bool TWELVE = false>
 struct MfmaCfg {
     using io = IoBF16;
-    static constexpr bool kMfma = true;
+    static constexpr bool kMfma = true, kWave = false;
     static constexpr bool kTwelve = TWELVE;
     static constexpr int n = LOGD, t = LOGT, e = 4 + LOGT, v = 3;
     static constexpr int w = n - 10 - t;        // log2(waves per token)
@@ -186,15 +152,77 @@ struct MfmaCfg {
     static_assert(kLdsBytesBackward <= 160u * 1024u, "token group does not fit LDS");
 };
 
+// Wave schedule: a token inside one wave, every stage in registers or between lanes (or on two or
+// four whole waves, with one LDS exchange between them).
+template <int LOGD, int LOGE, class Io>
+struct WaveCfg {
+    using io = Io;
+    static constexpr bool kMfma = false, kWave = true, kTwelve = false, kBwdTeams = false;
+    static constexpr int n = LOGD, e = LOGE, v = Io::kLogVec;
+    static constexpr int L = n - e < 6 ? n - e : 6, w = n - e - L;    // log2 lanes of a wave, waves per token
+    static_assert(wave_fits(n, e, v), "bad tile");
+    static constexpr PlanDesc plan = make_wave_plan(n, e, v);
+    static_assert(plan_is_complete(plan), "every butterfly stage must run exactly once");
+    static constexpr int P = plan.nphase;
+    static constexpr int D = 1 << n;
+    static constexpr int E = 1 << e;
+    static constexpr int V = 1 << v;
+    static constexpr int NV = E / V;
+    static constexpr int TPT = 1 << (n - e);    // threads per token
+    static constexpr int BT = w > 0 ? TPT : 256;        // w = 0: four waves that share nothing but the parameters
+    static constexpr int G = BT / TPT;
+    // persistent-grid size in workgroups per CU (measured optima at 2^24 ... 2^26 elements): rows so
+    // short that a workgroup pass is a few KiB want more of them in flight
+    static constexpr int kFwdGroupsPerCU = v == 3 || n <= 6 ? 4 : 2;
+    static constexpr int kBwdGroupsPerCU = n <= 6 ? 4 : (w == 2 || (v == 2 && n == 11) ? 1 : 2);
+    static constexpr int kBwdWavesPerSimd = w > 0 ? 1 : (e >= 5 ? 2 : 3);   // register budget of the backward
+    // windows of the forward walk (see MfmaCfg); mean / worst over twelve distances y - x, 256 MiB each
+    // way: d = 4096 92.3 / 107.0 us with one window, 90.6 / 91.4 with four; d = 1024 89.4 / 104.6 and
+    // 88.7 / 89.6; d = 8192 92.8 / 94.0 and 92.0 / 92.7 with two; d = 2048 92.2 / 93.6 and 91.8 / 92.6
+    static constexpr int kFwdCluster = v == 2 && n >= 10 ? (n == 10 || n == 12 ? 128 : 256) : 0;
+    static constexpr int kFwdClusterResid = v == 2 && n >= 10 ? 256 : 0;
+    static constexpr int kRow = D;
+    static constexpr unsigned real(unsigned i) { return i; }
+    static constexpr bool valid(unsigned) { return true; }
+    static constexpr unsigned phys(unsigned i) { return lds_phys_plain(i); }
+    static constexpr unsigned kTokenWords = D;
+    static constexpr unsigned kExchangeBytes = w > 0 ? G * D * 4u : 16u;
+    static constexpr unsigned kStageBytes = BT * NV * 16u;          // one tensor's token group, as stored
+    static_assert(G == 1 || 2u * kStageBytes >= G * kTokenWords * 4u, "the token sums reuse the stage buffers");
+};
+
+// Workgroup barrier for the LDS exchange.  __syncthreads() carries a release/acquire fence that
+// makes the wave wait for *all* its outstanding memory operations -- including the prefetches in
+// flight and the stores of the previous token, which have nothing to do with the exchange.  The
+// exchange only needs this wave's LDS writes to have completed (lgkmcnt) before the barrier.
+__device__ __forceinline__ void exchange_barrier() {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
 // Element offset of thread t (within its token) in phase PH.
 template <class C, int PH>
 __device__ __forceinline__ unsigned thread_elem_offset(unsigned t) {
+    if constexpr (C::kWave) t = wave_lane_to_bits(t, C::L);
     unsigned off = 0;
     static_for<0, C::n - C::e>([&](auto k) {
         constexpr int K = decltype(k)::value;
         off |= ((t >> K) & 1u) << C::plan.ph[PH].tb[K];
     });
     return off;
+}
+
+// First stage of the reverse order -- element bit and the register-index bit that carries it.
+template <class C>
+constexpr int wave_first_back_bit() {
+    return C::w > 0 ? C::v + 6 : C::L == 6 ? C::v + 5 : C::L == 5 ? C::v + 4 : 0;
+}
+template <class C>
+constexpr int wave_first_back_reg() {
+    int q = 0;
+    while (C::plan.ph[C::P - 1].rb[q] != wave_first_back_bit<C>()) ++q;
+    return q;
 }
 
 // Butterfly stages of phase PH, all in registers: (a, b) -> (a + b, a - b) on register pairs.
@@ -275,6 +303,69 @@ __device__ __forceinline__ void lds_get(float (&r)[C::E], const float* tok) {
     }
 }
 
+__device__ __forceinline__ unsigned lds_byte_address(const void* p) {
+    return (unsigned)(size_t)(const __attribute__((address_space(3))) unsigned char*)p;
+}
+
+// The same in assembly, for kernels in which the compiler would wait for every LDS-direct load in
+// flight -- the prefetches of the next token group -- before an access to the exchange region that
+// has nothing to do with them.  lds_get_raw waits for its own reads in the block that issues them.
+template <unsigned OFF>
+__device__ __forceinline__ void lds_write16(unsigned addr, const u32x4& q) {
+    static_assert(OFF < 65536u, "offset field of the instruction");
+    asm volatile("ds_write_b128 %0, %1 offset:%2" : : "v"(addr), "v"(q), "n"(OFF) : "memory");
+}
+
+template <class C, int PH>
+__device__ __forceinline__ void lds_put_raw(const float (&r)[C::E], const float* tok) {
+    static_assert(phase_is_vec4<C, PH>(), "16 bytes per access");
+    const unsigned addr = lds_byte_address(tok);
+    static_for<0, C::E / 4>([&](auto i) {
+        constexpr int I = decltype(i)::value * 4;
+        constexpr unsigned off = C::phys(reg_elem_offset(C::plan.ph[PH], C::e, I)) * 4u;
+        const u32x4 q = {__float_as_uint(r[I]), __float_as_uint(r[I + 1]), __float_as_uint(r[I + 2]), __float_as_uint(r[I + 3])};
+        lds_write16<off>(addr, q);
+    });
+}
+
+template <class C, int PH>
+__device__ __forceinline__ void lds_get_raw(float (&r)[C::E], const float* tok) {
+    static_assert(phase_is_vec4<C, PH>() && C::E % 16 == 0, "16 bytes per access, four accesses per block");
+    const unsigned addr = lds_byte_address(tok);
+    static_for<0, C::E / (C::E >= 32 ? 32 : 16)>([&](auto b) {
+        constexpr int N4 = C::E >= 32 ? 8 : 4, B = decltype(b)::value * N4 * 4;
+        const unsigned at = addr;
+        u32x4 q[N4];
+#define WHT_OFF(K) "n"(C::phys(reg_elem_offset(C::plan.ph[PH], C::e, B + 4 * (K))) * 4u)
+        if constexpr (N4 == 8)
+            asm volatile("ds_read_b128 %0, %8 offset:%9\n\tds_read_b128 %1, %8 offset:%10\n\t"
+                         "ds_read_b128 %2, %8 offset:%11\n\tds_read_b128 %3, %8 offset:%12\n\t"
+                         "ds_read_b128 %4, %8 offset:%13\n\tds_read_b128 %5, %8 offset:%14\n\t"
+                         "ds_read_b128 %6, %8 offset:%15\n\tds_read_b128 %7, %8 offset:%16\n\ts_waitcnt lgkmcnt(0)"
+                         : "=&v"(q[0]), "=&v"(q[1]), "=&v"(q[2]), "=&v"(q[3]), "=&v"(q[4]), "=&v"(q[5]), "=&v"(q[6]), "=&v"(q[7])
+                         : "v"(at), WHT_OFF(0), WHT_OFF(1), WHT_OFF(2), WHT_OFF(3), WHT_OFF(4), WHT_OFF(5), WHT_OFF(6), WHT_OFF(7)
+                         : "memory");
+        else
+            asm volatile("ds_read_b128 %0, %4 offset:%5\n\tds_read_b128 %1, %4 offset:%6\n\t"
+                         "ds_read_b128 %2, %4 offset:%7\n\tds_read_b128 %3, %4 offset:%8\n\ts_waitcnt lgkmcnt(0)"
+                         : "=&v"(q[0]), "=&v"(q[1]), "=&v"(q[2]), "=&v"(q[3])
+                         : "v"(at), WHT_OFF(0), WHT_OFF(1), WHT_OFF(2), WHT_OFF(3) : "memory");
+#undef WHT_OFF
+#pragma unroll
+        for (int k = 0; k < N4; ++k)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) r[B + 4 * k + j] = __uint_as_float(q[k][j]);
+    });
+    if constexpr (kPoisonLds) {
+        const u32x4 nan = {0x7fc00000u, 0x7fc00000u, 0x7fc00000u, 0x7fc00000u};
+        static_for<0, C::E / 4>([&](auto i) {
+            constexpr unsigned off = C::phys(reg_elem_offset(C::plan.ph[PH], C::e, decltype(i)::value * 4)) * 4u;
+            lds_write16<off>(addr, nan);
+        });
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    }
+}
+
 // Per-thread constants: LDS word offset of the thread in every phase, element offset in the first
 // and last phase (the global-memory layouts).
 template <class C>
@@ -282,6 +373,8 @@ struct ThreadMap {
     unsigned lds_off[kMaxPhases];
     unsigned first_elem, last_elem;     // offset within the row in memory
     bool first_ok, last_ok;             // false for a thread whose slots are padding (12 * 2^m rows)
+    float lane_sign[4];                 // wave schedule: -1 in the lanes of the lower butterfly output
+    float sign;                         // their product (see lane_stage)
     __device__ __forceinline__ void init(unsigned t, unsigned slot) {
         static_for<0, C::P>([&](auto p) {
             constexpr int PH = decltype(p)::value;
@@ -292,43 +385,166 @@ struct ThreadMap {
         last_elem = C::real(l);
         first_ok = C::valid(f);
         last_ok = C::valid(l);
+        sign = 1.0f;
+        if constexpr (C::kWave) {
+            const unsigned c = wave_lane_to_bits(t, C::L);
+            static_for<0, 4>([&](auto k) {
+                constexpr int K = decltype(k)::value;
+                lane_sign[K] = (K < C::L && ((c >> K) & 1u)) ? -1.0f : 1.0f;
+                sign *= lane_sign[K];
+            });
+        }
     }
 };
+
+// One butterfly stage between lanes: position K of the lane index, the partner's value read through a
+// DPP operand, one fused multiply-add per value:
+//     v <- v + s * partner,   s = +1 in the upper lane of the pair, -1 in the lower.
+// The lower lane so gets -(upper - lower), the negative of the butterfly's output.  Such signs pass
+// unchanged through every other stage (both lanes of any other pair carry the same one), so after all
+// lane stages a lane holds ThreadMap::sign times the transform, and the sign is folded into alpha.
+// INPUT_SIGN is the transposed form, v <- v - s * partner: it takes input that carries the sign and
+// gives the transform itself.  Products with +-1 are exact: the rounding is that of a plain addition.
+// Written in assembly: the compiler keeps the DPP read as a move of its own in front of the multiply-
+// add (twice the instructions).  It does not see the wait states around it either: two before a DPP
+// operand that the preceding instruction wrote, hence the s_nop in front, and the one behind for a
+// lane swap that may follow.
+#define WHT_FMAC_DPP(R, CTRL) "v_fmac_f32_dpp %" #R ", %" #R ", %4 " CTRL " row_mask:0xf bank_mask:0xf\n\t"
+#define WHT_FMAC_DPP4(CTRL)                                                                             \
+    asm("s_nop 1\n\t" WHT_FMAC_DPP(0, CTRL) WHT_FMAC_DPP(1, CTRL) WHT_FMAC_DPP(2, CTRL)                 \
+        WHT_FMAC_DPP(3, CTRL) "s_nop 1"                                                                \
+        : "+v"(r[i]), "+v"(r[i + 1]), "+v"(r[i + 2]), "+v"(r[i + 3]) : "v"(s))
+template <class C, int K, bool INPUT_SIGN>
+__device__ __forceinline__ void lane_stage(float (&r)[C::E], const ThreadMap<C>& tm) {
+    const float s = INPUT_SIGN ? -tm.lane_sign[K] : tm.lane_sign[K];
+#pragma unroll
+    for (int i = 0; i < C::E; i += 4) {
+        if constexpr (K == 0)      WHT_FMAC_DPP4("quad_perm:[1,0,3,2]");     // l ^ 1
+        else if constexpr (K == 1) WHT_FMAC_DPP4("quad_perm:[2,3,0,1]");     // l ^ 2
+        else if constexpr (K == 2) WHT_FMAC_DPP4("row_half_mirror");         // l ^ 7
+        else                       WHT_FMAC_DPP4("row_ror:8");               // l ^ 8
+    }
+}
+#undef WHT_FMAC_DPP4
+#undef WHT_FMAC_DPP
+
+// Exchange register bit Q with lane position 4 (ROW16) or 5.
+template <class C, int Q, bool ROW16>
+__device__ __forceinline__ void lane_swap(float (&r)[C::E]) {
+    static_for<0, C::E>([&](auto i) {
+        constexpr int I = decltype(i)::value;
+        if constexpr (!((I >> Q) & 1)) {
+            constexpr int J = I | (1 << Q);
+            const auto sw = [&] {
+                if constexpr (ROW16)
+                    return __builtin_amdgcn_permlane16_swap(__float_as_uint(r[I]), __float_as_uint(r[J]), false, false);
+                else
+                    return __builtin_amdgcn_permlane32_swap(__float_as_uint(r[I]), __float_as_uint(r[J]), false, false);
+            }();
+            r[I] = __uint_as_float(sw[0]);
+            r[J] = __uint_as_float(sw[1]);
+        }
+    });
+}
+
+// The stage on element bit BIT while the token is in the layout of phase PH.
+template <class C, int PH, int BIT, bool INPUT_SIGN>
+__device__ __forceinline__ void wave_stage(float (&r)[C::E], const ThreadMap<C>& tm) {
+    if constexpr ((C::plan.lane_bits >> BIT) & 1u) {
+        lane_stage<C, BIT - C::v, INPUT_SIGN>(r, tm);
+    } else {
+        static_for<0, C::e>([&](auto q) {
+            constexpr int Q = decltype(q)::value;
+            if constexpr (C::plan.ph[PH].rb[Q] == BIT)
+                static_for<0, C::E>([&](auto i) {
+                    constexpr int I = decltype(i)::value;
+                    if constexpr (!((I >> Q) & 1)) {
+                        const float a = r[I], b = r[I | (1 << Q)];
+                        r[I] = a + b;
+                        r[I | (1 << Q)] = a - b;
+                    }
+                });
+        });
+    }
+}
+
+// H_raw on the values of a token.  Forward order enters in the first layout and leaves in the last,
+// with the lanes' signs on the output; reverse order enters in the last layout with the signs on the
+// input and leaves in the first.  `lds` is the region of the exchange between waves (unused without
+// one); it is read after the barrier inside, so a put by another thread has to wait for a further one.
+//   SKIP: element bit whose stage the caller has run already (-1: none).
+template <class C, bool FORWARD_ORDER, int SKIP = -1>
+__device__ __forceinline__ void wave_transform(float (&r)[C::E], float* lds, const ThreadMap<C>& tm) {
+    constexpr int n = C::n, v = C::v, L = C::L, w = C::w;
+    auto stage = [&](auto phase, auto bit) {
+        if constexpr (decltype(bit)::value != SKIP)
+            wave_stage<C, decltype(phase)::value, decltype(bit)::value, !FORWARD_ORDER>(r, tm);
+    };
+    std::integral_constant<int, 0> first;
+    std::integral_constant<int, 1> second;
+    std::integral_constant<int, 2> third;
+    auto swaps = [&] {
+        if constexpr (L >= 5) lane_swap<C, C::e - 1, true>(r);
+        if constexpr (L == 6) lane_swap<C, C::e - 2, false>(r);
+    };
+    auto first_layout = [&] {
+        static_for<0, n>([&](auto b) {
+            constexpr int B = decltype(b)::value;
+            if constexpr (B < v + 4 || B > v + 5 + w) stage(first, b);
+        });
+        if constexpr (n > v + 5 && L <= 5) stage(first, std::integral_constant<int, v + 5>{});
+        if constexpr (n > v + 4 && L <= 4) stage(first, std::integral_constant<int, v + 4>{});
+    };
+    auto second_layout = [&] {
+        if constexpr (L == 6) stage(second, std::integral_constant<int, v + 5>{});
+        if constexpr (L >= 5) stage(second, std::integral_constant<int, v + 4>{});
+    };
+    auto exchange = [&](auto from, auto to) {
+        lds_put_raw<C, decltype(from)::value>(r, lds + tm.lds_off[decltype(from)::value]);
+        exchange_barrier();
+        lds_get_raw<C, decltype(to)::value>(r, lds + tm.lds_off[decltype(to)::value]);
+    };
+    auto wave_bits = [&] {
+        static_for<0, w>([&](auto k) { stage(third, std::integral_constant<int, v + 6 + decltype(k)::value>{}); });
+    };
+    if constexpr (FORWARD_ORDER) {
+        first_layout(); swaps(); second_layout();
+        if constexpr (w > 0) { exchange(second, third); wave_bits(); }
+    } else {
+        if constexpr (w > 0) { wave_bits(); exchange(third, second); }
+        second_layout(); swaps(); first_layout();
+    }
+}
 
 // H_raw applied to the 2^n values spread over the token's threads.
 //   FORWARD_ORDER: registers enter in the first phase's layout and leave in the last phase's;
 //   otherwise the phases run in reverse (enter in the last layout, leave in the first) -- the
 //   backward pass uses this so that dy can be consumed in the layout z was produced in.
 // Ends with a workgroup barrier when LDS was used, so the caller may reuse LDS at once.
-// Workgroup barrier for the LDS exchange.  __syncthreads() carries a release/acquire fence that
-// makes the wave wait for *all* its outstanding memory operations -- including the prefetches in
-// flight and the stores of the previous token, which have nothing to do with the exchange.  The
-// exchange only needs this wave's LDS writes to have completed (lgkmcnt) before the barrier.
-__device__ __forceinline__ void exchange_barrier() {
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-}
-
 template <class C, bool FORWARD_ORDER, bool TRAILING_BARRIER>
 __device__ __forceinline__ void transform(float (&r)[C::E], float* lds, const ThreadMap<C>& tm) {
-    static_for<0, C::P>([&](auto s) {
-        constexpr int S = decltype(s)::value;
-        constexpr int PH = FORWARD_ORDER ? S : C::P - 1 - S;
-        if constexpr (S > 0) lds_get<C, PH>(r, lds + tm.lds_off[PH]);
-        run_stages<C, PH>(r);
-        if constexpr (S + 1 < C::P) {
-            // a middle phase rewrites exactly the words it read, so only the hand-over to the
-            // next layout needs the barrier
-            lds_put<C, PH>(r, lds + tm.lds_off[PH]);
-            exchange_barrier();
-        }
-    });
-    // The next write into the exchange region must not overtake other waves' reads of this one.
-    // When the next transform runs in the opposite order (the backward kernel alternates), its
-    // first write goes, thread by thread, to exactly the words this thread has just read, and no
-    // barrier is needed; a kernel that only runs forward-order transforms needs it.
-    if constexpr (C::P > 1 && TRAILING_BARRIER) exchange_barrier();
+    if constexpr (C::kWave) {
+        wave_transform<C, FORWARD_ORDER>(r, lds, tm);
+        if constexpr (C::w > 0 && TRAILING_BARRIER) exchange_barrier();
+    } else {
+        static_for<0, C::P>([&](auto s) {
+            constexpr int S = decltype(s)::value;
+            constexpr int PH = FORWARD_ORDER ? S : C::P - 1 - S;
+            if constexpr (S > 0) lds_get<C, PH>(r, lds + tm.lds_off[PH]);
+            run_stages<C, PH>(r);
+            if constexpr (S + 1 < C::P) {
+                // a middle phase rewrites exactly the words it read, so only the hand-over to the
+                // next layout needs the barrier
+                lds_put<C, PH>(r, lds + tm.lds_off[PH]);
+                exchange_barrier();
+            }
+        });
+        // The next write into the exchange region must not overtake other waves' reads of this one.
+        // When the next transform runs in the opposite order (the backward kernel alternates), its
+        // first write goes, thread by thread, to exactly the words this thread has just read, and no
+        // barrier is needed; a kernel that only runs forward-order transforms needs it.
+        if constexpr (C::P > 1 && TRAILING_BARRIER) exchange_barrier();
+    }
 }
 
 // Global -> LDS staging -> registers.  x and dy are fetched with LDS-direct loads (the data goes
@@ -366,10 +582,6 @@ __device__ __forceinline__ void stage_issue(unsigned char* wave_slot, const type
 // including the next group's prefetch issued moments ago.  Which loads must have landed is known
 // here (wait_vmem below, issued by the caller first); the reads' own completion is awaited inside
 // this function, with the values tied to the wait so that no use can be scheduled before it.
-__device__ __forceinline__ unsigned lds_byte_address(const void* p) {
-    return (unsigned)(size_t)(const __attribute__((address_space(3))) unsigned char*)p;
-}
-
 //   OWN: the slot was filled by this wave's own loads and nobody else reads it (poisoned after the
 //   read in the debug build); false for a slot that another wave fetched or also reads.
 template <class C, bool OWN = true>
@@ -748,7 +960,7 @@ __global__ __launch_bounds__(C::BT) void forward_kernel(const typename C::io::el
     }
 
     float a[C::E], b[C::E];
-    param_get<C, LAST>(a, alpha, tm.last_elem, tm.last_ok, inv_sqrt_d<C>());
+    param_get<C, LAST>(a, alpha, tm.last_elem, tm.last_ok, inv_sqrt_d<C>() * tm.sign);
     param_get<C, LAST>(b, beta, tm.last_elem, tm.last_ok, 1.0f);
     wait_vmem<0>();
     for (; grp < grp_end; grp += step) {
@@ -819,7 +1031,7 @@ __global__ __launch_bounds__(C::BT) void forward_once_kernel(const typename C::i
     global_get<C, 0>(raw, x + row * C::kRow, tm.first_elem, tm.first_ok);
     if constexpr (RESID) global_get<C, LAST>(rraw, resid + row * C::kRow, tm.last_elem, tm.last_ok);
     float a[C::E], b[C::E];
-    param_get<C, LAST>(a, alpha, tm.last_elem, tm.last_ok, inv_sqrt_d<C>());
+    param_get<C, LAST>(a, alpha, tm.last_elem, tm.last_ok, inv_sqrt_d<C>() * tm.sign);
     param_get<C, LAST>(b, beta, tm.last_elem, tm.last_ok, 1.0f);
     HadamardB hb{}, hbp{};
     if constexpr (C::kMfma) hb = make_hadamard_b();
@@ -970,6 +1182,247 @@ __global__ __launch_bounds__(C::BT) void backward_kernel(const typename C::io::e
         }
     }
     }   // GRADS
+}
+
+// Read COUNT (1, 2 or 4) of the staged vectors, starting with vector FIRST; reads and wait in one block.
+template <class C, int FIRST, int COUNT>
+__device__ __forceinline__ void stage_read_some(uint4 (&raw)[COUNT], const unsigned char* wave_slot) {
+    static_assert(COUNT == 1 || COUNT == 2 || COUNT == 4, "unexpected vector count");
+    const unsigned addr = lds_byte_address(wave_slot) + (threadIdx.x & 63u) * 16u;
+    u32x4 v[COUNT];
+    if constexpr (COUNT == 1)
+        asm volatile("ds_read_b128 %0, %1 offset:%2\n\ts_waitcnt lgkmcnt(0)"
+                     : "=&v"(v[0]) : "v"(addr), "n"(FIRST * 1024) : "memory");
+    else if constexpr (COUNT == 2)
+        asm volatile("ds_read_b128 %0, %2 offset:%3\n\tds_read_b128 %1, %2 offset:%4\n\ts_waitcnt lgkmcnt(0)"
+                     : "=&v"(v[0]), "=&v"(v[1]) : "v"(addr), "n"(FIRST * 1024), "n"(FIRST * 1024 + 1024) : "memory");
+    else
+        asm volatile("ds_read_b128 %0, %4 offset:%5\n\tds_read_b128 %1, %4 offset:%6\n\t"
+                     "ds_read_b128 %2, %4 offset:%7\n\tds_read_b128 %3, %4 offset:%8\n\ts_waitcnt lgkmcnt(0)"
+                     : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3])
+                     : "v"(addr), "n"(FIRST * 1024), "n"(FIRST * 1024 + 1024), "n"(FIRST * 1024 + 2048),
+                       "n"(FIRST * 1024 + 3072) : "memory");
+#pragma unroll
+    for (int c = 0; c < COUNT; ++c) raw[c] = make_uint4(v[c].x, v[c].y, v[c].z, v[c].w);
+    if constexpr (kPoisonLds) {
+        const u32x4 nan = {0x7fc07fc0u, 0x7fc07fc0u, 0x7fc07fc0u, 0x7fc07fc0u};
+#pragma unroll
+        for (int c = 0; c < COUNT; ++c) {
+            const unsigned a = addr + (FIRST + c) * 1024;
+            asm volatile("ds_write_b128 %0, %1" : : "v"(a), "v"(nan) : "memory");
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    }
+}
+
+// Keep a value computed where it stands: the compiler otherwise sinks a sum that the loop only uses in
+// its next iteration to the end of the body, and with it everything the sum is made of stays live.
+template <int COUNT>
+__device__ __forceinline__ void pin(float* r) {
+#pragma unroll
+    for (int i = 0; i < COUNT; ++i) asm volatile("" : "+v"(r[i]));
+}
+
+// The rows of one wave's tokens: a wave-uniform base and a 32-bit offset per lane, so that an address
+// costs the vector unit nothing (loads and stores take base, offset and an immediate).
+template <class C>
+struct WaveRows {
+    static constexpr int W = C::TPT < 64 ? 64 / C::TPT : 1;     // tokens per wave
+    int64_t base;                                   // element index of the wave's first row (clamped to a valid row)
+    unsigned rel;                                   // this lane's row from there, in elements (clamped)
+    bool active;                                    // this lane's token exists
+    bool whole;                                     // all W tokens of the wave exist (wave-uniform)
+    __device__ __forceinline__ WaveRows(int64_t grp, int64_t N, unsigned wave, unsigned lane) {
+        const int64_t tok0 = grp * C::G + (C::w > 0 ? wave >> C::w : wave * W);
+        const int64_t left = N - tok0;              // tokens from the wave's first on, <= 0 past the end
+        const unsigned sl = C::TPT < 64 ? lane / C::TPT : 0u;
+        whole = left >= W;
+        base = (left > 0 ? tok0 : N - 1) * C::kRow;
+        const unsigned last = left >= W ? W - 1 : (left > 0 ? (unsigned)left - 1u : 0u);
+        rel = (sl < last ? sl : last) * C::kRow;
+        active = (int64_t)sl < left;
+    }
+};
+
+template <class C, int PH>
+__device__ __forceinline__ void wave_issue(unsigned char* wave_slot, const typename C::io::elem_t* tensor,
+                                           const WaveRows<C>& rows, unsigned thread_elem) {
+    const unsigned char* base = reinterpret_cast<const unsigned char*>(tensor + rows.base);
+    const unsigned off = (rows.rel + thread_elem) * (unsigned)sizeof(typename C::io::elem_t);
+    static_for<0, C::NV>([&](auto c) {
+        constexpr int Cc = decltype(c)::value;
+        constexpr unsigned elem = reg_elem_offset(C::plan.ph[PH], C::e, Cc * C::V);
+        __builtin_amdgcn_global_load_lds((global_cptr)(base + elem * sizeof(typename C::io::elem_t) + off),
+                                         (lds_ptr)(wave_slot + Cc * 1024), 16, 0, kStreamPolicy);
+    });
+}
+
+// backward of the wave schedule, which took the place of butterflies re-dealt two or three times through
+// LDS per transform (two one-word passes at d = 256; one wave per SIMD waiting on conflicting LDS accesses
+// at float32 d = 4096).  Bound by memory: 16384 x 4096 float32 in 131..135 us where the plain copy's rate
+// would take 130 (was 178..183); 65537 x 256 bfloat16 19.4 us against 16 (was 26.4); a stage costs one
+// vector instruction per value, between lanes as in registers.  With tokens inside a wave the four waves of a workgroup walk their
+// own tokens and never wait for one another: the loop has no barrier, and the transforms touch no LDS.
+// A token of two or four waves is the workgroup's only one and has one exchange per transform.
+//
+// Per iteration k (x(k) and dy(k) have landed in the wave's stage slots):
+//   r <- stage X;  issue x(k+1);  r = H_raw x;  dy(k) from the stage, a few vectors at a time:
+//   sums, and r <- alpha' dy (and its first stage) in place of the z that has been used;  issue dy(k+1);  transform back;
+//   wait for everything pending;  store dx(k).
+// Taking dy in pieces keeps one set of 2^e values live besides the sums and alpha'.
+template <class C, bool GRADS, bool DX>
+__global__ __launch_bounds__(C::BT, C::kBwdWavesPerSimd)
+void backward_wave_kernel(const typename C::io::elem_t* dy, const typename C::io::elem_t* x,
+                          const float* __restrict__ alpha, typename C::io::elem_t* dx,
+                          float* __restrict__ partials,   // [grid][2][kRow]
+                          int64_t N) {
+    static_assert(GRADS || DX, "nothing to compute");
+    constexpr int LAST = C::P - 1;
+    constexpr int Q = wave_first_back_reg<C>();
+    // vectors of dy taken at a time: 16 values, and the pairs of the first stage back together
+    constexpr int CH16 = C::NV * C::V < 16 ? C::NV : 16 / C::V, CH = CH16 * C::V < (2 << Q) ? (2 << Q) / C::V : CH16;
+    // separate LDS objects where there is an exchange: its accesses then do not wait for the prefetches
+    constexpr bool SPLIT = C::w > 0;
+    // two-wave tokens: filled up to 64 KiB per workgroup, so that the grid's two workgroups per CU
+    // cannot land as three on some CUs and one on others (135 against 139 us, 16384 x 4096 float32)
+    constexpr unsigned kFill = GRADS && C::w == 1 ? 65536u - 2u * C::kStageBytes : 0u;
+    __shared__ __align__(16) float lds[(kFill > C::kExchangeBytes ? kFill : C::kExchangeBytes) / 4];
+    __shared__ __align__(16) unsigned char stage_buf[(GRADS && !SPLIT ? 2 : 1) * C::kStageBytes];
+    __shared__ __align__(16) unsigned char stage_x_buf[GRADS && SPLIT ? C::kStageBytes : 16];
+    const unsigned wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63u;
+    ThreadMap<C> tm;
+    tm.init(threadIdx.x % C::TPT, threadIdx.x / C::TPT);
+    unsigned char* stage_g = stage_buf + wave * (C::NV * 1024);
+    unsigned char* stage_x = SPLIT ? stage_x_buf + (GRADS ? wave * (C::NV * 1024) : 0)
+                                   : stage_buf + (GRADS ? C::kStageBytes : 0) + wave * (C::NV * 1024);
+
+    const int64_t groups = (N + C::G - 1) / C::G, step = gridDim.x;
+    int64_t grp = blockIdx.x;
+    if (grp < groups) {
+        const WaveRows<C> rows(grp, N, wave, lane);
+        if constexpr (GRADS) wave_issue<C, 0>(stage_x, x, rows, tm.first_elem);
+        wave_issue<C, LAST>(stage_g, dy, rows, tm.last_elem);
+    }
+    float a[DX ? C::E : 1], da[GRADS ? C::E : 1], db[GRADS ? C::E : 1];
+    const float scale = inv_sqrt_d<C>() * tm.sign;             // the sign of dx's input and of z
+    if constexpr (DX) {
+        param_get<C, LAST>(a, alpha, tm.last_elem, true, scale);
+    }
+    if constexpr (GRADS) {
+#pragma unroll
+        for (int i = 0; i < C::E; ++i) { da[i] = 0.0f; db[i] = 0.0f; }
+    }
+    wait_vmem<0>();
+    for (; grp < groups; grp += step) {
+        const bool more = grp + step < groups;
+        const WaveRows<C> rows(grp, N, wave, lane), next(more ? grp + step : grp, N, wave, lane);
+        if (!rows.whole && !rows.active) {
+            // ragged last group: the clamped rows of missing tokens add nothing to the sums
+            const u32x4 zero = {0u, 0u, 0u, 0u};
+            const unsigned addr = lds_byte_address(stage_g) + lane * 16u;
+#pragma unroll
+            for (int c = 0; c < C::NV; ++c)
+                asm volatile("ds_write_b128 %0, %1 offset:%2" : : "v"(addr), "v"(zero), "n"(c * 1024) : "memory");
+        }
+        float r[C::E];
+        if constexpr (GRADS) {
+            uint4 raw[C::NV];
+            stage_read<C>(raw, stage_x);
+            if (more) wave_issue<C, 0>(stage_x, x, next, tm.first_elem);
+            unpack_all<C>(r, raw);
+            wave_transform<C, true>(r, lds, tm);
+            pin<C::E>(r);
+        }
+        static_for<0, C::NV / CH>([&](auto c) {
+            constexpr int FIRST = decltype(c)::value * CH, B = FIRST * C::V, COUNT = CH * C::V;
+            uint4 graw[CH];
+            stage_read_some<C, FIRST, CH>(graw, stage_g);
+            float g[COUNT];
+#pragma unroll
+            for (int i = 0; i < CH; ++i) C::io::unpack(graw[i], &g[i * C::V]);
+            if constexpr (GRADS) {
+#pragma unroll
+                for (int i = 0; i < COUNT; ++i) {
+                    da[B + i] = fmaf(g[i], r[B + i], da[B + i]);
+                    db[B + i] += g[i];
+                }
+                pin<COUNT>(da + B);
+                pin<COUNT>(db + B);
+            }
+            if constexpr (DX) {
+                // alpha' dy and the first stage in one: a product and two multiply-adds per pair
+                static_assert((2 << Q) <= COUNT, "a pair lies in one piece");
+#pragma unroll
+                for (int i = 0; i < COUNT; ++i)
+                    if (!((i >> Q) & 1)) {
+                        const int j = i | (1 << Q);
+                        const float p = g[j] * a[B + j];
+                        r[B + i] = fmaf(g[i], a[B + i], p);
+                        r[B + j] = fmaf(g[i], a[B + i], -p);
+                    }
+                pin<COUNT>(r + B);
+            }
+        });
+        if (more) wave_issue<C, LAST>(stage_g, dy, next, tm.last_elem);
+        if constexpr (DX) {
+            wave_transform<C, false, wave_first_back_bit<C>()>(r, lds, tm);
+            pin<C::E>(r);
+        }
+        // The exchange region: with both transforms each one's put goes, thread by thread, to the words
+        // that this thread's last get has read; with one alone the next put needs a barrier.
+        if constexpr (C::w > 0 && GRADS != DX) exchange_barrier();
+        if (more) wait_vmem<0>();
+        if constexpr (DX) {
+            unsigned char* base = reinterpret_cast<unsigned char*>(dx + rows.base);
+            const unsigned off = (rows.rel + tm.first_elem) * (unsigned)sizeof(typename C::io::elem_t);
+            if (rows.active)
+                static_for<0, C::NV>([&](auto c) {
+                    constexpr int Cc = decltype(c)::value;
+                    constexpr unsigned elem = reg_elem_offset(C::plan.ph[0], C::e, Cc * C::V);
+                    stream_store16(base + elem * sizeof(typename C::io::elem_t) + off, C::io::pack(&r[Cc * C::V]));
+                });
+        }
+    }
+    if constexpr (GRADS) {
+        // the token slots of the workgroup, added in slot order through LDS that is idle now
+        float* sums = SPLIT ? lds : reinterpret_cast<float*>(stage_buf);
+        float* row = partials + (size_t)blockIdx.x * 2 * C::kRow;
+        const float s = inv_sqrt_d<C>();
+#pragma unroll
+        for (int which = 0; which < 2; ++which) {
+            if (which == 0) {
+#pragma unroll
+                for (int i = 0; i < C::E; ++i) da[i] *= tm.sign;
+            }
+            if constexpr (C::G == 1) {                         // one token per workgroup: straight to the row
+                static_for<0, C::E / 4>([&](auto i) {
+                    constexpr int I = decltype(i)::value * 4;
+                    constexpr unsigned off = reg_elem_offset(C::plan.ph[LAST], C::e, I);
+                    const float4 q = which == 0 ? make_float4(da[I] * s, da[I + 1] * s, da[I + 2] * s, da[I + 3] * s)
+                                                : make_float4(db[I], db[I + 1], db[I + 2], db[I + 3]);
+                    *reinterpret_cast<float4*>(row + which * C::kRow + tm.last_elem + off) = q;
+                });
+                continue;
+            }
+            __syncthreads();
+            if (which == 0) lds_put<C, LAST>(da, sums + tm.lds_off[LAST]);
+            else            lds_put<C, LAST>(db, sums + tm.lds_off[LAST]);
+            __syncthreads();
+            for (unsigned j = threadIdx.x; j < (unsigned)C::D; j += C::BT) {
+                constexpr int CHAINS = C::G < 8 ? C::G : 8;    // short chains: less rounding, reads in flight
+                float acc[CHAINS];
+#pragma unroll
+                for (int c = 0; c < CHAINS; ++c) acc[c] = 0.0f;
+#pragma unroll
+                for (int gslot = 0; gslot < C::G; ++gslot) acc[gslot % CHAINS] += sums[gslot * C::kTokenWords + j];
+#pragma unroll
+                for (int half = CHAINS / 2; half >= 1; half /= 2)
+#pragma unroll
+                    for (int c = 0; c < half; ++c) acc[c] += acc[c + half];
+                row[which * C::kRow + j] = which == 0 ? acc[0] * s : acc[0];
+            }
+        }
+    }
 }
 
 // One team's per-thread sums (last layout) -> the workgroup's row out[kRow], times `scale`.  With
@@ -1164,8 +1617,8 @@ __global__ __launch_bounds__(3 * C::BT) void backward_teams_kernel(const typenam
 }
 
 // out[which][j] = sum over rows of partials[row][which][j].  Workgroup = CG float4 columns x
-// (1024 / CG) row lanes: lane r adds rows r, r + lanes, ... in index order, then the lane sums are
-// combined by a fixed binary tree -- one association, independent of scheduling, so the result is
+// (1024 / CG) row lanes: lane r adds rows r, r + lanes, ... four at a time (all four requested
+// before the first is used, added in pairs), then the lane sums are combined by a fixed binary tree -- one association, independent of scheduling, so the result is
 // bit-reproducible.  CG = 16 (256 contiguous bytes per row) for large d; CG = 4 keeps the grid wide
 // (d/16 x 2 workgroups) for small d, where this kernel is otherwise pure latency.
 template <int CG>
@@ -1180,9 +1633,16 @@ __global__ __launch_bounds__(1024) void reduce_partials_kernel(const float* __re
     const int which = blockIdx.y;
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
     if (col < d) {
-        for (int r = lane_row; r < rows; r += LANES) {
-            const float4 q = *reinterpret_cast<const float4*>(partials + ((size_t)r * 2 + which) * d + col);
-            acc.x += q.x; acc.y += q.y; acc.z += q.z; acc.w += q.w;
+        const float* base = partials + (size_t)which * d + col;
+        auto at = [&](int r) {
+            return r < rows ? *reinterpret_cast<const float4*>(base + (size_t)r * 2 * d) : make_float4(0.f, 0.f, 0.f, 0.f);
+        };
+        for (int r = lane_row; r < rows; r += 4 * LANES) {
+            const float4 q0 = at(r), q1 = at(r + LANES), q2 = at(r + 2 * LANES), q3 = at(r + 3 * LANES);
+            acc.x += (q0.x + q1.x) + (q2.x + q3.x);
+            acc.y += (q0.y + q1.y) + (q2.y + q3.y);
+            acc.z += (q0.z + q1.z) + (q2.z + q3.z);
+            acc.w += (q0.w + q1.w) + (q2.w + q3.w);
         }
     }
     part[lane_row][cg] = acc;

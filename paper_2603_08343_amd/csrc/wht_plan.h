@@ -4,8 +4,8 @@
 // registers.  A butterfly stage on element-index bit b (paper Fig. 2: pairs whose indices differ by
 // the stride 2^b) costs one add or subtract per element when bit b is a bit of the *register*
 // index, so the schedule is a short list of layouts ("phases"); each phase names which e element
-// bits are register-resident, the stages run on those, and between phases the token is re-dealt
-// through LDS.  Stages commute (they act on different index bits), so any order gives H_raw x.
+// bits are register-resident, the stages run on those, and between phases bits change places: through
+// LDS, or by swaps between the lanes of a wave.  Stages commute (they act on different index bits), so any order gives H_raw x.
 //
 // The first and the last layout keep element bits 0..v-1 in registers (2^v elements = one 16-byte
 // global vector) and give the lowest thread bits the next element bits, so that global loads and
@@ -27,11 +27,10 @@ struct PhaseDesc {
 struct PlanDesc {
     int n, e, v, nphase;
     unsigned mfma_bits;    // element bits transformed by the matrix-core rounds (in the first layout)
+    unsigned lane_bits;    // element bits transformed between lanes, by DPP operands (wave schedule)
     PhaseDesc ph[kMaxPhases];
 };
 
-constexpr int popcount_u(unsigned m) { int c = 0; while (m) { c += m & 1u; m >>= 1; } return c; }
-constexpr int lowest_bit(unsigned m) { int b = 0; while (!(m & 1u)) { m >>= 1; ++b; } return b; }
 
 constexpr unsigned reg_mask(const PhaseDesc& p, int e) {
     unsigned m = 0;
@@ -47,75 +46,6 @@ constexpr void fill_thread_bits(PhaseDesc& p, int n, int e) {
     for (; k < kMaxBits; ++k) p.tb[k] = 0;
 }
 
-// log2(values per thread) the library uses for a given log2 d: 32 values where the token is large
-// enough to keep 8 threads busy, never fewer than one 16-byte vector.
-constexpr int log_e_for(int logd, int logv) {
-    int e = logd - 3;
-    if (e > 5) e = 5;
-    if (e < logv) e = logv;
-    return e;
-}
-
-// n = log2 d, e = log2(values per thread), v = log2(elements per 16-byte vector);  v <= e <= n.
-constexpr PlanDesc make_plan(int n, int e, int v) {
-    PlanDesc pl{};
-    pl.n = n; pl.e = e; pl.v = v; pl.nphase = 0; pl.mfma_bits = 0;
-    const unsigned all = (1u << n) - 1u;
-    unsigned undone = all;
-
-    // first phase: the vector bits and the top e-v bits
-    PhaseDesc first{};
-    for (int q = 0; q < v; ++q) first.rb[q] = q;
-    for (int q = v; q < e; ++q) first.rb[q] = n - (e - v) + (q - v);
-    first.stages = reg_mask(first, e);
-    fill_thread_bits(first, n, e);
-    undone &= ~first.stages;
-    pl.ph[pl.nphase++] = first;
-    if (n == e) return pl;
-
-    // the last phase can take e-v new bits: reserve the top ones still undone for it -- but only
-    // bits >= v+3, so that its three lowest thread bits stay element bits v..v+2 (eight lanes
-    // cover 128 contiguous bytes of the global store)
-    unsigned reserved = 0;
-    {
-        int taken = 0;
-        for (int b = n - 1; b >= v + 3 && taken < e - v; --b)
-            if ((undone >> b) & 1u) { reserved |= 1u << b; ++taken; }
-    }
-    // middle phases: windows of e consecutive element bits, lowest undone bit first
-    unsigned middle = undone & ~reserved;
-    while (middle) {
-        int lo = lowest_bit(middle);
-        if (lo > n - e) lo = n - e;
-        PhaseDesc mid{};
-        for (int q = 0; q < e; ++q) mid.rb[q] = lo + q;
-        mid.stages = reg_mask(mid, e) & undone;
-        fill_thread_bits(mid, n, e);
-        undone &= ~mid.stages;
-        middle &= ~mid.stages;
-        pl.ph[pl.nphase++] = mid;
-    }
-    // last phase: vector bits, whatever is still undone, then top bits to fill the register index
-    PhaseDesc last{};
-    for (int q = 0; q < v; ++q) last.rb[q] = q;
-    {
-        int q = v;
-        unsigned used = (1u << v) - 1u;
-        for (int b = 0; b < n && q < e; ++b)
-            if ((undone >> b) & 1u) { last.rb[q++] = b; used |= 1u << b; }
-        for (int b = n - 1; b >= 0 && q < e; --b)
-            if (!((used >> b) & 1u)) { last.rb[q++] = b; used |= 1u << b; }
-        // keep the chunk bits ascending so register order follows memory order
-        for (int i = v; i < e; ++i)
-            for (int j = i + 1; j < e; ++j)
-                if (last.rb[j] < last.rb[i]) { int t = last.rb[i]; last.rb[i] = last.rb[j]; last.rb[j] = t; }
-    }
-    last.stages = undone;
-    fill_thread_bits(last, n, e);
-    pl.ph[pl.nphase++] = last;
-    return pl;
-}
-
 // Element offset contributed by register index r in a phase.
 constexpr unsigned reg_elem_offset(const PhaseDesc& p, int e, int r) {
     unsigned off = 0;
@@ -126,7 +56,7 @@ constexpr unsigned reg_elem_offset(const PhaseDesc& p, int e, int r) {
 
 // Every element bit must be butterflied exactly once over the phases.
 constexpr bool plan_is_complete(const PlanDesc& pl) {
-    unsigned seen = pl.mfma_bits;
+    unsigned seen = pl.mfma_bits | pl.lane_bits;
     for (int p = 0; p < pl.nphase; ++p) {
         if (seen & pl.ph[p].stages) return false;
         if (pl.ph[p].stages & ~reg_mask(pl.ph[p], pl.e)) return false;
@@ -197,6 +127,76 @@ constexpr int mfma_log_tiles(int logd, bool backward) {
 // allows, i.e. as many waves per token, which shortens each wave's chain of dependent instructions.
 constexpr int mfma_log_tiles_few(int logd) { return logd <= 12 ? 0 : 1; }
 
+// ---- the wave schedule: a token inside one wave (or two, four), hardly any LDS in the transform -----
+//
+// A token lies on 2^L lanes of one wave (L = n - e <= 6), 2^e values per lane, and a wave holds
+// 2^(6-L) tokens; a token that does not fit (n - e = 6 + w) lies on 2^w whole waves.  Element bits
+// v .. v+5 are the lane bits, v+6 .. v+5+w the wave bits, the rest register bits:
+//   lane positions 0..3 : butterflied in place, the partner's value read through a DPP operand;
+//   lane positions 4, 5 : exchanged with the top register bits (one permlane16/32 swap per register
+//                         pair) and then butterflied in registers.  The second layout is therefore
+//                         the first one with element bits v+4 <-> n-1 (and v+5 <-> n-2) exchanged;
+//   wave bits           : exchanged with register bits v, v+1 through LDS, the only re-deal there is.
+// The stages run in the order 0 .. v+3, v+6 .. n-1, v+5, v+4 whatever e is (w = 0), so that two
+// kernels with different values per lane give the same bits.
+constexpr PlanDesc make_wave_plan(int n, int e, int v) {
+    PlanDesc pl{};
+    const int T = n - e, L = T < 6 ? T : 6, w = T - L;
+    pl.n = n; pl.e = e; pl.v = v; pl.nphase = 1; pl.mfma_bits = 0; pl.lane_bits = 0;
+    for (int k = 0; k < L && k < 4; ++k) pl.lane_bits |= 1u << (v + k);
+    PhaseDesc first{};
+    for (int q = 0; q < v; ++q) first.rb[q] = q;
+    for (int q = v; q < e; ++q) first.rb[q] = n - (e - v) + (q - v);
+    first.stages = reg_mask(first, e);
+    fill_thread_bits(first, n, e);
+    pl.ph[0] = first;
+    unsigned done = first.stages;
+    if (L > 4) {
+        PhaseDesc next = first;
+        for (int k = 4; k < L; ++k) {
+            next.rb[e - 1 - (k - 4)] = first.tb[k];
+            next.tb[k] = first.rb[e - 1 - (k - 4)];
+        }
+        next.stages = reg_mask(next, e) & ~done;
+        done |= next.stages;
+        pl.ph[pl.nphase++] = next;
+    }
+    if (w > 0) {
+        PhaseDesc last = pl.ph[pl.nphase - 1];
+        for (int k = 0; k < w; ++k) {
+            const int lane = last.rb[v + k];
+            last.rb[v + k] = last.tb[6 + k];
+            last.tb[6 + k] = lane;
+        }
+        last.stages = reg_mask(last, e) & ~done;
+        pl.ph[pl.nphase++] = last;
+    }
+    return pl;
+}
+
+// Lane <-> element bits at lane positions 0..3.  The DPP operands at hand pair lane l with l ^ 1,
+// l ^ 2, l ^ 7 and l ^ 8; with c the element bits of a lane, l = c0*1 ^ c1*2 ^ c2*7 ^ c3*8.
+constexpr unsigned wave_lane_to_bits(unsigned l, int L) {
+    return L >= 3 ? l ^ ((l >> 2) & 1u) ^ ((l >> 1) & 2u) : l;
+}
+
+// The layout needs a register bit above the vector bits for every lane position above 3, and for
+// every wave bit.
+constexpr bool wave_fits(int n, int e, int v) {
+    const int T = n - e, L = T < 6 ? T : 6, w = T - L;
+    return T >= 0 && w <= 2 && e <= kMaxRegBits && e >= v && (L <= 4 || e - v >= L - 4) && e - v >= w;
+}
+// log2(values per lane): at least eight lanes per token where the vectors allow it (128 contiguous
+// bytes), 16 values if the token then fits a wave, 32 on up to four waves beyond that (64 for the
+// widest bfloat16 row).
+constexpr int wave_log_e(int n, int v) {
+    int e = n - 3 < 4 ? n - 3 : 4;
+    if (e < v) e = v;
+    if (n - e > 6) ++e;
+    while (!wave_fits(n, e, v)) ++e;
+    return e;
+}
+
 // ---- rows of 12 * 2^m elements on 2^n = 16 * 2^m slots ----------------------------------------
 // Slot index s = (r_hi << 8) | (b << 4) | r_lo  <->  element b * 2^m + (r_hi << 4 | r_lo), m = n - 4:
 // the block number b = 0..11 occupies slot bits 4..7, b = 12..15 are padding.  A bit permutation, so
@@ -237,21 +237,9 @@ constexpr int twelve_round_entry(unsigned m_in, unsigned m_out) {
 // Both are linear in the bits of i (phys(a | b) = phys(a) + phys(b) for disjoint a, b) and keep four
 // consecutive elements in one aligned 16-byte group.
 
-// Butterfly schedule, padded maps.  The LDS has 32 banks of 4 bytes.
-//   8-element vectors (bfloat16 I/O): +4 words every 64 elements keeps the 16-byte-per-lane accesses
-//   of the first/last layouts (lane stride 8 words) off each other's banks, +8 words every 256
-//   elements does the same for the one-word accesses of the middle layouts (9.4 % of LDS).
-//   4-element vectors (fp32 I/O): +4 words every 32 elements and +4 more every 128 elements; the
-//   middle layouts' one-word accesses (lanes 2^7 .. 2^10 elements apart) then spread over all banks.
-//   Measured at d = 8192: fp32 backward 4 % faster than with the map above; with bfloat16 I/O the
-//   bank-conflict cycle counter falls to a third, but the map costs 15.6 % of LDS, which there drops
-//   a CU from three resident workgroups to two (forward 12 % slower), so the 8-element case keeps
-//   the smaller map.
-constexpr unsigned lds_phys_pad(unsigned i, int v) {
-    return v == 3 ? i + ((i >> 6) << 2) + ((i >> 8) << 3)
-                  : i + ((i >> 5) << 2) + ((i >> 7) << 2);
-}
-constexpr unsigned lds_words_pad(unsigned d, int v) { return (lds_phys_pad(d - 1, v) + 1 + 3) & ~3u; }
+// Wave schedule: lane l's 16 bytes follow lane l-1's in every layout, so the plain index is free of
+// bank conflicts.
+constexpr unsigned lds_phys_plain(unsigned i) { return i; }
 
 // Matrix-core schedule: both layouts give lane l the 8 elements starting at 8*l (+ multiples of
 // 512) as two 16-byte accesses.  Moving element bit 2 above the six lane bits makes each of those

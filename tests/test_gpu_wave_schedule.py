@@ -1,0 +1,63 @@
+"""The wave schedule (every stage in registers or between lanes; float32 tensors, and bfloat16 below
+d = 1024) where it can go wrong: token counts around a workgroup pass (a wave holds 64 * values-per-lane
+/ d tokens), one token, and the size at which the forward call changes from the one-pass to the
+persistent kernel.  Tolerances as in parity.py; the two forward kernels do the same arithmetic in the
+same order, so their results have to be equal bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2603_08343_amd as wht
+from paper_2603_08343_amd import synth
+from parity import assert_grad_close, assert_io_close, nan_filled, to_gpu
+
+pytestmark = pytest.mark.gpu
+
+F32 = [(1 << n, "f32") for n in range(5, 14)]
+BF16 = [(1 << n, "bf16") for n in range(5, 10)]
+
+
+def _tokens_per_pass(d, dtype):
+    per_lane = min(16, max(d // 8, 4 if dtype == "f32" else 8))
+    return max(1, 256 * per_lane // d)
+
+
+@pytest.mark.parametrize("d,dtype", F32 + BF16)
+def test_backward_around_a_workgroup_pass(d, dtype):
+    G = _tokens_per_pass(d, dtype)
+    for N in sorted({1, max(1, G // 4 - 1), max(1, G - 1), G, G + 1, 3 * G + max(1, G // 4) + 1}):
+        print(f"[wave] backward d={d} {dtype} N={N}", flush=True)
+        inp = synth.make_inputs(N, d, dtype, seed=7 * d + N)
+        x, dy = to_gpu(inp.x, dtype), to_gpu(inp.dy, dtype)
+        a = torch.from_numpy(inp.alpha).cuda()
+        buf = nan_filled(N + 1, d, dtype)                    # the row after the last must keep its fill
+        dx, da, db = wht.wht_affine_backward(dy, x, a, dx=buf[:N])
+        torch.cuda.synchronize()
+        rdx, rda, rdb = oracle.backward(inp.dy, inp.x, inp.alpha, "fast")
+        assert_io_close(dx, rdx, dtype, f"dx d={d} N={N}")
+        assert_grad_close(da, rda, f"dalpha d={d} N={N}")
+        assert_grad_close(db, rdb, f"dbeta d={d} N={N}")
+        assert bool(torch.isnan(buf[N].float()).all())
+
+
+@pytest.mark.parametrize("d,dtype", F32 + BF16)
+def test_forward_kernels_agree_across_the_size_limit(d, dtype):
+    limit = 1 << (24 if dtype == "bf16" else (23 if d <= 2048 else 21))
+    lim = limit // d
+    N = lim + 37
+    print(f"[wave] forward limit d={d} {dtype} N={lim} and N={N}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(d)
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    x = torch.empty(N, d, device="cuda").normal_(generator=gen).to(tdt)
+    a = torch.empty(d, device="cuda").uniform_(0.5, 1.5, generator=gen)
+    b = torch.empty(d, device="cuda").normal_(0.0, 0.02, generator=gen)
+    y_few = wht.wht_affine_forward(x[:lim], a, b, y=nan_filled(lim, d, dtype))
+    y_all = wht.wht_affine_forward(x, a, b, y=nan_filled(N, d, dtype))
+    torch.cuda.synchronize()
+    bits = torch.int16 if dtype == "bf16" else torch.int32
+    assert torch.equal(y_few.view(bits), y_all[:lim].view(bits))
+    tail = x[lim - 3:].cpu()
+    host = tail.view(torch.int16).numpy().view(np.uint16) if dtype == "bf16" else tail.numpy()
+    ref = oracle.forward(np.ascontiguousarray(host), a.cpu().numpy(), b.cpu().numpy(), "fast")
+    assert_io_close(y_all[lim - 3:], ref, dtype, f"y d={d}")
