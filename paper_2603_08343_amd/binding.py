@@ -4,6 +4,11 @@ Argument marshalling only: torch supplies device memory and the stream, every st
 runs in the HIP kernels.  The `*_raw` calls take integer device addresses and return the status
 code; the tensor calls check shapes/dtypes, allocate outputs and the backward workspace with torch,
 and raise WhtAffineError on a non-zero status.
+
+A tensor call on the current stream first goes to the extension module _torch_marshal
+(csrc/torch_marshal.cpp), which does the same checks and allocations in native code and hands back
+None for anything but a plain valid call; the code here then decides, and words the errors.  Per call,
+one token of 4096 bfloat16 elements with residual and statistic: 10.1 us here, 5.5 us there.
 """
 import ctypes
 import os
@@ -123,6 +128,33 @@ def _torch():
     return _torch_module
 
 
+_native_module = None
+
+
+def _native():
+    """The extension module, loaded and told the library's addresses on the first tensor call."""
+    global _native_module
+    if _native_module is None:
+        torch, lib = _torch(), library()
+        try:
+            from . import _torch_marshal
+        except ImportError as e:
+            raise RuntimeError("the extension module _torch_marshal is missing or does not fit this torch: build it "
+                               "with `python -m paper_2603_08343_amd.build`") from e
+        names = ("wht_affine_forward", "wht_affine_forward_residual", "wht_affine_forward_residual_stats",
+                 "wht_affine_backward_workspace_bytes", "wht_affine_backward", "wht_affine_backward_static")
+        _torch_marshal.bind(*(ctypes.cast(getattr(lib, n), ctypes.c_void_p).value for n in names),
+                            torch._C._cuda_getCurrentRawStream)
+        _native_module = _torch_marshal
+    return _native_module
+
+
+def _outputs(out, where):
+    if type(out) is int:
+        raise WhtAffineError(out, where)
+    return out
+
+
 def _dtype_code(t, torch):
     if t.dtype == torch.float32:
         return DTYPE_F32
@@ -173,6 +205,10 @@ class _DeviceGuard:
 
 def wht_affine_forward(x, alpha, beta, y=None, stream=None):
     """y = alpha (.) (H x) + beta  (Eq. 1).  x: [N,d] float32|bfloat16 on the GPU; alpha, beta: [d] float32."""
+    if stream is None:
+        out = _native().forward(x, alpha, beta, None, y, None, False, False)
+        if out is not None:
+            return _outputs(out, "wht_affine_forward")
     torch = _torch()
     _check_io(x, "x", torch)
     N, d = x.shape
@@ -194,6 +230,10 @@ def wht_affine_forward(x, alpha, beta, y=None, stream=None):
 
 def wht_affine_forward_residual(x, alpha, beta, resid, y=None, stream=None):
     """y = resid + alpha (.) (H x) + beta: the layer with the block's residual add fused in."""
+    if stream is None:
+        out = _native().forward(x, alpha, beta, resid, y, None, True, False)
+        if out is not None:
+            return _outputs(out, "wht_affine_forward_residual")
     torch = _torch()
     _check_io(x, "x", torch)
     _check_io(resid, "resid", torch, like=x)
@@ -216,6 +256,10 @@ def wht_affine_forward_residual(x, alpha, beta, resid, y=None, stream=None):
 def wht_affine_forward_residual_stats(x, alpha, beta, resid, y=None, sumsq=None, stream=None):
     """(y, sumsq): y = resid + alpha (.) (H x) + beta and sumsq[n] = sum_j y[n,j]^2 (float32 [N]), the
     statistic of an RMS normalisation that follows the residual stream."""
+    if stream is None:
+        out = _native().forward(x, alpha, beta, resid, y, sumsq, True, True)
+        if out is not None:
+            return _outputs(out, "wht_affine_forward_residual_stats")
     torch = _torch()
     _check_io(x, "x", torch)
     _check_io(resid, "resid", torch, like=x)
@@ -246,6 +290,10 @@ def wht_affine_backward(dy, x, alpha, dx=None, dalpha=None, dbeta=None, workspac
     """Returns (dx, dalpha, dbeta) with dx = H(alpha (.) dy), dalpha = sum_n dy (.) Hx, dbeta = sum_n dy.
     want_dx=False or want_param_grads=False leaves those outputs out (None in the result); without
     the parameter gradients x is not needed and may be None."""
+    if stream is None:
+        out = _native().backward(dy, x, alpha, dx, dalpha, dbeta, workspace, bool(want_dx), bool(want_param_grads), False)
+        if out is not None:
+            return _outputs(out, "wht_affine_backward")
     torch = _torch()
     if not want_dx and not want_param_grads:
         raise ValueError("nothing to compute: want_dx and want_param_grads are both False")
@@ -300,6 +348,10 @@ def wht_affine_backward_static(dy, x, alpha, dx=None, dalpha=None, dbeta=None, s
     """wht_affine_backward without a workspace: the library's own static scratch holds the partial
     sums (for callers that must not allocate; pass dx, dalpha and dbeta in and nothing is
     allocated here either).  Returns (dx, dalpha, dbeta)."""
+    if stream is None:
+        out = _native().backward(dy, x, alpha, dx, dalpha, dbeta, None, True, True, True)
+        if out is not None:
+            return _outputs(out, "wht_affine_backward_static")
     torch = _torch()
     _check_io(dy, "dy", torch)
     if x is None:

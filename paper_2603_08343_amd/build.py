@@ -1,10 +1,13 @@
-"""Compile the HIP library (csrc/wht_affine.hip) for gfx950 into libwht_affine.so, in-tree.
+"""Compile the HIP library (csrc/wht_affine.hip) for gfx950 into libwht_affine.so, and the tensor calls'
+marshalling (csrc/torch_marshal.cpp) into the extension module _torch_marshal.so, in-tree.
 
-hipcc cross-compiles without a GPU.  Run as `python -m paper_2603_08343_amd.build`.
+hipcc cross-compiles without a GPU; the extension module takes the host compiler and torch's headers.  Run as `python -m paper_2603_08343_amd.build`.
 """
+import importlib.util
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 SRC = os.path.join(HERE, "csrc", "wht_affine.hip")
@@ -16,6 +19,10 @@ COPY_LIB = os.path.join(HERE, "libwht_copybench.so")
 # what it read with NaN, so that a read that comes before its data (a missing barrier or wait) shows
 # up as NaN; carries the widths 512, 4096, 8192, 16384 and 6144 only
 POISON_LIB = os.path.join(HERE, "libwht_affine_poison.so")
+
+# host code only: the tensor calls' checks and allocations (no device code, no HIP headers)
+MARSHAL_SRC = os.path.join(HERE, "csrc", "torch_marshal.cpp")
+MARSHAL_LIB = os.path.join(HERE, "_torch_marshal.so")
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
@@ -34,7 +41,19 @@ SOURCES = [SRC] + [os.path.join(HERE, "csrc", f) for f in ("wht_device.h", "wht_
 def build(verbose: bool = False, extra=()) -> str:
     _compile(COPY_SRC, COPY_LIB, verbose, extra)
     _compile(SRC, POISON_LIB, verbose, (*extra, "-DWHT_POISON_LDS"))
+    _compile_marshal(verbose)
     return _compile(SRC, LIB, verbose, extra)
+
+
+def _compile_marshal(verbose: bool) -> None:
+    torch_dir = os.path.dirname(importlib.util.find_spec("torch").origin)
+    lib_dir = os.path.join(torch_dir, "lib")
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+           "-isystem", os.path.join(torch_dir, "include"), "-isystem", sysconfig.get_paths()["include"],
+           "-o", MARSHAL_LIB, MARSHAL_SRC, "-L" + lib_dir, "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
 
 
 def _compile(src: str, lib: str, verbose: bool, extra=()) -> str:
@@ -55,8 +74,10 @@ def _compile(src: str, lib: str, verbose: bool, extra=()) -> str:
 def ensure_built(verbose: bool = False) -> str:
     """For harnesses (tests, smoke check, benchmark): compile only if nothing has been built yet.
     The binding itself never builds: a missing library is an error there."""
-    if not os.path.exists(LIB) or not os.path.exists(COPY_LIB) or not os.path.exists(POISON_LIB):
+    if not all(os.path.exists(lib) for lib in (LIB, COPY_LIB, POISON_LIB, MARSHAL_LIB)):
         build(verbose=verbose)
+    elif os.path.getmtime(MARSHAL_SRC) > os.path.getmtime(MARSHAL_LIB):
+        raise RuntimeError(f"{MARSHAL_LIB} is older than its source: run `python -m paper_2603_08343_amd.build`")
     elif any(os.path.getmtime(f) > min(os.path.getmtime(LIB), os.path.getmtime(POISON_LIB))
              for f in SOURCES if os.path.exists(f)):
         # a stale binary would be validated and recorded under the new sources' name
