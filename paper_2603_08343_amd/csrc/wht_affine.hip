@@ -97,49 +97,64 @@ static int launch_forward(const void* x, const float* alpha, const float* beta, 
     return hipGetLastError() == hipSuccess ? WHT_OK : WHT_ERR_LAUNCH;
 }
 
+// A call of a few token groups runs on one workgroup, which writes dalpha and dbeta itself: no partial
+// rows and no second launch, which costs the stream 2.5 us and the host 3.3.  The groups then run one
+// after the other; up to here that is no slower (us per call under graph replay, two launches / one):
+// 3 groups at d = 256 6.0 / 5.7, at d = 1024 6.1 / 4.9, at float32 d = 1024 6.6 / 6.4; 2 groups at
+// d = 4096 7.6 / 6.5, at d = 8192 6.6 / 5.4; 1 at d = 16384 11.0 / 8.1 and at float32 d = 4096 7.7 / 5.2,
+// where 2 already are 11.1 / 12.3 and 7.7 / 8.3.
+template <class C>
+static bool one_workgroup(int64_t N) {
+    constexpr int most = C::kRow <= 1024 ? 3 : (C::kMfma && C::P <= 2 ? 2 : 1);
+    return N <= (int64_t)most * C::G;
+}
+
 template <class C>
 static int launch_backward(const void* dy, const void* x, const float* alpha, void* dx, float* dalpha,
                            float* dbeta, int64_t N, void* workspace, hipStream_t stream) {
     using T = typename C::io::elem_t;
     const bool grads = dalpha != nullptr;
-    const int grid = grid_for<C>(N, grads);      // dx alone streams like a forward pass
+    const bool direct = grads && one_workgroup<C>(N);
+    const int grid = direct ? 1 : grid_for<C>(N, grads);      // dx alone streams like a forward pass
+    float* ws = static_cast<float*>(workspace);
+    const SumRows sums = direct ? SumRows{dalpha, dbeta, 0} : SumRows{ws, ws + C::kRow, 2 * C::kRow};
 
     if constexpr (C::kWave) {
         const T *dyp = static_cast<const T*>(dy), *xp = static_cast<const T*>(x);
         if (grads && dx)
             hipLaunchKernelGGL((backward_wave_kernel<C, true, true>), dim3(grid), dim3(C::BT), 0, stream, dyp, xp, alpha,
-                               static_cast<T*>(dx), static_cast<float*>(workspace), N);
+                               static_cast<T*>(dx), sums, N);
         else if (grads)
             hipLaunchKernelGGL((backward_wave_kernel<C, true, false>), dim3(grid), dim3(C::BT), 0, stream, dyp, xp, alpha,
-                               static_cast<T*>(nullptr), static_cast<float*>(workspace), N);
+                               static_cast<T*>(nullptr), sums, N);
         else
             hipLaunchKernelGGL((backward_wave_kernel<C, false, true>), dim3(grid), dim3(C::BT), 0, stream, dyp,
-                               static_cast<const T*>(nullptr), alpha, static_cast<T*>(dx), static_cast<float*>(nullptr), N);
+                               static_cast<const T*>(nullptr), alpha, static_cast<T*>(dx), sums, N);
     } else if (grads && dx) {
         if constexpr (C::kBwdTeams)
             hipLaunchKernelGGL((backward_teams_kernel<C>), dim3(grid), dim3(3 * C::BT), 0, stream,
                                static_cast<const T*>(dy), static_cast<const T*>(x), alpha, static_cast<T*>(dx),
-                               static_cast<float*>(workspace), N);
+                               sums, N);
         else
             hipLaunchKernelGGL((backward_kernel<C, true, true>), dim3(grid), dim3(C::BT), 0, stream,
                                static_cast<const T*>(dy), static_cast<const T*>(x), alpha, static_cast<T*>(dx),
-                               static_cast<float*>(workspace), N);
+                               sums, N);
     } else if (grads)
         hipLaunchKernelGGL((backward_kernel<C, true, false>), dim3(grid), dim3(C::BT), 0, stream,
                            static_cast<const T*>(dy), static_cast<const T*>(x), alpha, static_cast<T*>(nullptr),
-                           static_cast<float*>(workspace), N);
+                           sums, N);
     else
         hipLaunchKernelGGL((backward_kernel<C, false, true>), dim3(grid), dim3(C::BT), 0, stream,
                            static_cast<const T*>(dy), static_cast<const T*>(nullptr), alpha, static_cast<T*>(dx),
-                           static_cast<float*>(nullptr), N);
+                           sums, N);
     if (hipGetLastError() != hipSuccess) return WHT_ERR_LAUNCH;
-    if (!grads) return WHT_OK;
+    if (!grads || direct) return WHT_OK;
     if constexpr (C::kRow >= 4096)
         hipLaunchKernelGGL(reduce_partials_kernel<16>, dim3((C::kRow + 63) / 64, 2), dim3(1024), 0, stream,
-                           static_cast<const float*>(workspace), grid, C::kRow, dalpha, dbeta);
+                           ws, grid, C::kRow, dalpha, dbeta);
     else
         hipLaunchKernelGGL(reduce_partials_kernel<4>, dim3((C::kRow + 15) / 16, 2), dim3(1024), 0, stream,
-                           static_cast<const float*>(workspace), grid, C::kRow, dalpha, dbeta);
+                           ws, grid, C::kRow, dalpha, dbeta);
     return hipGetLastError() == hipSuccess ? WHT_OK : WHT_ERR_LAUNCH;
 }
 

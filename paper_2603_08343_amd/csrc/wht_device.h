@@ -858,6 +858,17 @@ __device__ __forceinline__ float inv_sqrt_d() {
 // (persistent grid).  Inputs of group k+1 are in flight (LDS-direct loads) while group k is
 // computed.  A ragged last group re-reads the last token (clamped row) and masks its stores.
 
+// Where a backward kernel's workgroup writes its sums: rows of the workspace ([grid][2][kRow]), or, for a
+// single workgroup, dalpha and dbeta themselves.
+struct SumRows {
+    float* dalpha;
+    float* dbeta;
+    int stride;                     // floats between the rows of consecutive workgroups
+    __device__ __forceinline__ float* row(int which) const {
+        return (which == 0 ? dalpha : dbeta) + (size_t)blockIdx.x * stride;
+    }
+};
+
 template <class C>
 struct Walker {
     int64_t N, groups;
@@ -1071,7 +1082,7 @@ __global__ __launch_bounds__(C::BT) void backward_kernel(const typename C::io::e
                                                          const typename C::io::elem_t* x,
                                                          const float* __restrict__ alpha,
                                                          typename C::io::elem_t* dx,
-                                                         float* __restrict__ partials,   // [grid][2][kRow]
+                                                         SumRows sums,
                                                          int64_t N) {
     static_assert(GRADS || DX, "nothing to compute");
     __shared__ __align__(16) float lds[C::kExchangeBytes / 4];
@@ -1156,9 +1167,9 @@ __global__ __launch_bounds__(C::BT) void backward_kernel(const typename C::io::e
     // Sum the G token slots of this workgroup through LDS, then write the workgroup's row.
     if constexpr (C::G > 1) __syncthreads();      // the last exchange's reads are done everywhere
     const float s = inv_sqrt_d<C>();
-    float* row = partials + (size_t)blockIdx.x * 2 * C::kRow;
 #pragma unroll
     for (int which = 0; which < 2; ++which) {
+        float* row = sums.row(which);
         if constexpr (C::G == 1) {
             static_for<0, C::E / 4>([&](auto i) {
                 constexpr int I = decltype(i)::value * 4;
@@ -1166,7 +1177,7 @@ __global__ __launch_bounds__(C::BT) void backward_kernel(const typename C::io::e
                 const float4 q = which == 0 ? make_float4(da[I] * s, da[I + 1] * s, da[I + 2] * s, da[I + 3] * s)
                                             : make_float4(db[I], db[I + 1], db[I + 2], db[I + 3]);
                 if (!C::kTwelve || tm.last_ok)
-                    *reinterpret_cast<float4*>(row + which * C::kRow + tm.last_elem + off) = q;
+                    *reinterpret_cast<float4*>(row + tm.last_elem + off) = q;
             });
         } else {
             if (which == 0) lds_put<C, LAST>(da, lds + tm.lds_off[LAST]);
@@ -1176,7 +1187,7 @@ __global__ __launch_bounds__(C::BT) void backward_kernel(const typename C::io::e
                 float acc = 0.0f;
 #pragma unroll
                 for (int gslot = 0; gslot < C::G; ++gslot) acc += lds[gslot * C::kTokenWords + C::phys(j)];
-                if (C::valid(j)) row[which * C::kRow + C::real(j)] = which == 0 ? acc * s : acc;
+                if (C::valid(j)) row[C::real(j)] = which == 0 ? acc * s : acc;
             }
             __syncthreads();
         }
@@ -1274,7 +1285,7 @@ template <class C, bool GRADS, bool DX>
 __global__ __launch_bounds__(C::BT, C::kBwdWavesPerSimd)
 void backward_wave_kernel(const typename C::io::elem_t* dy, const typename C::io::elem_t* x,
                           const float* __restrict__ alpha, typename C::io::elem_t* dx,
-                          float* __restrict__ partials,   // [grid][2][kRow]
+                          SumRows sums,
                           int64_t N) {
     static_assert(GRADS || DX, "nothing to compute");
     constexpr int LAST = C::P - 1;
@@ -1385,11 +1396,11 @@ void backward_wave_kernel(const typename C::io::elem_t* dy, const typename C::io
     }
     if constexpr (GRADS) {
         // the token slots of the workgroup, added in slot order through LDS that is idle now
-        float* sums = SPLIT ? lds : reinterpret_cast<float*>(stage_buf);
-        float* row = partials + (size_t)blockIdx.x * 2 * C::kRow;
+        float* slots = SPLIT ? lds : reinterpret_cast<float*>(stage_buf);
         const float s = inv_sqrt_d<C>();
 #pragma unroll
         for (int which = 0; which < 2; ++which) {
+            float* row = sums.row(which);
             if (which == 0) {
 #pragma unroll
                 for (int i = 0; i < C::E; ++i) da[i] *= tm.sign;
@@ -1400,13 +1411,13 @@ void backward_wave_kernel(const typename C::io::elem_t* dy, const typename C::io
                     constexpr unsigned off = reg_elem_offset(C::plan.ph[LAST], C::e, I);
                     const float4 q = which == 0 ? make_float4(da[I] * s, da[I + 1] * s, da[I + 2] * s, da[I + 3] * s)
                                                 : make_float4(db[I], db[I + 1], db[I + 2], db[I + 3]);
-                    *reinterpret_cast<float4*>(row + which * C::kRow + tm.last_elem + off) = q;
+                    *reinterpret_cast<float4*>(row + tm.last_elem + off) = q;
                 });
                 continue;
             }
             __syncthreads();
-            if (which == 0) lds_put<C, LAST>(da, sums + tm.lds_off[LAST]);
-            else            lds_put<C, LAST>(db, sums + tm.lds_off[LAST]);
+            if (which == 0) lds_put<C, LAST>(da, slots + tm.lds_off[LAST]);
+            else            lds_put<C, LAST>(db, slots + tm.lds_off[LAST]);
             __syncthreads();
             for (unsigned j = threadIdx.x; j < (unsigned)C::D; j += C::BT) {
                 constexpr int CHAINS = C::G < 8 ? C::G : 8;    // short chains: less rounding, reads in flight
@@ -1414,12 +1425,12 @@ void backward_wave_kernel(const typename C::io::elem_t* dy, const typename C::io
 #pragma unroll
                 for (int c = 0; c < CHAINS; ++c) acc[c] = 0.0f;
 #pragma unroll
-                for (int gslot = 0; gslot < C::G; ++gslot) acc[gslot % CHAINS] += sums[gslot * C::kTokenWords + j];
+                for (int gslot = 0; gslot < C::G; ++gslot) acc[gslot % CHAINS] += slots[gslot * C::kTokenWords + j];
 #pragma unroll
                 for (int half = CHAINS / 2; half >= 1; half /= 2)
 #pragma unroll
                     for (int c = 0; c < half; ++c) acc[c] += acc[c + half];
-                row[which * C::kRow + j] = which == 0 ? acc[0] * s : acc[0];
+                row[j] = which == 0 ? acc[0] * s : acc[0];
             }
         }
     }
@@ -1478,7 +1489,7 @@ __global__ __launch_bounds__(3 * C::BT) void backward_teams_kernel(const typenam
                                                                    const typename C::io::elem_t* x,
                                                                    const float* __restrict__ alpha,
                                                                    typename C::io::elem_t* dx,
-                                                                   float* __restrict__ partials,   // [grid][2][kRow]
+                                                                   SumRows sums,
                                                                    int64_t N) {
     static_assert(3 * C::BT <= 1024, "three teams must fit one workgroup");
     static_assert(C::kMfma && C::P == 2, "one exchange per transform");
@@ -1539,7 +1550,7 @@ __global__ __launch_bounds__(3 * C::BT) void backward_teams_kernel(const typenam
             for (int i = 0; i < C::E; ++i) da[i] = fmaf(g[i], r[i], da[i]);
             exchange_barrier();                                 // B2(k)
         }
-        write_partial_row<C>(da, lds_x, partials + (size_t)blockIdx.x * 2 * C::kRow, inv_sqrt_d<C>(), tid, tm);
+        write_partial_row<C>(da, lds_x, sums.row(0), inv_sqrt_d<C>(), tid, tm);
     } else if (team == 1) {
         if (grp < wk.groups) stage_issue<C, LAST>(stage_g0, dy + wk.row(grp) * C::kRow, tm.last_elem, tm.last_ok);
         float a[C::E], db[C::E];
@@ -1568,7 +1579,7 @@ __global__ __launch_bounds__(3 * C::BT) void backward_teams_kernel(const typenam
         }
         // the stage buffers are idle now (same size as an exchange region)
         write_partial_row<C>(db, reinterpret_cast<float*>(&stage_g_buf[0][0]),
-                             partials + (size_t)blockIdx.x * 2 * C::kRow + C::kRow, 1.0f, tid, tm);
+                             sums.row(1), 1.0f, tid, tm);
     } else {
         HadamardB hb{}, hbp{};
         hb = make_hadamard_b();
