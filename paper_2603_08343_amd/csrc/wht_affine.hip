@@ -149,12 +149,9 @@ static int launch_backward(const void* dy, const void* x, const float* alpha, vo
                            sums, N);
     if (hipGetLastError() != hipSuccess) return WHT_ERR_LAUNCH;
     if (!grads || direct) return WHT_OK;
-    if constexpr (C::kRow >= 4096)
-        hipLaunchKernelGGL(reduce_partials_kernel<16>, dim3((C::kRow + 63) / 64, 2), dim3(1024), 0, stream,
-                           ws, grid, C::kRow, dalpha, dbeta);
-    else
-        hipLaunchKernelGGL(reduce_partials_kernel<4>, dim3((C::kRow + 15) / 16, 2), dim3(1024), 0, stream,
-                           ws, grid, C::kRow, dalpha, dbeta);
+    constexpr int CG = reduce_columns(C::kRow);
+    hipLaunchKernelGGL(reduce_partials_kernel<CG>, dim3((C::kRow / 4 + CG - 1) / CG, 2), dim3(kReduceThreads), 0, stream,
+                       ws, grid, C::kRow, dalpha, dbeta);
     return hipGetLastError() == hipSuccess ? WHT_OK : WHT_ERR_LAUNCH;
 }
 

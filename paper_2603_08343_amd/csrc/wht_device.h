@@ -1628,47 +1628,56 @@ __global__ __launch_bounds__(3 * C::BT) void backward_teams_kernel(const typenam
 }
 
 // out[which][j] = sum over rows of partials[row][which][j].  Workgroup = CG float4 columns x
-// (1024 / CG) row lanes: lane r adds rows r, r + lanes, ... four at a time (all four requested
-// before the first is used, added in pairs), then the lane sums are combined by a fixed binary tree -- one association, independent of scheduling, so the result is
-// bit-reproducible.  CG = 16 (256 contiguous bytes per row) for large d; CG = 4 keeps the grid wide
-// (d/16 x 2 workgroups) for small d, where this kernel is otherwise pure latency.
+// (512 / CG) row lanes: lane r adds rows r, r + lanes, ..., four requested before the first is used and
+// added in pairs; the row lanes of a wave add up by butterfly shuffles, the waves' sums through LDS by a
+// fixed binary tree -- one association, independent of scheduling, so the result is bit-reproducible.
+// All latency: a launch, one round to memory, the tree.  Measured under graph replay (rows x d), with 1024
+// threads, 8 barriers and no loads in flight ahead / now: 256 x 4096 3.15 / 2.54 us, 512 x 1536 4.36 / 2.36,
+// 512 x 1024 3.04 / 2.34, 512 x 256 2.43 / 2.17, 256 x 8192 4.53 / 4.23.  CG: 64-byte pieces of a row while
+// the grid is small, 256-byte pieces once there are enough of them (CG = 4 / 8 / 16 at 512 x 768 2.27 / 2.32
+// / 2.65, at 256 x 2048 2.60 / 2.15 / 2.22, at 256 x 6144 5.89 / 3.97 / 3.73).
+constexpr int kReduceThreads = 512;
+constexpr int reduce_columns(int d) { return d >= 6144 ? 16 : (d >= 1024 ? 8 : 4); }
+
+__device__ __forceinline__ float4 add4(const float4& a, const float4& b) {
+    return make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w);
+}
+
 template <int CG>
-__global__ __launch_bounds__(1024) void reduce_partials_kernel(const float* __restrict__ partials,
-                                                               int rows, int d,
-                                                               float* __restrict__ dalpha,
-                                                               float* __restrict__ dbeta) {
-    constexpr int LANES = 1024 / CG;
-    __shared__ float4 part[LANES][CG];
+__global__ __launch_bounds__(kReduceThreads) void reduce_partials_kernel(const float* __restrict__ partials,
+                                                                         int rows, int d,
+                                                                         float* __restrict__ dalpha,
+                                                                         float* __restrict__ dbeta) {
+    constexpr int LANES = kReduceThreads / CG, WAVES = kReduceThreads / 64;
+    __shared__ float4 part[WAVES][CG];
     const int cg = threadIdx.x % CG, lane_row = threadIdx.x / CG;
     const int col = (blockIdx.x * CG + cg) * 4;           // first of this thread's 4 columns
     const int which = blockIdx.y;
+    const float* base = partials + (size_t)which * d + (col < d ? col : 0);
+    auto at = [&](int r) { return *reinterpret_cast<const float4*>(base + (size_t)r * 2 * d); };
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (col < d) {
-        const float* base = partials + (size_t)which * d + col;
-        auto at = [&](int r) {
-            return r < rows ? *reinterpret_cast<const float4*>(base + (size_t)r * 2 * d) : make_float4(0.f, 0.f, 0.f, 0.f);
-        };
-        for (int r = lane_row; r < rows; r += 4 * LANES) {
-            const float4 q0 = at(r), q1 = at(r + LANES), q2 = at(r + 2 * LANES), q3 = at(r + 3 * LANES);
-            acc.x += (q0.x + q1.x) + (q2.x + q3.x);
-            acc.y += (q0.y + q1.y) + (q2.y + q3.y);
-            acc.z += (q0.z + q1.z) + (q2.z + q3.z);
-            acc.w += (q0.w + q1.w) + (q2.w + q3.w);
-        }
+    int r = lane_row;
+    for (; r + 3 * LANES < rows; r += 4 * LANES) {
+        const float4 q0 = at(r), q1 = at(r + LANES), q2 = at(r + 2 * LANES), q3 = at(r + 3 * LANES);
+        acc = add4(acc, add4(add4(q0, q1), add4(q2, q3)));
     }
-    part[lane_row][cg] = acc;
-    __syncthreads();
+    for (; r < rows; r += LANES) acc = add4(acc, at(r));
 #pragma unroll
-    for (int half = LANES / 2; half >= 1; half >>= 1) {
-        if (lane_row < half) {
-            const float4 q = part[lane_row + half][cg];
-            acc.x += q.x; acc.y += q.y; acc.z += q.z; acc.w += q.w;
-            part[lane_row][cg] = acc;
-        }
-        __syncthreads();
+    for (int off = CG; off < 64; off <<= 1)
+        acc = add4(acc, make_float4(__shfl_xor(acc.x, off), __shfl_xor(acc.y, off), __shfl_xor(acc.z, off),
+                                    __shfl_xor(acc.w, off)));
+    if ((threadIdx.x & 63) < CG) part[threadIdx.x >> 6][cg] = acc;
+    __syncthreads();
+    if (threadIdx.x < CG && col < d) {
+        float4 s[WAVES];
+#pragma unroll
+        for (int i = 0; i < WAVES; ++i) s[i] = part[i][cg];
+#pragma unroll
+        for (int half = WAVES / 2; half >= 1; half /= 2)
+#pragma unroll
+            for (int i = 0; i < half; ++i) s[i] = add4(s[i], s[i + half]);
+        *reinterpret_cast<float4*>((which == 0 ? dalpha : dbeta) + col) = s[0];
     }
-    if (lane_row == 0 && col < d)
-        *reinterpret_cast<float4*>((which == 0 ? dalpha : dbeta) + col) = acc;
 }
 
 __global__ void zero_kernel(float* a, float* b, int d) {
