@@ -858,6 +858,21 @@ __device__ __forceinline__ float inv_sqrt_d() {
 // (persistent grid).  Inputs of group k+1 are in flight (LDS-direct loads) while group k is
 // computed.  A ragged last group re-reads the last token (clamped row) and masks its stores.
 
+// Four sums of a partial row.  Every workgroup writes its row at the end of the kernel, and rows that lie
+// dirty in L2 are written back before the next kernel adds them up: rows of 2048 to 4096 columns are streamed
+// past the caches instead (256 rows of 4096: 12.6 -> 11.0 us for the call, of 2048: 10.0 -> 9.4).  Shorter
+// rows and rows of 8192 measured no gain, and a call of few rows loses 0.2 us.
+template <int ROW>
+__device__ __forceinline__ void put_sums(float* out, const float4& q) {
+    const u32x4 v = {__float_as_uint(q.x), __float_as_uint(q.y), __float_as_uint(q.z), __float_as_uint(q.w)};
+    if constexpr (ROW >= 2048 && ROW <= 4096) __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(out));
+    else *reinterpret_cast<u32x4*>(out) = v;
+}
+
+__device__ __forceinline__ float4 add4(const float4& a, const float4& b) {
+    return make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w);
+}
+
 // Where a backward kernel's workgroup writes its sums: rows of the workspace ([grid][2][kRow]), or, for a
 // single workgroup, dalpha and dbeta themselves.
 struct SumRows {
@@ -1063,6 +1078,62 @@ __global__ __launch_bounds__(C::BT) void forward_once_kernel(const typename C::i
     global_put<C, LAST, false>(r, y + tok * C::kRow, tm.last_elem, tok < N && tm.last_ok);
 }
 
+// The sums of a workgroup's G token slots (in LDS, one region of kTokenWords floats each) added up, times
+// `scale`, to its row: four columns per thread at a time (one where there are more threads than that), the
+// slots in up to eight chains that are combined by a fixed tree (short chains: less rounding, LDS reads in
+// flight).  Four columns against one, and 16-byte stores against 4-byte ones, at 32768 x 1536: 63.4 against
+// 68.7 us for the call.
+template <class C>
+__device__ __forceinline__ void add_token_slots(float* out, const float* slots, unsigned tid, float scale) {
+    constexpr int CHAINS = C::G < 8 ? C::G : 8;
+    if constexpr (C::D >= 4 * C::BT) {
+        for (unsigned j = 4 * tid; j < (unsigned)C::D; j += 4 * C::BT) {
+            float4 acc[CHAINS];
+#pragma unroll
+            for (int g = 0; g < C::G; ++g) {
+                const float4 q = *reinterpret_cast<const float4*>(slots + g * C::kTokenWords + C::phys(j));
+                acc[g % CHAINS] = g < CHAINS ? q : add4(acc[g % CHAINS], q);
+            }
+#pragma unroll
+            for (int half = CHAINS / 2; half >= 1; half /= 2)
+#pragma unroll
+                for (int c = 0; c < half; ++c) acc[c] = add4(acc[c], acc[c + half]);
+            if (C::valid(j))
+                put_sums<C::kRow>(out + C::real(j), make_float4(acc[0].x * scale, acc[0].y * scale, acc[0].z * scale,
+                                                                acc[0].w * scale));
+        }
+    } else {
+        for (unsigned j = tid; j < (unsigned)C::D; j += C::BT) {
+            float acc[CHAINS];
+#pragma unroll
+            for (int g = 0; g < C::G; ++g) {
+                const float q = slots[g * C::kTokenWords + C::phys(j)];
+                acc[g % CHAINS] = g < CHAINS ? q : acc[g % CHAINS] + q;
+            }
+#pragma unroll
+            for (int half = CHAINS / 2; half >= 1; half /= 2)
+#pragma unroll
+                for (int c = 0; c < half; ++c) acc[c] += acc[c + half];
+            if (C::valid(j)) out[C::real(j)] = acc[0] * scale;
+        }
+    }
+}
+
+// A thread's sums (last layout) times `scale` straight to the row: for a padded row that is the workgroup's
+// only token, where the walk over the slots' memory offsets costs more than the 32-byte pieces.
+template <class C>
+__device__ __forceinline__ void put_thread_sums(const float (&acc)[C::E], float* out, float scale, const ThreadMap<C>& tm) {
+    static_for<0, C::E / 4>([&](auto i) {
+        constexpr int I = decltype(i)::value * 4;
+        constexpr unsigned off = C::real(reg_elem_offset(C::plan.ph[C::P - 1], C::e, I));
+        if (!C::kTwelve || tm.last_ok)
+            put_sums<C::kRow>(out + tm.last_elem + off,
+                              make_float4(acc[I] * scale, acc[I + 1] * scale, acc[I + 2] * scale, acc[I + 3] * scale));
+    });
+}
+template <class C>
+constexpr bool sums_through_lds() { return !(C::kTwelve && C::G == 1); }
+
 // backward:  z = H x (recomputed);  dalpha += dy z;  dbeta += dy;  dx = H_raw((alpha/sqrt d) dy)
 // Each workgroup keeps its dalpha/dbeta sums in registers and at the end writes one row of partial
 // sums; reduce_partials_kernel adds the rows in a fixed order, so the result does not depend on
@@ -1165,32 +1236,18 @@ __global__ __launch_bounds__(C::BT) void backward_kernel(const typename C::io::e
     }
     if constexpr (GRADS) {
     // Sum the G token slots of this workgroup through LDS, then write the workgroup's row.
-    if constexpr (C::G > 1) __syncthreads();      // the last exchange's reads are done everywhere
     const float s = inv_sqrt_d<C>();
 #pragma unroll
     for (int which = 0; which < 2; ++which) {
-        float* row = sums.row(which);
-        if constexpr (C::G == 1) {
-            static_for<0, C::E / 4>([&](auto i) {
-                constexpr int I = decltype(i)::value * 4;
-                constexpr unsigned off = C::real(reg_elem_offset(C::plan.ph[LAST], C::e, I));
-                const float4 q = which == 0 ? make_float4(da[I] * s, da[I + 1] * s, da[I + 2] * s, da[I + 3] * s)
-                                            : make_float4(db[I], db[I + 1], db[I + 2], db[I + 3]);
-                if (!C::kTwelve || tm.last_ok)
-                    *reinterpret_cast<float4*>(row + tm.last_elem + off) = q;
-            });
-        } else {
-            if (which == 0) lds_put<C, LAST>(da, lds + tm.lds_off[LAST]);
-            else            lds_put<C, LAST>(db, lds + tm.lds_off[LAST]);
-            __syncthreads();
-            for (unsigned j = threadIdx.x; j < (unsigned)C::D; j += C::BT) {
-                float acc = 0.0f;
-#pragma unroll
-                for (int gslot = 0; gslot < C::G; ++gslot) acc += lds[gslot * C::kTokenWords + C::phys(j)];
-                if (C::valid(j)) row[C::real(j)] = which == 0 ? acc * s : acc;
-            }
-            __syncthreads();
+        if constexpr (!sums_through_lds<C>()) {
+            put_thread_sums<C>(which == 0 ? da : db, sums.row(which), which == 0 ? s : 1.0f, tm);
+            continue;
         }
+        __syncthreads();                          // the last exchange, or the first sums, have been read everywhere
+        if (which == 0) lds_put<C, LAST>(da, lds + tm.lds_off[LAST]);
+        else            lds_put<C, LAST>(db, lds + tm.lds_off[LAST]);
+        __syncthreads();
+        add_token_slots<C>(sums.row(which), lds, threadIdx.x, which == 0 ? s : 1.0f);
     }
     }   // GRADS
 }
@@ -1406,60 +1463,29 @@ void backward_wave_kernel(const typename C::io::elem_t* dy, const typename C::io
                 for (int i = 0; i < C::E; ++i) da[i] *= tm.sign;
             }
             if constexpr (C::G == 1) {                         // one token per workgroup: straight to the row
-                static_for<0, C::E / 4>([&](auto i) {
-                    constexpr int I = decltype(i)::value * 4;
-                    constexpr unsigned off = reg_elem_offset(C::plan.ph[LAST], C::e, I);
-                    const float4 q = which == 0 ? make_float4(da[I] * s, da[I + 1] * s, da[I + 2] * s, da[I + 3] * s)
-                                                : make_float4(db[I], db[I + 1], db[I + 2], db[I + 3]);
-                    *reinterpret_cast<float4*>(row + tm.last_elem + off) = q;
-                });
+                put_thread_sums<C>(which == 0 ? da : db, row, which == 0 ? s : 1.0f, tm);
                 continue;
             }
             __syncthreads();
             if (which == 0) lds_put<C, LAST>(da, slots + tm.lds_off[LAST]);
             else            lds_put<C, LAST>(db, slots + tm.lds_off[LAST]);
             __syncthreads();
-            for (unsigned j = threadIdx.x; j < (unsigned)C::D; j += C::BT) {
-                constexpr int CHAINS = C::G < 8 ? C::G : 8;    // short chains: less rounding, reads in flight
-                float acc[CHAINS];
-#pragma unroll
-                for (int c = 0; c < CHAINS; ++c) acc[c] = 0.0f;
-#pragma unroll
-                for (int gslot = 0; gslot < C::G; ++gslot) acc[gslot % CHAINS] += slots[gslot * C::kTokenWords + j];
-#pragma unroll
-                for (int half = CHAINS / 2; half >= 1; half /= 2)
-#pragma unroll
-                    for (int c = 0; c < half; ++c) acc[c] += acc[c + half];
-                row[j] = which == 0 ? acc[0] * s : acc[0];
-            }
+            add_token_slots<C>(row, slots, threadIdx.x, which == 0 ? s : 1.0f);
         }
     }
 }
 
-// One team's per-thread sums (last layout) -> the workgroup's row out[kRow], times `scale`.  With
-// several token slots per workgroup the slots are added through `lds_sum` (an idle region of
-// G * kTokenWords floats), between two workgroup barriers that every wave of the workgroup passes.
+// One team's per-thread sums (last layout) -> the workgroup's row out[kRow], times `scale`, through `slots`
+// (an idle region of G * kTokenWords floats): with one workgroup barrier, which every wave passes.
 template <class C>
-__device__ __forceinline__ void write_partial_row(const float (&acc)[C::E], float* lds_sum, float* out,
+__device__ __forceinline__ void write_partial_row(const float (&acc)[C::E], float* slots, float* out,
                                                   float scale, unsigned tid, const ThreadMap<C>& tm) {
-    constexpr int LAST = C::P - 1;
-    if constexpr (C::G == 1) {
-        static_for<0, C::E / 4>([&](auto i) {
-            constexpr int I = decltype(i)::value * 4;
-            constexpr unsigned off = C::real(reg_elem_offset(C::plan.ph[LAST], C::e, I));
-            const float4 q = make_float4(acc[I] * scale, acc[I + 1] * scale, acc[I + 2] * scale, acc[I + 3] * scale);
-            if (!C::kTwelve || tm.last_ok) *reinterpret_cast<float4*>(out + tm.last_elem + off) = q;
-        });
+    if constexpr (sums_through_lds<C>()) {
+        lds_put<C, C::P - 1>(acc, slots + tm.lds_off[C::P - 1]);
+        __syncthreads();
+        add_token_slots<C>(out, slots, tid, scale);
     } else {
-        lds_put<C, LAST>(acc, lds_sum + tm.lds_off[LAST]);
-        __syncthreads();
-        for (unsigned j = tid; j < (unsigned)C::D; j += C::BT) {
-            float sum = 0.0f;
-#pragma unroll
-            for (int gslot = 0; gslot < C::G; ++gslot) sum += lds_sum[gslot * C::kTokenWords + C::phys(j)];
-            if (C::valid(j)) out[C::real(j)] = sum * scale;
-        }
-        __syncthreads();
+        put_thread_sums<C>(acc, out, scale, tm);
     }
 }
 
@@ -1617,13 +1643,13 @@ __global__ __launch_bounds__(3 * C::BT) void backward_teams_kernel(const typenam
             exchange_barrier();                                 // B2(k): token k is in the exchange region
             prev = grp;
         }
+        if constexpr (sums_through_lds<C>()) exchange_barrier();        // the barrier of the other teams' row writes
         if (prev >= 0) {
             float g[C::E];
             f32x16 d1[C::T];
             first_half(g, d1);
             second_half(g, d1, prev);
         }
-        if constexpr (C::G > 1) { __syncthreads(); __syncthreads(); }   // the other teams' closing barriers
     }
 }
 
@@ -1638,10 +1664,6 @@ __global__ __launch_bounds__(3 * C::BT) void backward_teams_kernel(const typenam
 // / 2.65, at 256 x 2048 2.60 / 2.15 / 2.22, at 256 x 6144 5.89 / 3.97 / 3.73).
 constexpr int kReduceThreads = 512;
 constexpr int reduce_columns(int d) { return d >= 6144 ? 16 : (d >= 1024 ? 8 : 4); }
-
-__device__ __forceinline__ float4 add4(const float4& a, const float4& b) {
-    return make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w);
-}
 
 template <int CG>
 __global__ __launch_bounds__(kReduceThreads) void reduce_partials_kernel(const float* __restrict__ partials,
