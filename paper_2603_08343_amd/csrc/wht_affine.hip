@@ -25,7 +25,12 @@ constexpr int kNumCU = 256;             // MI355X
 template <class C>
 static int grid_for(int64_t N, bool backward) {
     const int64_t groups = (N + C::G - 1) / C::G;
-    const int64_t cap = (int64_t)kNumCU * (backward ? C::kBwdGroupsPerCU : C::kFwdGroupsPerCU);
+    int per_cu = backward ? C::kBwdGroupsPerCU : C::kFwdGroupsPerCU;
+    // float32 d = 4096: up to three token groups per CU a second workgroup there costs more in partial rows
+    // than it saves (one / two per CU, us per call: N = 512 15.8 / 18.9, 768 18.9 / 19.2, 1024 22.2 / 21.9)
+    if constexpr (C::kWave)
+        if (backward && C::w == 1 && groups <= 3 * kNumCU) per_cu = 1;
+    const int64_t cap = (int64_t)kNumCU * per_cu;
     return (int)(groups < cap ? groups : cap);
 }
 
@@ -46,14 +51,16 @@ static int forward_cluster(int64_t N, int grid, bool resid) {
 //     12.0 against 13.3 us), 2^22 above, 2^21 for rows of 12 * 2^m elements;
 //   wave schedule: bfloat16 2^24 (65536 tokens of 256 elements: 12.7 against 13.3 us; twice that: 26.9
 //     against 23.9), float32 2^23 up to d = 2048 (8192 tokens of 1024: 11.7 against 12.8; twice that:
-//     25.3 against 23.3) and 2^21 above (1024 tokens of 4096: 8.4 against 7.6).
+//     25.3 against 23.3) and 2^21 above (1024 tokens of 4096: 8.4 against 7.6), 2^22 there with the
+//     residual add (600 tokens of 4096 with the statistic: 8.0 against 8.7).
 // Both kernels do the same arithmetic on a token in the same order, so the switch is invisible in y
 // (the norm statistic is summed in the order of the launch shape: its last bits may differ).
 template <class C>
-static bool few_tokens(int64_t N) {
+static bool few_tokens(int64_t N, bool resid) {
     constexpr int limit = C::kTwelve ? 21 : C::kMfma ? (C::n <= 11 ? 24 : 22)
                                           : C::v == 3 ? 24 : (C::n <= 11 ? 23 : 21);
-    return N * C::kRow <= (int64_t(1) << limit);
+    constexpr bool wide_f32 = C::kWave && C::v == 2 && C::n >= 12;
+    return N * C::kRow <= (int64_t(1) << (wide_f32 && resid ? limit + 1 : limit));
 }
 
 template <class C>
@@ -173,7 +180,7 @@ template <class CF, class CB = CF, class CO = CF>
 static int run(Op op, Args& a) {
     switch (op) {
     case Op::Forward:
-        if (few_tokens<CO>(a.N))
+        if (few_tokens<CO>(a.N, a.resid != nullptr))
             return launch_forward_once<CO>(a.x, a.alpha, a.beta, a.resid, a.y, a.sumsq, a.N, a.stream);
         return launch_forward<CF>(a.x, a.alpha, a.beta, a.resid, a.y, a.sumsq, a.N, a.stream);
     case Op::Backward: return launch_backward<CB>(a.dy, a.x, a.alpha, a.dx, a.dalpha, a.dbeta, a.N,

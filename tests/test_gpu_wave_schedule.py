@@ -41,6 +41,21 @@ def test_backward_around_a_workgroup_pass(d, dtype):
         assert bool(torch.isnan(buf[N].float()).all())
 
 
+@pytest.mark.parametrize("N", [257, 768, 769])
+def test_backward_where_the_grid_changes(N):
+    # float32 d = 4096: one workgroup per CU up to 768 tokens, two beyond
+    d = 4096
+    print(f"[wave] backward d={d} f32 N={N}", flush=True)
+    inp = synth.make_inputs(N, d, "f32", seed=N)
+    x, dy = to_gpu(inp.x, "f32"), to_gpu(inp.dy, "f32")
+    dx, da, db = wht.wht_affine_backward(dy, x, torch.from_numpy(inp.alpha).cuda(), dx=nan_filled(N, d, "f32"))
+    torch.cuda.synchronize()
+    rdx, rda, rdb = oracle.backward(inp.dy, inp.x, inp.alpha, "fast")
+    assert_io_close(dx, rdx, "f32", f"dx N={N}")
+    assert_grad_close(da, rda, f"dalpha N={N}")
+    assert_grad_close(db, rdb, f"dbeta N={N}")
+
+
 @pytest.mark.parametrize("d,dtype", F32 + BF16)
 def test_forward_kernels_agree_across_the_size_limit(d, dtype):
     limit = 1 << (24 if dtype == "bf16" else (23 if d <= 2048 else 21))
