@@ -190,9 +190,9 @@ static int run(Op op, Args& a) {
 }
 
 // Schedule choice: bfloat16 tokens of 1024 elements or more take the matrix-core schedule, the
-// rest the wave schedule, in which every stage is additions.  WHT_AFFINE_SCHEDULE=butterfly in the environment (read once per
-// process; the library's only environment variable) forces the wave schedule for those too:
-// it exists so that both schedules of one build can be tested and profiled against each other.
+// rest the wave schedule, in which every stage is additions.  WHT_AFFINE_SCHEDULE=butterfly in the
+// environment (read once per process; the library's only environment variable) forces the wave
+// schedule for those too: it exists so that both schedules of one build can be tested and profiled against each other.
 static bool use_mfma() {
     static const bool on = [] {
         const char* v = getenv("WHT_AFFINE_SCHEDULE");
