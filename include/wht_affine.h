@@ -43,8 +43,9 @@
  *     carries it to a relative error of at most 2^-17 (five hundred times finer than the bfloat16
  *     output's own rounding).  float32 tensors never take this path.
  *   - Non-finite inputs: NaN propagates.  An infinite input makes the token's outputs +-Inf or NaN
- *     with float32 tensors (Inf - Inf in a butterfly) and NaN with bfloat16 tensors of d >= 1024
- *     (the two-term representation of Inf is Inf + NaN).
+ *     with float32 tensors and bfloat16 tensors of d <= 512 (Inf - Inf in a butterfly) and NaN with
+ *     the other bfloat16 tensors (the two-term representation of Inf is Inf + NaN).  Other tokens'
+ *     outputs are not touched, and dalpha and dbeta take from it what their formulas say.
  *   - All tensor pointers must be 16-byte aligned.  y may alias x exactly, dx may alias dy or x
  *     exactly; partial overlap is undefined.
  *   - The return value is a wht_status_t.  Arguments are validated before anything is enqueued, so

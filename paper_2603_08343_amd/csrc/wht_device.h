@@ -558,6 +558,7 @@ constexpr int kStreamPolicy = 2;   // cache-policy operand of the load: "nt" (re
 typedef const __attribute__((address_space(1))) void* global_cptr;
 typedef __attribute__((address_space(3))) void* lds_ptr;
 
+//   ok: false in the padding lanes of a 12 * 2^m row, whose stage slots are never used.
 template <class C, int PH>
 __device__ __forceinline__ void stage_issue(unsigned char* wave_slot, const typename C::io::elem_t* row,
                                             unsigned thread_elem, bool ok) {
@@ -565,7 +566,6 @@ __device__ __forceinline__ void stage_issue(unsigned char* wave_slot, const type
         constexpr int Cc = decltype(c)::value;
         constexpr unsigned off = C::real(reg_elem_offset(C::plan.ph[PH], C::e, Cc * C::V));
         if constexpr (C::kTwelve) {
-            // padding lanes fetch nothing (their stage slots are never used); the others fetch
             // 32-byte pieces, two instructions per 128-byte line: cached, so the line is read once
             if (ok)
                 __builtin_amdgcn_global_load_lds((global_cptr)(row + thread_elem + off),
@@ -856,7 +856,8 @@ __device__ __forceinline__ float inv_sqrt_d() {
 // ------------------------------------------------------------------------------------------------
 // Kernels.  A workgroup holds G token slots of TPT threads each and strides over token groups
 // (persistent grid).  Inputs of group k+1 are in flight (LDS-direct loads) while group k is
-// computed.  A ragged last group re-reads the last token (clamped row) and masks its stores.
+// computed.  In a ragged last group a slot without a token re-reads the last token (clamped row), or reads
+// nothing where dx could be stored over that row meanwhile; its stores and its sums are left out.
 
 // Four sums of a partial row.  Every workgroup writes its row at the end of the kernel, and rows that lie
 // dirty in L2 are written back before the next kernel adds them up: rows of 2048 to 4096 columns are streamed
@@ -892,6 +893,13 @@ struct Walker {
     __device__ __forceinline__ int64_t row(int64_t grp) const {       // clamped: always a valid row
         const int64_t tok = token(grp);
         return tok < N ? tok : N - 1;
+    }
+    // Whether the slot fetches anything for group grp (matrix-core schedule: a slot is whole waves).  The
+    // clamped row of a slot without a token is another slot's, which the backward pass may overwrite (dx may
+    // alias x or dy); where no barrier keeps that store behind this read, the slot reads nothing.
+    __device__ __forceinline__ bool fetches(int64_t grp) const {
+        if constexpr (C::G == 1 || C::P > 1) return true;
+        else return grp * C::G + (unsigned)__builtin_amdgcn_readfirstlane(slot) < N;
     }
 };
 
@@ -1174,7 +1182,7 @@ __global__ __launch_bounds__(C::BT) void backward_kernel(const typename C::io::e
 
     const int64_t step = gridDim.x;
     int64_t grp = blockIdx.x;
-    if (grp < wk.groups) {
+    if (grp < wk.groups && wk.fetches(grp)) {
         if constexpr (GRADS) stage_issue<C, 0>(stage_x, x + wk.row(grp) * C::kRow, tm.first_elem, tm.first_ok);
         stage_issue<C, LAST>(stage_g, dy + wk.row(grp) * C::kRow, tm.last_elem, tm.last_ok);
     }
@@ -1195,7 +1203,7 @@ __global__ __launch_bounds__(C::BT) void backward_kernel(const typename C::io::e
         }
         stage_read<C>(graw, stage_g);
         zero_padding<C>(graw, tm.last_ok);
-        if (more) {
+        if (more && wk.fetches(grp + step)) {
             if constexpr (GRADS)
                 stage_issue<C, 0>(stage_x, x + wk.row(grp + step) * C::kRow, tm.first_elem, tm.first_ok);
             stage_issue<C, LAST>(stage_g, dy + wk.row(grp + step) * C::kRow, tm.last_elem, tm.last_ok);
@@ -1203,26 +1211,21 @@ __global__ __launch_bounds__(C::BT) void backward_kernel(const typename C::io::e
         float g[C::E];
         const int64_t tok = wk.token(grp);
         const bool active = C::G == 1 || tok < N;             // one slot per workgroup: never ragged
-        auto take_dy = [&]() {
-            unpack_all<C>(g, graw);
-            if constexpr (C::G > 1) {
-                if (!active) {                                // ragged last group: contribute nothing
-#pragma unroll
-                    for (int i = 0; i < C::E; ++i) g[i] = 0.0f;
-                }
-            }
-        };
         if constexpr (GRADS) {
             float r[C::E];
             transform_from_raw<C, !BOTH>(r, raw, lds, tm, hb, hb2);   // r = H_raw x, last layout
-            take_dy();
+            unpack_all<C>(g, graw);
+            // a slot of a ragged last group that has no token adds nothing, whatever its stage holds (a
+            // product with zero would do for finite values only)
+            if (active) {
 #pragma unroll
-            for (int i = 0; i < C::E; ++i) {
-                da[i] = fmaf(g[i], r[i], da[i]);              // 1/sqrt d applied once at the end
-                db[i] += g[i];
+                for (int i = 0; i < C::E; ++i) {
+                    da[i] = fmaf(g[i], r[i], da[i]);          // 1/sqrt d applied once at the end
+                    db[i] += g[i];
+                }
             }
         } else {
-            take_dy();
+            unpack_all<C>(g, graw);
         }
         if constexpr (DX) {
 #pragma unroll
@@ -1299,11 +1302,13 @@ struct WaveRows {
     int64_t base;                                   // element index of the wave's first row (clamped to a valid row)
     unsigned rel;                                   // this lane's row from there, in elements (clamped)
     bool active;                                    // this lane's token exists
+    bool any;                                       // the wave has a token (wave-uniform)
     bool whole;                                     // all W tokens of the wave exist (wave-uniform)
     __device__ __forceinline__ WaveRows(int64_t grp, int64_t N, unsigned wave, unsigned lane) {
         const int64_t tok0 = grp * C::G + (C::w > 0 ? wave >> C::w : wave * W);
         const int64_t left = N - tok0;              // tokens from the wave's first on, <= 0 past the end
         const unsigned sl = C::TPT < 64 ? lane / C::TPT : 0u;
+        any = left > 0;
         whole = left >= W;
         base = (left > 0 ? tok0 : N - 1) * C::kRow;
         const unsigned last = left >= W ? W - 1 : (left > 0 ? (unsigned)left - 1u : 0u);
@@ -1325,12 +1330,24 @@ __device__ __forceinline__ void wave_issue(unsigned char* wave_slot, const typen
     });
 }
 
+// Zeros for this lane's vectors of a wave's stage slot.
+template <class C>
+__device__ __forceinline__ void zero_stage(const unsigned char* wave_slot) {
+    const u32x4 zero = {0u, 0u, 0u, 0u};
+    const unsigned addr = lds_byte_address(wave_slot) + (threadIdx.x & 63u) * 16u;
+#pragma unroll
+    for (int c = 0; c < C::NV; ++c)
+        asm volatile("ds_write_b128 %0, %1 offset:%2" : : "v"(addr), "v"(zero), "n"(c * 1024) : "memory");
+}
+
 // backward of the wave schedule, which took the place of butterflies re-dealt two or three times through
 // LDS per transform (two one-word passes at d = 256; one wave per SIMD waiting on conflicting LDS accesses
 // at float32 d = 4096).  Bound by memory: 16384 x 4096 float32 in 131..135 us where the plain copy's rate
 // would take 130 (was 178..183); 65537 x 256 bfloat16 19.4 us against 16 (was 26.4); a stage costs one
 // vector instruction per value, between lanes as in registers.  With tokens inside a wave the four waves of a workgroup walk their
 // own tokens and never wait for one another: the loop has no barrier, and the transforms touch no LDS.
+// A wave past the last token therefore fetches nothing: the last row is another wave's, and that wave may
+// have stored dx over it (dx may alias x or dy).
 // A token of two or four waves is the workgroup's only one and has one exchange per transform.
 //
 // Per iteration k (x(k) and dy(k) have landed in the wave's stage slots):
@@ -1368,8 +1385,10 @@ void backward_wave_kernel(const typename C::io::elem_t* dy, const typename C::io
     int64_t grp = blockIdx.x;
     if (grp < groups) {
         const WaveRows<C> rows(grp, N, wave, lane);
-        if constexpr (GRADS) wave_issue<C, 0>(stage_x, x, rows, tm.first_elem);
-        wave_issue<C, LAST>(stage_g, dy, rows, tm.last_elem);
+        if (rows.any) {
+            if constexpr (GRADS) wave_issue<C, 0>(stage_x, x, rows, tm.first_elem);
+            wave_issue<C, LAST>(stage_g, dy, rows, tm.last_elem);
+        }
     }
     float a[DX ? C::E : 1], da[GRADS ? C::E : 1], db[GRADS ? C::E : 1];
     const float scale = inv_sqrt_d<C>() * tm.sign;             // the sign of dx's input and of z
@@ -1384,19 +1403,17 @@ void backward_wave_kernel(const typename C::io::elem_t* dy, const typename C::io
     for (; grp < groups; grp += step) {
         const bool more = grp + step < groups;
         const WaveRows<C> rows(grp, N, wave, lane), next(more ? grp + step : grp, N, wave, lane);
-        if (!rows.whole && !rows.active) {
-            // ragged last group: the clamped rows of missing tokens add nothing to the sums
-            const u32x4 zero = {0u, 0u, 0u, 0u};
-            const unsigned addr = lds_byte_address(stage_g) + lane * 16u;
-#pragma unroll
-            for (int c = 0; c < C::NV; ++c)
-                asm volatile("ds_write_b128 %0, %1 offset:%2" : : "v"(addr), "v"(zero), "n"(c * 1024) : "memory");
+        if (C::G > 1 && !rows.whole && !rows.active) {
+            // ragged last group: zeros for the missing tokens' x and dy, so that they add nothing to the sums
+            // (dy alone would do for finite x only)
+            zero_stage<C>(stage_g);
+            if constexpr (GRADS) zero_stage<C>(stage_x);
         }
         float r[C::E];
         if constexpr (GRADS) {
             uint4 raw[C::NV];
             stage_read<C>(raw, stage_x);
-            if (more) wave_issue<C, 0>(stage_x, x, next, tm.first_elem);
+            if (more && next.any) wave_issue<C, 0>(stage_x, x, next, tm.first_elem);
             unpack_all<C>(r, raw);
             wave_transform<C, true>(r, lds, tm);
             pin<C::E>(r);
@@ -1431,7 +1448,7 @@ void backward_wave_kernel(const typename C::io::elem_t* dy, const typename C::io
                 pin<COUNT>(r + B);
             }
         });
-        if (more) wave_issue<C, LAST>(stage_g, dy, next, tm.last_elem);
+        if (more && next.any) wave_issue<C, LAST>(stage_g, dy, next, tm.last_elem);
         if constexpr (DX) {
             wave_transform<C, false, wave_first_back_bit<C>()>(r, lds, tm);
             pin<C::E>(r);
@@ -1554,8 +1571,6 @@ __global__ __launch_bounds__(3 * C::BT) void backward_teams_kernel(const typenam
             stage_read<C>(raw, stage_x);
             zero_padding<C>(raw, tm.first_ok);
             if (more) stage_issue<C, 0>(stage_x, x + wk.row(grp + step) * C::kRow, tm.first_elem, tm.first_ok);
-            const int64_t tok = wk.token(grp);
-            const bool active = C::G == 1 || tok < N;
             float r[C::E], g[C::E];
             mfma_rounds_from_bf16<C>(r, raw, hb, hb2);
             run_stages<C, 0>(r);
@@ -1566,14 +1581,10 @@ __global__ __launch_bounds__(3 * C::BT) void backward_teams_kernel(const typenam
             zero_padding<C>(graw, tm.last_ok);
             run_stages<C, LAST>(r);
             unpack_all<C>(g, graw);
-            if constexpr (C::G > 1) {
-                if (!active) {
+            if (C::G == 1 || wk.token(grp) < N) {               // a ragged last group's clamped rows add nothing
 #pragma unroll
-                    for (int i = 0; i < C::E; ++i) g[i] = 0.0f;
-                }
+                for (int i = 0; i < C::E; ++i) da[i] = fmaf(g[i], r[i], da[i]);
             }
-#pragma unroll
-            for (int i = 0; i < C::E; ++i) da[i] = fmaf(g[i], r[i], da[i]);
             exchange_barrier();                                 // B2(k)
         }
         write_partial_row<C>(da, lds_x, sums.row(0), inv_sqrt_d<C>(), tid, tm);
