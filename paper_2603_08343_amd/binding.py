@@ -8,10 +8,12 @@ and raise WhtAffineError on a non-zero status.
 A tensor call on the current stream first goes to the extension module _torch_marshal
 (csrc/torch_marshal.cpp), which does the same checks and allocations in native code and hands back
 None for anything but a plain valid call; the code here then decides, and words the errors.  Per call,
-one token of 4096 bfloat16 elements with residual and statistic: 10.1 us here, 5.5 us there.
+one token of 4096 bfloat16 elements with residual and statistic: 10.1 us here, 5.5 us there.  Without
+the module (not built, or built for another torch) every call is taken here, after one warning.
 """
 import ctypes
 import os
+import warnings
 
 DTYPE_F32 = 0
 DTYPE_BF16 = 1
@@ -131,21 +133,33 @@ def _torch():
 _native_module = None
 
 
+class _NoNative:
+    """Stands in for the extension module where it cannot be used: declines every call."""
+    forward = backward = staticmethod(lambda *args: None)
+
+
+def _load_native(torch, lib):
+    current_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    try:
+        from . import _torch_marshal
+        built_for = getattr(_torch_marshal, "torch_version", "unknown")
+        if current_stream is None or built_for != str(torch.__version__):
+            raise ImportError(f"built for torch {built_for}, this is {torch.__version__}")
+    except ImportError as e:
+        warnings.warn(f"the extension module _torch_marshal cannot be used ({e}): tensor calls take about 5 us longer "
+                      "each; build it with `python -m paper_2603_08343_amd.build`", RuntimeWarning, stacklevel=4)
+        return _NoNative
+    names = ("wht_affine_forward", "wht_affine_forward_residual", "wht_affine_forward_residual_stats",
+             "wht_affine_backward_workspace_bytes", "wht_affine_backward", "wht_affine_backward_static")
+    _torch_marshal.bind(*(ctypes.cast(getattr(lib, n), ctypes.c_void_p).value for n in names), current_stream)
+    return _torch_marshal
+
+
 def _native():
     """The extension module, loaded and told the library's addresses on the first tensor call."""
     global _native_module
     if _native_module is None:
-        torch, lib = _torch(), library()
-        try:
-            from . import _torch_marshal
-        except ImportError as e:
-            raise RuntimeError("the extension module _torch_marshal is missing or does not fit this torch: build it "
-                               "with `python -m paper_2603_08343_amd.build`") from e
-        names = ("wht_affine_forward", "wht_affine_forward_residual", "wht_affine_forward_residual_stats",
-                 "wht_affine_backward_workspace_bytes", "wht_affine_backward", "wht_affine_backward_static")
-        _torch_marshal.bind(*(ctypes.cast(getattr(lib, n), ctypes.c_void_p).value for n in names),
-                            torch._C._cuda_getCurrentRawStream)
-        _native_module = _torch_marshal
+        _native_module = _load_native(_torch(), library())
     return _native_module
 
 

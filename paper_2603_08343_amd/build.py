@@ -3,6 +3,7 @@ marshalling (csrc/torch_marshal.cpp) into the extension module _torch_marshal.so
 
 hipcc cross-compiles without a GPU; the extension module takes the host compiler and torch's headers.  Run as `python -m paper_2603_08343_amd.build`.
 """
+import importlib.metadata
 import importlib.util
 import os
 import subprocess
@@ -50,6 +51,7 @@ def _compile_marshal(verbose: bool) -> None:
     lib_dir = os.path.join(torch_dir, "lib")
     cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
            "-isystem", os.path.join(torch_dir, "include"), "-isystem", sysconfig.get_paths()["include"],
+           f'-DWHT_TORCH_VERSION="{importlib.metadata.version("torch")}"',
            "-o", MARSHAL_LIB, MARSHAL_SRC, "-L" + lib_dir, "-ltorch_python", "-ltorch_cpu", "-lc10"]
     if verbose:
         print(" ".join(cmd), flush=True)

@@ -3,9 +3,10 @@
 // What bounds a decoding call is the host: in Python the checks, the output allocation and the ctypes
 // call took 8.0 us (forward), 10.1 us (forward + residual + statistic) and 16.4 us (backward), for
 // kernels of 2 to 3 us.  Here the same calls take 4.4, 5.5 and 10.3 us, of which a launch is 3.3 us
-// and an allocation 0.6 us.  These functions do the same for the calls that a program makes all the time -- plain tensors on the
-// current device and stream, all arguments valid -- and return None for every other call, which
-// binding.py then takes through its own code: the checks and their messages stand there, once.
+// and an allocation 0.6 us.  These functions do the same for the calls that a program makes all the
+// time -- plain tensors on the current device and stream, all arguments valid -- and return None for
+// every other call, which binding.py then takes through its own code: the checks and their messages
+// stand there, once.
 //
 //   None            not a call for this path (wrong type, shape, dtype, device, layout; no tokens; a
 //                   subclass or a wrapped tensor; an active torch function or dispatch mode)
@@ -252,4 +253,9 @@ PyModuleDef module_def = {PyModuleDef_HEAD_INIT, "_torch_marshal", nullptr, -1, 
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__torch_marshal(void) { return PyModule_Create(&module_def); }
+// torch_version: the torch this was compiled for (named by build.py); binding.py uses the module with no other.
+PyMODINIT_FUNC PyInit__torch_marshal(void) {
+    PyObject* m = PyModule_Create(&module_def);
+    if (m && PyModule_AddStringConstant(m, "torch_version", WHT_TORCH_VERSION) < 0) Py_CLEAR(m);
+    return m;
+}
