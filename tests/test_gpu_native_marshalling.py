@@ -139,10 +139,16 @@ def test_streams_modes_and_wrapped_tensors(monkeypatch):
     x, dy, r, a, b = _args()
     ref = wht.wht_affine_forward(x, a, b)
     side = torch.cuda.Stream()
-    side.wait_stream(torch.cuda.current_stream())
-    with torch.cuda.stream(side):                             # the current stream is the one the call goes to
-        y = wht.wht_affine_forward(x, a, b)
-    torch.cuda.current_stream().wait_stream(side)
+    # the current stream is the one the call goes to: there x gets its values only after a long fill, so a
+    # call on any other stream would read zeros
+    late, fill = torch.zeros_like(x), torch.empty(1 << 29, device="cuda")
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        fill.zero_()
+        fill.add_(1.0)
+        late.copy_(x)
+        y = wht.wht_affine_forward(late, a, b)
+    torch.cuda.synchronize()
     assert torch.equal(y, ref) and torch.equal(wht.wht_affine_forward(x, a, b, stream=side), ref)
     # a batched tensor (vmap) has no address: refused by both
     _same(lambda: torch.vmap(lambda t: wht.wht_affine_forward(t, a, b))(x.view(1, N, D)), monkeypatch, "vmap")

@@ -91,7 +91,7 @@ def test_backward_every_d(d, dtype):
 
 @pytest.mark.parametrize("d", TWELVE_D)
 def test_forward_twelve_widths(d):
-    # 67 / 9 tokens: ragged last pass for every tokens-per-workgroup value (4 at d = 768, else 1)
+    # 67 / 9 tokens: ragged last pass for every tokens-per-workgroup value (4, 2 or 1)
     N = 67 if d <= 1536 else 9
     _announce(f"forward d={d} (12 * 2^m) bf16 N={N}")
     inp = synth.make_inputs(N, d, "bf16", seed=d, backward=False)
@@ -176,27 +176,28 @@ def test_reduction_over_odd_token_counts(N, d, dtype):
     check_backward_full(synth.make_inputs(N, d, dtype, seed=N), f"bwd N={N} d={d}")
 
 
-@pytest.mark.parametrize("N", [2048, 2085, 4099])
-def test_forward_clustered_deal_with_ragged_regions(N):
-    # d = 8192 with at least 4 x 512 token groups: the forward kernels deal the groups to clusters of
-    # workgroups, each with its own contiguous region (four regions, two with the residual); token
-    # counts that do not divide evenly leave the last region short.  Every element is checked.
-    _announce(f"clustered forward d=8192 N={N}")
-    inp = synth.make_inputs(N, 8192, "bf16", seed=N)
-    x, resid = to_gpu(inp.x, "bf16"), to_gpu(inp.dy, "bf16")
+@pytest.mark.parametrize("d,dtype,N", [(8192, "bf16", 2048), (8192, "bf16", 2085), (8192, "bf16", 4099),
+                                       (8192, "f32", 2085), (4096, "f32", 2085), (1024, "f32", 8333)])
+def test_forward_clustered_deal_with_ragged_regions(d, dtype, N):
+    # at least 4 x 512 token groups: the forward kernels deal the groups to clusters of workgroups, each
+    # with its own contiguous region (two or four regions, two with the residual); token counts that do
+    # not divide evenly leave the last region short.  Every element is checked.
+    _announce(f"clustered forward d={d} {dtype} N={N}")
+    inp = synth.make_inputs(N, d, dtype, seed=N)
+    x, resid = to_gpu(inp.x, dtype), to_gpu(inp.dy, dtype)
     a, b = torch.from_numpy(inp.alpha).cuda(), torch.from_numpy(inp.beta).cuda()
     y = wht.wht_affine_forward(x, a, b)
     yr = wht.wht_affine_forward_residual(x, a, b, resid)
     torch.cuda.synchronize()
-    assert_io_close(y, oracle.forward(inp.x, inp.alpha, inp.beta, "fast"), "bf16", f"clustered y N={N}")
-    assert_io_close(yr, oracle.forward_residual(inp.x, inp.alpha, inp.beta, inp.dy, "fast"), "bf16",
-                    f"clustered y+resid N={N}")
+    assert_io_close(y, oracle.forward(inp.x, inp.alpha, inp.beta, "fast"), dtype, f"clustered y d={d} N={N}")
+    assert_io_close(yr, oracle.forward_residual(inp.x, inp.alpha, inp.beta, inp.dy, "fast"), dtype,
+                    f"clustered y+resid d={d} N={N}")
 
 
 def test_many_passes_per_workgroup():
     # more token groups than the grid cap: every workgroup loops several times, last pass ragged
     inp = synth.make_inputs(70005, 256, "bf16", seed=3)
-    _announce("grid-stride d=256 N=70005 (tokens per workgroup 32, 2188 groups)")
+    _announce("grid-stride d=256 N=70005 (16 tokens per workgroup, 4376 groups)")
     check_forward_full(inp, "fwd strided")
     inp2 = synth.make_inputs(140001, 64, "f32", seed=4)
     _announce("grid-stride d=64 N=140001")
@@ -206,21 +207,20 @@ def test_many_passes_per_workgroup():
 
 # ------------------------------------------------------------------ few tokens per call (decoding)
 #
-# Calls of up to 2^22 elements (2^24 for bfloat16 rows of 1024 and 2048 elements, 2^21 for d = 12 * 2^m)
-# run on a kernel of their own:
-# one token group per workgroup, no token loop.  The small cases above pass through it; the cases
-# here pin the decode shapes of the paper's Table 2 widths, the hand-over to the persistent kernel
-# and that kernel just above the limit, where it has the fewest passes per workgroup.
+# Calls of few elements run on a kernel of their own: one token group per workgroup, no token loop.  The
+# small cases above pass through it; the cases here pin the decode shapes of the paper's Table 2 widths,
+# the hand-over to the persistent kernel and that kernel just above the limit, where it has the fewest
+# passes per workgroup.
 
-def _few_token_limit(d, dtype="bf16"):
+def _few_token_limit(d, dtype="bf16", resid=False):
     """Largest N that runs the one-pass kernel (the library's rule, restated)."""
     if d % 3 == 0:
-        elems = 1 << 21
-    elif dtype == "bf16" and d in (1024, 2048):
-        elems = 1 << 24
+        log_elems = 21
+    elif dtype == "bf16":
+        log_elems = 24 if d <= 2048 else 22
     else:
-        elems = 1 << 22
-    return elems // d
+        log_elems = 23 if d <= 2048 else (22 if resid else 21)
+    return (1 << log_elems) // d
 
 
 @pytest.mark.parametrize("N", [1, 16, 64, 256])
@@ -268,17 +268,20 @@ def test_forward_on_both_sides_of_the_few_token_limit(d, dtype):
                        N, dtype, f"limit d={d} y")
 
 
-@pytest.mark.parametrize("d,dtype", [(256, "f32"), (512, "bf16"), (1024, "bf16"), (2048, "bf16"), (4096, "bf16"),
-                                     (768, "bf16"), (6144, "bf16"), (16384, "bf16"), (4096, "f32")])
+@pytest.mark.parametrize("d,dtype", [(d, "bf16") for d in (32, 64, 128, 256, 512, 1024, 2048, 4096, 768, 6144, 16384)] +
+                         [(d, "f32") for d in ALL_D[:-1]])
 def test_forward_residual_stats_above_the_few_token_limit(d, dtype):
-    # the persistent kernel's residual + statistic variant, ragged last group, every width class
-    N = _few_token_limit(d, dtype) + 37
+    # the persistent kernel's residual and residual + statistic variants, ragged last group, every width class
+    N = _few_token_limit(d, dtype, resid=True) + 37
     _announce(f"forward+residual+stats above the few-token limit d={d} {dtype} N={N}")
     inp = synth.make_inputs(N, d, dtype, seed=d + 13)
     x, resid = to_gpu(inp.x, dtype), to_gpu(inp.dy, dtype)
     a, b = torch.from_numpy(inp.alpha).cuda(), torch.from_numpy(inp.beta).cuda()
     y, ss = wht.wht_affine_forward_residual_stats(x, a, b, resid, y=nan_filled(N, d, dtype))
+    plain = wht.wht_affine_forward_residual(x, a, b, resid, y=nan_filled(N, d, dtype))
     torch.cuda.synchronize()
+    assert torch.equal(plain.view(torch.int16 if dtype == "bf16" else torch.int32),
+                       y.view(torch.int16 if dtype == "bf16" else torch.int32))
     got = to_f64(ss)
     for lo in range(0, N, CHUNK):
         hi = min(N, lo + CHUNK)
@@ -593,10 +596,12 @@ def test_autograd_module_matches_oracle(d, dtype):
 
 
 @pytest.mark.parametrize("d,dtype,N", [(64, "f32", 70), (512, "bf16", 131), (1024, "bf16", 263), (4096, "bf16", 35),
-                                       (8192, "bf16", 129), (768, "bf16", 67), (6144, "bf16", 9), (8192, "f32", 9)])
+                                       (8192, "bf16", 129), (768, "bf16", 67), (6144, "bf16", 9), (8192, "f32", 9),
+                                       (4096, "f32", 1031), (8192, "f32", 1031), (256, "f32", 8211), (512, "bf16", 8211)])
 def test_backward_with_outputs_left_out(d, dtype, N):
     """dx alone (frozen parameters) and the parameter gradients alone: the values must be those of
-    the full call, bit for bit, and hence the oracle's."""
+    the full call, bit for bit, and hence the oracle's.  The last four counts give a workgroup several
+    token groups in each of the three kernels (dx alone runs on up to four workgroups per CU)."""
     _announce(f"backward, optional outputs d={d} {dtype} N={N}")
     inp = synth.make_inputs(N, d, dtype, seed=d + 3)
     x, dy = to_gpu(inp.x, dtype), to_gpu(inp.dy, dtype)

@@ -3,9 +3,12 @@ of an exchange region or of a wave's own stage slot the thread overwrites what i
 read that comes before the data it is meant to see -- a missing barrier between a put and a get, a
 missing wait on a prefetch -- returns NaN there instead of the previous token group's plausible
 values, so the ordinary comparison against the oracle turns a synchronisation mistake into a hard
-failure.  Widths in this build: 512 (butterfly schedule, LDS re-deals), 4096 and 8192 (matrix-core
-schedule, one exchange; the three-team backward), 16384 (two exchanges in the backward), 6144
-(12 * 2^m rows), bf16 and, up to 8192, float32."""
+failure.  Widths in this build: bf16 4096 and 8192 (matrix-core schedule, one exchange; the three-team
+backward), 16384 (two exchanges in the backward), 6144 (12 * 2^m rows), 512 (wave schedule, no
+exchange), and float32 512, 4096 and 8192 (wave schedule with a token on part of one wave, on two and
+on four).  Token counts: past the few-token limit of the residual forward (2^24, 2^23, 2^22 or 2^21
+elements), and more token groups than any backward kernel has workgroups, so that every kernel refills
+its stages and re-uses its exchange region; 300 tokens of 512 run the one-pass forward kernel."""
 import ctypes
 
 import numpy as np
@@ -38,7 +41,8 @@ def poison_lib():
 
 
 @pytest.mark.parametrize("d,dtype,N", [(512, "bf16", 300), (512, "f32", 300), (4096, "bf16", 1031), (4096, "f32", 70),
-                                       (8192, "bf16", 700), (8192, "f32", 300), (16384, "bf16", 300), (6144, "bf16", 600)])
+                                       (8192, "bf16", 700), (8192, "f32", 300), (16384, "bf16", 600), (6144, "bf16", 600),
+                                       (512, "bf16", 32805), (512, "f32", 16421), (4096, "f32", 1061), (8192, "f32", 1061)])
 def test_poisoned_lds_build_matches_the_oracle(d, dtype, N):
     print(f"[poison] d={d} {dtype} N={N}", flush=True)
     lib = poison_lib()
@@ -60,8 +64,11 @@ def test_poisoned_lds_build_matches_the_oracle(d, dtype, N):
                                    N, d, code, ws.data_ptr(), need, stream) == 0
     dx_only = nan_filled(N, d, dtype)
     assert lib.wht_affine_backward(dy.data_ptr(), 0, a.data_ptr(), dx_only.data_ptr(), 0, 0, N, d, code, 0, 0, stream) == 0
+    da_only, db_only = torch.full((d,), float("nan"), device="cuda"), torch.full((d,), float("nan"), device="cuda")
+    assert lib.wht_affine_backward(dy.data_ptr(), x.data_ptr(), a.data_ptr(), 0, da_only.data_ptr(), db_only.data_ptr(),
+                                   N, d, code, ws.data_ptr(), need, stream) == 0
     torch.cuda.synchronize()
-    method = "matrix" if d <= 512 else "fast"
+    method = "matrix" if d <= 512 and N <= 300 else "fast"
     assert_io_close(y, oracle.forward(inp.x, inp.alpha, inp.beta, method), dtype, f"poison fwd d={d}")
     ref_yr, ref_ss = oracle.forward_residual_stats(inp.x, inp.alpha, inp.beta, inp.dy, method)
     assert_io_close(yr, ref_yr, dtype, f"poison fwd+resid d={d}")
@@ -71,3 +78,4 @@ def test_poisoned_lds_build_matches_the_oracle(d, dtype, N):
     assert_io_close(dx_only, rdx, dtype, f"poison bwd dx-only d={d}")
     assert_grad_close(da, rda, f"poison dalpha d={d}")
     assert_grad_close(db, rdb, f"poison dbeta d={d}")
+    assert torch.equal(da_only, da) and torch.equal(db_only, db)

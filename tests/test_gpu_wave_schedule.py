@@ -19,8 +19,12 @@ BF16 = [(1 << n, "bf16") for n in range(5, 10)]
 
 
 def _tokens_per_pass(d, dtype):
+    """256 threads of 16 values (an eighth of a short row, 32 where 64 lanes of 16 would not hold the row);
+    one token where it takes two or four waves.  The library's rule, restated."""
     per_lane = min(16, max(d // 8, 4 if dtype == "f32" else 8))
-    return max(1, 256 * per_lane // d)
+    if d > 64 * per_lane:
+        per_lane = 32
+    return 256 * per_lane // d if d <= 64 * per_lane else 1
 
 
 @pytest.mark.parametrize("d,dtype", F32 + BF16)
