@@ -1,7 +1,8 @@
 """Compile the HIP library (csrc/wht_affine.hip) for gfx950 into libwht_affine.so, and the tensor calls'
 marshalling (csrc/torch_marshal.cpp) into the extension module _torch_marshal.so, in-tree.
 
-hipcc cross-compiles without a GPU; the extension module takes the host compiler and torch's headers.  Run as `python -m paper_2603_08343_amd.build`.
+hipcc cross-compiles without a GPU; the extension module takes the host compiler and torch's headers.
+Run as `python -m paper_2603_08343_amd.build`.
 """
 import importlib.metadata
 import importlib.util
@@ -35,8 +36,8 @@ HIPCC_FLAGS = [
     "-mllvm", "-amdgpu-mfma-vgpr-form=1",
     "-Wall", "-Wno-unused-function",
 ]
-SOURCES = [SRC] + [os.path.join(HERE, "csrc", f) for f in ("wht_device.h", "wht_plan.h")] + \
-          [os.path.join(os.path.dirname(HERE), "include", "wht_affine.h")]
+HEADER = os.path.join(os.path.dirname(HERE), "include", "wht_affine.h")
+SOURCES = [SRC, HEADER] + [os.path.join(HERE, "csrc", f) for f in ("wht_device.h", "wht_plan.h", "wht_validate.h")]
 
 
 def build(verbose: bool = False, extra=()) -> str:
@@ -78,7 +79,7 @@ def ensure_built(verbose: bool = False) -> str:
     The binding itself never builds: a missing library is an error there."""
     if not all(os.path.exists(lib) for lib in (LIB, COPY_LIB, POISON_LIB, MARSHAL_LIB)):
         build(verbose=verbose)
-    elif os.path.getmtime(MARSHAL_SRC) > os.path.getmtime(MARSHAL_LIB):
+    elif any(os.path.getmtime(f) > os.path.getmtime(MARSHAL_LIB) for f in (MARSHAL_SRC, HEADER)):
         raise RuntimeError(f"{MARSHAL_LIB} is older than its source: run `python -m paper_2603_08343_amd.build`")
     elif any(os.path.getmtime(f) > min(os.path.getmtime(LIB), os.path.getmtime(POISON_LIB))
              for f in SOURCES if os.path.exists(f)):
