@@ -36,10 +36,6 @@ typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 // x, dy are read once and y, dx written once: stream them past the caches (non-temporal).
-__device__ __forceinline__ uint4 stream_load16(const void* p) {
-    const u32x4 v = __builtin_nontemporal_load(static_cast<const u32x4*>(p));
-    return make_uint4(v.x, v.y, v.z, v.w);
-}
 __device__ __forceinline__ void stream_store16(void* p, const uint4& q) {
     const u32x4 v = {q.x, q.y, q.z, q.w};
     __builtin_nontemporal_store(v, static_cast<u32x4*>(p));
@@ -108,6 +104,7 @@ struct MfmaCfg {
     static_assert(n >= 10 && w >= 0 && w <= 2 * (1 + t) && e <= kMaxRegBits, "bad tile");
     static constexpr PlanDesc plan = make_mfma_plan(n, t);
     static_assert(plan_is_complete(plan), "every stage must run exactly once");
+    static_assert(plan_keeps_vectors(plan), "16 bytes per LDS access");
     static constexpr int P = plan.nphase;
     static constexpr int D = 1 << n;
     static constexpr int E = 1 << e;
@@ -157,12 +154,13 @@ struct MfmaCfg {
 template <int LOGD, int LOGE, class Io>
 struct WaveCfg {
     using io = Io;
-    static constexpr bool kMfma = false, kWave = true, kTwelve = false, kBwdTeams = false;
+    static constexpr bool kMfma = false, kWave = true, kTwelve = false;
     static constexpr int n = LOGD, e = LOGE, v = Io::kLogVec;
     static constexpr int L = n - e < 6 ? n - e : 6, w = n - e - L;    // log2 lanes of a wave, waves per token
     static_assert(wave_fits(n, e, v), "bad tile");
     static constexpr PlanDesc plan = make_wave_plan(n, e, v);
     static_assert(plan_is_complete(plan), "every butterfly stage must run exactly once");
+    static_assert(plan_keeps_vectors(plan), "16 bytes per LDS access");
     static constexpr int P = plan.nphase;
     static constexpr int D = 1 << n;
     static constexpr int E = 1 << e;
@@ -244,7 +242,7 @@ __device__ __forceinline__ void run_stages(float (&r)[C::E]) {
     });
 }
 
-// Debug build (WHT_POISON_LDS, used by csrc/poison_check.hip only): a thread that has read its
+// Debug build (WHT_POISON_LDS, loaded by one GPU test only): a thread that has read its
 // values from an exchange region or from its own stage slot overwrites them with NaN.  A read that
 // comes too early -- before the data it is meant to see has been written or has landed, i.e. a
 // missing barrier or a missing wait -- then returns NaN instead of last iteration's plausible
@@ -255,44 +253,25 @@ constexpr bool kPoisonLds = true;
 constexpr bool kPoisonLds = false;
 #endif
 
-template <class C, int PH>
-constexpr bool phase_is_vec4() { return C::plan.ph[PH].rb[0] == 0 && C::plan.ph[PH].rb[1] == 1; }
-
 // Registers <-> LDS in the layout of phase PH.  `tok` points at this token's LDS region plus the
 // thread's own (runtime) offset; register offsets are compile-time immediates.
 template <class C, int PH>
 __device__ __forceinline__ void lds_put(const float (&r)[C::E], float* tok) {
-    if constexpr (phase_is_vec4<C, PH>()) {
-        static_for<0, C::E / 4>([&](auto i) {
-            constexpr int I = decltype(i)::value * 4;
-            constexpr unsigned off = C::phys(reg_elem_offset(C::plan.ph[PH], C::e, I));
-            *reinterpret_cast<float4*>(tok + off) = make_float4(r[I], r[I + 1], r[I + 2], r[I + 3]);
-        });
-    } else {
-        static_for<0, C::E>([&](auto i) {
-            constexpr int I = decltype(i)::value;
-            constexpr unsigned off = C::phys(reg_elem_offset(C::plan.ph[PH], C::e, I));
-            tok[off] = r[I];
-        });
-    }
+    static_for<0, C::E / 4>([&](auto i) {
+        constexpr int I = decltype(i)::value * 4;
+        constexpr unsigned off = C::phys(reg_elem_offset(C::plan.ph[PH], C::e, I));
+        *reinterpret_cast<float4*>(tok + off) = make_float4(r[I], r[I + 1], r[I + 2], r[I + 3]);
+    });
 }
 
 template <class C, int PH>
 __device__ __forceinline__ void lds_get(float (&r)[C::E], const float* tok) {
-    if constexpr (phase_is_vec4<C, PH>()) {
-        static_for<0, C::E / 4>([&](auto i) {
-            constexpr int I = decltype(i)::value * 4;
-            constexpr unsigned off = C::phys(reg_elem_offset(C::plan.ph[PH], C::e, I));
-            const float4 q = *reinterpret_cast<const float4*>(tok + off);
-            r[I] = q.x; r[I + 1] = q.y; r[I + 2] = q.z; r[I + 3] = q.w;
-        });
-    } else {
-        static_for<0, C::E>([&](auto i) {
-            constexpr int I = decltype(i)::value;
-            constexpr unsigned off = C::phys(reg_elem_offset(C::plan.ph[PH], C::e, I));
-            r[I] = tok[off];
-        });
-    }
+    static_for<0, C::E / 4>([&](auto i) {
+        constexpr int I = decltype(i)::value * 4;
+        constexpr unsigned off = C::phys(reg_elem_offset(C::plan.ph[PH], C::e, I));
+        const float4 q = *reinterpret_cast<const float4*>(tok + off);
+        r[I] = q.x; r[I + 1] = q.y; r[I + 2] = q.z; r[I + 3] = q.w;
+    });
     if constexpr (kPoisonLds) {
         const float nan = __uint_as_float(0x7fc00000u);
         static_for<0, C::E>([&](auto i) {
@@ -318,7 +297,6 @@ __device__ __forceinline__ void lds_write16(unsigned addr, const u32x4& q) {
 
 template <class C, int PH>
 __device__ __forceinline__ void lds_put_raw(const float (&r)[C::E], const float* tok) {
-    static_assert(phase_is_vec4<C, PH>(), "16 bytes per access");
     const unsigned addr = lds_byte_address(tok);
     static_for<0, C::E / 4>([&](auto i) {
         constexpr int I = decltype(i)::value * 4;
@@ -330,7 +308,7 @@ __device__ __forceinline__ void lds_put_raw(const float (&r)[C::E], const float*
 
 template <class C, int PH>
 __device__ __forceinline__ void lds_get_raw(float (&r)[C::E], const float* tok) {
-    static_assert(phase_is_vec4<C, PH>() && C::E % 16 == 0, "16 bytes per access, four accesses per block");
+    static_assert(C::E % 16 == 0, "four accesses per block");
     const unsigned addr = lds_byte_address(tok);
     static_for<0, C::E / (C::E >= 32 ? 32 : 16)>([&](auto b) {
         constexpr int N4 = C::E >= 32 ? 8 : 4, B = decltype(b)::value * N4 * 4;
@@ -516,35 +494,31 @@ __device__ __forceinline__ void wave_transform(float (&r)[C::E], float* lds, con
     }
 }
 
-// H_raw applied to the 2^n values spread over the token's threads.
+// The stages of the matrix-core schedule that are not in its rounds, on the 2^n values spread over the
+// token's threads.
 //   FORWARD_ORDER: registers enter in the first phase's layout and leave in the last phase's;
 //   otherwise the phases run in reverse (enter in the last layout, leave in the first) -- the
 //   backward pass uses this so that dy can be consumed in the layout z was produced in.
-// Ends with a workgroup barrier when LDS was used, so the caller may reuse LDS at once.
+// With TRAILING_BARRIER it ends with a workgroup barrier when LDS was used, so the caller may reuse LDS at once.
 template <class C, bool FORWARD_ORDER, bool TRAILING_BARRIER>
 __device__ __forceinline__ void transform(float (&r)[C::E], float* lds, const ThreadMap<C>& tm) {
-    if constexpr (C::kWave) {
-        wave_transform<C, FORWARD_ORDER>(r, lds, tm);
-        if constexpr (C::w > 0 && TRAILING_BARRIER) exchange_barrier();
-    } else {
-        static_for<0, C::P>([&](auto s) {
-            constexpr int S = decltype(s)::value;
-            constexpr int PH = FORWARD_ORDER ? S : C::P - 1 - S;
-            if constexpr (S > 0) lds_get<C, PH>(r, lds + tm.lds_off[PH]);
-            run_stages<C, PH>(r);
-            if constexpr (S + 1 < C::P) {
-                // a middle phase rewrites exactly the words it read, so only the hand-over to the
-                // next layout needs the barrier
-                lds_put<C, PH>(r, lds + tm.lds_off[PH]);
-                exchange_barrier();
-            }
-        });
-        // The next write into the exchange region must not overtake other waves' reads of this one.
-        // When the next transform runs in the opposite order (the backward kernel alternates), its
-        // first write goes, thread by thread, to exactly the words this thread has just read, and no
-        // barrier is needed; a kernel that only runs forward-order transforms needs it.
-        if constexpr (C::P > 1 && TRAILING_BARRIER) exchange_barrier();
-    }
+    static_for<0, C::P>([&](auto s) {
+        constexpr int S = decltype(s)::value;
+        constexpr int PH = FORWARD_ORDER ? S : C::P - 1 - S;
+        if constexpr (S > 0) lds_get<C, PH>(r, lds + tm.lds_off[PH]);
+        run_stages<C, PH>(r);
+        if constexpr (S + 1 < C::P) {
+            // a middle phase rewrites exactly the words it read, so only the hand-over to the
+            // next layout needs the barrier
+            lds_put<C, PH>(r, lds + tm.lds_off[PH]);
+            exchange_barrier();
+        }
+    });
+    // The next write into the exchange region must not overtake other waves' reads of this one.
+    // When the next transform runs in the opposite order (the backward kernel alternates), its
+    // first write goes, thread by thread, to exactly the words this thread has just read, and no
+    // barrier is needed; a kernel that only runs forward-order transforms needs it.
+    if constexpr (C::P > 1 && TRAILING_BARRIER) exchange_barrier();
 }
 
 // Global -> LDS staging -> registers.  x and dy are fetched with LDS-direct loads (the data goes
@@ -828,17 +802,22 @@ template <class C, bool TRAILING_BARRIER>
 __device__ __forceinline__ void transform_from_raw(float (&r)[C::E], const uint4 (&raw)[C::NV],
                                                    float* lds, const ThreadMap<C>& tm,
                                                    const HadamardB& b, const HadamardB& b2) {
-    if constexpr (C::kMfma) mfma_rounds_from_bf16<C>(r, raw, b, b2);
-    else                    unpack_all<C>(r, raw);
-    transform<C, true, TRAILING_BARRIER>(r, lds, tm);
+    if constexpr (C::kMfma) {
+        mfma_rounds_from_bf16<C>(r, raw, b, b2);
+        transform<C, true, TRAILING_BARRIER>(r, lds, tm);
+    } else {
+        unpack_all<C>(r, raw);
+        wave_transform<C, true>(r, lds, tm);
+        if constexpr (C::w > 0 && TRAILING_BARRIER) exchange_barrier();
+    }
 }
 
-// registers in the last layout -> H_raw (.) in the first layout.
+// registers in the last layout -> H_raw (.) in the first layout (matrix-core schedule).
 template <class C, bool TRAILING_BARRIER = false>
 __device__ __forceinline__ void transform_back(float (&r)[C::E], float* lds, const ThreadMap<C>& tm,
                                                const HadamardB& b, const HadamardB& b2) {
     transform<C, false, TRAILING_BARRIER>(r, lds, tm);
-    if constexpr (C::kMfma) mfma_rounds_from_f32<C>(r, b, b2);
+    mfma_rounds_from_f32<C>(r, b, b2);
 }
 
 template <class C>
@@ -1163,7 +1142,7 @@ __global__ __launch_bounds__(C::BT) void backward_kernel(const typename C::io::e
                                                          typename C::io::elem_t* dx,
                                                          SumRows sums,
                                                          int64_t N) {
-    static_assert(GRADS || DX, "nothing to compute");
+    static_assert(C::kMfma && (GRADS || DX), "matrix-core schedule; something to compute");
     __shared__ __align__(16) float lds[C::kExchangeBytes / 4];
     __shared__ __align__(16) unsigned char stage_x_buf[GRADS ? C::kStageBytes : 16];
     __shared__ __align__(16) unsigned char stage_g_buf[C::kStageBytes];
@@ -1174,7 +1153,7 @@ __global__ __launch_bounds__(C::BT) void backward_kernel(const typename C::io::e
     ThreadMap<C> tm;
     tm.init(t, wk.slot);
     HadamardB hb{}, hbp{};
-    if constexpr (C::kMfma) hb = make_hadamard_b();
+    hb = make_hadamard_b();
     if constexpr (C::kTwelve) hbp = make_paley_b(hb);
     const HadamardB& hb2 = C::kTwelve ? hbp : hb;
     unsigned char* stage_x = stage_x_buf + (GRADS ? (threadIdx.x >> 6) * (C::NV * 1024) : 0);

@@ -65,6 +65,14 @@ constexpr bool plan_is_complete(const PlanDesc& pl) {
     return seen == (1u << pl.n) - 1u;
 }
 
+// Every layout keeps element bits 0 and 1 in the low register bits: four consecutive values, one 16-byte
+// LDS access.
+constexpr bool plan_keeps_vectors(const PlanDesc& pl) {
+    for (int p = 0; p < pl.nphase; ++p)
+        if (pl.ph[p].rb[0] != 0 || pl.ph[p].rb[1] != 1) return false;
+    return true;
+}
+
 // ---- the matrix-core schedule (bfloat16 I/O, d >= 1024) ---------------------------------------
 //
 // H_32 applied along five element bits is a 32x32 (+-1) matrix product, which the MFMA unit does
