@@ -35,6 +35,15 @@ NUM_SIMD = 256 * 4            # MI355X: 256 CUs x 4 SIMDs
 NUM_XCD = 8                   # GRBM_GUI_ACTIVE comes back summed over the 8 XCDs
 
 
+def _workload(name):
+    """A named workload, or N,d,dtype (for example 65537,256,bf16)."""
+    from paper_2603_08343_amd import synth
+    if "," not in name:
+        return synth.WORKLOADS[name]
+    N, d, dtype = name.split(",")
+    return synth.Workload(name, int(N), int(d), dtype, True)
+
+
 def drive(args):
     import os
     if args.schedule == "butterfly":
@@ -43,9 +52,8 @@ def drive(args):
     import torch
     import bench
     import paper_2603_08343_amd as wht
-    from paper_2603_08343_amd import synth
 
-    w = synth.WORKLOADS[args.workload]
+    w = _workload(args.workload)
     tdt = torch.bfloat16 if w.dtype == "bf16" else torch.float32
     g = torch.Generator(device="cuda").manual_seed(0)
     x = torch.randn(w.N, w.d, device="cuda", generator=g).to(tdt)
@@ -141,12 +149,12 @@ def _short(name: str) -> str:
 
 
 def summarize(args):
-    from paper_2603_08343_amd import synth
-    w = synth.WORKLOADS[args.workload]
+    w = _workload(args.workload)
     s = 2 if w.dtype == "bf16" else 4
     algo = {"forward_kernel": 2 * w.N * w.d * s + 8 * w.d, "forward_once_kernel": 2 * w.N * w.d * s + 8 * w.d,
             "backward_kernel": 3 * w.N * w.d * s + 12 * w.d,
-            "backward_teams_kernel": 3 * w.N * w.d * s + 12 * w.d}
+            "backward_teams_kernel": 3 * w.N * w.d * s + 12 * w.d,
+            "backward_wave_kernel": 3 * w.N * w.d * s + 12 * w.d}
     out = [f"workload {w.name}: N={w.N} d={w.d} {w.dtype} I/O"]
 
     if args.kernel_stats:
@@ -239,7 +247,8 @@ def main():
     d = sub.add_parser("drive")
     d.add_argument("--workload", default="C5_large")
     d.add_argument("--steps", type=int, default=3)
-    d.add_argument("--schedule", choices=["default", "butterfly"], default="default")
+    d.add_argument("--schedule", choices=["default", "butterfly"], default="default",
+                   help="butterfly: the wave schedule (all stages as additions) for bf16, d >= 1024 too")
     d.set_defaults(fn=drive)
     c = sub.add_parser("series")
     c.add_argument("--workload", default="C5_large")
