@@ -36,7 +36,8 @@ def parse():
     ap.add_argument("--no-cpu", action="store_true", help="skip the CPU-oracle baseline leg")
     ap.add_argument("--cpu-seconds", type=float, default=12.0, help="target CPU time of the oracle sample")
     ap.add_argument("--schedule", choices=["default", "butterfly"], default="default",
-                    help="butterfly: force the butterfly schedule for bf16, d >= 1024 (WHT_AFFINE_SCHEDULE)")
+                    help="butterfly: the wave schedule (all stages as additions) for bf16, d >= 1024 too "
+                         "(WHT_AFFINE_SCHEDULE)")
     args = ap.parse_args()
     if args.schedule == "butterfly":
         os.environ["WHT_AFFINE_SCHEDULE"] = "butterfly"       # read by the library when it is loaded
@@ -659,8 +660,9 @@ def main():
     dom_ms = bwd_ms if w.backward else fwd_ms
     dom_bytes = algorithmic_bytes(w.N, w.d, w.dtype, dom)
     achieved = dom_bytes / (dom_ms * 1e-3) / 1e9
-    dom_kernel = ("backward_teams_kernel" if w.d in (3072, 4096, 6144, 8192) and w.dtype == "bf16" else "backward_kernel") \
-        if w.backward else "forward_kernel"
+    matrix_cores = w.dtype == "bf16" and w.d >= 768 and (args.schedule == "default" or w.d % 3 == 0)
+    dom_kernel = "forward_kernel" if not w.backward else "backward_wave_kernel" if not matrix_cores else \
+        "backward_teams_kernel" if w.d in (3072, 4096, 6144, 8192) else "backward_kernel"
     roofline = {"bound": "hbm",
                 "kernel": dom_kernel + (" (+ reduce_partials_kernel: the interval timed is the whole "
                                         "wht_affine_backward call)" if w.backward else ""),
@@ -681,8 +683,7 @@ def main():
         # what the path computes in: float32 vector arithmetic and float32 accumulation; on the
         # matrix-core schedule (bf16 I/O, d >= 1024) a float32 value enters a +-1 matrix round as two
         # bfloat16 terms hi + lo (relative error <= 2^-17), the round's products being exact
-        "dtype": "f32 (matrix-core rounds on bf16 hi+lo pairs, f32 accumulate)" if w.dtype == "bf16" and w.d >= 768
-                 else "f32",
+        "dtype": "f32 (matrix-core rounds on bf16 hi+lo pairs, f32 accumulate)" if matrix_cores else "f32",
         "data": "synthetic",
         "config": {"workload": f"{w.name}: N={w.N} tokens, d={w.d}, {w.dtype} I/O, "
                                f"{'forward+backward' if w.backward else 'forward'}",

@@ -840,8 +840,10 @@ __device__ __forceinline__ float inv_sqrt_d() {
 
 // Four sums of a partial row.  Every workgroup writes its row at the end of the kernel, and rows that lie
 // dirty in L2 are written back before the next kernel adds them up: rows of 2048 to 4096 columns are streamed
-// past the caches instead (256 rows of 4096: 12.6 -> 11.0 us for the call, of 2048: 10.0 -> 9.4).  Shorter
-// rows and rows of 8192 measured no gain, and a call of few rows loses 0.2 us.
+// past the caches instead.  Graph replay, plain / streamed, us per call: 256 rows of 4096 columns 12.7 / 11.1,
+// of 2048 10.1 / 9.5, of 3072 10.8 / 10.2.  Fewer rows lose: 3 to 128 rows of 4096 columns 6.5..8.8 / 6.8..9.2,
+// of 2048 6.8..8.6 / 7.0..8.9; a single workgroup's row takes the same time either way (4.2 / 4.2).  Shorter
+// rows and rows of 8192 measured no gain.
 template <int ROW>
 __device__ __forceinline__ void put_sums(float* out, const float4& q) {
     const u32x4 v = {__float_as_uint(q.x), __float_as_uint(q.y), __float_as_uint(q.z), __float_as_uint(q.w)};
@@ -1321,9 +1323,10 @@ __device__ __forceinline__ void zero_stage(const unsigned char* wave_slot) {
 
 // backward of the wave schedule, which took the place of butterflies re-dealt two or three times through
 // LDS per transform (two one-word passes at d = 256; one wave per SIMD waiting on conflicting LDS accesses
-// at float32 d = 4096).  Bound by memory: 16384 x 4096 float32 in 131..135 us where the plain copy's rate
-// would take 130 (was 178..183); 65537 x 256 bfloat16 19.4 us against 16 (was 26.4); a stage costs one
-// vector instruction per value, between lanes as in registers.  With tokens inside a wave the four waves of a workgroup walk their
+// at float32 d = 4096).  Bound by memory (vector issue 41 and 39 % of the SIMD cycles, no bank conflict in
+// the loop): median kernel time 16384 x 4096 float32 136 us where the plain copy's rate would take 130 (was
+// 181), 65537 x 256 bfloat16 19.2 us against 16 (was 27.0); a stage costs one vector instruction per value,
+// between lanes as in registers.  With tokens inside a wave the four waves of a workgroup walk their
 // own tokens and never wait for one another: the loop has no barrier, and the transforms touch no LDS.
 // A wave past the last token therefore fetches nothing: the last row is another wave's, and that wave may
 // have stored dx over it (dx may alias x or dy).
@@ -1648,8 +1651,8 @@ __global__ __launch_bounds__(3 * C::BT) void backward_teams_kernel(const typenam
 // added in pairs; the row lanes of a wave add up by butterfly shuffles, the waves' sums through LDS by a
 // fixed binary tree -- one association, independent of scheduling, so the result is bit-reproducible.
 // All latency: a launch, one round to memory, the tree.  Measured under graph replay (rows x d), with 1024
-// threads, 8 barriers and no loads in flight ahead / now: 256 x 4096 3.15 / 2.54 us, 512 x 1536 4.36 / 2.36,
-// 512 x 1024 3.04 / 2.34, 512 x 256 2.43 / 2.17, 256 x 8192 4.53 / 4.23.  CG: 64-byte pieces of a row while
+// threads, 8 barriers and no loads in flight ahead / now: 256 x 4096 3.15 / 2.54 us, 512 x 1024 3.04 / 2.34,
+// 512 x 256 2.43 / 2.17, 256 x 8192 4.53 / 4.23.  CG: 64-byte pieces of a row while
 // the grid is small, 256-byte pieces once there are enough of them (CG = 4 / 8 / 16 at 512 x 768 2.27 / 2.32
 // / 2.65, at 256 x 2048 2.60 / 2.15 / 2.22, at 256 x 6144 5.89 / 3.97 / 3.73).
 constexpr int kReduceThreads = 512;

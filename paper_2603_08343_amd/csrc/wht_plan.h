@@ -5,7 +5,8 @@
 // the stride 2^b) costs one add or subtract per element when bit b is a bit of the *register*
 // index, so the schedule is a short list of layouts ("phases"); each phase names which e element
 // bits are register-resident, the stages run on those, and between phases bits change places: through
-// LDS, or by swaps between the lanes of a wave.  Stages commute (they act on different index bits), so any order gives H_raw x.
+// LDS, or by swaps between the lanes of a wave.  Stages commute (they act on different index bits), so any
+// order gives H_raw x.
 //
 // The first and the last layout keep element bits 0..v-1 in registers (2^v elements = one 16-byte
 // global vector) and give the lowest thread bits the next element bits, so that global loads and
@@ -245,8 +246,10 @@ constexpr int twelve_round_entry(unsigned m_in, unsigned m_out) {
 // Both are linear in the bits of i (phys(a | b) = phys(a) + phys(b) for disjoint a, b) and keep four
 // consecutive elements in one aligned 16-byte group.
 
-// Wave schedule: lane l's 16 bytes follow lane l-1's in every layout, so the plain index is free of
-// bank conflicts.
+// Wave schedule: at float32, where the exchange between waves serves d = 4096 and 8192, lane l's 16 bytes
+// follow lane l-1's in every layout and the plain index is free of bank conflicts.  (bfloat16 rows of several
+// waves, which run here only when the matrix-core schedule is switched off, have a lane stride of 32 bytes
+// and do conflict.)
 constexpr unsigned lds_phys_plain(unsigned i) { return i; }
 
 // Matrix-core schedule: both layouts give lane l the 8 elements starting at 8*l (+ multiples of
