@@ -176,62 +176,134 @@ static bool check(const char* kind, const PlanDesc& pl, PhysFn phys, unsigned wo
     return ok;
 }
 
-// Rows of 12 * 2^m elements on 16 * 2^m slots: the slot map must be a bijection from the valid slots
-// onto the row, additive over bits, and "Sylvester butterflies on every slot bit but 4..7, the
-// order-12 round matrix along bits 3..7" must equal the definition
-//     out[j] = sum_k P12[j / L][k / L] * (-1)^popcount(j & k & (L - 1)) * x[k],   L = 2^m.
-static bool check_twelve(int n) {
-    const unsigned S = 1u << n, L = S / 16, D = 12 * L;
-    bool ok = true;
-    std::vector<int> hit(D, 0);
-    for (unsigned s = 0; s < S; ++s) {
-        if (!twelve_valid(s)) continue;
-        const unsigned el = twelve_elem(s, n);
-        if (el >= D) { ok = false; continue; }
-        ++hit[el];
-        for (int b = 0; b < n; ++b)        // additivity over single bits
-            if ((s >> b) & 1u)
-                if (twelve_elem(s, n) != twelve_elem(s & ~(1u << b), n) + twelve_elem(1u << b, n)) ok = false;
-        if ((s & 7u) == 0 && twelve_elem(s | 7u, n) != el + 7) ok = false;    // 8-element vectors stay whole
-    }
-    for (unsigned el = 0; el < D; ++el) if (hit[el] != 1) ok = false;
-    // the definition, on a small pseudo-random integer row (exact in double)
-    std::vector<double> x(D), want(D), slot(S, 0.0);
-    uint32_t rng = 12345u + (uint32_t)n;
-    for (unsigned k = 0; k < D; ++k) { rng = rng * 1664525u + 1013904223u; x[k] = (double)((int)(rng >> 24) - 128); }
-    if (n <= 12) {
-        for (unsigned j = 0; j < D; ++j) {
-            double acc = 0;
-            for (unsigned k = 0; k < D; ++k) {
-                const int p = ((paley12_minus_row(j / L) >> (k / L)) & 1u) ? -1 : 1;
-                const int sy = (__builtin_popcount(j & k & (L - 1)) & 1) ? -1 : 1;
-                acc += p * sy * x[k];
-            }
-            want[j] = acc;
+// Rows of 12 * 2^m elements: the layouts must be bijections onto the token's elements (or the two tokens of
+// 768), the exchange places distinct, and the two rounds -- emulated from the operand words the kernels load and
+// the 16x16x32 product's lane layout -- with the stages after them must equal the definition
+//     out[j] = sum_k P12[j / L][k / L] * (-1)^popcount(j & k & (L - 1)) * x[k],   L = 2^m,
+// in forward order (rounds first) and in reverse.
+typedef std::vector<std::vector<double>> Regs;         // [lane of the token's waves][24]
+
+// D[i][j] += sum_k A[i][k] B[k][j]:  A: lane i + 16 (k / 8), element k % 8;  B: lane j + 16 (k / 8), element
+// k % 8;  D: lane j + 16 (i / 4), register i % 4.  Operands hold 8 values of each of the 64 lanes.
+static void product(const double (&A)[64][8], const double (&B)[64][8], double (&D)[64][4]) {
+    for (int i = 0; i < 16; ++i)
+        for (int j = 0; j < 16; ++j)
+            for (int k = 0; k < 32; ++k)
+                D[j + 16 * (i / 4)][i % 4] += A[i + 16 * (k / 8)][k % 8] * B[j + 16 * (k / 8)][k % 8];
+}
+
+static double word_value(unsigned word, int odd) {
+    const unsigned h = odd ? word >> 16 : word & 0xffffu;
+    return h == 0u ? 0.0 : (h == 0x3F80u ? 1.0 : (h == 0xBF80u ? -1.0 : NAN));
+}
+
+static void twelve_rounds(std::vector<double>* lanes, int m) {        // one wave: 64 x 24 registers
+    double d1[3][2][64][4] = {}, out[64][24] = {};
+    for (int v = 0; v < 3; ++v)
+        for (int h = 0; h < 2; ++h) {
+            double A[64][8], B[64][8];
+            for (int l = 0; l < 64; ++l)
+                for (int e = 0; e < 8; ++e) {
+                    A[l][e] = lanes[l][8 * v + e];
+                    B[l][e] = word_value(twelve_round1_word(l, h, e / 2), e & 1);
+                }
+            product(A, B, d1[v][h]);
         }
-        for (unsigned s = 0; s < S; ++s) if (twelve_valid(s)) slot[s] = x[twelve_elem(s, n)];
-        for (int b = 0; b < n; ++b) {                       // Sylvester bits: all but 3..7
-            if (b >= 3 && b <= 7) continue;
-            for (unsigned s = 0; s < S; ++s)
-                if (!((s >> b) & 1u)) {
-                    const double a = slot[s], c = slot[s | (1u << b)];
-                    slot[s] = a + c; slot[s | (1u << b)] = a - c;
+    for (int h = 0; h < 2; ++h)
+        for (int pair = 0; pair < 2; ++pair) {
+            double A[64][8], B[64][8], S[64][8], main[64][4] = {}, shared[64][4] = {};
+            for (int l = 0; l < 64; ++l)
+                for (int e = 0; e < 8; ++e) {
+                    A[l][e] = d1[(e / 4) == pair ? pair : 2][h][l][e % 4];
+                    B[l][e] = word_value(twelve_round2_word(l, pair, false, e / 2, m), e & 1);
+                    S[l][e] = word_value(twelve_round2_word(l, pair, true, e / 2, m), e & 1);
+                }
+            product(A, B, main);
+            product(A, S, shared);
+            for (int l = 0; l < 64; ++l)
+                for (int i = 0; i < 4; ++i) {
+                    out[l][8 * pair + 4 * h + i] += main[l][i];
+                    out[l][16 + 4 * h + i] += shared[l][i];
                 }
         }
-        std::vector<double> out(S, 0.0);
-        for (unsigned s = 0; s < S; ++s) {                  // the 32 x 32 round along bits 3..7
-            const unsigned m_out = (s >> 3) & 31u, rest = s & ~(31u << 3);
-            double acc = 0;
-            for (unsigned m_in = 0; m_in < 32; ++m_in)
-                acc += twelve_round_entry(m_in, m_out) * slot[rest | (m_in << 3)];
-            out[s] = acc;
+    for (int l = 0; l < 64; ++l)
+        for (int i = 0; i < 24; ++i)       // the stage on r6, which the product has done for vector 2
+            lanes[l][i] = m == 6 || i >= 16 ? out[l][i] : (i < 8 ? out[l][i] + out[l][8 + i] : out[l][i - 8] - out[l][i]);
+}
+
+// a - b in the upper of two places of one vector, a + b in the lower (the kernels' DPP stages, signs resolved)
+static void lane_stage(Regs& r, int pos) {
+    const Regs old = r;
+    for (unsigned t = 0; t < r.size(); ++t)
+        for (int i = 0; i < 24; ++i) {
+            const double own = old[t][i], other = old[t ^ (1u << pos)][i];
+            r[t][i] = ((t >> pos) & 1u) ? other - own : own + other;
         }
-        for (unsigned s = 0; s < S; ++s) {
-            if (twelve_valid(s)) { if (out[s] != want[twelve_elem(s, n)]) ok = false; }
-            else if (out[s] != 0.0) ok = false;             // padding stays zero
-        }
+}
+
+static bool check_twelve(int m) {
+    const unsigned L = 1u << m, D = 12 * L;
+    const int w = twelve_wave_bits(m);
+    const unsigned W = 1u << w, T = 64 * W, tokens = m == 6 ? 2 : 1;
+    bool ok = true;
+    auto place = [&](unsigned t) { return LaneWave{t & 63u, t >> 6}; };
+    auto elem = [&](unsigned t, int vec, bool last) {           // index within the wave's tokens
+        LaneWave p = place(t);
+        if (last) p = twelve_swap(p.lane, p.wave, w);
+        return twelve_elem(p.lane, p.wave, vec, m) + (m == 6 ? twelve_pair(p.lane, vec) * D : 0u);
+    };
+    for (bool last : {false, true}) {
+        std::vector<int> hit(D * tokens, 0);
+        for (unsigned t = 0; t < T; ++t)
+            for (int vec = 0; vec < 3; ++vec)
+                for (int i = 0; i < 8; ++i) {
+                    const unsigned e = elem(t, vec, last) + i;
+                    if (e >= D * tokens) { ok = false; continue; }
+                    ++hit[e];
+                }
+        for (int h : hit) if (h != 1) ok = false;
     }
-    std::printf("twelve    n=%2d row=%u slots=%u %s\n", n, D, S, ok ? "ok" : "FAIL");
+    std::vector<int> words(W * kTwelveBlockWords, 0), column(12 * (L + 16), 0);
+    for (unsigned t = 0; t < T; ++t) {
+        const LaneWave p = place(t), q = twelve_swap(p.lane, p.wave, w), back = twelve_swap(q.lane, q.wave, w);
+        if (back.lane != p.lane || back.wave != p.wave || q.wave >= W) ok = false;
+        const unsigned at = twelve_place(q.lane, q.wave);
+        if (at + 3 >= words.size() || at % 4 != 0 || words[at]++) ok = false;
+    }
+    for (unsigned e = 0; e < D; ++e)
+        if (twelve_column(e, m) >= column.size() || column[twelve_column(e, m)]++) ok = false;
+    std::vector<double> x(D * tokens), want(D * tokens, 0.0);
+    uint32_t rng = 12345u + (uint32_t)m;
+    for (double& v : x) { rng = rng * 1664525u + 1013904223u; v = (double)((int)(rng >> 24) - 128); }   // exact in double
+    for (unsigned tok = 0; tok < tokens; ++tok) {
+        std::vector<double> z(x.begin() + tok * D, x.begin() + (tok + 1) * D);
+        for (unsigned s = 1; s < L; s *= 2)                    // Sylvester stages inside every block
+            for (unsigned k = 0; k < D; ++k)
+                if (!(k & s)) { const double a = z[k], c = z[k + s]; z[k] = a + c; z[k + s] = a - c; }
+        for (unsigned j = 0; j < D; ++j)
+            for (unsigned k = 0; k < 12; ++k)
+                want[tok * D + j] += (((paley12_minus_row(j / L) >> k) & 1u) ? -1 : 1) * z[k * L + j % L];
+    }
+    for (int reverse = 0; reverse < 2; ++reverse) {
+        Regs r(T, std::vector<double>(24));
+        for (unsigned t = 0; t < T; ++t)
+            for (int i = 0; i < 24; ++i) r[t][i] = x[elem(t, i / 8, reverse != 0) + i % 8];
+        auto rounds = [&] { for (unsigned wave = 0; wave < W; ++wave) twelve_rounds(&r[64 * wave], m); };
+        auto exchange = [&] {
+            const Regs old = r;
+            for (unsigned t = 0; t < T; ++t) {
+                const LaneWave p = place(t), q = twelve_swap(p.lane, p.wave, w);
+                r[q.lane + 64 * q.wave] = old[t];
+            }
+        };
+        auto wave_stages = [&] { for (int k = 0; k < w; ++k) lane_stage(r, twelve_lane_pos(k)); };
+        if (!reverse) { rounds(); exchange(); wave_stages(); }
+        else          { wave_stages(); exchange(); rounds(); }
+        for (unsigned t = 0; t < T; ++t)
+            for (int i = 0; i < 24; ++i)
+                if (r[t][i] != want[elem(t, i / 8, reverse == 0) + i % 8]) ok = false;
+    }
+    std::printf("twelve    n=%2d row=%u waves=%u %s\n", m + 4, D, W, ok ? "ok" : "FAIL");
     return ok;
 }
 
@@ -245,7 +317,7 @@ int main(int argc, char** argv) {
     }
     bool ok = true;
     const bool verbose = argc > 1;
-    for (int n = 10; n <= 14; ++n) ok = check_twelve(n) && ok;
+    for (int m = 6; m <= 10; ++m) ok = check_twelve(m) && ok;
     for (int v : {2, 3})
         for (int n = 5; n <= (v == 2 ? 13 : 14); ++n) {
             const PlanDesc pl = make_wave_plan(n, wave_log_e(n, v), v);

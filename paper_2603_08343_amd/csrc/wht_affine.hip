@@ -241,22 +241,34 @@ static int dispatch_d(int logd, Op op, Args& a) {
     }
 }
 
-// Rows of 12 * 2^m elements (bfloat16): matrix-core schedule on 16 * 2^m slots.
-template <int LOGS>
+// Rows of 12 * 2^m elements (bfloat16); logd = m + 4.  Calls of few tokens put two waves on what one wave computes
+// elsewhere, up to m = 8 (above, the exchange between twice as many waves takes more than that saves: one token of
+// 6144 3.8 us so, 3.4 without).
+// Tensors of up to 128 MiB (32 MiB where the backward pass reads both) are read with the default cache policy, larger ones streamed.  What has
+// been read with the default policy stays in the Infinity Cache: a backward call that follows its forward call finds
+// x there, and a caller that comes back to the same small tensors finds them.  us per call, default policy in
+// both directions / in forward alone / in neither, twelve sets of buffers in turn: a step of 32768 x 768 51.7 / 49.5
+// / 52.6, of 32768 x 1536 90.6 / 89.4 / 94.3, backward alone 34.1 / 32.5 / 32.5 and 61.1 / 58.0 / 57.9; three sets in
+// turn: backward of 16384 x 768 18.6 / 21.5 / 21.4, of 8192 x 1536 19.2 / 22.6 / 22.5.  A forward call alone on an
+// input that lies in memory loses 2..4 % to streaming (8192 x 6144 39.4 against 38.4), one of 400 MB 6 %.
+template <int M>
 static int run_twelve(Op op, Args& a) {
-    return run<MfmaCfg<LOGS, mfma_log_tiles(LOGS, false), true>, MfmaCfg<LOGS, mfma_log_tiles(LOGS, true), true>,
-               MfmaCfg<LOGS, mfma_log_tiles_few(LOGS), true>>(op, a);
+    const int64_t bytes = a.N * TwelveCfg<M>::kRow * 2;
+    const bool one_input = op == Op::Forward || (op == Op::Backward && !a.dalpha);      // dx alone reads dy only
+    if (bytes <= (int64_t(one_input ? 128 : 32) << 20))
+        return run<TwelveCfg<M, false, true>, TwelveCfg<M, false, true>, TwelveCfg<M, (M <= 8), true>>(op, a);
+    return run<TwelveCfg<M>, TwelveCfg<M>, TwelveCfg<M, (M <= 8), true>>(op, a);
 }
 
-static int dispatch_twelve(int logslots, Op op, Args& a) {
-    switch (logslots) {
+static int dispatch_twelve(int logd, Op op, Args& a) {
+    switch (logd) {
 #if WHT_ALL_WIDTHS
-    case 10: return run_twelve<10>(op, a);
-    case 11: return run_twelve<11>(op, a);
-    case 12: return run_twelve<12>(op, a);
-    case 14: return run_twelve<14>(op, a);
+    case 10: return run_twelve<6>(op, a);
+    case 11: return run_twelve<7>(op, a);
+    case 12: return run_twelve<8>(op, a);
+    case 14: return run_twelve<10>(op, a);
 #endif
-    case 13: return run_twelve<13>(op, a);
+    case 13: return run_twelve<9>(op, a);
     default: return WHT_ERR_BAD_DIM;
     }
 }

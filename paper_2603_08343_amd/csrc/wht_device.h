@@ -9,9 +9,8 @@
 //     of 32x32 +-1 products on the MFMA unit (exact products, float32 accumulation), the rest as
 //     register butterflies plus one LDS exchange across the waves of a token.
 // Widths d = 12 * 2^m (bfloat16, d >= 768; the paper's Table 2 trains d = 768 and 1536 and leaves the
-// matrix undefined there) use H_raw = P12 (x) S_{2^m}, P12 a symmetric order-12 Hadamard matrix: the
-// matrix-core schedule runs on a row padded to 16 * 2^m slots, with P12 inside the second round's
-// +-1 matrix (see MfmaCfg).
+// matrix undefined there) use H_raw = P12 (x) S_{2^m}, P12 a symmetric order-12 Hadamard matrix: a
+// matrix-core schedule of their own, with P12 inside the second round's +-1 matrix (see TwelveCfg).
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -31,6 +30,8 @@ __device__ __forceinline__ void static_for(F&& f) {
         static_for<I + 1, N>(f);
     }
 }
+
+constexpr int kStreamPolicy = 2;   // cache-policy operand of a load: "nt" (read once, do not retain)
 
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
@@ -84,21 +85,13 @@ struct IoBF16 {
 // per-(d, dtype) configuration
 
 // Matrix-core schedule (bfloat16 I/O, d >= 1024): 2^LOGT MFMA tiles of 1024 elements per wave.
-//
-// TWELVE: the row in memory has 12 * 2^m elements (m = LOGD - 4) and the schedule runs on 2^LOGD
-// "slots".  Slot index s = (r_hi << 8) | (b << 4) | r_lo  <->  element b * 2^m + (r_hi << 4 | r_lo):
-// the block number b = 0..11 sits in slot bits 4..7 (b = 12..15 are empty slots, held as zeros and
-// never loaded or stored), so that the second round, which contracts slot bits 3..7, sees the pair
-// (element bit 3, block) and applies  P12 (x) H_2  there; every other slot bit is an ordinary
-// Sylvester bit.  Bits 6 and 7 are lane bits in both memory layouts, so a slot's validity is a
-// property of the lane: lanes 24..31 and 56..63 of every wave sit out the loads and stores, and
-// per instruction the others touch 64 contiguous bytes of every block, as two 32-byte lane pairs
-// (l, l+1) and (l+32, l+33).
-template <int LOGD, int LOGT, bool TWELVE = false>
+template <int LOGD, int LOGT>
 struct MfmaCfg {
     using io = IoBF16;
-    static constexpr bool kMfma = true, kWave = false;
-    static constexpr bool kTwelve = TWELVE;
+    static constexpr bool kMfma = true, kWave = false, kTwelve = false;
+    static constexpr int kPair = 1;             // tokens per slot
+    static constexpr int kSums = 1 << (4 + LOGT);                   // column sums per thread
+    static constexpr bool kHalf = false, kKeep = false;            // see TwelveCfg
     static constexpr int n = LOGD, t = LOGT, e = 4 + LOGT, v = 3;
     static constexpr int w = n - 10 - t;        // log2(waves per token)
     static_assert(n >= 10 && w >= 0 && w <= 2 * (1 + t) && e <= kMaxRegBits, "bad tile");
@@ -121,7 +114,8 @@ struct MfmaCfg {
     // the full backward of a schedule with one LDS exchange runs on three teams of waves
     // (backward_teams_kernel), one workgroup per CU
     static constexpr bool kBwdTeams = plan.nphase == 2 && 3 * BT <= 1024;
-    static constexpr int kBwdGroupsPerCU = kBwdTeams ? 1 : (TWELVE ? (n == 11 ? 1 : 2) : ((n == 11 || n >= 13) ? 1 : 2));
+    static constexpr int kBwdGroupsPerCU = kBwdTeams || n == 11 || n >= 13 ? 1 : 2;
+    static constexpr int kBwdWavesPerSimd = 1;
     // Forward: workgroups per cluster (0 = one interleave over the whole grid).  With every
     // workgroup in one moving window of rows, the read stream and the write stream keep a fixed
     // address distance, and for about 40 % of the distances y - x (period 128 MiB, and again 512 KiB)
@@ -133,14 +127,10 @@ struct MfmaCfg {
     // with the residual as a third stream two windows measured best (mean 263 us against 274 us
     // with four and 268 us with one, d = 8192)
     static constexpr int kFwdClusterResid = n >= 12 ? 256 : 0;
-    static constexpr int kRow = TWELVE ? 3 * (D / 4) : D;       // elements per row in memory
-    static constexpr unsigned real(unsigned s) {                // slot index -> element index
-        return TWELVE ? twelve_elem(s, n) : s;
-    }
-    static constexpr bool valid(unsigned s) { return !TWELVE || twelve_valid(s); }
-    static_assert(!TWELVE || ((reg_mask(plan.ph[0], e) | reg_mask(plan.ph[P - 1], e)) & 0xC0u) == 0,
-                  "block bits 6 and 7 must be lane bits in the memory layouts");
+    static constexpr int kRow = D;
     static constexpr unsigned phys(unsigned i) { return lds_phys_rot(i); }
+    // LDS word of registers I .. I+3 relative to the thread's own offset, in the layout of phase PH
+    template <int PH> static constexpr unsigned lds_reg(int I) { return phys(reg_elem_offset(plan.ph[PH], e, I)); }
     static constexpr unsigned kTokenWords = D;
     static constexpr unsigned kExchangeBytes = (P > 1 || G > 1) ? G * kTokenWords * 4u : 16u;
     static constexpr unsigned kStageBytes = BT * NV * 16u;          // one tensor's token group, as stored
@@ -149,12 +139,57 @@ struct MfmaCfg {
     static_assert(kLdsBytesBackward <= 160u * 1024u, "token group does not fit LDS");
 };
 
+// Rows of 12 * 2^LOGM elements (bfloat16): the matrix-core rounds of wht_plan.h, 24 values per lane and no lane,
+// vector or 128-byte line in part.  It took the place of the power-of-two schedule on rows padded to 16 * 2^m, in
+// which a quarter of the lanes sat out every load and store and every instruction worked on a quarter of zeros: the
+// large calls were bound by instruction issue there (75 % of the vector slots at 6144) and are bound by memory
+// (forward) or nearly so here.  us per call, before / after: forward 32768 x 6144 153 / 137 (5.9 TB/s; a copy in
+// this layout 130), backward 262 / 229 (5.3 TB/s), a step of 32768 x 768 56.4 / 48.6, of 32768 x 1536 100 / 88,
+// backward of 16384 x 12288 358 / 256 (one exchange per transform instead of two).  A wave computes 24 values per
+// lane where it computed 16, and two tokens of 768: calls of one to a few tokens per CU take up to 0.6 us longer
+// in the backward pass of 768 and 6144 (64 tokens 6.2 / 6.6 and 8.1 / 8.7).
+// HALF (few tokens per call): two waves share the 1536 elements of one.  Both fetch them and each computes the
+// results of one value of r2 -- half of round 1, half of round 2 and of everything behind -- so nothing but the
+// fetch is done twice and the chain of dependent instructions is half as long: one token of 768 with the statistic
+// 3.3 -> 2.8 us per call, one of 1536 2.1 (padded rows: 2.6 and 2.5).
+// KEEP: x and dy are read with the default cache policy and so stay in the Infinity Cache (see run_twelve).
+template <int LOGM, bool HALF = false, bool KEEP = false>
+struct TwelveCfg {
+    using io = IoBF16;
+    static constexpr bool kMfma = true, kWave = false, kTwelve = true, kHalf = HALF, kKeep = KEEP;
+    static constexpr int m = LOGM, n = m + 4, v = 3, w = twelve_wave_bits(m);
+    static_assert(m >= 6 && w <= 3, "three lane positions take wave bits");
+    static constexpr int P = w > 0 ? 2 : 1;     // layouts: the second one only after an exchange
+    static constexpr int V = HALF ? 4 : 8, NV = 3, E = NV * V;      // values per vector behind the rounds
+    static constexpr int TPT = (HALF ? 128 : 64) << w;              // threads per token (per two tokens of 768)
+    static constexpr int kPair = m == 6 ? 2 : 1;                    // tokens per wave
+    static constexpr int kSums = E - (kPair - 1) * V;               // column sums per thread: vectors 0 and 1 in one
+    static constexpr int BT = TPT > 256 ? TPT : 256;
+    static constexpr int G = BT / TPT * kPair;
+    static constexpr int kRow = 12 << m, D = kRow;
+    static constexpr int kFwdGroupsPerCU = 2;
+    static constexpr bool kBwdTeams = P == 2 && 3 * BT <= 1024;
+    // two workgroups per CU; three and four: forward 32768 x 768 20.7 / 21.9 / 22.3 us, 6144 146 / 152 / 159
+    static constexpr int kBwdGroupsPerCU = kBwdTeams || m == 10 ? 1 : 2;
+    static constexpr int kBwdWavesPerSimd = m <= 7 ? 2 : 1;
+    static constexpr int kFwdCluster = m >= 8 ? 128 : 0, kFwdClusterResid = m >= 8 ? 256 : 0;
+    template <int PH> static constexpr unsigned lds_reg(int I) { return (I / 4) * ((HALF ? 2 : 1) * kTwelveBlockWords << w); }
+    static constexpr unsigned phys(unsigned e) { return twelve_column(e, m); }      // column sums
+    static constexpr unsigned kExchangeWords = P > 1 ? 6u * (kTwelveBlockWords << w) : 0u;
+    static constexpr unsigned kColumnWords = 12u * ((1u << m) + 16u);
+    static constexpr unsigned kTokenWords = kExchangeWords < kColumnWords ? kColumnWords : kExchangeWords;
+    static constexpr unsigned kExchangeBytes = G / kPair * kTokenWords * 4u;
+    static constexpr unsigned kStageBytes = BT * NV * 16u;
+    static_assert(kExchangeBytes + 2u * kStageBytes <= 160u * 1024u, "token group does not fit LDS");
+};
+
 // Wave schedule: a token inside one wave, every stage in registers or between lanes (or on two or
 // four whole waves, with one LDS exchange between them).
 template <int LOGD, int LOGE, class Io>
 struct WaveCfg {
     using io = Io;
-    static constexpr bool kMfma = false, kWave = true, kTwelve = false;
+    static constexpr bool kMfma = false, kWave = true, kTwelve = false, kHalf = false, kKeep = false;
+    static constexpr int kPair = 1, kSums = 1 << LOGE;
     static constexpr int n = LOGD, e = LOGE, v = Io::kLogVec;
     static constexpr int L = n - e < 6 ? n - e : 6, w = n - e - L;    // log2 lanes of a wave, waves per token
     static_assert(wave_fits(n, e, v), "bad tile");
@@ -180,9 +215,9 @@ struct WaveCfg {
     static constexpr int kFwdCluster = v == 2 && n >= 10 ? (n == 10 || n == 12 ? 128 : 256) : 0;
     static constexpr int kFwdClusterResid = v == 2 && n >= 10 ? 256 : 0;
     static constexpr int kRow = D;
-    static constexpr unsigned real(unsigned i) { return i; }
-    static constexpr bool valid(unsigned) { return true; }
     static constexpr unsigned phys(unsigned i) { return lds_phys_plain(i); }
+    // LDS word of registers I .. I+3 relative to the thread's own offset, in the layout of phase PH
+    template <int PH> static constexpr unsigned lds_reg(int I) { return phys(reg_elem_offset(plan.ph[PH], e, I)); }
     static constexpr unsigned kTokenWords = D;
     static constexpr unsigned kExchangeBytes = w > 0 ? G * D * 4u : 16u;
     static constexpr unsigned kStageBytes = BT * NV * 16u;          // one tensor's token group, as stored
@@ -259,7 +294,7 @@ template <class C, int PH>
 __device__ __forceinline__ void lds_put(const float (&r)[C::E], float* tok) {
     static_for<0, C::E / 4>([&](auto i) {
         constexpr int I = decltype(i)::value * 4;
-        constexpr unsigned off = C::phys(reg_elem_offset(C::plan.ph[PH], C::e, I));
+        constexpr unsigned off = C::template lds_reg<PH>(I);
         *reinterpret_cast<float4*>(tok + off) = make_float4(r[I], r[I + 1], r[I + 2], r[I + 3]);
     });
 }
@@ -268,7 +303,7 @@ template <class C, int PH>
 __device__ __forceinline__ void lds_get(float (&r)[C::E], const float* tok) {
     static_for<0, C::E / 4>([&](auto i) {
         constexpr int I = decltype(i)::value * 4;
-        constexpr unsigned off = C::phys(reg_elem_offset(C::plan.ph[PH], C::e, I));
+        constexpr unsigned off = C::template lds_reg<PH>(I);
         const float4 q = *reinterpret_cast<const float4*>(tok + off);
         r[I] = q.x; r[I + 1] = q.y; r[I + 2] = q.z; r[I + 3] = q.w;
     });
@@ -276,7 +311,7 @@ __device__ __forceinline__ void lds_get(float (&r)[C::E], const float* tok) {
         const float nan = __uint_as_float(0x7fc00000u);
         static_for<0, C::E>([&](auto i) {
             constexpr int I = decltype(i)::value;
-            constexpr unsigned off = C::phys(reg_elem_offset(C::plan.ph[PH], C::e, I));
+            constexpr unsigned off = C::template lds_reg<PH>(I & ~3) + (I & 3);
             const_cast<float*>(tok)[off] = nan;
         });
     }
@@ -300,7 +335,7 @@ __device__ __forceinline__ void lds_put_raw(const float (&r)[C::E], const float*
     const unsigned addr = lds_byte_address(tok);
     static_for<0, C::E / 4>([&](auto i) {
         constexpr int I = decltype(i)::value * 4;
-        constexpr unsigned off = C::phys(reg_elem_offset(C::plan.ph[PH], C::e, I)) * 4u;
+        constexpr unsigned off = C::template lds_reg<PH>(I) * 4u;
         const u32x4 q = {__float_as_uint(r[I]), __float_as_uint(r[I + 1]), __float_as_uint(r[I + 2]), __float_as_uint(r[I + 3])};
         lds_write16<off>(addr, q);
     });
@@ -314,7 +349,7 @@ __device__ __forceinline__ void lds_get_raw(float (&r)[C::E], const float* tok) 
         constexpr int N4 = C::E >= 32 ? 8 : 4, B = decltype(b)::value * N4 * 4;
         const unsigned at = addr;
         u32x4 q[N4];
-#define WHT_OFF(K) "n"(C::phys(reg_elem_offset(C::plan.ph[PH], C::e, B + 4 * (K))) * 4u)
+#define WHT_OFF(K) "n"(C::template lds_reg<PH>(B + 4 * (K)) * 4u)
         if constexpr (N4 == 8)
             asm volatile("ds_read_b128 %0, %8 offset:%9\n\tds_read_b128 %1, %8 offset:%10\n\t"
                          "ds_read_b128 %2, %8 offset:%11\n\tds_read_b128 %3, %8 offset:%12\n\t"
@@ -337,7 +372,7 @@ __device__ __forceinline__ void lds_get_raw(float (&r)[C::E], const float* tok) 
     if constexpr (kPoisonLds) {
         const u32x4 nan = {0x7fc00000u, 0x7fc00000u, 0x7fc00000u, 0x7fc00000u};
         static_for<0, C::E / 4>([&](auto i) {
-            constexpr unsigned off = C::phys(reg_elem_offset(C::plan.ph[PH], C::e, decltype(i)::value * 4)) * 4u;
+            constexpr unsigned off = C::template lds_reg<PH>(decltype(i)::value * 4) * 4u;
             lds_write16<off>(addr, nan);
         });
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -350,19 +385,15 @@ template <class C>
 struct ThreadMap {
     unsigned lds_off[kMaxPhases];
     unsigned first_elem, last_elem;     // offset within the row in memory
-    bool first_ok, last_ok;             // false for a thread whose slots are padding (12 * 2^m rows)
-    float lane_sign[4];                 // wave schedule: -1 in the lanes of the lower butterfly output
+    float lane_sign[4];                 // stages between lanes: -1 in the lanes of the lower butterfly output
     float sign;                         // their product (see lane_stage)
     __device__ __forceinline__ void init(unsigned t, unsigned slot) {
         static_for<0, C::P>([&](auto p) {
             constexpr int PH = decltype(p)::value;
             lds_off[PH] = slot * C::kTokenWords + C::phys(thread_elem_offset<C, PH>(t));
         });
-        const unsigned f = thread_elem_offset<C, 0>(t), l = thread_elem_offset<C, C::P - 1>(t);
-        first_elem = C::real(f);
-        last_elem = C::real(l);
-        first_ok = C::valid(f);
-        last_ok = C::valid(l);
+        first_elem = thread_elem_offset<C, 0>(t);
+        last_elem = thread_elem_offset<C, C::P - 1>(t);
         sign = 1.0f;
         if constexpr (C::kWave) {
             const unsigned c = wave_lane_to_bits(t, C::L);
@@ -374,6 +405,55 @@ struct ThreadMap {
         }
     }
 };
+
+// Rows of 12 * 2^m elements: vector 0 (vector 1 lies a fixed distance behind it) and vector 2.
+template <int LOGM, bool HALF, bool KEEP>
+struct ThreadMap<TwelveCfg<LOGM, HALF, KEEP>> {
+    using C = TwelveCfg<LOGM, HALF, KEEP>;
+    int half;                           // HALF: the value of r2 that the wave computes
+    unsigned lds_off[2];
+    unsigned first_elem, last_elem, first_elem2, last_elem2;
+    unsigned columns, columns2;         // LDS words of the column sums, in the last layout
+    bool second;                        // vector 2 belongs to the second of the pair, in the first layout
+    float lane_sign[3];                 // stages on the wave bits: -1 in the lanes of the lower butterfly output
+    float sign;                         // their product
+    __device__ __forceinline__ void init(unsigned t, unsigned slot) {
+        const unsigned lane = t & 63u, wave = HALF ? t >> 7 : t >> 6;
+        half = HALF ? (t >> 6) & 1u : 0;
+        const LaneWave to = twelve_swap(lane, wave, C::w);
+        const unsigned block = slot * C::kTokenWords + half * (kTwelveBlockWords << C::w);
+        lds_off[0] = block + twelve_place(to.lane, to.wave);
+        lds_off[1] = block + twelve_place(lane, wave);
+        first_elem = twelve_elem(lane, wave, 0, C::m);
+        first_elem2 = twelve_elem(lane, wave, 2, C::m);
+        last_elem = twelve_elem(to.lane, to.wave, 0, C::m) + 4u * half;
+        last_elem2 = twelve_elem(to.lane, to.wave, 2, C::m) + 4u * half;
+        second = twelve_pair(lane, 2) != 0u;
+        sign = 1.0f;
+        static_for<0, C::w>([&](auto k) {
+            constexpr int K = decltype(k)::value;
+            lane_sign[K] = ((lane >> twelve_lane_pos(K)) & 1u) ? -1.0f : 1.0f;
+            sign *= lane_sign[K];
+        });
+        columns = slot * C::kTokenWords + C::phys(last_elem);
+        columns2 = slot * C::kTokenWords + C::phys(last_elem2);
+    }
+};
+
+// Offset in its row of vector VEC of the thread in the layout of phase PH (OUT: of what the rounds leave, where that
+// is half a vector).  next_row: rows of 768, two tokens
+// to a wave, distance from the first token's row to the second's (0 where there is no second).
+template <class C, int PH, int VEC, bool OUT = (PH > 0)>
+__device__ __forceinline__ unsigned vector_offset(const ThreadMap<C>& tm, unsigned next_row) {
+    if constexpr (C::kTwelve) {
+        const unsigned step = C::kPair == 2 ? next_row : 64u;
+        if constexpr (VEC == 2) return (OUT ? tm.last_elem2 : tm.first_elem2) + (C::kPair == 2 && tm.second ? next_row : 0u);
+        else return (OUT ? tm.last_elem : tm.first_elem) + VEC * step;
+    } else {
+        constexpr unsigned off = reg_elem_offset(C::plan.ph[PH], C::e, VEC * C::V);
+        return (PH == 0 ? tm.first_elem : tm.last_elem) + off;
+    }
+}
 
 // One butterfly stage between lanes: position K of the lane index, the partner's value read through a
 // DPP operand, one fused multiply-add per value:
@@ -494,6 +574,30 @@ __device__ __forceinline__ void wave_transform(float (&r)[C::E], float* lds, con
     }
 }
 
+// Rows of 12 * 2^m elements: the stages on the wave bits, between the lanes of the last layout.  INPUT_SIGN as above.
+#define WHT_FMAC_DPP12(CTRL)                                                                              \
+    asm("s_nop 1\n\t" WHT_FMAC_DPP(0, CTRL) WHT_FMAC_DPP(1, CTRL) WHT_FMAC_DPP(2, CTRL) WHT_FMAC_DPP(3, CTRL)   \
+        WHT_FMAC_DPP(4, CTRL) WHT_FMAC_DPP(5, CTRL) WHT_FMAC_DPP(6, CTRL) WHT_FMAC_DPP(7, CTRL)             \
+        WHT_FMAC_DPP(8, CTRL) WHT_FMAC_DPP(9, CTRL) WHT_FMAC_DPP(10, CTRL) WHT_FMAC_DPP(11, CTRL)           \
+        : "+v"(r[i]), "+v"(r[i + 1]), "+v"(r[i + 2]), "+v"(r[i + 3]), "+v"(r[i + 4]), "+v"(r[i + 5]),     \
+          "+v"(r[i + 6]), "+v"(r[i + 7]), "+v"(r[i + 8]), "+v"(r[i + 9]), "+v"(r[i + 10]), "+v"(r[i + 11]) : "v"(s))
+#define WHT_FMAC_DPP(R, CTRL) "v_fmac_f32_dpp %" #R ", %" #R ", %12 " CTRL " row_mask:0xf bank_mask:0xf\n\t"
+template <class C, bool INPUT_SIGN>
+__device__ __forceinline__ void wave_bit_stages(float (&r)[C::E], const ThreadMap<C>& tm) {
+    static_for<0, C::w>([&](auto k) {
+        constexpr int K = twelve_lane_pos(decltype(k)::value);
+        const float s = INPUT_SIGN ? -tm.lane_sign[decltype(k)::value] : tm.lane_sign[decltype(k)::value];
+#pragma unroll
+        for (int i = 0; i < C::E; i += 12) {
+            if constexpr (K == 0)      WHT_FMAC_DPP12("quad_perm:[1,0,3,2]");
+            else if constexpr (K == 1) WHT_FMAC_DPP12("quad_perm:[2,3,0,1]");
+            else                       WHT_FMAC_DPP12("row_ror:8");
+        }
+    });
+}
+#undef WHT_FMAC_DPP12
+#undef WHT_FMAC_DPP
+
 // The stages of the matrix-core schedule that are not in its rounds, on the 2^n values spread over the
 // token's threads.
 //   FORWARD_ORDER: registers enter in the first phase's layout and leave in the last phase's;
@@ -502,6 +606,23 @@ __device__ __forceinline__ void wave_transform(float (&r)[C::E], float* lds, con
 // With TRAILING_BARRIER it ends with a workgroup barrier when LDS was used, so the caller may reuse LDS at once.
 template <class C, bool FORWARD_ORDER, bool TRAILING_BARRIER>
 __device__ __forceinline__ void transform(float (&r)[C::E], float* lds, const ThreadMap<C>& tm) {
+    if constexpr (C::kTwelve) {
+        if constexpr (FORWARD_ORDER) {
+            if constexpr (C::P > 1) {
+                lds_put<C, 0>(r, lds + tm.lds_off[0]);
+                exchange_barrier();
+                lds_get<C, 1>(r, lds + tm.lds_off[1]);
+                wave_bit_stages<C, false>(r, tm);
+            }
+        } else {
+            if constexpr (C::P > 1) {
+                wave_bit_stages<C, true>(r, tm);
+                lds_put<C, 1>(r, lds + tm.lds_off[1]);
+                exchange_barrier();
+                lds_get<C, 0>(r, lds + tm.lds_off[0]);
+            }
+        }
+    } else
     static_for<0, C::P>([&](auto s) {
         constexpr int S = decltype(s)::value;
         constexpr int PH = FORWARD_ORDER ? S : C::P - 1 - S;
@@ -521,6 +642,35 @@ __device__ __forceinline__ void transform(float (&r)[C::E], float* lds, const Th
     if constexpr (C::P > 1 && TRAILING_BARRIER) exchange_barrier();
 }
 
+// The tokens of a workgroup's slots.
+template <class C>
+struct Walker {
+    int64_t N, groups;
+    unsigned slot;
+    // first token of the slot
+    __device__ __forceinline__ int64_t token(int64_t grp) const {
+        return grp * C::G + slot * C::kPair;
+    }
+    __device__ __forceinline__ int64_t row(int64_t grp) const {       // clamped: always a valid row
+        const int64_t tok = token(grp);
+        return tok < N ? tok : N - 1;
+    }
+    // From the first row of a slot to its second, where it has two: 0 past the last token, so that the first
+    // is read again.
+    __device__ __forceinline__ unsigned next_row(int64_t grp) const {
+        if constexpr (C::kPair == 2)
+            return grp * C::G + 2 * (unsigned)__builtin_amdgcn_readfirstlane(slot) + 1 < N ? C::kRow : 0u;
+        else return 0u;
+    }
+    // Whether the slot fetches anything for group grp (matrix-core schedule: a slot is whole waves).  The
+    // clamped row of a slot without a token is another slot's, which the backward pass may overwrite (dx may
+    // alias x or dy); where no barrier keeps that store behind this read, the slot reads nothing.
+    __device__ __forceinline__ bool fetches(int64_t grp) const {
+        if constexpr (C::G == 1 || C::P > 1) return true;
+        else return grp * C::G + C::kPair * (unsigned)__builtin_amdgcn_readfirstlane(slot) < N;
+    }
+};
+
 // Global -> LDS staging -> registers.  x and dy are fetched with LDS-direct loads (the data goes
 // from memory into LDS without passing through registers), a whole iteration before they are used,
 // so that tens of KiB per workgroup are in flight at all times at no register cost.  An LDS-direct
@@ -528,26 +678,20 @@ __device__ __forceinline__ void transform(float (&r)[C::E], float* lds, const Th
 // 1 KiB slot per vector, reads back exactly what it fetched, and needs no workgroup barrier --
 // only its own vmcnt (loads return in issue order) and lgkmcnt waits, which are written out here
 // because the compiler does not track the dependence between an LDS-direct load and a later LDS read.
-constexpr int kStreamPolicy = 2;   // cache-policy operand of the load: "nt" (read once, do not retain)
 typedef const __attribute__((address_space(1))) void* global_cptr;
 typedef __attribute__((address_space(3))) void* lds_ptr;
 
-//   ok: false in the padding lanes of a 12 * 2^m row, whose stage slots are never used.
 template <class C, int PH>
-__device__ __forceinline__ void stage_issue(unsigned char* wave_slot, const typename C::io::elem_t* row,
-                                            unsigned thread_elem, bool ok) {
+__device__ __forceinline__ void stage_issue(unsigned char* wave_slot, const typename C::io::elem_t* tensor,
+                                            const Walker<C>& wk, int64_t grp, const ThreadMap<C>& tm) {
+    const typename C::io::elem_t* row = tensor + wk.row(grp) * C::kRow;
+    const unsigned next = wk.next_row(grp);
     static_for<0, C::NV>([&](auto c) {
         constexpr int Cc = decltype(c)::value;
-        constexpr unsigned off = C::real(reg_elem_offset(C::plan.ph[PH], C::e, Cc * C::V));
-        if constexpr (C::kTwelve) {
-            // 32-byte pieces, two instructions per 128-byte line: cached, so the line is read once
-            if (ok)
-                __builtin_amdgcn_global_load_lds((global_cptr)(row + thread_elem + off),
-                                                 (lds_ptr)(wave_slot + Cc * 1024), 16, 0, 0);
-        } else {
-            __builtin_amdgcn_global_load_lds((global_cptr)(row + thread_elem + off),
-                                             (lds_ptr)(wave_slot + Cc * 1024), 16, 0, kStreamPolicy);
-        }
+        const typename C::io::elem_t* p = row + vector_offset<C, PH, Cc>(tm, next);
+        // (the builtin takes a literal)
+        if constexpr (C::kKeep) __builtin_amdgcn_global_load_lds((global_cptr)p, (lds_ptr)(wave_slot + Cc * 1024), 16, 0, 0);
+        else __builtin_amdgcn_global_load_lds((global_cptr)p, (lds_ptr)(wave_slot + Cc * 1024), 16, 0, kStreamPolicy);
     });
 }
 
@@ -560,7 +704,7 @@ __device__ __forceinline__ void stage_issue(unsigned char* wave_slot, const type
 //   read in the debug build); false for a slot that another wave fetched or also reads.
 template <class C, bool OWN = true>
 __device__ __forceinline__ void stage_read(uint4 (&raw)[C::NV], const unsigned char* wave_slot) {
-    static_assert(C::NV == 1 || C::NV == 2 || C::NV == 4 || C::NV == 8, "unexpected vector count");
+    static_assert(C::NV <= 4 || C::NV == 8, "unexpected vector count");
     const unsigned addr = lds_byte_address(wave_slot) + (threadIdx.x & 63u) * 16u;
     u32x4 v[C::NV];
 #pragma unroll
@@ -572,6 +716,8 @@ __device__ __forceinline__ void stage_read(uint4 (&raw)[C::NV], const unsigned c
         asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(v[0]) : : "memory");
     else if constexpr (C::NV == 2)
         asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(v[0]), "+v"(v[1]) : : "memory");
+    else if constexpr (C::NV == 3)
+        asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]) : : "memory");
     else if constexpr (C::NV == 4)
         asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]) : : "memory");
     else
@@ -591,13 +737,19 @@ __device__ __forceinline__ void stage_read(uint4 (&raw)[C::NV], const unsigned c
     }
 }
 
-// Padding lanes of a 12 * 2^m row read stale LDS: replace it by zeros (the padding's value).
+// Rows of 768, two tokens to a wave: zeros in the wave's stage slot for the tokens that a ragged last group does
+// not have.  (Zeros in the registers instead cost 44 moves per iteration, ragged or not.)
 template <class C>
-__device__ __forceinline__ void zero_padding(uint4 (&raw)[C::NV], bool ok) {
-    if constexpr (C::kTwelve) {
-#pragma unroll
-        for (int c = 0; c < C::NV; ++c)
-            if (!ok) raw[c] = make_uint4(0u, 0u, 0u, 0u);
+__device__ __forceinline__ void zero_missing(unsigned char* wave_slot, const Walker<C>& wk, int64_t grp, const ThreadMap<C>& tm) {
+    if constexpr (C::kPair == 2) {
+        const int64_t left = wk.N - (grp * C::G + 2 * (unsigned)__builtin_amdgcn_readfirstlane(wk.slot));
+        if (left < 2) {
+            const u32x4 zero = {0u, 0u, 0u, 0u};
+            const unsigned addr = lds_byte_address(wave_slot) + (threadIdx.x & 63u) * 16u;
+            if (left < 1) asm volatile("ds_write_b128 %0, %1" : : "v"(addr), "v"(zero) : "memory");
+            asm volatile("ds_write_b128 %0, %1 offset:1024" : : "v"(addr), "v"(zero) : "memory");
+            if (left < 1 || tm.second) asm volatile("ds_write_b128 %0, %1 offset:2048" : : "v"(addr), "v"(zero) : "memory");
+        }
     }
 }
 
@@ -610,39 +762,50 @@ template <class C>
 __device__ __forceinline__ void unpack_all(float (&r)[C::E], const uint4 (&raw)[C::NV]) {
     static_for<0, C::NV>([&](auto c) {
         constexpr int Cc = decltype(c)::value;
-        C::io::unpack(raw[Cc], &r[Cc * C::V]);
-    });
-}
-
-// STREAM: non-temporal stores.  Rows of 12 * 2^m elements are written in 32-byte pieces: there
-// plain stores, which L2 merges into whole lines, are used instead (17 % faster in the forward
-// kernel at d = 6144, 6 % in the backward kernel, and no partial-line write traffic).
-template <class C, int PH, bool STREAM = true>
-__device__ __forceinline__ void global_put(const float (&r)[C::E], typename C::io::elem_t* row,
-                                           unsigned thread_elem, bool active) {
-    static_for<0, C::NV>([&](auto c) {
-        constexpr int Cc = decltype(c)::value;
-        constexpr unsigned off = C::real(reg_elem_offset(C::plan.ph[PH], C::e, Cc * C::V));
-        if (active) {
-            if constexpr (STREAM) stream_store16(row + thread_elem + off, C::io::pack(&r[Cc * C::V]));
-            else *reinterpret_cast<uint4*>(row + thread_elem + off) = C::io::pack(&r[Cc * C::V]);
+        if constexpr (C::kHalf) {
+            float both[8];
+            C::io::unpack(raw[Cc], both);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) r[Cc * 4 + i] = both[i];
+        } else {
+            C::io::unpack(raw[Cc], &r[Cc * C::V]);
         }
     });
 }
 
-// float32 parameter vector -> registers in the layout of phase PH, times `scale`.
-template <class C, int PH>
-__device__ __forceinline__ void param_get(float (&r)[C::E], const float* p, unsigned thread_elem,
-                                          bool ok, float scale) {
-    // Padding lanes of a 12 * 2^m row read block 0 instead (in bounds) and scale it to zero: a load
-    // under a per-lane condition costs the compiler a second copy of every parameter register.
-    const unsigned base = (!C::kTwelve || ok) ? thread_elem : 0u;
-    const float sc = (!C::kTwelve || ok) ? scale : 0.0f;
+// STREAM: non-temporal stores.  Stores the vectors of the tokens that exist.
+template <class C, int PH, bool STREAM = true>
+__device__ __forceinline__ void global_put(const float (&r)[C::E], typename C::io::elem_t* tensor,
+                                           const Walker<C>& wk, int64_t grp, const ThreadMap<C>& tm) {
+    const int64_t tok = wk.token(grp);
+    typename C::io::elem_t* row = tensor + tok * C::kRow;
+    static_for<0, C::NV>([&](auto c) {
+        constexpr int Cc = decltype(c)::value;
+        bool active = C::G == 1 || tok < wk.N;
+        if constexpr (C::kPair == 2) active = tok + (Cc == 2 ? (tm.second ? 1 : 0) : Cc) < wk.N;
+        if (active) {
+            typename C::io::elem_t* p = row + vector_offset<C, PH, Cc, (PH > 0 || C::kHalf)>(tm, C::kRow);
+            if constexpr (C::kHalf)
+                *reinterpret_cast<uint2*>(p) = make_uint2(C::io::pack2(r[4 * Cc], r[4 * Cc + 1]), C::io::pack2(r[4 * Cc + 2], r[4 * Cc + 3]));
+            else if constexpr (STREAM) stream_store16(p, C::io::pack(&r[Cc * C::V]));
+            else *reinterpret_cast<uint4*>(p) = C::io::pack(&r[Cc * C::V]);
+        }
+    });
+}
+
+// float32 parameter vector -> registers in the layout of the last phase, times `scale` and, where SIGNED, the
+// signs that this layout carries.
+template <class C, bool SIGNED>
+__device__ __forceinline__ void param_get(float (&r)[C::E], const float* p, const ThreadMap<C>& tm, float scale) {
+    const float s = SIGNED ? scale * tm.sign : scale;
     static_for<0, C::E / 4>([&](auto i) {
-        constexpr int I = decltype(i)::value * 4;
-        constexpr unsigned off = C::real(reg_elem_offset(C::plan.ph[PH], C::e, I));
-        const float4 q = *reinterpret_cast<const float4*>(p + base + off);
-        r[I] = q.x * sc; r[I + 1] = q.y * sc; r[I + 2] = q.z * sc; r[I + 3] = q.w * sc;
+        constexpr int I = decltype(i)::value * 4, VEC = I / C::V;
+        if constexpr (C::kPair == 2 && VEC == 1) {       // the same columns as vector 0
+            for (int k = 0; k < 4; ++k) r[I + k] = r[I - C::V + k];
+        } else {
+            const float4 q = *reinterpret_cast<const float4*>(p + vector_offset<C, C::P - 1, VEC, true>(tm, 0u) + I % C::V);
+            r[I] = q.x * s; r[I + 1] = q.y * s; r[I + 2] = q.z * s; r[I + 3] = q.w * s;
+        }
     });
 }
 
@@ -685,37 +848,6 @@ __device__ __forceinline__ HadamardB make_hadamard_b() {
     return b;
 }
 
-// Second-round matrix for rows of 12 * 2^m elements.  The round contracts slot bits 3..7: bit 3 is
-// an ordinary Sylvester bit, bits 4..7 are the block number, so with m = bit3 + 2 * block the
-// matrix is  M[m_in][m_out] = (-1)^(bit3_in & bit3_out) * P12[block_in][block_out], and zero when
-// either block is one of the four empty ones.  In the operand layout above the second round's K
-// index arrives with bits 2 and 3 exchanged and its column index in natural order, hence
-// B[k][j] = M[swap23(k)][j], M = twelve_round_entry (wht_plan.h).
-__device__ __forceinline__ HadamardB make_paley_b(const HadamardB& sylvester) {
-    const unsigned lane = threadIdx.x & 63u;
-    const unsigned j = lane & 31u, kg = lane >> 5;
-    uint32_t w[2][4];
-#pragma unroll
-    for (int half = 0; half < 2; ++half)
-#pragma unroll
-        for (int p = 0; p < 4; ++p) {
-            uint32_t pair = 0;
-#pragma unroll
-            for (int odd = 0; odd < 2; ++odd) {
-                const unsigned k = (2u * p) | (unsigned)odd | (kg << 3) | ((unsigned)half << 4);
-                const unsigned m_in = (k & 0x13u) | ((k & 4u) << 1) | ((k & 8u) >> 1);
-                const int sign = twelve_round_entry(m_in, j);
-                const uint32_t entry = sign == 0 ? 0u : (sign < 0 ? 0xBF80u : 0x3F80u);   // bf16 0, -1, +1
-                pair |= entry << (16 * odd);
-            }
-            w[half][p] = pair;
-        }
-    HadamardB b = sylvester;
-    b.k_lo = __builtin_bit_cast(bf16x8, make_uint4(w[0][0], w[0][1], w[0][2], w[0][3]));
-    b.k_hi = __builtin_bit_cast(bf16x8, make_uint4(w[1][0], w[1][1], w[1][2], w[1][3]));
-    return b;
-}
-
 // One round on bfloat16 data straight from memory: products and sums are exact up to the
 // accumulator's float32 rounding.
 __device__ __forceinline__ f32x16 hadamard_round_bf16(const uint4& a_lo, const uint4& a_hi,
@@ -726,22 +858,27 @@ __device__ __forceinline__ f32x16 hadamard_round_bf16(const uint4& a_lo, const u
     return acc;
 }
 
-// One round on float32 data: each value is split into bf16 hi + bf16 lo (hi = RNE(v), lo =
-// RNE(v - hi); v - hi is exact, so |v - hi - lo| <= 2^-17 |v|) and both parts go through the same
-// +-1 product, accumulated in float32.  v - hi is formed with plain vector instructions (widen hi by
+// float32 values as bf16 hi + bf16 lo (hi = RNE(v), lo = RNE(v - hi); v - hi is exact, so |v - hi - lo|
+// <= 2^-17 |v|): both parts go through the same +-1 product, accumulated in float32.  v - hi is formed with plain vector instructions (widen hi by
 // a shift / a mask, subtract): the bf16 dot-product instruction would do it in one, but it executes
 // on the matrix pipeline and stalls behind the rounds' own MFMAs (measured: 20 cycles per dot
 // instruction next to back-to-back MFMAs, against 4.4 alone).
-__device__ __forceinline__ f32x16 hadamard_round_f32(const float* v, const HadamardB& b) {
-    uint32_t hi[8], lo[8];
+template <int PAIRS>
+__device__ __forceinline__ void split_bf16(const float* v, uint32_t* hi, uint32_t* lo) {
 #pragma unroll
-    for (int p = 0; p < 8; ++p) {
+    for (int p = 0; p < PAIRS; ++p) {
         const uint32_t h = IoBF16::pack2(v[2 * p], v[2 * p + 1]);
         const float l0 = v[2 * p] - __uint_as_float(h << 16);
         const float l1 = v[2 * p + 1] - __uint_as_float(h & 0xffff0000u);
         hi[p] = h;
         lo[p] = IoBF16::pack2(l0, l1);
     }
+}
+
+// One round on float32 data.
+__device__ __forceinline__ f32x16 hadamard_round_f32(const float* v, const HadamardB& b) {
+    uint32_t hi[8], lo[8];
+    split_bf16<8>(v, hi, lo);
     f32x16 acc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     const bf16x8 lo0 = __builtin_bit_cast(bf16x8, make_uint4(lo[0], lo[1], lo[2], lo[3]));
     const bf16x8 lo1 = __builtin_bit_cast(bf16x8, make_uint4(lo[4], lo[5], lo[6], lo[7]));
@@ -754,56 +891,175 @@ __device__ __forceinline__ f32x16 hadamard_round_f32(const float* v, const Hadam
     return acc;
 }
 
-// Both rounds on every tile of the thread: bits 0..9 of the element index.  b is the Sylvester
-// matrix; b2, the second round's matrix, is the same except for rows of 12 * 2^m elements.  Round 1 of every tile
+// Rows of 12 * 2^m elements: the two rounds of wht_plan.h on v_mfma_f32_16x16x32_bf16,
+//   A[i][k]: lane = i + 16*(k/8), element k%8;   B[k][j]: lane = j + 16*(k/8), element k%8;
+//   D[i][j]: lane = j + 16*(i/4), register i%4.
+// What bounds them is the two-term split of round 2's input, 3 vector instructions per value; the products are
+// 22 (from bfloat16) or 28 of 16 cycles per wave.
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x8 __attribute__((ext_vector_type(8)));
+
+struct TwelveB {
+    bf16x8 b1[2];                   // round 1, by output half
+    bf16x8 main[2], shared[2];      // round 2, by pair: results for vector `pair`, for vector 2
+};
+template <class C>
+__device__ __forceinline__ TwelveB make_twelve_b(const ThreadMap<C>& tm) {
+    const unsigned lane = threadIdx.x & 63u;
+    auto words = [](auto f) { return __builtin_bit_cast(bf16x8, make_uint4(f(0), f(1), f(2), f(3))); };
+    TwelveB b;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        b.b1[i] = words([&](int word) { return twelve_round1_word(lane, C::kHalf ? tm.half : i, word); });
+        b.main[i] = words([&](int word) { return twelve_round2_word(lane, i, false, word, C::m); });
+        b.shared[i] = words([&](int word) { return twelve_round2_word(lane, i, true, word, C::m); });
+    }
+    return b;
+}
+__device__ __forceinline__ f32x4 product16(const bf16x8& a, const bf16x8& b, const f32x4& acc) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc, 0, 0, 0);
+}
+
+template <class C>
+__device__ __forceinline__ void twelve_round2(float (&r)[C::E], const f32x4 (&d1)[3][C::V / 4], const TwelveB& b, bool second) {
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    static_for<0, C::V / 4>([&](auto half) {
+        constexpr int H = decltype(half)::value;
+        uint32_t hi[3][2], lo[3][2];
+#pragma unroll
+        for (int v = 0; v < 3; ++v) {
+            const float q[4] = {d1[v][H][0], d1[v][H][1], d1[v][H][2], d1[v][H][3]};
+            split_bf16<2>(q, hi[v], lo[v]);
+        }
+        // operands of pair 0 and 1, lo and hi: slices of the registers (0, 2, 1)
+        bf16x8 a[2][2];
+#pragma unroll
+        for (int term = 0; term < 2; ++term) {
+            const uint32_t (&q)[3][2] = term == 0 ? lo : hi;
+            if constexpr (C::kPair == 2) {
+                // two tokens: zeros for the other one's values (a product with zero would let its NaN in)
+                const bool upper = (threadIdx.x & 32u) != 0u;
+                a[term][0] = __builtin_bit_cast(bf16x8, make_uint4(q[0][0], q[0][1], upper ? 0u : q[2][0], upper ? 0u : q[2][1]));
+                a[term][1] = __builtin_bit_cast(bf16x8, make_uint4(upper ? q[2][0] : 0u, upper ? q[2][1] : 0u, q[1][0], q[1][1]));
+            } else {
+                const u32x8 all = {q[0][0], q[0][1], q[2][0], q[2][1], q[1][0], q[1][1], 0u, 0u};
+                a[term][0] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(all, all, 0, 1, 2, 3));
+                a[term][1] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(all, all, 2, 3, 4, 5));
+            }
+        }
+        f32x4 out[3];
+        out[0] = product16(a[1][0], b.main[0], product16(a[0][0], b.main[0], zero));
+        out[1] = product16(a[1][1], b.main[1], product16(a[0][1], b.main[1], zero));
+        if constexpr (C::kPair == 2) {
+            const f32x4 s0 = product16(a[1][0], b.shared[0], product16(a[0][0], b.shared[0], zero));
+            const f32x4 s1 = product16(a[1][1], b.shared[1], product16(a[0][1], b.shared[1], zero));
+#pragma unroll
+            for (int i = 0; i < 4; ++i) out[2][i] = second ? s1[i] : s0[i];
+        } else {
+            out[2] = product16(a[0][1], b.shared[1], product16(a[0][0], b.shared[0], zero));
+            out[2] = product16(a[1][1], b.shared[1], product16(a[1][0], b.shared[0], out[2]));
+        }
+#pragma unroll
+        for (int v = 0; v < 3; ++v)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) r[C::V * v + 4 * H + i] = out[v][i];
+    });
+    if constexpr (C::kPair == 1) {                          // the stage on r6; vector 2's is in the product
+#pragma unroll
+        for (int i = 0; i < C::V; ++i) {
+            const float p = r[i], q = r[C::V + i];
+            r[i] = p + q;
+            r[C::V + i] = p - q;
+        }
+    }
+}
+
+// The schedule's matrices, and its rounds on a thread's values.
+template <class C>
+using RoundB = std::conditional_t<C::kTwelve, TwelveB, HadamardB>;
+template <class C>
+__device__ __forceinline__ RoundB<C> make_round_b(const ThreadMap<C>& tm) {
+    if constexpr (C::kTwelve) return make_twelve_b<C>(tm);
+    else return make_hadamard_b();
+}
+
+// Both rounds on every tile of the thread: bits 0..9 of the element index.  Round 1 of every tile
 // is issued before any round 2, so that one tile's split has the other tile's matrix instructions
 // to overlap with.  (Explicit MFMA/VALU interleave hints on top of this measured no gain.)
-//   from raw bfloat16 (the forward input x): round 1 needs no split
 template <class C>
-__device__ __forceinline__ void mfma_rounds_from_bf16(float (&r)[C::E], const uint4 (&raw)[C::NV],
-                                                      const HadamardB& b, const HadamardB& b2) {
-    f32x16 d1[C::T];
-    static_for<0, C::T>([&](auto tile) {
-        constexpr int Tl = decltype(tile)::value;
-        d1[Tl] = hadamard_round_bf16(raw[2 * Tl], raw[2 * Tl + 1], b);
-    });
+__device__ __forceinline__ void mfma_round2(float (&r)[C::E], const f32x16 (&d1)[C::T], const HadamardB& b) {
     static_for<0, C::T>([&](auto tile) {
         constexpr int Tl = decltype(tile)::value;
         float v[16];
 #pragma unroll
         for (int i = 0; i < 16; ++i) v[i] = d1[Tl][i];
-        const f32x16 d2 = hadamard_round_f32(v, b2);
+        const f32x16 d2 = hadamard_round_f32(v, b);
 #pragma unroll
         for (int i = 0; i < 16; ++i) r[16 * Tl + i] = d2[i];
     });
 }
-//   from float32 registers in the first layout (the backward pass's alpha' (.) dy)
+//   from raw bfloat16 (the forward input x): round 1 needs no split
 template <class C>
-__device__ __forceinline__ void mfma_rounds_from_f32(float (&r)[C::E], const HadamardB& b,
-                                                     const HadamardB& b2) {
-    f32x16 d1[C::T];
-    static_for<0, C::T>([&](auto tile) {
-        constexpr int Tl = decltype(tile)::value;
-        d1[Tl] = hadamard_round_f32(&r[16 * Tl], b);
-    });
-    static_for<0, C::T>([&](auto tile) {
-        constexpr int Tl = decltype(tile)::value;
-        float v[16];
+__device__ __forceinline__ void mfma_rounds_from_bf16(float (&r)[C::E], const uint4 (&raw)[C::NV], const RoundB<C>& b,
+                                                      const ThreadMap<C>& tm) {
+    if constexpr (C::kTwelve) {
+        const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+        f32x4 d1[3][C::V / 4];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) v[i] = d1[Tl][i];
-        const f32x16 d2 = hadamard_round_f32(v, b2);
+        for (int v = 0; v < 3; ++v)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) r[16 * Tl + i] = d2[i];
-    });
+            for (int h = 0; h < C::V / 4; ++h) d1[v][h] = product16(__builtin_bit_cast(bf16x8, raw[v]), b.b1[h], zero);
+        twelve_round2<C>(r, d1, b, tm.second);
+    } else {
+        f32x16 d1[C::T];
+        static_for<0, C::T>([&](auto tile) {
+            constexpr int Tl = decltype(tile)::value;
+            d1[Tl] = hadamard_round_bf16(raw[2 * Tl], raw[2 * Tl + 1], b);
+        });
+        mfma_round2<C>(r, d1, b);
+    }
+}
+//   from float32 registers in the first layout (the backward pass's alpha' (.) dy): round 1, and both
+template <class C>
+using Round1 = std::conditional_t<C::kTwelve, f32x4[3][2], f32x16[C::kTwelve ? 1 : C::E / 16]>;
+template <class C>
+__device__ __forceinline__ void mfma_round1_from_f32(const float (&r)[C::E], Round1<C>& d1, const RoundB<C>& b) {
+    if constexpr (C::kTwelve) {
+        const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int v = 0; v < 3; ++v) {
+            uint32_t hi[4], lo[4];
+            split_bf16<4>(&r[8 * v], hi, lo);
+            const bf16x8 a_hi = __builtin_bit_cast(bf16x8, make_uint4(hi[0], hi[1], hi[2], hi[3]));
+            const bf16x8 a_lo = __builtin_bit_cast(bf16x8, make_uint4(lo[0], lo[1], lo[2], lo[3]));
+#pragma unroll
+            for (int h = 0; h < 2; ++h) d1[v][h] = product16(a_hi, b.b1[h], product16(a_lo, b.b1[h], zero));
+        }
+    } else {
+        static_for<0, C::T>([&](auto tile) {
+            constexpr int Tl = decltype(tile)::value;
+            d1[Tl] = hadamard_round_f32(&r[16 * Tl], b);
+        });
+    }
+}
+template <class C>
+__device__ __forceinline__ void mfma_round2(float (&r)[C::E], const Round1<C>& d1, const RoundB<C>& b, const ThreadMap<C>& tm) {
+    if constexpr (C::kTwelve) twelve_round2<C>(r, d1, b, tm.second);
+    else mfma_round2<C>(r, d1, b);
+}
+template <class C>
+__device__ __forceinline__ void mfma_rounds_from_f32(float (&r)[C::E], const RoundB<C>& b, const ThreadMap<C>& tm) {
+    Round1<C> d1;
+    mfma_round1_from_f32<C>(r, d1, b);
+    mfma_round2<C>(r, d1, b, tm);
 }
 
 // raw x[tok] (first layout) -> H_raw x in the last layout, whichever schedule C is.
 template <class C, bool TRAILING_BARRIER>
 __device__ __forceinline__ void transform_from_raw(float (&r)[C::E], const uint4 (&raw)[C::NV],
-                                                   float* lds, const ThreadMap<C>& tm,
-                                                   const HadamardB& b, const HadamardB& b2) {
+                                                   float* lds, const ThreadMap<C>& tm, const RoundB<C>& b) {
     if constexpr (C::kMfma) {
-        mfma_rounds_from_bf16<C>(r, raw, b, b2);
+        mfma_rounds_from_bf16<C>(r, raw, b, tm);
         transform<C, true, TRAILING_BARRIER>(r, lds, tm);
     } else {
         unpack_all<C>(r, raw);
@@ -814,10 +1070,9 @@ __device__ __forceinline__ void transform_from_raw(float (&r)[C::E], const uint4
 
 // registers in the last layout -> H_raw (.) in the first layout (matrix-core schedule).
 template <class C, bool TRAILING_BARRIER = false>
-__device__ __forceinline__ void transform_back(float (&r)[C::E], float* lds, const ThreadMap<C>& tm,
-                                               const HadamardB& b, const HadamardB& b2) {
+__device__ __forceinline__ void transform_back(float (&r)[C::E], float* lds, const ThreadMap<C>& tm, const RoundB<C>& b) {
     transform<C, false, TRAILING_BARRIER>(r, lds, tm);
-    mfma_rounds_from_f32<C>(r, b, b2);
+    mfma_rounds_from_f32<C>(r, b, tm);
 }
 
 template <class C>
@@ -866,35 +1121,41 @@ struct SumRows {
     }
 };
 
-template <class C>
-struct Walker {
-    int64_t N, groups;
-    unsigned slot;
-    __device__ __forceinline__ int64_t token(int64_t grp) const { return grp * C::G + slot; }
-    __device__ __forceinline__ int64_t row(int64_t grp) const {       // clamped: always a valid row
-        const int64_t tok = token(grp);
-        return tok < N ? tok : N - 1;
-    }
-    // Whether the slot fetches anything for group grp (matrix-core schedule: a slot is whole waves).  The
-    // clamped row of a slot without a token is another slot's, which the backward pass may overwrite (dx may
-    // alias x or dy); where no barrier keeps that store behind this read, the slot reads nothing.
-    __device__ __forceinline__ bool fetches(int64_t grp) const {
-        if constexpr (C::G == 1 || C::P > 1) return true;
-        else return grp * C::G + (unsigned)__builtin_amdgcn_readfirstlane(slot) < N;
-    }
-};
-
 // sumsq[tok] = sum of the token's r[i]^2 (the values as they stand, before rounding for the store):
 // each thread squares its values, the lanes of a token add up by butterfly shuffles, and a token that
 // spans several waves adds the wave sums through `wave_sums` (one float per wave of the workgroup)
 // in a fixed order, behind one workgroup barrier that every wave passes.
 template <class C>
 __device__ __forceinline__ void token_sumsq(const float (&r)[C::E], float* wave_sums, float* __restrict__ sumsq,
-                                            int64_t tok, int64_t N, unsigned t, unsigned slot, bool lane_ok) {
+                                            int64_t tok, int64_t N, unsigned t, unsigned slot, const ThreadMap<C>& tm) {
+    if constexpr (C::kPair == 2) {            // two tokens to a wave
+        float sq[2] = {0.0f, 0.0f}, both = 0.0f;
+#pragma unroll
+        for (int i = 0; i < C::V; ++i) {
+            sq[0] = fmaf(r[i], r[i], sq[0]);
+            sq[1] = fmaf(r[C::V + i], r[C::V + i], sq[1]);
+            both = fmaf(r[2 * C::V + i], r[2 * C::V + i], both);
+        }
+        sq[0] += tm.second ? 0.0f : both;
+        sq[1] += tm.second ? both : 0.0f;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            sq[0] += __shfl_xor(sq[0], off);
+            sq[1] += __shfl_xor(sq[1], off);
+        }
+        if constexpr (C::TPT > 64) {                        // two waves to those
+            float* mine = wave_sums + 2 * (threadIdx.x >> 6);
+            if ((threadIdx.x & 63u) < 2) mine[t & 1u] = (t & 1u) == 0 ? sq[0] : sq[1];
+            exchange_barrier();
+            if (t < 2 && tok + t < N) sumsq[tok + t] = mine[t] + mine[2 + t];
+        } else {
+            if (t < 2 && tok + t < N) sumsq[tok + t] = t == 0 ? sq[0] : sq[1];
+        }
+        return;
+    }
     float sq = 0.0f;
 #pragma unroll
     for (int i = 0; i < C::E; ++i) sq = fmaf(r[i], r[i], sq);
-    if (C::kTwelve && !lane_ok) sq = 0.0f;                  // padding lanes hold no elements
     constexpr int kLanes = C::TPT < 64 ? C::TPT : 64;       // lanes of one wave that share a token
 #pragma unroll
     for (int off = 1; off < kLanes; off <<= 1) sq += __shfl_xor(sq, off);
@@ -951,10 +1212,6 @@ __global__ __launch_bounds__(C::BT) void forward_kernel(const typename C::io::el
     Walker<C> wk{N, (N + C::G - 1) / C::G, threadIdx.x / C::TPT};
     ThreadMap<C> tm;
     tm.init(t, wk.slot);
-    HadamardB hb{}, hbp{};
-    if constexpr (C::kMfma) hb = make_hadamard_b();
-    if constexpr (C::kTwelve) hbp = make_paley_b(hb);
-    const HadamardB& hb2 = C::kTwelve ? hbp : hb;
     unsigned char* stage = stage_buf + (threadIdx.x >> 6) * (C::NV * 1024);
     unsigned char* stage_r = stage_r_buf + (RESID ? (threadIdx.x >> 6) * (C::NV * 1024) : 0);
 
@@ -969,28 +1226,29 @@ __global__ __launch_bounds__(C::BT) void forward_kernel(const typename C::io::el
     const int64_t grp_end = (clus + 1) * per < wk.groups ? (clus + 1) * per : wk.groups;
     // first token's fetch goes out before anything else; the parameters load in its shadow
     if (grp < grp_end) {
-        stage_issue<C, 0>(stage, x + wk.row(grp) * C::kRow, tm.first_elem, tm.first_ok);
+        stage_issue<C, 0>(stage, x, wk, grp, tm);
         if constexpr (RESID)
-            stage_issue<C, LAST>(stage_r, resid + wk.row(grp) * C::kRow, tm.last_elem, tm.last_ok);
+            stage_issue<C, LAST>(stage_r, resid, wk, grp, tm);
     }
 
     float a[C::E], b[C::E];
-    param_get<C, LAST>(a, alpha, tm.last_elem, tm.last_ok, inv_sqrt_d<C>() * tm.sign);
-    param_get<C, LAST>(b, beta, tm.last_elem, tm.last_ok, 1.0f);
+    param_get<C, true>(a, alpha, tm, inv_sqrt_d<C>());
+    param_get<C, false>(b, beta, tm, 1.0f);
+    RoundB<C> hb{};
+    if constexpr (C::kMfma) hb = make_round_b<C>(tm);
     wait_vmem<0>();
     for (; grp < grp_end; grp += step) {
         const bool more = grp + step < grp_end;
         uint4 raw[C::NV], rraw[RESID ? C::NV : 1];
         stage_read<C>(raw, stage);
-        zero_padding<C>(raw, tm.first_ok);
         if constexpr (RESID) stage_read<C>(rraw, stage_r);
         if (more) {
-            stage_issue<C, 0>(stage, x + wk.row(grp + step) * C::kRow, tm.first_elem, tm.first_ok);
+            stage_issue<C, 0>(stage, x, wk, grp + step, tm);
             if constexpr (RESID)
-                stage_issue<C, LAST>(stage_r, resid + wk.row(grp + step) * C::kRow, tm.last_elem, tm.last_ok);
+                stage_issue<C, LAST>(stage_r, resid, wk, grp + step, tm);
         }
         float r[C::E];
-        transform_from_raw<C, true>(r, raw, lds, tm, hb, hb2);
+        transform_from_raw<C, true>(r, raw, lds, tm, hb);
         if constexpr (RESID) {
             float res[C::E];
             unpack_all<C>(res, rraw);
@@ -1000,25 +1258,29 @@ __global__ __launch_bounds__(C::BT) void forward_kernel(const typename C::io::el
 #pragma unroll
             for (int i = 0; i < C::E; ++i) r[i] = fmaf(r[i], a[i], b[i]);
         }
-        const int64_t tok = wk.token(grp);
-        if constexpr (STATS) token_sumsq<C>(r, wave_sums, sumsq, tok, N, t, wk.slot, tm.last_ok);
+        if constexpr (STATS) token_sumsq<C>(r, wave_sums, sumsq, wk.token(grp), N, t, wk.slot, tm);
         if (more) wait_vmem<0>();
-        global_put<C, LAST, !C::kTwelve>(r, y + tok * C::kRow, tm.last_elem, tok < N && tm.last_ok);
+        global_put<C, LAST>(r, y, wk, grp, tm);
     }
 }
 
-// One 16-byte vector per NV of a row, in the layout of phase PH, straight into registers (cached
-// load).  Padding lanes of a 12 * 2^m row read the row's first block instead (in bounds) and hold zeros.
-template <class C, int PH>
-__device__ __forceinline__ void global_get(uint4 (&raw)[C::NV], const typename C::io::elem_t* row,
-                                           unsigned thread_elem, bool ok) {
-    const unsigned base = (!C::kTwelve || ok) ? thread_elem : 0u;
+// A row's vectors in the layout of phase PH, straight into registers (cached loads).
+//   OUT: as the rounds leave them, i.e. half vectors where a thread computes half of one
+template <class C, int PH, bool OUT = false>
+__device__ __forceinline__ void global_get(uint4 (&raw)[C::NV], const typename C::io::elem_t* tensor,
+                                           const Walker<C>& wk, int64_t grp, const ThreadMap<C>& tm) {
+    const typename C::io::elem_t* row = tensor + wk.row(grp) * C::kRow;
+    const unsigned next = wk.next_row(grp);
     static_for<0, C::NV>([&](auto c) {
         constexpr int Cc = decltype(c)::value;
-        constexpr unsigned off = C::real(reg_elem_offset(C::plan.ph[PH], C::e, Cc * C::V));
-        raw[Cc] = *reinterpret_cast<const uint4*>(row + base + off);
+        const typename C::io::elem_t* p = row + vector_offset<C, PH, Cc, OUT>(tm, next);
+        if constexpr (OUT && C::kHalf) {
+            const uint2 q = *reinterpret_cast<const uint2*>(p);
+            raw[Cc] = make_uint4(q.x, q.y, 0u, 0u);
+        } else {
+            raw[Cc] = *reinterpret_cast<const uint4*>(p);
+        }
     });
-    zero_padding<C>(raw, ok);
 }
 
 // forward for a few tokens (decoding, paper Sec. 5: one token per sequence and step): one token
@@ -1034,26 +1296,24 @@ __global__ __launch_bounds__(C::BT) void forward_once_kernel(const typename C::i
                                                              typename C::io::elem_t* y,
                                                              float* __restrict__ sumsq, int64_t N) {
     static_assert(!STATS || RESID, "the statistic belongs to the residual-stream output");
-    __shared__ float wave_sums[STATS ? C::BT / 64 : 1];
+    __shared__ float wave_sums[STATS ? C::kPair * C::BT / 64 : 1];
     __shared__ __align__(16) float lds[C::kExchangeBytes / 4];
     constexpr int LAST = C::P - 1;
-    const unsigned t = threadIdx.x % C::TPT, slot = threadIdx.x / C::TPT;
+    const unsigned t = threadIdx.x % C::TPT;
+    const Walker<C> wk{N, (N + C::G - 1) / C::G, threadIdx.x / C::TPT};
+    const int64_t grp = blockIdx.x;
     ThreadMap<C> tm;
-    tm.init(t, slot);
-    const int64_t tok = (int64_t)blockIdx.x * C::G + slot;
-    const int64_t row = tok < N ? tok : N - 1;                  // a ragged group re-reads the last token
+    tm.init(t, wk.slot);
     uint4 raw[C::NV], rraw[RESID ? C::NV : 1];
-    global_get<C, 0>(raw, x + row * C::kRow, tm.first_elem, tm.first_ok);
-    if constexpr (RESID) global_get<C, LAST>(rraw, resid + row * C::kRow, tm.last_elem, tm.last_ok);
+    global_get<C, 0>(raw, x, wk, grp, tm);                      // a ragged group re-reads the last token
+    if constexpr (RESID) global_get<C, LAST, true>(rraw, resid, wk, grp, tm);
     float a[C::E], b[C::E];
-    param_get<C, LAST>(a, alpha, tm.last_elem, tm.last_ok, inv_sqrt_d<C>() * tm.sign);
-    param_get<C, LAST>(b, beta, tm.last_elem, tm.last_ok, 1.0f);
-    HadamardB hb{}, hbp{};
-    if constexpr (C::kMfma) hb = make_hadamard_b();
-    if constexpr (C::kTwelve) hbp = make_paley_b(hb);
-    const HadamardB& hb2 = C::kTwelve ? hbp : hb;
+    param_get<C, true>(a, alpha, tm, inv_sqrt_d<C>());
+    param_get<C, false>(b, beta, tm, 1.0f);
+    RoundB<C> hb{};
+    if constexpr (C::kMfma) hb = make_round_b<C>(tm);
     float r[C::E];
-    transform_from_raw<C, false>(r, raw, lds, tm, hb, hb2);
+    transform_from_raw<C, false>(r, raw, lds, tm, hb);
     if constexpr (RESID) {
         float res[C::E];
         unpack_all<C>(res, rraw);
@@ -1063,8 +1323,8 @@ __global__ __launch_bounds__(C::BT) void forward_once_kernel(const typename C::i
 #pragma unroll
         for (int i = 0; i < C::E; ++i) r[i] = fmaf(r[i], a[i], b[i]);
     }
-    if constexpr (STATS) token_sumsq<C>(r, wave_sums, sumsq, tok, N, t, slot, tm.last_ok);
-    global_put<C, LAST, false>(r, y + tok * C::kRow, tm.last_elem, tok < N && tm.last_ok);
+    if constexpr (STATS) token_sumsq<C>(r, wave_sums, sumsq, wk.token(grp), N, t, wk.slot, tm);
+    global_put<C, LAST, false>(r, y, wk, grp, tm);
 }
 
 // The sums of a workgroup's G token slots (in LDS, one region of kTokenWords floats each) added up, times
@@ -1074,12 +1334,17 @@ __global__ __launch_bounds__(C::BT) void forward_once_kernel(const typename C::i
 // 68.7 us for the call.
 template <class C>
 __device__ __forceinline__ void add_token_slots(float* out, const float* slots, unsigned tid, float scale) {
-    constexpr int CHAINS = C::G < 8 ? C::G : 8;
-    if constexpr (C::D >= 4 * C::BT) {
-        for (unsigned j = 4 * tid; j < (unsigned)C::D; j += 4 * C::BT) {
+    constexpr int SLOTS = C::G / C::kPair, CHAINS = SLOTS < 8 ? SLOTS : 8;
+    if constexpr (C::D >= 4 * C::BT || C::kTwelve) {
+        // unrolled: the reads of one pass do not wait for the stores of the one before
+        constexpr int PASSES = (C::D + 4 * C::BT - 1) / (4 * C::BT);
+#pragma unroll
+        for (int pass = 0; pass < PASSES; ++pass) {
+            const unsigned j = 4 * (tid + pass * C::BT);
+            if (C::D % (4 * C::BT) != 0 && j >= (unsigned)C::D) break;
             float4 acc[CHAINS];
 #pragma unroll
-            for (int g = 0; g < C::G; ++g) {
+            for (int g = 0; g < SLOTS; ++g) {
                 const float4 q = *reinterpret_cast<const float4*>(slots + g * C::kTokenWords + C::phys(j));
                 acc[g % CHAINS] = g < CHAINS ? q : add4(acc[g % CHAINS], q);
             }
@@ -1087,15 +1352,13 @@ __device__ __forceinline__ void add_token_slots(float* out, const float* slots, 
             for (int half = CHAINS / 2; half >= 1; half /= 2)
 #pragma unroll
                 for (int c = 0; c < half; ++c) acc[c] = add4(acc[c], acc[c + half]);
-            if (C::valid(j))
-                put_sums<C::kRow>(out + C::real(j), make_float4(acc[0].x * scale, acc[0].y * scale, acc[0].z * scale,
-                                                                acc[0].w * scale));
+            put_sums<C::kRow>(out + j, make_float4(acc[0].x * scale, acc[0].y * scale, acc[0].z * scale, acc[0].w * scale));
         }
     } else {
         for (unsigned j = tid; j < (unsigned)C::D; j += C::BT) {
             float acc[CHAINS];
 #pragma unroll
-            for (int g = 0; g < C::G; ++g) {
+            for (int g = 0; g < SLOTS; ++g) {
                 const float q = slots[g * C::kTokenWords + C::phys(j)];
                 acc[g % CHAINS] = g < CHAINS ? q : acc[g % CHAINS] + q;
             }
@@ -1103,25 +1366,54 @@ __device__ __forceinline__ void add_token_slots(float* out, const float* slots, 
             for (int half = CHAINS / 2; half >= 1; half /= 2)
 #pragma unroll
                 for (int c = 0; c < half; ++c) acc[c] += acc[c + half];
-            if (C::valid(j)) out[C::real(j)] = acc[0] * scale;
+            out[j] = acc[0] * scale;
         }
     }
 }
 
-// A thread's sums (last layout) times `scale` straight to the row: for a padded row that is the workgroup's
-// only token, where the walk over the slots' memory offsets costs more than the 32-byte pieces.
+// A thread's sums (last layout) to its token's slot for add_token_slots.
+template <class C>
+__device__ __forceinline__ void sums_to_slot(const float (&acc)[C::kSums], float* slots, const ThreadMap<C>& tm) {
+    if constexpr (C::kPair == 2) {                          // lanes l and l ^ 8 hold the same columns in vector 2
+#pragma unroll
+        for (int i = 0; i < C::V; i += 4) {
+            float both[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const float v = acc[C::V + i + k];
+                both[k] = v + __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x128, 0xf, 0xf, false));   // row_ror:8
+            }
+            *reinterpret_cast<float4*>(slots + tm.columns + i) = make_float4(acc[i], acc[i + 1], acc[i + 2], acc[i + 3]);
+            if (!tm.second) *reinterpret_cast<float4*>(slots + tm.columns2 + i) = make_float4(both[0], both[1], both[2], both[3]);
+        }
+    } else if constexpr (C::kTwelve) {
+        static_for<0, C::E / 4>([&](auto i) {
+            constexpr int I = decltype(i)::value * 4, VEC = I / C::V;
+            float* at = slots + (VEC == 2 ? tm.columns2 : tm.columns + VEC * 64) + I % C::V;
+            *reinterpret_cast<float4*>(at) = make_float4(acc[I], acc[I + 1], acc[I + 2], acc[I + 3]);
+        });
+    } else {
+        lds_put<C, C::P - 1>(acc, slots + tm.lds_off[C::P - 1]);
+    }
+}
+
+// A thread's sums (last layout) times `scale` straight to the row, where the workgroup has one token.
 template <class C>
 __device__ __forceinline__ void put_thread_sums(const float (&acc)[C::E], float* out, float scale, const ThreadMap<C>& tm) {
     static_for<0, C::E / 4>([&](auto i) {
         constexpr int I = decltype(i)::value * 4;
-        constexpr unsigned off = C::real(reg_elem_offset(C::plan.ph[C::P - 1], C::e, I));
-        if (!C::kTwelve || tm.last_ok)
-            put_sums<C::kRow>(out + tm.last_elem + off,
-                              make_float4(acc[I] * scale, acc[I + 1] * scale, acc[I + 2] * scale, acc[I + 3] * scale));
+        put_sums<C::kRow>(out + vector_offset<C, C::P - 1, I / C::V>(tm, 0u) + I % C::V,
+                          make_float4(acc[I] * scale, acc[I + 1] * scale, acc[I + 2] * scale, acc[I + 3] * scale));
     });
 }
+// dalpha without the signs that the last layout carries in z.
 template <class C>
-constexpr bool sums_through_lds() { return !(C::kTwelve && C::G == 1); }
+__device__ __forceinline__ void unsign_sums(float (&da)[C::kSums], const ThreadMap<C>& tm) {
+    if constexpr (C::kWave || (C::kTwelve && C::P > 1)) {
+#pragma unroll
+        for (int i = 0; i < C::E; ++i) da[i] *= tm.sign;
+    }
+}
 
 // backward:  z = H x (recomputed);  dalpha += dy z;  dbeta += dy;  dx = H_raw((alpha/sqrt d) dy)
 // Each workgroup keeps its dalpha/dbeta sums in registers and at the end writes one row of partial
@@ -1138,7 +1430,7 @@ constexpr bool sums_through_lds() { return !(C::kTwelve && C::G == 1); }
 // traffic of a forward pass); without DX nothing is transformed back or stored.  With only one of
 // the two, consecutive transforms run in the same order and need the trailing barrier again.
 template <class C, bool GRADS, bool DX>
-__global__ __launch_bounds__(C::BT) void backward_kernel(const typename C::io::elem_t* dy,
+__global__ __launch_bounds__(C::BT, C::kBwdWavesPerSimd) void backward_kernel(const typename C::io::elem_t* dy,
                                                          const typename C::io::elem_t* x,
                                                          const float* __restrict__ alpha,
                                                          typename C::io::elem_t* dx,
@@ -1154,55 +1446,53 @@ __global__ __launch_bounds__(C::BT) void backward_kernel(const typename C::io::e
     Walker<C> wk{N, (N + C::G - 1) / C::G, threadIdx.x / C::TPT};
     ThreadMap<C> tm;
     tm.init(t, wk.slot);
-    HadamardB hb{}, hbp{};
-    hb = make_hadamard_b();
-    if constexpr (C::kTwelve) hbp = make_paley_b(hb);
-    const HadamardB& hb2 = C::kTwelve ? hbp : hb;
     unsigned char* stage_x = stage_x_buf + (GRADS ? (threadIdx.x >> 6) * (C::NV * 1024) : 0);
     unsigned char* stage_g = stage_g_buf + (threadIdx.x >> 6) * (C::NV * 1024);
 
     const int64_t step = gridDim.x;
     int64_t grp = blockIdx.x;
     if (grp < wk.groups && wk.fetches(grp)) {
-        if constexpr (GRADS) stage_issue<C, 0>(stage_x, x + wk.row(grp) * C::kRow, tm.first_elem, tm.first_ok);
-        stage_issue<C, LAST>(stage_g, dy + wk.row(grp) * C::kRow, tm.last_elem, tm.last_ok);
+        if constexpr (GRADS) stage_issue<C, 0>(stage_x, x, wk, grp, tm);
+        stage_issue<C, LAST>(stage_g, dy, wk, grp, tm);
     }
 
-    float a[DX ? C::E : 1], da[GRADS ? C::E : 1], db[GRADS ? C::E : 1];
-    if constexpr (DX) param_get<C, LAST>(a, alpha, tm.last_elem, tm.last_ok, inv_sqrt_d<C>());
+    float a[DX ? C::E : 1], da[GRADS ? C::kSums : 1], db[GRADS ? C::kSums : 1];
+    if constexpr (DX) param_get<C, true>(a, alpha, tm, inv_sqrt_d<C>());
     if constexpr (GRADS) {
 #pragma unroll
-        for (int i = 0; i < C::E; ++i) { da[i] = 0.0f; db[i] = 0.0f; }
+        for (int i = 0; i < C::kSums; ++i) { da[i] = 0.0f; db[i] = 0.0f; }
     }
+    const RoundB<C> hb = make_round_b<C>(tm);
     wait_vmem<0>();
     for (; grp < wk.groups; grp += step) {
         const bool more = grp + step < wk.groups;
         uint4 raw[GRADS ? C::NV : 1], graw[C::NV];
         if constexpr (GRADS) {
+            zero_missing<C>(stage_x, wk, grp, tm);
+            zero_missing<C>(stage_g, wk, grp, tm);
             stage_read<C>(raw, stage_x);
-            zero_padding<C>(raw, tm.first_ok);
         }
         stage_read<C>(graw, stage_g);
-        zero_padding<C>(graw, tm.last_ok);
         if (more && wk.fetches(grp + step)) {
             if constexpr (GRADS)
-                stage_issue<C, 0>(stage_x, x + wk.row(grp + step) * C::kRow, tm.first_elem, tm.first_ok);
-            stage_issue<C, LAST>(stage_g, dy + wk.row(grp + step) * C::kRow, tm.last_elem, tm.last_ok);
+                stage_issue<C, 0>(stage_x, x, wk, grp + step, tm);
+            stage_issue<C, LAST>(stage_g, dy, wk, grp + step, tm);
         }
         float g[C::E];
-        const int64_t tok = wk.token(grp);
-        const bool active = C::G == 1 || tok < N;             // one slot per workgroup: never ragged
+        // one slot per workgroup: never ragged; two tokens per slot: zero_missing
+        const bool active = C::G == 1 || C::kPair == 2 || wk.token(grp) < N;
         if constexpr (GRADS) {
             float r[C::E];
-            transform_from_raw<C, !BOTH>(r, raw, lds, tm, hb, hb2);   // r = H_raw x, last layout
+            transform_from_raw<C, !BOTH>(r, raw, lds, tm, hb);   // r = H_raw x, last layout
             unpack_all<C>(g, graw);
             // a slot of a ragged last group that has no token adds nothing, whatever its stage holds (a
             // product with zero would do for finite values only)
             if (active) {
 #pragma unroll
                 for (int i = 0; i < C::E; ++i) {
-                    da[i] = fmaf(g[i], r[i], da[i]);          // 1/sqrt d applied once at the end
-                    db[i] += g[i];
+                    const int at = C::kPair == 2 && i >= C::V ? i - C::V : i;
+                    da[at] = fmaf(g[i], r[i], da[at]);        // 1/sqrt d applied once at the end
+                    db[at] += g[i];
                 }
             }
         } else {
@@ -1211,9 +1501,9 @@ __global__ __launch_bounds__(C::BT) void backward_kernel(const typename C::io::e
         if constexpr (DX) {
 #pragma unroll
             for (int i = 0; i < C::E; ++i) g[i] *= a[i];
-            transform_back<C, !BOTH>(g, lds, tm, hb, hb2);    // g = H_raw(alpha' dy), first layout
+            transform_back<C, !BOTH>(g, lds, tm, hb);    // g = H_raw(alpha' dy), first layout
             if (more) wait_vmem<0>();
-            global_put<C, 0, !C::kTwelve>(g, dx + tok * C::kRow, tm.first_elem, active && tm.first_ok);
+            global_put<C, 0>(g, dx, wk, grp, tm);
         } else {
             if (more) wait_vmem<0>();
         }
@@ -1221,15 +1511,11 @@ __global__ __launch_bounds__(C::BT) void backward_kernel(const typename C::io::e
     if constexpr (GRADS) {
     // Sum the G token slots of this workgroup through LDS, then write the workgroup's row.
     const float s = inv_sqrt_d<C>();
+    unsign_sums<C>(da, tm);
 #pragma unroll
     for (int which = 0; which < 2; ++which) {
-        if constexpr (!sums_through_lds<C>()) {
-            put_thread_sums<C>(which == 0 ? da : db, sums.row(which), which == 0 ? s : 1.0f, tm);
-            continue;
-        }
         __syncthreads();                          // the last exchange, or the first sums, have been read everywhere
-        if (which == 0) lds_put<C, LAST>(da, lds + tm.lds_off[LAST]);
-        else            lds_put<C, LAST>(db, lds + tm.lds_off[LAST]);
+        sums_to_slot<C>(which == 0 ? da : db, lds, tm);
         __syncthreads();
         add_token_slots<C>(sums.row(which), lds, threadIdx.x, which == 0 ? s : 1.0f);
     }
@@ -1373,10 +1659,7 @@ void backward_wave_kernel(const typename C::io::elem_t* dy, const typename C::io
         }
     }
     float a[DX ? C::E : 1], da[GRADS ? C::E : 1], db[GRADS ? C::E : 1];
-    const float scale = inv_sqrt_d<C>() * tm.sign;             // the sign of dx's input and of z
-    if constexpr (DX) {
-        param_get<C, LAST>(a, alpha, tm.last_elem, true, scale);
-    }
+    if constexpr (DX) param_get<C, true>(a, alpha, tm, inv_sqrt_d<C>());      // with the sign of dx's input and of z
     if constexpr (GRADS) {
 #pragma unroll
         for (int i = 0; i < C::E; ++i) { da[i] = 0.0f; db[i] = 0.0f; }
@@ -1457,17 +1740,13 @@ void backward_wave_kernel(const typename C::io::elem_t* dy, const typename C::io
 #pragma unroll
         for (int which = 0; which < 2; ++which) {
             float* row = sums.row(which);
-            if (which == 0) {
-#pragma unroll
-                for (int i = 0; i < C::E; ++i) da[i] *= tm.sign;
-            }
+            if (which == 0) unsign_sums<C>(da, tm);
             if constexpr (C::G == 1) {                         // one token per workgroup: straight to the row
                 put_thread_sums<C>(which == 0 ? da : db, row, which == 0 ? s : 1.0f, tm);
                 continue;
             }
             __syncthreads();
-            if (which == 0) lds_put<C, LAST>(da, slots + tm.lds_off[LAST]);
-            else            lds_put<C, LAST>(db, slots + tm.lds_off[LAST]);
+            sums_to_slot<C>(which == 0 ? da : db, slots, tm);
             __syncthreads();
             add_token_slots<C>(row, slots, threadIdx.x, which == 0 ? s : 1.0f);
         }
@@ -1479,13 +1758,9 @@ void backward_wave_kernel(const typename C::io::elem_t* dy, const typename C::io
 template <class C>
 __device__ __forceinline__ void write_partial_row(const float (&acc)[C::E], float* slots, float* out,
                                                   float scale, unsigned tid, const ThreadMap<C>& tm) {
-    if constexpr (sums_through_lds<C>()) {
-        lds_put<C, C::P - 1>(acc, slots + tm.lds_off[C::P - 1]);
-        __syncthreads();
-        add_token_slots<C>(out, slots, tid, scale);
-    } else {
-        put_thread_sums<C>(acc, out, scale, tm);
-    }
+    sums_to_slot<C>(acc, slots, tm);
+    __syncthreads();
+    add_token_slots<C>(out, slots, tid, scale);
 }
 
 // backward (all three outputs) on three teams of waves per workgroup, 3 * C::BT threads, for the
@@ -1521,7 +1796,9 @@ __global__ __launch_bounds__(3 * C::BT) void backward_teams_kernel(const typenam
     __shared__ __align__(16) float lds_x[C::kExchangeBytes / 4];
     __shared__ __align__(16) float lds_g[C::kExchangeBytes / 4];
     __shared__ __align__(16) unsigned char stage_x_buf[C::kStageBytes];
-    __shared__ __align__(16) unsigned char stage_g_buf[2][C::kStageBytes];
+    // two buffers; at the end the dbeta sums of the token slots
+    constexpr unsigned kSlotBytes = C::G / C::kPair * C::kTokenWords * 4u;
+    __shared__ __align__(16) unsigned char stage_g_buf[kSlotBytes > 2u * C::kStageBytes ? kSlotBytes : 2u * C::kStageBytes];
     constexpr int LAST = 1;
     const unsigned team = threadIdx.x / C::BT;                // wave-uniform: BT is a multiple of 64
     const unsigned tid = threadIdx.x % C::BT;
@@ -1531,18 +1808,17 @@ __global__ __launch_bounds__(3 * C::BT) void backward_teams_kernel(const typenam
     tm.init(t, wk.slot);
     const unsigned wave_off = (tid >> 6) * (C::NV * 1024);
     unsigned char* stage_x = stage_x_buf + wave_off;
-    unsigned char* stage_g0 = stage_g_buf[0] + wave_off;
-    unsigned char* stage_g1 = stage_g_buf[1] + wave_off;
+    unsigned char* stage_g0 = stage_g_buf + wave_off;
+    unsigned char* stage_g1 = stage_g_buf + C::kStageBytes + wave_off;
 
     const int64_t step = gridDim.x;
     int64_t grp = blockIdx.x;
 
     if (team == 0) {
-        HadamardB hb{}, hbp{};
-        hb = make_hadamard_b();
-        if constexpr (C::kTwelve) hbp = make_paley_b(hb);
-        const HadamardB& hb2 = C::kTwelve ? hbp : hb;
-        if (grp < wk.groups) stage_issue<C, 0>(stage_x, x + wk.row(grp) * C::kRow, tm.first_elem, tm.first_ok);
+        // (before the first fetch: with it behind, the compiler waits for the prefetch at every exchange, 284 against
+        // 270 us at 32768 x 8192)
+        const RoundB<C> hb = make_round_b<C>(tm);
+        if (grp < wk.groups) stage_issue<C, 0>(stage_x, x, wk, grp, tm);
         float da[C::E];
 #pragma unroll
         for (int i = 0; i < C::E; ++i) da[i] = 0.0f;
@@ -1551,17 +1827,16 @@ __global__ __launch_bounds__(3 * C::BT) void backward_teams_kernel(const typenam
             uint4 raw[C::NV], graw[C::NV];
             wait_vmem<0>();                                     // x(k) has landed
             stage_read<C>(raw, stage_x);
-            zero_padding<C>(raw, tm.first_ok);
-            if (more) stage_issue<C, 0>(stage_x, x + wk.row(grp + step) * C::kRow, tm.first_elem, tm.first_ok);
+            if (more) stage_issue<C, 0>(stage_x, x, wk, grp + step, tm);
             float r[C::E], g[C::E];
-            mfma_rounds_from_bf16<C>(r, raw, hb, hb2);
-            run_stages<C, 0>(r);
+            mfma_rounds_from_bf16<C>(r, raw, hb, tm);
+            if constexpr (!C::kTwelve) run_stages<C, 0>(r);
             lds_put<C, 0>(r, lds_x + tm.lds_off[0]);
             exchange_barrier();                                 // B1(k)
             lds_get<C, LAST>(r, lds_x + tm.lds_off[LAST]);
             stage_read<C, false>(graw, par ? stage_g1 : stage_g0);     // fetched by the Y1 waves, read by both
-            zero_padding<C>(graw, tm.last_ok);
-            run_stages<C, LAST>(r);
+            if constexpr (C::kTwelve) wave_bit_stages<C, false>(r, tm);
+            else run_stages<C, LAST>(r);
             unpack_all<C>(g, graw);
             if (C::G == 1 || wk.token(grp) < N) {               // a ragged last group's clamped rows add nothing
 #pragma unroll
@@ -1569,11 +1844,12 @@ __global__ __launch_bounds__(3 * C::BT) void backward_teams_kernel(const typenam
             }
             exchange_barrier();                                 // B2(k)
         }
+        unsign_sums<C>(da, tm);
         write_partial_row<C>(da, lds_x, sums.row(0), inv_sqrt_d<C>(), tid, tm);
     } else if (team == 1) {
-        if (grp < wk.groups) stage_issue<C, LAST>(stage_g0, dy + wk.row(grp) * C::kRow, tm.last_elem, tm.last_ok);
+        if (grp < wk.groups) stage_issue<C, LAST>(stage_g0, dy, wk, grp, tm);
         float a[C::E], db[C::E];
-        param_get<C, LAST>(a, alpha, tm.last_elem, tm.last_ok, inv_sqrt_d<C>());
+        param_get<C, true>(a, alpha, tm, inv_sqrt_d<C>());
 #pragma unroll
         for (int i = 0; i < C::E; ++i) db[i] = 0.0f;
         for (int par = 0; grp < wk.groups; grp += step, par ^= 1) {
@@ -1581,8 +1857,7 @@ __global__ __launch_bounds__(3 * C::BT) void backward_teams_kernel(const typenam
             uint4 graw[C::NV];
             wait_vmem<0>();                                     // dy(k) has landed
             stage_read<C, false>(graw, par ? stage_g1 : stage_g0);
-            zero_padding<C>(graw, tm.last_ok);
-            if (more) stage_issue<C, LAST>(par ? stage_g0 : stage_g1, dy + wk.row(grp + step) * C::kRow, tm.last_elem, tm.last_ok);
+            if (more) stage_issue<C, LAST>(par ? stage_g0 : stage_g1, dy, wk, grp + step, tm);
             float g[C::E];
             unpack_all<C>(g, graw);
             if (C::G == 1 || wk.token(grp) < N) {               // a ragged last group's clamped rows add nothing
@@ -1591,55 +1866,39 @@ __global__ __launch_bounds__(3 * C::BT) void backward_teams_kernel(const typenam
             }
 #pragma unroll
             for (int i = 0; i < C::E; ++i) g[i] *= a[i];
-            run_stages<C, LAST>(g);
+            if constexpr (C::kTwelve) wave_bit_stages<C, true>(g, tm);
+            else run_stages<C, LAST>(g);
             exchange_barrier();                                 // B1(k): the Y2 waves have read token k-1
             lds_put<C, LAST>(g, lds_g + tm.lds_off[LAST]);
             exchange_barrier();                                 // B2(k)
         }
-        // the stage buffers are idle now (same size as an exchange region)
-        write_partial_row<C>(db, reinterpret_cast<float*>(&stage_g_buf[0][0]),
-                             sums.row(1), 1.0f, tid, tm);
+        // the stage buffers are idle now
+        write_partial_row<C>(db, reinterpret_cast<float*>(stage_g_buf), sums.row(1), 1.0f, tid, tm);
     } else {
-        HadamardB hb{}, hbp{};
-        hb = make_hadamard_b();
-        if constexpr (C::kTwelve) hbp = make_paley_b(hb);
-        const HadamardB& hb2 = C::kTwelve ? hbp : hb;
+        const RoundB<C> hb = make_round_b<C>(tm);
         int64_t prev = -1;                                      // token group whose Y data is in the exchange region
-        auto first_half = [&](float (&g)[C::E], f32x16 (&d1)[C::T]) {
+        auto first_half = [&](float (&g)[C::E], Round1<C>& d1) {
             lds_get<C, 0>(g, lds_g + tm.lds_off[0]);
-            run_stages<C, 0>(g);
-            static_for<0, C::T>([&](auto tile) {
-                constexpr int Tl = decltype(tile)::value;
-                d1[Tl] = hadamard_round_f32(&g[16 * Tl], hb);
-            });
+            if constexpr (!C::kTwelve) run_stages<C, 0>(g);
+            mfma_round1_from_f32<C>(g, d1, hb);
         };
-        auto second_half = [&](float (&g)[C::E], f32x16 (&d1)[C::T], int64_t grp_done) {
-            static_for<0, C::T>([&](auto tile) {
-                constexpr int Tl = decltype(tile)::value;
-                float v[16];
-#pragma unroll
-                for (int i = 0; i < 16; ++i) v[i] = d1[Tl][i];
-                const f32x16 d2 = hadamard_round_f32(v, hb2);
-#pragma unroll
-                for (int i = 0; i < 16; ++i) g[16 * Tl + i] = d2[i];
-            });
-            const int64_t tok = wk.token(grp_done);
-            const bool active = C::G == 1 || tok < N;
-            global_put<C, 0, !C::kTwelve>(g, dx + tok * C::kRow, tm.first_elem, active && tm.first_ok);
+        auto second_half = [&](float (&g)[C::E], const Round1<C>& d1, int64_t grp_done) {
+            mfma_round2<C>(g, d1, hb, tm);
+            global_put<C, 0>(g, dx, wk, grp_done, tm);
         };
         for (; grp < wk.groups; grp += step) {
             float g[C::E];
-            f32x16 d1[C::T];
+            Round1<C> d1;
             if (prev >= 0) first_half(g, d1);
             exchange_barrier();                                 // B1(k)
             if (prev >= 0) second_half(g, d1, prev);
             exchange_barrier();                                 // B2(k): token k is in the exchange region
             prev = grp;
         }
-        if constexpr (sums_through_lds<C>()) exchange_barrier();        // the barrier of the other teams' row writes
+        exchange_barrier();                                     // the barrier of the other teams' row writes
         if (prev >= 0) {
             float g[C::E];
-            f32x16 d1[C::T];
+            Round1<C> d1;
             first_half(g, d1);
             second_half(g, d1, prev);
         }

@@ -206,14 +206,54 @@ constexpr int wave_log_e(int n, int v) {
     return e;
 }
 
-// ---- rows of 12 * 2^m elements on 2^n = 16 * 2^m slots ----------------------------------------
-// Slot index s = (r_hi << 8) | (b << 4) | r_lo  <->  element b * 2^m + (r_hi << 4 | r_lo), m = n - 4:
-// the block number b = 0..11 occupies slot bits 4..7, b = 12..15 are padding.  A bit permutation, so
-// additive over disjoint bit sets like the LDS maps below.
-constexpr unsigned twelve_elem(unsigned s, int n) {
-    return (((s >> 4) & 15u) << (n - 4)) | ((s >> 8) << 4) | (s & 15u);
+// ---- rows of 12 * 2^m elements (bfloat16, m = 6..10) --------------------------------------------
+//
+// Element e = b * 2^m + r, block b = 0..11.  H_raw = P12 (x) S_{2^m}: the order-12 matrix across the
+// blocks, Sylvester stages on the bits of r.  A wave holds 1536 elements, three 16-byte vectors (8
+// consecutive elements, r bits 0..2) per lane and no empty place:
+//   vectors 0, 1: rows of blocks 0..7,   lane = b0 b1 r3 b2 r4 r5 (bit 0 first), the vector's number is "pair"
+//   vector  2   : rows of blocks 8..11,  lane = b0 b1 r3 pair r4 r5
+// "pair" is r6, or for m = 6 the second of the wave's two tokens.  Bits r7.. are the wave's number within
+// the token.  Two matrix-core rounds of 16x16x32 products transform r0..r5 and the blocks in place:
+//   round 1 contracts the 32 values (r0 r1 r2 r4 r5) of every row, 16 rows a product: rows change places
+//           with columns, and the rows' index (block, r3) is then in the registers and lane bits 4, 5;
+//   round 2 contracts the 24 values (block, r3): a row's operand is 16 values of vector 0 or 1 and its half
+//           of vector 2's, the other half multiplied by zeros; results of blocks 8..11 of both halves are
+//           accumulated side by side into vector 2, for m > 6 with the stage on r6 between them done by the
+//           signs of that product.
+// So the products unpack and pack the odd quarter: no vector or lane is idle anywhere else, where a row
+// padded to 16 blocks left a quarter of the lanes and of every instruction's work empty.
+constexpr int twelve_wave_bits(int m) { return m > 7 ? m - 7 : 0; }      // log2(waves per token)
+constexpr unsigned twelve_block(unsigned lane, int vec) {
+    return (lane & 3u) | (vec == 2 ? 8u : ((lane >> 3) & 1u) << 2);
 }
-constexpr bool twelve_valid(unsigned s) { return ((s >> 6) & 3u) != 3u; }
+constexpr unsigned twelve_pair(unsigned lane, int vec) { return vec == 2 ? (lane >> 3) & 1u : (unsigned)vec; }
+// First element of the vector a lane holds in the first layout (m = 6: within its own token).
+constexpr unsigned twelve_elem(unsigned lane, unsigned wave, int vec, int m) {
+    return (twelve_block(lane, vec) << m) | (((lane >> 2) & 1u) << 3) | ((lane >> 4) << 4) |
+           (m > 6 ? twelve_pair(lane, vec) << 6 : 0u) | (wave << 7);
+}
+// The last layout (tokens of several waves): wave bits k = 0, 1, 2 exchanged with lane positions 0, 1, 3,
+// where their stages run through DPP operands.  Its own inverse.
+constexpr int twelve_lane_pos(int k) { return k < 2 ? k : 3; }
+struct LaneWave { unsigned lane, wave; };
+constexpr LaneWave twelve_swap(unsigned lane, unsigned wave, int w) {
+    LaneWave s{lane, wave};
+    for (int k = 0; k < w; ++k) {
+        const int p = twelve_lane_pos(k);
+        const unsigned x = ((lane >> p) ^ (wave >> k)) & 1u;
+        s.lane ^= x << p;
+        s.wave ^= x << k;
+    }
+    return s;
+}
+// Exchange region of a token: one block of 64 16-byte places per (four registers, wave), and 16 bytes more, so
+// that the lanes of a scattered access differ in their banks.  Every thread puts in the order of one layout and
+// gets in the order of the other.
+constexpr unsigned kTwelveBlockWords = 64u * 4u + 4u;
+constexpr unsigned twelve_place(unsigned lane, unsigned wave) { return wave * kTwelveBlockWords + lane * 4u; }
+// Column sums in LDS: 16 words more after every block, for the same reason.
+constexpr unsigned twelve_column(unsigned e, int m) { return e + 16u * (e >> m); }
 
 // P12: symmetric order-12 Hadamard matrix (Paley's second construction over GF(5)), first row and
 // column +1.  Bit c of row r's mask is set where P12[r][c] = -1.
@@ -233,13 +273,32 @@ constexpr bool paley12_packing_matches() {
     return true;
 }
 static_assert(paley12_packing_matches(), "packed P12 masks");
-// Entry of the matrix the second matrix-core round applies along slot bits 3..7 of such a row:
-// index m = bit3 + 2 * block;  (-1)^(bit3_in & bit3_out) * P12[block_in][block_out], 0 on padding.
-constexpr int twelve_round_entry(unsigned m_in, unsigned m_out) {
-    const unsigned bi = m_in >> 1, bo = m_out >> 1;
-    if (bi >= 12u || bo >= 12u) return 0;
-    const unsigned minus = ((paley12_minus_row(bi) >> bo) ^ (m_in & m_out)) & 1u;
-    return minus ? -1 : 1;
+// Operand words of the rounds' matrices for a lane: bf16 pairs, elements 2*word and 2*word + 1 of the lane's 8
+// (matrix row k = 8 * (lane / 16) + element, column j = lane % 16).  Built on every launch, so in few operations.
+constexpr unsigned kBothSigns = 0x80008000u;
+// Round 1, output half `half`: column j stands for (r0 r1 | r4 r5) = (j0 j1 | j2 j3), half for r2, row k for
+// (r0 r1 r2 r4 r5); the sign is the parity of row & column.
+constexpr unsigned twelve_round1_word(unsigned lane, int half, int word) {
+    const unsigned j = lane & 15u, both = (j >> 2) & (lane >> 4), base = (both ^ (both >> 1)) & 1u;      // r4, r5
+    const unsigned first = 0x3F803F80u | (base << 15) | ((base ^ j) << 31);                             // r0: element 1
+    const unsigned r1 = (word & 1) && (j & 2u) ? kBothSigns : 0u;
+    return first ^ r1 ^ ((word & 2) && half ? kBothSigns : 0u);
+}
+// Round 2 on the rows of `pair`, results for vectors 0 / 1 (shared = false) or 2.  Matrix rows: the four registers
+// of vector `pair` and of vector 2, in this order for pair 0 and in the other for pair 1 (the registers then lie
+// side by side as 0, 2, 1 and both operands are slices of them); lanes of vector 2 that belong to the other
+// pair are zero.  Columns of vector 2 that do are zero for m = 6, and else hold the stage on r6: minus where both
+// the row and the column are of pair 1.
+constexpr unsigned twelve_round2_word(unsigned lane, int pair, bool shared, int word, int m) {
+    const unsigned j = lane & 15u, g = lane >> 4;
+    const bool second = (word >> 1) != pair;                     // registers of vector 2
+    const unsigned wrong_column = shared && m == 6 ? (j >> 3) ^ (unsigned)pair : 0u;
+    const unsigned wrong_row = second ? (g >> 1) ^ (unsigned)pair : 0u;
+    const unsigned keep = ((wrong_column | wrong_row) & 1u) - 1u;               // all ones or none
+    const unsigned flip = (g & (j >> 2) & 1u) ^ (shared && pair && m > 6 ? (j >> 3) & 1u : 0u);      // r3, r6
+    const unsigned minus = paley12_minus_row(twelve_block(j, shared ? 2 : 0)) ^ ((0u - flip) & 0xfffu);
+    const unsigned at = (second ? minus >> 8 : minus >> (4u * (g >> 1))) >> (2 * (word & 1));
+    return (0x3F803F80u | (((at << 15) | (at << 30)) & kBothSigns)) & keep;
 }
 
 // ---- LDS address maps -------------------------------------------------------------------------

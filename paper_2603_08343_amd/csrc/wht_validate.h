@@ -9,8 +9,7 @@
 
 namespace wht {
 
-// What a width d is to the library: log2 of the number of slots the schedule runs on, and whether
-// the row is a power of two or 12 * 2^m.
+// What a width d is to the library: log2 d, or m + 4 for d = 12 * 2^m, and which of the two it is.
 struct Width { int logd; bool twelve; };
 
 inline int log2_exact(int32_t d) {

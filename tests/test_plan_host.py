@@ -2,8 +2,8 @@
 with g++ and verifies, for every configuration the library instantiates, that each butterfly stage
 runs exactly once, that every layout is a bijection, that LDS addresses stay inside the token's
 region, and -- by emulating the phases on the CPU -- that the schedule computes H_raw x; for rows
-of 12 * 2^m elements, that the slot map is a bijection and that the padded schedule equals the
-Kronecker definition."""
+of 12 * 2^m elements, that the layouts are bijections and that the rounds, emulated from the operand
+words and lane layouts the kernels use, equal the Kronecker definition."""
 import os
 import subprocess
 
