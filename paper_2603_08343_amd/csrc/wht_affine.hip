@@ -48,17 +48,17 @@ static int forward_cluster(int64_t N, int grid, bool resid) {
 // under HIP-graph replay, bfloat16: 2.1 against 3.2 us per call for one token of 4096 elements.  The
 // persistent kernel takes over where the two break even:
 //   matrix-core schedule: 2^24 elements per call at d = 1024 and 2048 (16384 tokens of 1024 elements:
-//     12.0 against 13.3 us), 2^22 above, 2^21 for rows of 12 * 2^m elements;
-//   wave schedule: bfloat16 2^24 (65536 tokens of 256 elements: 12.7 against 13.3 us; twice that: 26.9
-//     against 23.9), float32 2^23 up to d = 2048 (8192 tokens of 1024: 11.7 against 12.8; twice that:
-//     25.3 against 23.3) and 2^21 above (1024 tokens of 4096: 8.4 against 7.6), 2^22 there with the
-//     residual add (600 tokens of 4096 with the statistic: 8.0 against 8.7).
+//     11.2 against 13.4 us), 2^22 above;
+//   wave schedule: bfloat16 2^24 (65536 tokens of 256 elements: 11.2 against 13.0 us), float32 2^23 up to
+//     d = 2048 (8192 tokens of 1024: 10.8 against 13.2) and 2^21 above (1024 tokens of 4096: 8.4 against
+//     7.6), 2^22 there with the residual add (600 tokens of 4096 with the statistic: 8.0 against 8.7).
+// Those are times on inputs that earlier calls left in the Infinity Cache; on inputs from memory the two break even
+// at the 2^24 and 2^23 (65601 tokens of 256: 14.3 against 13.7 us).  Rows of 12 * 2^m elements: run_twelve.
 // Both kernels do the same arithmetic on a token in the same order, so the switch is invisible in y
 // (the norm statistic is summed in the order of the launch shape: its last bits may differ).
 template <class C>
 static bool few_tokens(int64_t N, bool resid) {
-    constexpr int limit = C::kTwelve ? 21 : C::kMfma ? (C::n <= 11 ? 24 : 22)
-                                          : C::v == 3 ? 24 : (C::n <= 11 ? 23 : 21);
+    constexpr int limit = C::kMfma ? (C::n <= 11 ? 24 : 22) : C::v == 3 ? 24 : (C::n <= 11 ? 23 : 21);
     constexpr bool wide_f32 = C::kWave && C::v == 2 && C::n >= 12;
     return N * C::kRow <= (int64_t(1) << (wide_f32 && resid ? limit + 1 : limit));
 }
@@ -241,9 +241,13 @@ static int dispatch_d(int logd, Op op, Args& a) {
     }
 }
 
-// Rows of 12 * 2^m elements (bfloat16); logd = m + 4.  Calls of few tokens put two waves on what one wave computes
-// elsewhere, up to m = 8 (above, the exchange between twice as many waves takes more than that saves: one token of
-// 6144 3.8 us so, 3.4 without).
+// Rows of 12 * 2^m elements (bfloat16); logd = m + 4.
+// Few tokens: two waves on what one wave computes elsewhere up to 2^20 elements (2^21 at m = 8, never above, where the
+// exchange between twice as many waves takes more than that saves: 4 tokens of 6144 3.8 us so, 3.4 without); then
+// the same kernel with whole waves up to 3 * 2^20 (2^23 at m = 10); then the persistent kernel.  us per call,
+// halves / whole / persistent: 819 x 768 2.55 / 3.25 / 3.5, 2048 x 768 with the statistic 4.85 / 4.2 / 4.5, 4096 x 768 6.0 /
+// 5.0 / 5.15, 5461 x 768 8.0 / 6.7 / 5.7, 512 x 6144 whole 5.9 / persistent 6.6, 682 x 6144 7.9 / 7.3, 341 x 12288
+// 9.6 / 12.3, 682 x 12288 14.5 / 15.0.
 // Tensors of up to 128 MiB (32 MiB where the backward pass reads both) are read with the default cache policy, larger ones streamed.  What has
 // been read with the default policy stays in the Infinity Cache: a backward call that follows its forward call finds
 // x there, and a caller that comes back to the same small tensors finds them.  us per call, default policy in
@@ -253,11 +257,21 @@ static int dispatch_d(int logd, Op op, Args& a) {
 // input that lies in memory loses 2..4 % to streaming (8192 x 6144 39.4 against 38.4), one of 400 MB 6 %.
 template <int M>
 static int run_twelve(Op op, Args& a) {
-    const int64_t bytes = a.N * TwelveCfg<M>::kRow * 2;
-    const bool one_input = op == Op::Forward || (op == Op::Backward && !a.dalpha);      // dx alone reads dy only
-    if (bytes <= (int64_t(one_input ? 128 : 32) << 20))
-        return run<TwelveCfg<M, false, true>, TwelveCfg<M, false, true>, TwelveCfg<M, (M <= 8), true>>(op, a);
-    return run<TwelveCfg<M>, TwelveCfg<M>, TwelveCfg<M, (M <= 8), true>>(op, a);
+    const int64_t elems = a.N * TwelveCfg<M>::kRow, bytes = 2 * elems;
+    if (op == Op::Forward) {
+        if constexpr (M <= 8)
+            if (elems <= (int64_t(1) << (M <= 7 ? 20 : 21)))
+                return launch_forward_once<TwelveCfg<M, true>>(a.x, a.alpha, a.beta, a.resid, a.y, a.sumsq, a.N, a.stream);
+        if (elems <= (M <= 9 ? int64_t(3) << 20 : int64_t(1) << 23))
+            return launch_forward_once<TwelveCfg<M>>(a.x, a.alpha, a.beta, a.resid, a.y, a.sumsq, a.N, a.stream);
+        if (bytes <= (int64_t(128) << 20))
+            return launch_forward<TwelveCfg<M, false, true>>(a.x, a.alpha, a.beta, a.resid, a.y, a.sumsq, a.N, a.stream);
+        return launch_forward<TwelveCfg<M>>(a.x, a.alpha, a.beta, a.resid, a.y, a.sumsq, a.N, a.stream);
+    }
+    if (op == Op::Workspace) { a.workspace_out = workspace_for<TwelveCfg<M>>(a.N); return WHT_OK; }
+    if (bytes <= (int64_t(a.dalpha ? 32 : 128) << 20))             // dx alone reads dy only
+        return launch_backward<TwelveCfg<M, false, true>>(a.dy, a.x, a.alpha, a.dx, a.dalpha, a.dbeta, a.N, a.workspace, a.stream);
+    return launch_backward<TwelveCfg<M>>(a.dy, a.x, a.alpha, a.dx, a.dalpha, a.dbeta, a.N, a.workspace, a.stream);
 }
 
 static int dispatch_twelve(int logd, Op op, Args& a) {

@@ -793,20 +793,42 @@ __device__ __forceinline__ void global_put(const float (&r)[C::E], typename C::i
     });
 }
 
-// float32 parameter vector -> registers in the layout of the last phase, times `scale` and, where SIGNED, the
-// signs that this layout carries.
-template <class C, bool SIGNED>
-__device__ __forceinline__ void param_get(float (&r)[C::E], const float* p, const ThreadMap<C>& tm, float scale) {
-    const float s = SIGNED ? scale * tm.sign : scale;
+template <class C>
+__device__ __forceinline__ float inv_sqrt_d() {
+    if constexpr (C::kTwelve) {
+        // d = 3 * 2^(n-2): 1/sqrt(3) or 1/sqrt(6), rounded once, times a power of two
+        return ((C::n - 2) % 2 == 0) ? 0.57735026918962576451f / float(1 << ((C::n - 2) / 2))
+                                     : 0.40824829046386301637f / float(1 << ((C::n - 2) / 2));
+    }
+    // exact power of two for even log2 d; one rounding of 1/sqrt(2) * 2^-k otherwise
+    return (C::n % 2 == 0) ? 1.0f / float(1 << (C::n / 2))
+                           : 0.70710678118654752440f / float(1 << (C::n / 2));
+}
+
+// float32 parameter vector -> registers in the layout of the last phase.
+template <class C>
+__device__ __forceinline__ void param_load(float (&r)[C::E], const float* p, const ThreadMap<C>& tm) {
     static_for<0, C::E / 4>([&](auto i) {
         constexpr int I = decltype(i)::value * 4, VEC = I / C::V;
-        if constexpr (C::kPair == 2 && VEC == 1) {       // the same columns as vector 0
+        if constexpr (C::kPair == 2 && VEC == 1) {                     // the same columns as vector 0
             for (int k = 0; k < 4; ++k) r[I + k] = r[I - C::V + k];
         } else {
             const float4 q = *reinterpret_cast<const float4*>(p + vector_offset<C, C::P - 1, VEC, true>(tm, 0u) + I % C::V);
-            r[I] = q.x * s; r[I + 1] = q.y * s; r[I + 2] = q.z * s; r[I + 3] = q.w * s;
+            r[I] = q.x; r[I + 1] = q.y; r[I + 2] = q.z; r[I + 3] = q.w;
         }
     });
+}
+// alpha / sqrt d, with the signs that the last layout carries.
+template <class C>
+__device__ __forceinline__ void scale_alpha(float (&a)[C::E], const ThreadMap<C>& tm) {
+    const float s = inv_sqrt_d<C>() * tm.sign;
+#pragma unroll
+    for (int i = 0; i < C::E; ++i) a[i] *= s;
+}
+template <class C>
+__device__ __forceinline__ void alpha_get(float (&a)[C::E], const float* p, const ThreadMap<C>& tm) {
+    param_load<C>(a, p, tm);
+    scale_alpha<C>(a, tm);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1075,18 +1097,6 @@ __device__ __forceinline__ void transform_back(float (&r)[C::E], float* lds, con
     mfma_rounds_from_f32<C>(r, b, tm);
 }
 
-template <class C>
-__device__ __forceinline__ float inv_sqrt_d() {
-    if constexpr (C::kTwelve) {
-        // d = 3 * 2^(n-2): 1/sqrt(3) or 1/sqrt(6), rounded once, times a power of two
-        return ((C::n - 2) % 2 == 0) ? 0.57735026918962576451f / float(1 << ((C::n - 2) / 2))
-                                     : 0.40824829046386301637f / float(1 << ((C::n - 2) / 2));
-    }
-    // exact power of two for even log2 d; one rounding of 1/sqrt(2) * 2^-k otherwise
-    return (C::n % 2 == 0) ? 1.0f / float(1 << (C::n / 2))
-                           : 0.70710678118654752440f / float(1 << (C::n / 2));
-}
-
 // ------------------------------------------------------------------------------------------------
 // Kernels.  A workgroup holds G token slots of TPT threads each and strides over token groups
 // (persistent grid).  Inputs of group k+1 are in flight (LDS-direct loads) while group k is
@@ -1232,8 +1242,8 @@ __global__ __launch_bounds__(C::BT) void forward_kernel(const typename C::io::el
     }
 
     float a[C::E], b[C::E];
-    param_get<C, true>(a, alpha, tm, inv_sqrt_d<C>());
-    param_get<C, false>(b, beta, tm, 1.0f);
+    alpha_get<C>(a, alpha, tm);
+    param_load<C>(b, beta, tm);
     RoundB<C> hb{};
     if constexpr (C::kMfma) hb = make_round_b<C>(tm);
     wait_vmem<0>();
@@ -1283,11 +1293,26 @@ __device__ __forceinline__ void global_get(uint4 (&raw)[C::NV], const typename C
     });
 }
 
+// Keep a value computed where it stands: the compiler otherwise sinks a sum that the loop only uses in
+// its next iteration to the end of the body, and with it everything the sum is made of stays live.
+template <int COUNT>
+__device__ __forceinline__ void pin(float* r) {
+#pragma unroll
+    for (int i = 0; i < COUNT; ++i) asm volatile("" : "+v"(r[i]));
+}
+
 // forward for a few tokens (decoding, paper Sec. 5: one token per sequence and step): one token
 // group per workgroup and nothing else.  With so little work a launch is one memory round trip
 // long, so everything the group needs -- x, alpha, beta, the residual -- is requested at once,
 // straight into registers, before anything is awaited; there is no token loop, no prefetch stage and
 // no walk over the grid, whose set-up costs the persistent kernel about a microsecond per launch.
+// Where the store is conditional (several tokens per workgroup) the compiler moves the loads of the residual, alpha
+// and beta, with the arithmetic on them, into that condition, behind the transform, and the launch becomes two
+// round trips long.  HOLD: a scheduling barrier keeps them in front and the pinned results keep the arithmetic out of
+// the condition.  us per call, without / with: 49152 x 256 10.8 / 9.1 (13.6 / 11.7 on inputs from memory), 100000 x 64
+// 6.6 / 5.5, 4000 x 1024 float32 7.4 / 6.2, 16000 x 1024 11.9 / 11.1, 3001 x 2048 with residual 7.6 / 7.05; one token of
+// 1024 or 2048 1.68 / 1.73 and 1.85 / 1.92.  With one token per workgroup the compiler's own place for these loads,
+// between the products, is the better one (4096 x 1000: 4.45 / 4.74), as it is for rows of 12 * 2^m (6144 x 4: 3.4 / 3.7).
 template <class C, bool RESID, bool STATS = false>
 __global__ __launch_bounds__(C::BT) void forward_once_kernel(const typename C::io::elem_t* x,
                                                              const float* __restrict__ alpha,
@@ -1308,12 +1333,16 @@ __global__ __launch_bounds__(C::BT) void forward_once_kernel(const typename C::i
     global_get<C, 0>(raw, x, wk, grp, tm);                      // a ragged group re-reads the last token
     if constexpr (RESID) global_get<C, LAST, true>(rraw, resid, wk, grp, tm);
     float a[C::E], b[C::E];
-    param_get<C, true>(a, alpha, tm, inv_sqrt_d<C>());
-    param_get<C, false>(b, beta, tm, 1.0f);
+    param_load<C>(a, alpha, tm);
+    param_load<C>(b, beta, tm);
+    constexpr bool HOLD = C::G > 1 && !C::kTwelve;
+    if constexpr (HOLD) __builtin_amdgcn_sched_barrier(0);
+    else scale_alpha<C>(a, tm);
     RoundB<C> hb{};
     if constexpr (C::kMfma) hb = make_round_b<C>(tm);
     float r[C::E];
     transform_from_raw<C, false>(r, raw, lds, tm, hb);
+    if constexpr (HOLD) scale_alpha<C>(a, tm);                 // here, so that nothing before waits for alpha
     if constexpr (RESID) {
         float res[C::E];
         unpack_all<C>(res, rraw);
@@ -1323,6 +1352,7 @@ __global__ __launch_bounds__(C::BT) void forward_once_kernel(const typename C::i
 #pragma unroll
         for (int i = 0; i < C::E; ++i) r[i] = fmaf(r[i], a[i], b[i]);
     }
+    if constexpr (HOLD) pin<C::E>(r);
     if constexpr (STATS) token_sumsq<C>(r, wave_sums, sumsq, wk.token(grp), N, t, wk.slot, tm);
     global_put<C, LAST, false>(r, y, wk, grp, tm);
 }
@@ -1457,7 +1487,7 @@ __global__ __launch_bounds__(C::BT, C::kBwdWavesPerSimd) void backward_kernel(co
     }
 
     float a[DX ? C::E : 1], da[GRADS ? C::kSums : 1], db[GRADS ? C::kSums : 1];
-    if constexpr (DX) param_get<C, true>(a, alpha, tm, inv_sqrt_d<C>());
+    if constexpr (DX) alpha_get<C>(a, alpha, tm);
     if constexpr (GRADS) {
 #pragma unroll
         for (int i = 0; i < C::kSums; ++i) { da[i] = 0.0f; db[i] = 0.0f; }
@@ -1551,14 +1581,6 @@ __device__ __forceinline__ void stage_read_some(uint4 (&raw)[COUNT], const unsig
         }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     }
-}
-
-// Keep a value computed where it stands: the compiler otherwise sinks a sum that the loop only uses in
-// its next iteration to the end of the body, and with it everything the sum is made of stays live.
-template <int COUNT>
-__device__ __forceinline__ void pin(float* r) {
-#pragma unroll
-    for (int i = 0; i < COUNT; ++i) asm volatile("" : "+v"(r[i]));
 }
 
 // The rows of one wave's tokens: a wave-uniform base and a 32-bit offset per lane, so that an address
@@ -1659,7 +1681,7 @@ void backward_wave_kernel(const typename C::io::elem_t* dy, const typename C::io
         }
     }
     float a[DX ? C::E : 1], da[GRADS ? C::E : 1], db[GRADS ? C::E : 1];
-    if constexpr (DX) param_get<C, true>(a, alpha, tm, inv_sqrt_d<C>());      // with the sign of dx's input and of z
+    if constexpr (DX) alpha_get<C>(a, alpha, tm);      // with the sign of dx's input and of z
     if constexpr (GRADS) {
 #pragma unroll
         for (int i = 0; i < C::E; ++i) { da[i] = 0.0f; db[i] = 0.0f; }
@@ -1849,7 +1871,7 @@ __global__ __launch_bounds__(3 * C::BT) void backward_teams_kernel(const typenam
     } else if (team == 1) {
         if (grp < wk.groups) stage_issue<C, LAST>(stage_g0, dy, wk, grp, tm);
         float a[C::E], db[C::E];
-        param_get<C, true>(a, alpha, tm, inv_sqrt_d<C>());
+        alpha_get<C>(a, alpha, tm);
 #pragma unroll
         for (int i = 0; i < C::E; ++i) db[i] = 0.0f;
         for (int par = 0; grp < wk.groups; grp += step, par ^= 1) {

@@ -13,7 +13,8 @@ from parity import assert_grad_close, assert_io_close, nan_filled, to_gpu
 
 pytestmark = pytest.mark.gpu
 
-FEW = {768: (1 << 21) // 768, 1536: (1 << 21) // 1536, 3072: (1 << 21) // 3072, 6144: (1 << 21) // 6144, 12288: (1 << 21) // 12288}
+# elements per call up to which the one-pass forward kernel runs, with half waves and with whole ones
+FEW = {768: (1 << 20, 3 << 20), 1536: (1 << 20, 3 << 20), 3072: (1 << 21, 3 << 20), 6144: (3 << 20,), 12288: (1 << 23,)}
 
 
 @pytest.mark.parametrize("d,N", [(768, n) for n in (1, 2, 3, 4, 5, 8, 9, 23, 24, 25, 47, 4099)] +
@@ -42,8 +43,8 @@ def test_every_output_at_partial_waves(d, N):
 
 @pytest.mark.parametrize("d", [768, 1536, 3072, 6144, 12288])
 def test_rows_are_the_same_on_both_sides_of_every_limit(d):
-    # few-token limit; 32 MiB (backward) and 128 MiB (forward, dx alone) a tensor
-    for N, back in ((FEW[d], False), ((32 << 20) // (2 * d), True), ((128 << 20) // (2 * d), False)):
+    # few-token limits; 32 MiB (backward) and 128 MiB (forward, dx alone) a tensor
+    for N, back in (*((limit // d, False) for limit in FEW[d]), ((32 << 20) // (2 * d), True), ((128 << 20) // (2 * d), False)):
         print(f"[twelve] d={d} N={N}", flush=True)
         gen = torch.Generator(device="cuda").manual_seed(N)
         x = torch.empty(N + 1, d, dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
