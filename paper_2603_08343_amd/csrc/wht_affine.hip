@@ -35,12 +35,18 @@ static int grid_for(int64_t N, bool backward) {
 }
 
 // Workgroups per cluster of the forward kernel: the configuration's figure when the grid divides
-// into such clusters and every workgroup has several token groups to walk, else the whole grid.
+// into such clusters and every workgroup has many token groups to walk, else the whole grid.  Clusters spread
+// the loss at unlucky address distances (see MfmaCfg), but each ends with its own ragged last round and their
+// windows make short tensors slower: up to 24 rounds the plain interleave is ahead at every width.  us per call, four
+// clusters / one: 8.5 rounds of 4096 27.5 / 25.7, of 8192 28.2 / 25.8, of 3072 21.0 / 20.2, of float32 1024 26.3 /
+// 24.6, 17 rounds of 8192 51.0 / 48.7, 24 rounds of 4096 68.0 / 66.4; 32 rounds of 4096 91.9 / 94..99, of 8192 94 / 94..96,
+// of 3072 72.3 / 70.4 (rows of 12 * 2^m stay with one up to 48), 64 rounds of 8192 186 / 193..202, of 6144 139 / 137..146.
 template <class C>
 static int forward_cluster(int64_t N, int grid, bool resid) {
     const int64_t groups = (N + C::G - 1) / C::G;
     const int want = resid ? C::kFwdClusterResid : C::kFwdCluster;
-    if (want > 0 && grid % want == 0 && grid > want && groups >= 4 * (int64_t)grid) return want;
+    constexpr int rounds = C::kTwelve ? 48 : 32;
+    if (want > 0 && grid % want == 0 && grid > want && groups >= rounds * (int64_t)grid) return want;
     return grid;
 }
 
