@@ -115,10 +115,10 @@ static int launch_forward(const void* x, const float* alpha, const float* beta, 
 // after the other; up to here that is no slower (us per call under graph replay, two launches / one):
 // 3 groups at d = 256 6.0 / 5.7, at d = 1024 6.1 / 4.9, at float32 d = 1024 6.6 / 6.4; 2 groups at
 // d = 4096 7.6 / 6.5, at d = 8192 6.6 / 5.4; 1 at d = 16384 11.0 / 8.1 and at float32 d = 4096 7.7 / 5.2,
-// where 2 already are 11.1 / 12.3 and 7.7 / 8.3.
+// where 2 already are 11.1 / 12.3 and 7.7 / 8.3; 2 at d = 768 5.8 (3: 6.6 / 7.1), 1 at d = 12288 9.1 (2: 11.4 / 12.2).
 template <class C>
 static bool one_workgroup(int64_t N) {
-    constexpr int most = C::kRow <= 1024 ? 3 : (C::kMfma && C::P <= 2 ? 2 : 1);
+    constexpr int most = C::kRow >= 12288 ? 1 : (C::kRow <= 1024 && !C::kTwelve ? 3 : (C::kMfma && C::P <= 2 ? 2 : 1));
     return N <= (int64_t)most * C::G;
 }
 

@@ -1846,9 +1846,10 @@ __global__ __launch_bounds__(3 * C::BT) void backward_teams_kernel(const typenam
 
     if (team == 0) {
         // (before the first fetch: with it behind, the compiler waits for the prefetch at every exchange, 284 against
-        // 270 us at 32768 x 8192)
+        // 270 us at 32768 x 8192; not so for rows of 12 * 2^m elements)
+        if (C::kTwelve && grp < wk.groups) stage_issue<C, 0>(stage_x, x, wk, grp, tm);
         const RoundB<C> hb = make_round_b<C>(tm);
-        if (grp < wk.groups) stage_issue<C, 0>(stage_x, x, wk, grp, tm);
+        if (!C::kTwelve && grp < wk.groups) stage_issue<C, 0>(stage_x, x, wk, grp, tm);
         float da[C::E];
 #pragma unroll
         for (int i = 0; i < C::E; ++i) da[i] = 0.0f;
