@@ -241,6 +241,34 @@ static void lane_stage(Regs& r, int pos) {
         }
 }
 
+// In place (y = x): no wave may store what another wave has still to fetch, unless an exchange or a barrier lies
+// between the two.
+static bool check_twelve_in_place(int m, bool half) {
+    const int w = twelve_wave_bits(m);
+    const unsigned waves = (1u << w) * (half ? 2u : 1u), D = 12u << m;
+    std::vector<unsigned> fetched(2 * D, 0), stored(2 * D, 0);        // by element: bit set of the waves
+    for (unsigned wave = 0; wave < waves; ++wave)
+        for (unsigned lane = 0; lane < 64; ++lane)
+            for (int vec = 0; vec < 3; ++vec) {
+                const unsigned h = half ? wave & 1u : 0u, token = m == 6 ? twelve_pair(lane, vec) * D : 0u;
+                const LaneWave to = twelve_swap(lane, wave >> (half ? 1 : 0), w);
+                const unsigned in = token + twelve_elem(lane, wave >> (half ? 1 : 0), vec, m);
+                const unsigned out = token + twelve_elem(to.lane, to.wave, vec, m);
+                for (unsigned i = 0; i < 8; ++i) {
+                    fetched[in + i] |= 1u << wave;
+                    if (!half || i / 4 == h) stored[out + i] |= 1u << wave;
+                }
+            }
+    bool crossed = false, ok = true;
+    for (unsigned e = 0; e < D * (m == 6 ? 2 : 1); ++e) {
+        if (__builtin_popcount(stored[e]) != 1) ok = false;           // stored once
+        if (fetched[e] & ~stored[e]) crossed = true;
+    }
+    if (crossed && w == 0 && !twelve_store_barrier(m, half)) ok = false;
+    std::printf("in place  row=%u half=%d crossed=%d %s\n", D, half, crossed, ok ? "ok" : "FAIL");
+    return ok;
+}
+
 static bool check_twelve(int m) {
     const unsigned L = 1u << m, D = 12 * L;
     const int w = twelve_wave_bits(m);
@@ -318,6 +346,9 @@ int main(int argc, char** argv) {
     bool ok = true;
     const bool verbose = argc > 1;
     for (int m = 6; m <= 10; ++m) ok = check_twelve(m) && ok;
+    for (int m = 6; m <= 10; ++m)
+        for (bool half : {false, true})
+            if (!half || m <= 8) ok = check_twelve_in_place(m, half) && ok;
     for (int v : {2, 3})
         for (int n = 5; n <= (v == 2 ? 13 : 14); ++n) {
             const PlanDesc pl = make_wave_plan(n, wave_log_e(n, v), v);

@@ -91,7 +91,7 @@ struct MfmaCfg {
     static constexpr bool kMfma = true, kWave = false, kTwelve = false;
     static constexpr int kPair = 1;             // tokens per slot
     static constexpr int kSums = 1 << (4 + LOGT);                   // column sums per thread
-    static constexpr bool kHalf = false, kKeep = false;            // see TwelveCfg
+    static constexpr bool kHalf = false, kKeep = false, kStoreBarrier = false;      // see TwelveCfg
     static constexpr int n = LOGD, t = LOGT, e = 4 + LOGT, v = 3;
     static constexpr int w = n - 10 - t;        // log2(waves per token)
     static_assert(n >= 10 && w >= 0 && w <= 2 * (1 + t) && e <= kMaxRegBits, "bad tile");
@@ -150,7 +150,7 @@ struct MfmaCfg {
 // in the backward pass of 768 and 6144 (64 tokens 6.2 / 6.6 and 8.1 / 8.7).
 // HALF (few tokens per call): two waves share the 1536 elements of one.  Both fetch them and each computes the
 // results of one value of r2 -- half of round 1, half of round 2 and of everything behind -- so nothing but the
-// fetch is done twice and the chain of dependent instructions is half as long: one token of 768 with the statistic
+// fetch is done twice (a barrier then keeps one wave's stores behind the other's fetch, where y is x) and the chain of dependent instructions is half as long: one token of 768 with the statistic
 // 3.3 -> 2.8 us per call, one of 1536 2.1 (padded rows: 2.6 and 2.5).
 // KEEP: x and dy are read with the default cache policy and so stay in the Infinity Cache (see run_twelve).
 template <int LOGM, bool HALF = false, bool KEEP = false>
@@ -160,6 +160,7 @@ struct TwelveCfg {
     static constexpr int m = LOGM, n = m + 4, v = 3, w = twelve_wave_bits(m);
     static_assert(m >= 6 && w <= 3, "three lane positions take wave bits");
     static constexpr int P = w > 0 ? 2 : 1;     // layouts: the second one only after an exchange
+    static constexpr bool kStoreBarrier = twelve_store_barrier(m, HALF);
     static constexpr int V = HALF ? 4 : 8, NV = 3, E = NV * V;      // values per vector behind the rounds
     static constexpr int TPT = (HALF ? 128 : 64) << w;              // threads per token (per two tokens of 768)
     static constexpr int kPair = m == 6 ? 2 : 1;                    // tokens per wave
@@ -188,7 +189,7 @@ struct TwelveCfg {
 template <int LOGD, int LOGE, class Io>
 struct WaveCfg {
     using io = Io;
-    static constexpr bool kMfma = false, kWave = true, kTwelve = false, kHalf = false, kKeep = false;
+    static constexpr bool kMfma = false, kWave = true, kTwelve = false, kHalf = false, kKeep = false, kStoreBarrier = false;
     static constexpr int kPair = 1, kSums = 1 << LOGE;
     static constexpr int n = LOGD, e = LOGE, v = Io::kLogVec;
     static constexpr int L = n - e < 6 ? n - e : 6, w = n - e - L;    // log2 lanes of a wave, waves per token
@@ -1361,6 +1362,10 @@ __global__ __launch_bounds__(C::BT) void forward_once_kernel(const typename C::i
         for (int i = 0; i < C::E; ++i) r[i] = fmaf(r[i], a[i], b[i]);
     }
     if constexpr (HOLD) pin<C::E>(r);
+    if constexpr (C::kStoreBarrier && !STATS) {             // (STATS: the barrier of token_sumsq)
+        pin<C::E>(r);                                       // x has been read
+        exchange_barrier();
+    }
     if constexpr (STATS) token_sumsq<C>(r, wave_sums, sumsq, wk.token(grp), N, t, wk.slot, tm);
     global_put<C, LAST, false>(r, y, wk, grp, tm);
 }

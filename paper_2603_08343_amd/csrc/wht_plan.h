@@ -247,6 +247,10 @@ constexpr LaneWave twelve_swap(unsigned lane, unsigned wave, int w) {
     }
     return s;
 }
+// Half waves (two waves on the same 1536 elements): both fetch whole vectors, and each stores the half of every
+// vector that it computes.  In place (y = x) a store must therefore stay behind the other wave's fetch: the exchange
+// keeps it there, or a barrier where there is none.
+constexpr bool twelve_store_barrier(int m, bool half) { return half && twelve_wave_bits(m) == 0; }
 // Exchange region of a token: one block of 64 16-byte places per (four registers, wave), and 16 bytes more, so
 // that the lanes of a scattered access differ in their banks.  Every thread puts in the order of one layout and
 // gets in the order of the other.

@@ -67,6 +67,29 @@ def test_rows_are_the_same_on_both_sides_of_every_limit(d):
             assert bool(((g1[1] - g0[1] - last).abs() <= 1e-6 * g0[1].abs().max()).all())
 
 
+@pytest.mark.parametrize("d,N", [(768, n) for n in (1, 2, 5, 300, 512, 513, 1023, 1024, 1025, 1365, 1366, 4097)] +
+                         [(1536, n) for n in (1, 3, 200, 256, 257, 512, 513, 682, 683, 2049)] + [(3072, n) for n in (1, 200, 682, 683, 1025)])
+def test_forward_in_place_is_the_forward_out_of_place(d, N):
+    # two waves that both fetch the whole of a row, of which each stores a part: bit for bit
+    print(f"[twelve] in place d={d} N={N}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(d + N)
+    x = torch.empty(N, d, dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+    resid = torch.empty_like(x).normal_(generator=gen)
+    a, b = torch.rand(d, device="cuda", generator=gen) + 0.5, torch.randn(d, device="cuda", generator=gen)
+    y, yr = wht.wht_affine_forward(x, a, b), wht.wht_affine_forward_residual(x, a, b, resid)
+    ys, ss = wht.wht_affine_forward_residual_stats(x, a, b, resid)
+    assert torch.equal(yr, ys)
+    for _ in range(20):
+        same = [x.clone() for _ in range(3)]
+        wht.wht_affine_forward(same[0], a, b, y=same[0])
+        wht.wht_affine_forward_residual(same[1], a, b, resid, y=same[1])
+        _, s1 = wht.wht_affine_forward_residual_stats(same[2], a, b, resid, y=same[2])
+        onto = resid.clone()
+        wht.wht_affine_forward_residual(x, a, b, onto, y=onto)
+        assert torch.equal(same[0], y) and torch.equal(same[1], yr) and torch.equal(same[2], ys) and torch.equal(s1, ss)
+        assert torch.equal(onto, yr)
+
+
 @pytest.mark.parametrize("value", [float("inf"), float("nan")])
 @pytest.mark.parametrize("N,row", [(2, 0), (2, 1), (9, 4), (9, 8), (4098, 2049)])
 def test_a_pair_of_768_keeps_a_non_finite_row_to_itself(N, row, value):
