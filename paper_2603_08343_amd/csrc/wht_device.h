@@ -150,8 +150,9 @@ struct MfmaCfg {
 // in the backward pass of 768 and 6144 (64 tokens 6.2 / 6.6 and 8.1 / 8.7).
 // HALF (few tokens per call): two waves share the 1536 elements of one.  Both fetch them and each computes the
 // results of one value of r2 -- half of round 1, half of round 2 and of everything behind -- so nothing but the
-// fetch is done twice (a barrier then keeps one wave's stores behind the other's fetch, where y is x) and the chain of dependent instructions is half as long: one token of 768 with the statistic
-// 3.3 -> 2.8 us per call, one of 1536 2.1 (padded rows: 2.6 and 2.5).
+// fetch is done twice (a barrier then keeps one wave's stores behind the other's fetch, where y is x) and the chain
+// of dependent instructions is half as long: one token of 768 with the statistic 3.3 -> 2.8 us per call, one of 1536
+// 2.1 (padded rows: 2.6 and 2.5).
 // KEEP: x and dy are read with the default cache policy and so stay in the Infinity Cache (see run_twelve).
 template <int LOGM, bool HALF = false, bool KEEP = false>
 struct TwelveCfg {
@@ -174,9 +175,9 @@ struct TwelveCfg {
     static constexpr int kBwdGroupsPerCU = kBwdTeams || m == 10 ? 1 : 2;
     static constexpr int kBwdWavesPerSimd = m <= 7 ? 2 : 1;
     static constexpr int kFwdCluster = m >= 8 ? 128 : 0, kFwdClusterResid = m >= 8 ? 256 : 0;
-    template <int PH> static constexpr unsigned lds_reg(int I) { return (I / 4) * ((HALF ? 2 : 1) * kTwelveBlockWords << w); }
+    template <int PH> static constexpr unsigned lds_reg(int I) { return twelve_exchange_reg(I, w, HALF); }
     static constexpr unsigned phys(unsigned e) { return twelve_column(e, m); }      // column sums
-    static constexpr unsigned kExchangeWords = P > 1 ? 6u * (kTwelveBlockWords << w) : 0u;
+    static constexpr unsigned kExchangeWords = P > 1 ? twelve_exchange_words(w) : 0u;
     static constexpr unsigned kColumnWords = 12u * ((1u << m) + 16u);
     static constexpr unsigned kTokenWords = kExchangeWords < kColumnWords ? kColumnWords : kExchangeWords;
     static constexpr unsigned kExchangeBytes = G / kPair * kTokenWords * 4u;
@@ -423,7 +424,7 @@ struct ThreadMap<TwelveCfg<LOGM, HALF, KEEP>> {
         const unsigned lane = t & 63u, wave = HALF ? t >> 7 : t >> 6;
         half = HALF ? (t >> 6) & 1u : 0;
         const LaneWave to = twelve_swap(lane, wave, C::w);
-        const unsigned block = slot * C::kTokenWords + half * (kTwelveBlockWords << C::w);
+        const unsigned block = slot * C::kTokenWords + twelve_exchange_half(half, C::w);
         lds_off[0] = block + twelve_place(to.lane, to.wave);
         lds_off[1] = block + twelve_place(lane, wave);
         first_elem = twelve_elem(lane, wave, 0, C::m);

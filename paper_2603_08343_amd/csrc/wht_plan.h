@@ -256,6 +256,10 @@ constexpr bool twelve_store_barrier(int m, bool half) { return half && twelve_wa
 // gets in the order of the other.
 constexpr unsigned kTwelveBlockWords = 64u * 4u + 4u;
 constexpr unsigned twelve_place(unsigned lane, unsigned wave) { return wave * kTwelveBlockWords + lane * 4u; }
+constexpr unsigned twelve_exchange_words(int w) { return 6u * (kTwelveBlockWords << w); }
+// Registers I .. I+3 of a thread; half waves: 12 registers, the two halves' blocks in turn.
+constexpr unsigned twelve_exchange_reg(int I, int w, bool half) { return (I / 4) * ((half ? 2u : 1u) * kTwelveBlockWords << w); }
+constexpr unsigned twelve_exchange_half(unsigned half, int w) { return half * (kTwelveBlockWords << w); }
 // Column sums in LDS: 16 words more after every block, for the same reason.
 constexpr unsigned twelve_column(unsigned e, int m) { return e + 16u * (e >> m); }
 
