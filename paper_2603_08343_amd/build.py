@@ -19,7 +19,7 @@ COPY_SRC = os.path.join(HERE, "csrc", "copy_bench.hip")
 COPY_LIB = os.path.join(HERE, "libwht_copybench.so")
 # debug build of the layer's library for one GPU test: after every LDS read the thread overwrites
 # what it read with NaN, so that a read that comes before its data (a missing barrier or wait) shows
-# up as NaN; carries the widths 512, 4096, 8192, 16384 and 6144 only
+# up as NaN; carries the widths 512, 4096, 8192, 16384, 768, 3072, 6144 and 12288 only
 POISON_LIB = os.path.join(HERE, "libwht_affine_poison.so")
 
 # host code only: the tensor calls' checks and allocations (no device code, no HIP headers)

@@ -283,11 +283,11 @@ static int run_twelve(Op op, Args& a) {
 static int dispatch_twelve(int logd, Op op, Args& a) {
     switch (logd) {
 #if WHT_ALL_WIDTHS
-    case 10: return run_twelve<6>(op, a);
     case 11: return run_twelve<7>(op, a);
+#endif
+    case 10: return run_twelve<6>(op, a);
     case 12: return run_twelve<8>(op, a);
     case 14: return run_twelve<10>(op, a);
-#endif
     case 13: return run_twelve<9>(op, a);
     default: return WHT_ERR_BAD_DIM;
     }

@@ -4,11 +4,13 @@ read that comes before the data it is meant to see -- a missing barrier between 
 missing wait on a prefetch -- returns NaN there instead of the previous token group's plausible
 values, so the ordinary comparison against the oracle turns a synchronisation mistake into a hard
 failure.  Widths in this build: bf16 4096 and 8192 (matrix-core schedule, one exchange; the three-team
-backward), 16384 (two exchanges in the backward), 6144 (12 * 2^m rows), 512 (wave schedule, no
+backward), 16384 (two exchanges in the backward), 768 (two tokens to a wave, a missing one's zeros in the stage),
+3072 (half waves with an exchange), 6144, 12288 (single-team backward with an exchange), 512 (wave schedule, no
 exchange), and float32 512, 4096 and 8192 (wave schedule with a token on part of one wave, on two and
 on four).  Token counts: past the few-token limit of the residual forward (2^24, 2^23, 2^22 or 2^21
 elements), and more token groups than any backward kernel has workgroups, so that every kernel refills
-its stages and re-uses its exchange region; 300 tokens of 512 run the one-pass forward kernel."""
+its stages and re-uses its exchange region; 300 tokens of 512 run the one-pass forward kernel, as do the smaller counts
+of 768, 3072 (half waves, whole waves) and 12288.  Odd counts of 768 leave half a wave without a token."""
 import ctypes
 
 import numpy as np
@@ -42,7 +44,8 @@ def poison_lib():
 
 @pytest.mark.parametrize("d,dtype,N", [(512, "bf16", 300), (512, "f32", 300), (4096, "bf16", 1031), (4096, "f32", 70),
                                        (8192, "bf16", 700), (8192, "f32", 300), (16384, "bf16", 600), (6144, "bf16", 600),
-                                       (512, "bf16", 32805), (512, "f32", 16421), (4096, "f32", 1061), (8192, "f32", 1061)])
+                                       (768, "bf16", 9), (768, "bf16", 8197), (3072, "bf16", 301), (3072, "bf16", 701), (3072, "bf16", 1031),
+                                       (12288, "bf16", 259), (12288, "bf16", 701), (512, "bf16", 32805), (512, "f32", 16421), (4096, "f32", 1061), (8192, "f32", 1061)])
 def test_poisoned_lds_build_matches_the_oracle(d, dtype, N):
     print(f"[poison] d={d} {dtype} N={N}", flush=True)
     lib = poison_lib()
