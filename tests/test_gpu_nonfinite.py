@@ -20,7 +20,7 @@ pytestmark = pytest.mark.gpu
 WAVE = [(64, "f32", 32, 8), (256, "f32", 16, 4), (1024, "f32", 4, 1), (2048, "f32", 4, 1), (32, "bf16", 64, 16),
         (256, "bf16", 16, 4), (512, "bf16", 8, 2)]
 WIDE = [(4096, "f32", 1, 1), (8192, "f32", 1, 1)]                     # two and four waves per token
-MATRIX = [(768, "bf16", 4, 1), (1024, "bf16", 4, 1), (1536, "bf16", 4, 1), (2048, "bf16", 4, 1), (4096, "bf16", 2, 1),
+MATRIX = [(768, "bf16", 8, 2), (1024, "bf16", 4, 1), (1536, "bf16", 4, 1), (2048, "bf16", 4, 1), (4096, "bf16", 2, 1),
           (3072, "bf16", 2, 1)]
 
 

@@ -13,7 +13,7 @@ from parity import assert_grad_close, assert_io_close, to_gpu
 pytestmark = pytest.mark.gpu
 
 # width, dtype, tokens of a workgroup pass
-SHAPES = [(32, "bf16", 64), (512, "bf16", 8), (768, "bf16", 4), (1024, "bf16", 4), (1536, "bf16", 4), (2048, "bf16", 4),
+SHAPES = [(32, "bf16", 64), (512, "bf16", 8), (768, "bf16", 8), (1024, "bf16", 4), (1536, "bf16", 4), (2048, "bf16", 4),
           (3072, "bf16", 2), (4096, "bf16", 2), (6144, "bf16", 1), (8192, "bf16", 1), (12288, "bf16", 1),
           (16384, "bf16", 1), (64, "f32", 32), (1024, "f32", 4), (2048, "f32", 4), (4096, "f32", 1), (8192, "f32", 1)]
 

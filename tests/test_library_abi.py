@@ -120,7 +120,9 @@ def test_workspace_query():
     assert q(32768, 8192, 1) <= 64 << 20
     # rows of 12 * 2^m elements: the partial rows have the row's real length
     assert q(1, 6144, 1) == 2 * 6144 * 4
-    assert q(4, 768, 1) == 2 * 768 * 4            # four tokens share a workgroup at d = 768
+    # tokens of a workgroup pass, which tests/test_gpu_one_workgroup_backward.py and test_gpu_nonfinite.py rely on
+    for d, group in ((768, 8), (1536, 4), (3072, 2), (6144, 1), (12288, 1)):
+        assert q(group, d, 1) == 2 * d * 4 and q(group + 1, d, 1) == 2 * (2 * d * 4)
     assert q(10, 768, 0) == 0 and q(10, 24576, 1) == 0
 
 
