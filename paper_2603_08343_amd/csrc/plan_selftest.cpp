@@ -180,7 +180,7 @@ static bool check(const char* kind, const PlanDesc& pl, PhysFn phys, unsigned wo
 // 768), the exchange must go through the LDS words the kernels use, and the two rounds -- emulated from the operand
 // words the kernels load and the 16x16x32 product's lane layout -- with the stages after them must equal the definition
 //     out[j] = sum_k P12[j / L][k / L] * (-1)^popcount(j & k & (L - 1)) * x[k],   L = 2^m,
-// in forward order (rounds first) and in reverse, and in forward order on half waves.
+// in forward order (rounds first) and in reverse.
 typedef std::vector<std::vector<double>> Regs;         // [lane of the token's waves][24]
 
 // D[i][j] += sum_k A[i][k] B[k][j]:  A: lane i + 16 (k / 8), element k % 8;  B: lane j + 16 (k / 8), element
@@ -197,51 +197,45 @@ static double word_value(unsigned word, int odd) {
     return h == 0u ? 0.0 : (h == 0x3F80u ? 1.0 : (h == 0xBF80u ? -1.0 : NAN));
 }
 
-// One output half (value of r2) of one wave's two rounds: values 4h .. 4h+3 of every vector, from its 64 x 24 inputs.
-static void twelve_rounds_half(const std::vector<double>* lanes, int m, int h, double (&out)[64][3][4]) {
-    double d1[3][64][4] = {};
-    for (int v = 0; v < 3; ++v) {
-        double A[64][8], B[64][8];
-        for (int l = 0; l < 64; ++l)
-            for (int e = 0; e < 8; ++e) {
-                A[l][e] = lanes[l][8 * v + e];
-                B[l][e] = word_value(twelve_round1_word(l, h, e / 2), e & 1);
-            }
-        product(A, B, d1[v]);
-    }
-    double sum[3][64][4] = {};
-    for (int pair = 0; pair < 2; ++pair) {
-        double A[64][8], B[64][8], S[64][8];
-        for (int l = 0; l < 64; ++l)
-            for (int e = 0; e < 8; ++e) {
-                A[l][e] = d1[(e / 4) == pair ? pair : 2][l][e % 4];
-                B[l][e] = word_value(twelve_round2_word(l, pair, false, e / 2, m), e & 1);
-                S[l][e] = word_value(twelve_round2_word(l, pair, true, e / 2, m), e & 1);
-            }
-        product(A, B, sum[pair]);
-        product(A, S, sum[2]);
-    }
-    for (int l = 0; l < 64; ++l)
-        for (int i = 0; i < 4; ++i) {          // the stage on r6, which the product has done for vector 2
-            const double a = sum[0][l][i], b = sum[1][l][i];
-            out[l][0][i] = m == 6 ? a : a + b;
-            out[l][1][i] = m == 6 ? b : a - b;
-            out[l][2][i] = sum[2][l][i];
-        }
-}
-
 static void twelve_rounds(std::vector<double>* lanes, int m) {        // one wave: 64 x 24 registers
-    double out[2][64][3][4];
-    for (int h = 0; h < 2; ++h) twelve_rounds_half(lanes, m, h, out[h]);
+    double d1[3][2][64][4] = {}, out[64][24] = {};
+    for (int v = 0; v < 3; ++v)
+        for (int h = 0; h < 2; ++h) {
+            double A[64][8], B[64][8];
+            for (int l = 0; l < 64; ++l)
+                for (int e = 0; e < 8; ++e) {
+                    A[l][e] = lanes[l][8 * v + e];
+                    B[l][e] = word_value(twelve_round1_word(l, h, e / 2), e & 1);
+                }
+            product(A, B, d1[v][h]);
+        }
+    for (int h = 0; h < 2; ++h)
+        for (int pair = 0; pair < 2; ++pair) {
+            double A[64][8], B[64][8], S[64][8], main[64][4] = {}, shared[64][4] = {};
+            for (int l = 0; l < 64; ++l)
+                for (int e = 0; e < 8; ++e) {
+                    A[l][e] = d1[(e / 4) == pair ? pair : 2][h][l][e % 4];
+                    B[l][e] = word_value(twelve_round2_word(l, pair, false, e / 2, m), e & 1);
+                    S[l][e] = word_value(twelve_round2_word(l, pair, true, e / 2, m), e & 1);
+                }
+            product(A, B, main);
+            product(A, S, shared);
+            for (int l = 0; l < 64; ++l)
+                for (int i = 0; i < 4; ++i) {
+                    out[l][8 * pair + 4 * h + i] += main[l][i];
+                    out[l][16 + 4 * h + i] += shared[l][i];
+                }
+        }
     for (int l = 0; l < 64; ++l)
-        for (int i = 0; i < 24; ++i) lanes[l][i] = out[(i / 4) % 2][l][i / 8][i % 4];
+        for (int i = 0; i < 24; ++i)       // the stage on r6, which the product has done for vector 2
+            lanes[l][i] = m == 6 || i >= 16 ? out[l][i] : (i < 8 ? out[l][i] + out[l][8 + i] : out[l][i - 8] - out[l][i]);
 }
 
 // a - b in the upper of two places of one vector, a + b in the lower (the kernels' DPP stages, signs resolved)
 static void lane_stage(Regs& r, int pos) {
     const Regs old = r;
     for (unsigned t = 0; t < r.size(); ++t)
-        for (size_t i = 0; i < r[t].size(); ++i) {
+        for (int i = 0; i < 24; ++i) {
             const double own = old[t][i], other = old[t ^ (1u << pos)][i];
             r[t][i] = ((t >> pos) & 1u) ? other - own : own + other;
         }
@@ -249,16 +243,16 @@ static void lane_stage(Regs& r, int pos) {
 
 // The exchange as the kernels do it: every thread puts its registers, four at a time, into the LDS words of one
 // layout and gets them from those of the other.  Words inside the region, 16-byte aligned, written once, all read.
-static bool twelve_exchange(Regs& r, int w, bool half, bool put_last) {
+static bool twelve_exchange(Regs& r, int w, bool put_last) {
     std::vector<double> lds(twelve_exchange_words(w), NAN);
     bool ok = true;
     for (bool get : {false, true})
         for (unsigned t = 0; t < r.size(); ++t) {
-            const unsigned lane = t & 63u, wave = half ? t >> 7 : t >> 6, h = half ? (t >> 6) & 1u : 0u;
+            const unsigned lane = t & 63u, wave = t >> 6;
             const LaneWave to = twelve_swap(lane, wave, w);
             const unsigned at = get == put_last ? twelve_place(to.lane, to.wave) : twelve_place(lane, wave);
-            for (unsigned i = 0; i < r[t].size(); i += 4) {
-                const unsigned word = twelve_exchange_half(h, w) + at + twelve_exchange_reg((int)i, w, half);
+            for (unsigned i = 0; i < 24; i += 4) {
+                const unsigned word = at + twelve_exchange_reg((int)i, w);
                 if (word % 4 != 0 || word + 4 > lds.size()) return false;
                 for (unsigned k = 0; k < 4; ++k) {
                     if (!get && !std::isnan(lds[word + k])) ok = false;
@@ -271,31 +265,28 @@ static bool twelve_exchange(Regs& r, int w, bool half, bool put_last) {
     return ok;
 }
 
-// In place (y = x): no wave may store what another wave has still to fetch, unless an exchange or a barrier lies
-// between the two.
-static bool check_twelve_in_place(int m, bool half) {
+// In place (y = x, dx = dy): without an exchange between them, no wave may store what another has still to fetch.
+static bool check_twelve_in_place(int m) {
     const int w = twelve_wave_bits(m);
-    const unsigned waves = (1u << w) * (half ? 2u : 1u), D = 12u << m;
-    std::vector<unsigned> fetched(2 * D, 0), stored(2 * D, 0);        // by element: bit set of the waves
-    for (unsigned wave = 0; wave < waves; ++wave)
+    const unsigned D = 12u << m, tokens = m == 6 ? 2 : 1;
+    std::vector<unsigned> fetched(tokens * D, 0), stored(tokens * D, 0);        // by element: bit set of the waves
+    for (unsigned wave = 0; wave < 1u << w; ++wave)
         for (unsigned lane = 0; lane < 64; ++lane)
             for (int vec = 0; vec < 3; ++vec) {
-                const unsigned h = half ? wave & 1u : 0u, token = m == 6 ? twelve_pair(lane, vec) * D : 0u;
-                const LaneWave to = twelve_swap(lane, wave >> (half ? 1 : 0), w);
-                const unsigned in = token + twelve_elem(lane, wave >> (half ? 1 : 0), vec, m);
-                const unsigned out = token + twelve_elem(to.lane, to.wave, vec, m);
+                const unsigned token = m == 6 ? twelve_pair(lane, vec) * D : 0u;
+                const LaneWave to = twelve_swap(lane, wave, w);
                 for (unsigned i = 0; i < 8; ++i) {
-                    fetched[in + i] |= 1u << wave;
-                    if (!half || i / 4 == h) stored[out + i] |= 1u << wave;
+                    fetched[token + twelve_elem(lane, wave, vec, m) + i] |= 1u << wave;
+                    stored[token + twelve_elem(to.lane, to.wave, vec, m) + i] |= 1u << wave;
                 }
             }
     bool crossed = false, ok = true;
-    for (unsigned e = 0; e < D * (m == 6 ? 2 : 1); ++e) {
+    for (unsigned e = 0; e < tokens * D; ++e) {
         if (__builtin_popcount(stored[e]) != 1) ok = false;           // stored once
         if (fetched[e] & ~stored[e]) crossed = true;
     }
-    if (crossed && w == 0 && !twelve_store_barrier(m, half)) ok = false;
-    std::printf("in place  row=%u half=%d crossed=%d %s\n", D, half, crossed, ok ? "ok" : "FAIL");
+    if (crossed && w == 0) ok = false;
+    std::printf("in place  row=%u crossed=%d %s\n", D, crossed, ok ? "ok" : "FAIL");
     return ok;
 }
 
@@ -345,37 +336,13 @@ static bool check_twelve(int m) {
         for (unsigned t = 0; t < T; ++t)
             for (int i = 0; i < 24; ++i) r[t][i] = x[elem(t, i / 8, reverse != 0) + i % 8];
         auto rounds = [&] { for (unsigned wave = 0; wave < W; ++wave) twelve_rounds(&r[64 * wave], m); };
-        auto exchange = [&] { if (w > 0) ok = twelve_exchange(r, w, false, reverse != 0) && ok; };
+        auto exchange = [&] { if (w > 0) ok = twelve_exchange(r, w, reverse != 0) && ok; };
         auto wave_stages = [&] { for (int k = 0; k < w; ++k) lane_stage(r, twelve_lane_pos(k)); };
         if (!reverse) { rounds(); exchange(); wave_stages(); }
         else          { wave_stages(); exchange(); rounds(); }
         for (unsigned t = 0; t < T; ++t)
             for (int i = 0; i < 24; ++i)
                 if (r[t][i] != want[elem(t, i / 8, reverse == 0) + i % 8]) ok = false;
-    }
-    // Half waves (forward, few tokens): thread t of 2 T computes the r2 = (t / 64) % 2 results of wave t / 128 and
-    // stores them as half vectors.
-    if (m <= 8) {
-        Regs r(2 * T, std::vector<double>(12));
-        for (unsigned wave = 0; wave < 2 * W; ++wave) {
-            std::vector<double> in[64];
-            for (unsigned l = 0; l < 64; ++l)
-                for (int i = 0; i < 24; ++i) in[l].push_back(x[elem(l + 64 * (wave / 2), i / 8, false) + i % 8]);
-            double out[64][3][4];
-            twelve_rounds_half(in, m, (int)(wave & 1u), out);
-            for (unsigned l = 0; l < 64; ++l)
-                for (int i = 0; i < 12; ++i) r[l + 64 * wave][i] = out[l][i / 4][i % 4];
-        }
-        if (w > 0) ok = twelve_exchange(r, w, true, false) && ok;
-        for (int k = 0; k < w; ++k) lane_stage(r, twelve_lane_pos(k));
-        std::vector<int> stored(D * tokens, 0);
-        for (unsigned t = 0; t < 2 * T; ++t)
-            for (int i = 0; i < 12; ++i) {
-                const unsigned e = elem((t & 63u) | (t >> 7) << 6, i / 4, true) + 4u * ((t >> 6) & 1u) + i % 4;
-                ++stored[e];
-                if (r[t][i] != want[e]) ok = false;
-            }
-        for (int s : stored) if (s != 1) ok = false;
     }
     std::printf("twelve    n=%2d row=%u waves=%u %s\n", m + 4, D, W, ok ? "ok" : "FAIL");
     return ok;
@@ -392,9 +359,7 @@ int main(int argc, char** argv) {
     bool ok = true;
     const bool verbose = argc > 1;
     for (int m = 6; m <= 10; ++m) ok = check_twelve(m) && ok;
-    for (int m = 6; m <= 10; ++m)
-        for (bool half : {false, true})
-            if (!half || m <= 8) ok = check_twelve_in_place(m, half) && ok;
+    for (int m = 6; m <= 10; ++m) ok = check_twelve_in_place(m) && ok;
     for (int v : {2, 3})
         for (int n = 5; n <= (v == 2 ? 13 : 14); ++n) {
             const PlanDesc pl = make_wave_plan(n, wave_log_e(n, v), v);

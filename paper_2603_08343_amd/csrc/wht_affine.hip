@@ -248,12 +248,14 @@ static int dispatch_d(int logd, Op op, Args& a) {
 }
 
 // Rows of 12 * 2^m elements (bfloat16); logd = m + 4.
-// Few tokens: two waves on what one wave computes elsewhere up to 2^20 elements (2^21 at m = 8, never above, where the
-// exchange between twice as many waves takes more than that saves: 4 tokens of 6144 3.8 us so, 3.4 without); then
-// the same kernel with whole waves up to 3 * 2^20 (2^23 at m = 10); then the persistent kernel.  us per call,
-// halves / whole / persistent: 819 x 768 2.55 / 3.25 / 3.5, 2048 x 768 with the statistic 4.85 / 4.2 / 4.5, 4096 x 768 6.0 /
-// 5.0 / 5.15, 5461 x 768 8.0 / 6.7 / 5.7, 512 x 6144 whole 5.9 / persistent 6.6, 682 x 6144 7.9 / 7.3, 341 x 12288
-// 9.6 / 12.3, 682 x 12288 14.5 / 15.0.
+// Few tokens: one pass, in workgroups of one token (two of 768), up to 3 * 2^20 elements (2^23 at m = 10), then the
+// persistent kernel.  Workgroups of 256 threads, with up to eight tokens, leave CUs without any, and from 257 of them
+// on put two on one CU beside others with one.  us per call under graph replay, 256 threads / one token per
+// workgroup, inputs that come back and inputs from memory: 341 x 768 3.33 / 2.34 and 3.95 / 2.97, 1365 x 768 3.56 / 3.14 and
+// 4.25 / 3.77, 1365 x 1536 5.60 / 4.80 and 6.31 / 5.50, 683 x 3072 6.01 / 4.83 and 6.76 / 5.70, 483 x 1536 with the statistic
+// 4.21 / 3.51 and 5.36 / 4.76.  One pass / persistent: 3863 x 768 5.47 / 5.36 and 6.01 / 6.38, 5461 x 768 6.70 / 6.01 and 7.14 /
+// 7.86, 965 x 3072 5.93 / 6.85, 1365 x 3072 8.01 / 7.59, 512 x 6144 5.9 / 6.6, 682 x 6144 7.9 / 7.3, 341 x 12288 9.6 / 12.3,
+// 682 x 12288 14.5 / 15.0.
 // Tensors of up to 128 MiB (32 MiB where the backward pass reads both) are read with the default cache policy, larger ones streamed.  What has
 // been read with the default policy stays in the Infinity Cache: a backward call that follows its forward call finds
 // x there, and a caller that comes back to the same small tensors finds them.  us per call, default policy in
@@ -265,18 +267,15 @@ template <int M>
 static int run_twelve(Op op, Args& a) {
     const int64_t elems = a.N * TwelveCfg<M>::kRow, bytes = 2 * elems;
     if (op == Op::Forward) {
-        if constexpr (M <= 8)
-            if (elems <= (int64_t(1) << (M <= 7 ? 20 : 21)))
-                return launch_forward_once<TwelveCfg<M, true>>(a.x, a.alpha, a.beta, a.resid, a.y, a.sumsq, a.N, a.stream);
         if (elems <= (M <= 9 ? int64_t(3) << 20 : int64_t(1) << 23))
-            return launch_forward_once<TwelveCfg<M>>(a.x, a.alpha, a.beta, a.resid, a.y, a.sumsq, a.N, a.stream);
+            return launch_forward_once<TwelveCfg<M, false, 64>>(a.x, a.alpha, a.beta, a.resid, a.y, a.sumsq, a.N, a.stream);
         if (bytes <= (int64_t(128) << 20))
-            return launch_forward<TwelveCfg<M, false, true>>(a.x, a.alpha, a.beta, a.resid, a.y, a.sumsq, a.N, a.stream);
+            return launch_forward<TwelveCfg<M, true>>(a.x, a.alpha, a.beta, a.resid, a.y, a.sumsq, a.N, a.stream);
         return launch_forward<TwelveCfg<M>>(a.x, a.alpha, a.beta, a.resid, a.y, a.sumsq, a.N, a.stream);
     }
     if (op == Op::Workspace) { a.workspace_out = workspace_for<TwelveCfg<M>>(a.N); return WHT_OK; }
     if (bytes <= (int64_t(a.dalpha ? 32 : 128) << 20))             // dx alone reads dy only
-        return launch_backward<TwelveCfg<M, false, true>>(a.dy, a.x, a.alpha, a.dx, a.dalpha, a.dbeta, a.N, a.workspace, a.stream);
+        return launch_backward<TwelveCfg<M, true>>(a.dy, a.x, a.alpha, a.dx, a.dalpha, a.dbeta, a.N, a.workspace, a.stream);
     return launch_backward<TwelveCfg<M>>(a.dy, a.x, a.alpha, a.dx, a.dalpha, a.dbeta, a.N, a.workspace, a.stream);
 }
 

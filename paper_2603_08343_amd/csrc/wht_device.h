@@ -91,7 +91,7 @@ struct MfmaCfg {
     static constexpr bool kMfma = true, kWave = false, kTwelve = false;
     static constexpr int kPair = 1;             // tokens per slot
     static constexpr int kSums = 1 << (4 + LOGT);                   // column sums per thread
-    static constexpr bool kHalf = false, kKeep = false, kStoreBarrier = false;      // see TwelveCfg
+    static constexpr bool kKeep = false;        // see TwelveCfg
     static constexpr int n = LOGD, t = LOGT, e = 4 + LOGT, v = 3;
     static constexpr int w = n - 10 - t;        // log2(waves per token)
     static_assert(n >= 10 && w >= 0 && w <= 2 * (1 + t) && e <= kMaxRegBits, "bad tile");
@@ -148,25 +148,20 @@ struct MfmaCfg {
 // backward of 16384 x 12288 358 / 256 (one exchange per transform instead of two).  A wave computes 24 values per
 // lane where it computed 16, and two tokens of 768: calls of one to a few tokens per CU take up to 0.6 us longer
 // in the backward pass of 768 and 6144 (64 tokens 6.2 / 6.6 and 8.1 / 8.7).
-// HALF (few tokens per call): two waves share the 1536 elements of one.  Both fetch them and each computes the
-// results of one value of r2 -- half of round 1, half of round 2 and of everything behind -- so nothing but the
-// fetch is done twice (a barrier then keeps one wave's stores behind the other's fetch, where y is x) and the chain
-// of dependent instructions is half as long: one token of 768 with the statistic 3.3 -> 2.8 us per call, one of 1536
-// 2.1 (padded rows: 2.6 and 2.5).
+// LEAST: threads of a workgroup, where a token (two of 768) takes fewer.
 // KEEP: x and dy are read with the default cache policy and so stay in the Infinity Cache (see run_twelve).
-template <int LOGM, bool HALF = false, bool KEEP = false>
+template <int LOGM, bool KEEP = false, int LEAST = 256>
 struct TwelveCfg {
     using io = IoBF16;
-    static constexpr bool kMfma = true, kWave = false, kTwelve = true, kHalf = HALF, kKeep = KEEP;
+    static constexpr bool kMfma = true, kWave = false, kTwelve = true, kKeep = KEEP;
     static constexpr int m = LOGM, n = m + 4, v = 3, w = twelve_wave_bits(m);
     static_assert(m >= 6 && w <= 3, "three lane positions take wave bits");
     static constexpr int P = w > 0 ? 2 : 1;     // layouts: the second one only after an exchange
-    static constexpr bool kStoreBarrier = twelve_store_barrier(m, HALF);
-    static constexpr int V = HALF ? 4 : 8, NV = 3, E = NV * V;      // values per vector behind the rounds
-    static constexpr int TPT = (HALF ? 128 : 64) << w;              // threads per token (per two tokens of 768)
+    static constexpr int V = 8, NV = 3, E = NV * V;
+    static constexpr int TPT = 64 << w;         // threads per token (per two tokens of 768)
     static constexpr int kPair = m == 6 ? 2 : 1;                    // tokens per wave
     static constexpr int kSums = E - (kPair - 1) * V;               // column sums per thread: vectors 0 and 1 in one
-    static constexpr int BT = TPT > 256 ? TPT : 256;
+    static constexpr int BT = TPT > LEAST ? TPT : LEAST;
     static constexpr int G = BT / TPT * kPair;
     static constexpr int kRow = 12 << m, D = kRow;
     static constexpr int kFwdGroupsPerCU = 2;
@@ -175,7 +170,7 @@ struct TwelveCfg {
     static constexpr int kBwdGroupsPerCU = kBwdTeams || m == 10 ? 1 : 2;
     static constexpr int kBwdWavesPerSimd = m <= 7 ? 2 : 1;
     static constexpr int kFwdCluster = m >= 8 ? 128 : 0, kFwdClusterResid = m >= 8 ? 256 : 0;
-    template <int PH> static constexpr unsigned lds_reg(int I) { return twelve_exchange_reg(I, w, HALF); }
+    template <int PH> static constexpr unsigned lds_reg(int I) { return twelve_exchange_reg(I, w); }
     static constexpr unsigned phys(unsigned e) { return twelve_column(e, m); }      // column sums
     static constexpr unsigned kExchangeWords = P > 1 ? twelve_exchange_words(w) : 0u;
     static constexpr unsigned kColumnWords = 12u * ((1u << m) + 16u);
@@ -190,7 +185,7 @@ struct TwelveCfg {
 template <int LOGD, int LOGE, class Io>
 struct WaveCfg {
     using io = Io;
-    static constexpr bool kMfma = false, kWave = true, kTwelve = false, kHalf = false, kKeep = false, kStoreBarrier = false;
+    static constexpr bool kMfma = false, kWave = true, kTwelve = false, kKeep = false;
     static constexpr int kPair = 1, kSums = 1 << LOGE;
     static constexpr int n = LOGD, e = LOGE, v = Io::kLogVec;
     static constexpr int L = n - e < 6 ? n - e : 6, w = n - e - L;    // log2 lanes of a wave, waves per token
@@ -410,10 +405,9 @@ struct ThreadMap {
 };
 
 // Rows of 12 * 2^m elements: vector 0 (vector 1 lies a fixed distance behind it) and vector 2.
-template <int LOGM, bool HALF, bool KEEP>
-struct ThreadMap<TwelveCfg<LOGM, HALF, KEEP>> {
-    using C = TwelveCfg<LOGM, HALF, KEEP>;
-    int half;                           // HALF: the value of r2 that the wave computes
+template <int LOGM, bool KEEP, int LEAST>
+struct ThreadMap<TwelveCfg<LOGM, KEEP, LEAST>> {
+    using C = TwelveCfg<LOGM, KEEP, LEAST>;
     unsigned lds_off[2];
     unsigned first_elem, last_elem, first_elem2, last_elem2;
     unsigned columns, columns2;         // LDS words of the column sums, in the last layout
@@ -421,16 +415,14 @@ struct ThreadMap<TwelveCfg<LOGM, HALF, KEEP>> {
     float lane_sign[3];                 // stages on the wave bits: -1 in the lanes of the lower butterfly output
     float sign;                         // their product
     __device__ __forceinline__ void init(unsigned t, unsigned slot) {
-        const unsigned lane = t & 63u, wave = HALF ? t >> 7 : t >> 6;
-        half = HALF ? (t >> 6) & 1u : 0;
+        const unsigned lane = t & 63u, wave = t >> 6;
         const LaneWave to = twelve_swap(lane, wave, C::w);
-        const unsigned block = slot * C::kTokenWords + twelve_exchange_half(half, C::w);
-        lds_off[0] = block + twelve_place(to.lane, to.wave);
-        lds_off[1] = block + twelve_place(lane, wave);
+        lds_off[0] = slot * C::kTokenWords + twelve_place(to.lane, to.wave);
+        lds_off[1] = slot * C::kTokenWords + twelve_place(lane, wave);
         first_elem = twelve_elem(lane, wave, 0, C::m);
         first_elem2 = twelve_elem(lane, wave, 2, C::m);
-        last_elem = twelve_elem(to.lane, to.wave, 0, C::m) + 4u * half;
-        last_elem2 = twelve_elem(to.lane, to.wave, 2, C::m) + 4u * half;
+        last_elem = twelve_elem(to.lane, to.wave, 0, C::m);
+        last_elem2 = twelve_elem(to.lane, to.wave, 2, C::m);
         second = twelve_pair(lane, 2) != 0u;
         sign = 1.0f;
         static_for<0, C::w>([&](auto k) {
@@ -443,15 +435,14 @@ struct ThreadMap<TwelveCfg<LOGM, HALF, KEEP>> {
     }
 };
 
-// Offset in its row of vector VEC of the thread in the layout of phase PH (OUT: of what the rounds leave, where that
-// is half a vector).  next_row: rows of 768, two tokens
+// Offset in its row of vector VEC of the thread in the layout of phase PH.  next_row: rows of 768, two tokens
 // to a wave, distance from the first token's row to the second's (0 where there is no second).
-template <class C, int PH, int VEC, bool OUT = (PH > 0)>
+template <class C, int PH, int VEC>
 __device__ __forceinline__ unsigned vector_offset(const ThreadMap<C>& tm, unsigned next_row) {
     if constexpr (C::kTwelve) {
         const unsigned step = C::kPair == 2 ? next_row : 64u;
-        if constexpr (VEC == 2) return (OUT ? tm.last_elem2 : tm.first_elem2) + (C::kPair == 2 && tm.second ? next_row : 0u);
-        else return (OUT ? tm.last_elem : tm.first_elem) + VEC * step;
+        if constexpr (VEC == 2) return (PH > 0 ? tm.last_elem2 : tm.first_elem2) + (C::kPair == 2 && tm.second ? next_row : 0u);
+        else return (PH > 0 ? tm.last_elem : tm.first_elem) + VEC * step;
     } else {
         constexpr unsigned off = reg_elem_offset(C::plan.ph[PH], C::e, VEC * C::V);
         return (PH == 0 ? tm.first_elem : tm.last_elem) + off;
@@ -772,14 +763,7 @@ template <class C>
 __device__ __forceinline__ void unpack_all(float (&r)[C::E], const uint4 (&raw)[C::NV]) {
     static_for<0, C::NV>([&](auto c) {
         constexpr int Cc = decltype(c)::value;
-        if constexpr (C::kHalf) {
-            float both[8];
-            C::io::unpack(raw[Cc], both);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) r[Cc * 4 + i] = both[i];
-        } else {
-            C::io::unpack(raw[Cc], &r[Cc * C::V]);
-        }
+        C::io::unpack(raw[Cc], &r[Cc * C::V]);
     });
 }
 
@@ -794,10 +778,8 @@ __device__ __forceinline__ void global_put(const float (&r)[C::E], typename C::i
         bool active = C::G == 1 || tok < wk.N;
         if constexpr (C::kPair == 2) active = tok + (Cc == 2 ? (tm.second ? 1 : 0) : Cc) < wk.N;
         if (active) {
-            typename C::io::elem_t* p = row + vector_offset<C, PH, Cc, (PH > 0 || C::kHalf)>(tm, C::kRow);
-            if constexpr (C::kHalf)
-                *reinterpret_cast<uint2*>(p) = make_uint2(C::io::pack2(r[4 * Cc], r[4 * Cc + 1]), C::io::pack2(r[4 * Cc + 2], r[4 * Cc + 3]));
-            else if constexpr (STREAM) stream_store16(p, C::io::pack(&r[Cc * C::V]));
+            typename C::io::elem_t* p = row + vector_offset<C, PH, Cc>(tm, C::kRow);
+            if constexpr (STREAM) stream_store16(p, C::io::pack(&r[Cc * C::V]));
             else *reinterpret_cast<uint4*>(p) = C::io::pack(&r[Cc * C::V]);
         }
     });
@@ -823,7 +805,7 @@ __device__ __forceinline__ void param_load(float (&r)[C::E], const float* p, con
         if constexpr (C::kPair == 2 && VEC == 1) {                     // the same columns as vector 0
             for (int k = 0; k < 4; ++k) r[I + k] = r[I - C::V + k];
         } else {
-            const float4 q = *reinterpret_cast<const float4*>(p + vector_offset<C, C::P - 1, VEC, true>(tm, 0u) + I % C::V);
+            const float4 q = *reinterpret_cast<const float4*>(p + vector_offset<C, C::P - 1, VEC>(tm, 0u) + I % C::V);
             r[I] = q.x; r[I + 1] = q.y; r[I + 2] = q.z; r[I + 3] = q.w;
         }
     });
@@ -936,13 +918,13 @@ struct TwelveB {
     bf16x8 main[2], shared[2];      // round 2, by pair: results for vector `pair`, for vector 2
 };
 template <class C>
-__device__ __forceinline__ TwelveB make_twelve_b(const ThreadMap<C>& tm) {
+__device__ __forceinline__ TwelveB make_twelve_b() {
     const unsigned lane = threadIdx.x & 63u;
     auto words = [](auto f) { return __builtin_bit_cast(bf16x8, make_uint4(f(0), f(1), f(2), f(3))); };
     TwelveB b;
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-        b.b1[i] = words([&](int word) { return twelve_round1_word(lane, C::kHalf ? tm.half : i, word); });
+        b.b1[i] = words([&](int word) { return twelve_round1_word(lane, i, word); });
         b.main[i] = words([&](int word) { return twelve_round2_word(lane, i, false, word, C::m); });
         b.shared[i] = words([&](int word) { return twelve_round2_word(lane, i, true, word, C::m); });
     }
@@ -1010,8 +992,8 @@ __device__ __forceinline__ void twelve_round2(float (&r)[C::E], const f32x4 (&d1
 template <class C>
 using RoundB = std::conditional_t<C::kTwelve, TwelveB, HadamardB>;
 template <class C>
-__device__ __forceinline__ RoundB<C> make_round_b(const ThreadMap<C>& tm) {
-    if constexpr (C::kTwelve) return make_twelve_b<C>(tm);
+__device__ __forceinline__ RoundB<C> make_round_b() {
+    if constexpr (C::kTwelve) return make_twelve_b<C>();
     else return make_hadamard_b();
 }
 
@@ -1163,14 +1145,7 @@ __device__ __forceinline__ void token_sumsq(const float (&r)[C::E], float* wave_
             sq[0] += __shfl_xor(sq[0], off);
             sq[1] += __shfl_xor(sq[1], off);
         }
-        if constexpr (C::TPT > 64) {                        // two waves to those
-            float* mine = wave_sums + 2 * (threadIdx.x >> 6);
-            if ((threadIdx.x & 63u) < 2) mine[t & 1u] = (t & 1u) == 0 ? sq[0] : sq[1];
-            exchange_barrier();
-            if (t < 2 && tok + t < N) sumsq[tok + t] = mine[t] + mine[2 + t];
-        } else {
-            if (t < 2 && tok + t < N) sumsq[tok + t] = t == 0 ? sq[0] : sq[1];
-        }
+        if (t < 2 && tok + t < N) sumsq[tok + t] = t == 0 ? sq[0] : sq[1];
         return;
     }
     float sq = 0.0f;
@@ -1255,7 +1230,7 @@ __global__ __launch_bounds__(C::BT) void forward_kernel(const typename C::io::el
     alpha_get<C>(a, alpha, tm);
     param_load<C>(b, beta, tm);
     RoundB<C> hb{};
-    if constexpr (C::kMfma) hb = make_round_b<C>(tm);
+    if constexpr (C::kMfma) hb = make_round_b<C>();
     wait_vmem<0>();
     for (; grp < grp_end; grp += step) {
         const bool more = grp + step < grp_end;
@@ -1285,21 +1260,15 @@ __global__ __launch_bounds__(C::BT) void forward_kernel(const typename C::io::el
 }
 
 // A row's vectors in the layout of phase PH, straight into registers (cached loads).
-//   OUT: as the rounds leave them, i.e. half vectors where a thread computes half of one
-template <class C, int PH, bool OUT = false>
+template <class C, int PH>
 __device__ __forceinline__ void global_get(uint4 (&raw)[C::NV], const typename C::io::elem_t* tensor,
                                            const Walker<C>& wk, int64_t grp, const ThreadMap<C>& tm) {
     const typename C::io::elem_t* row = tensor + wk.row(grp) * C::kRow;
     const unsigned next = wk.next_row(grp);
     static_for<0, C::NV>([&](auto c) {
         constexpr int Cc = decltype(c)::value;
-        const typename C::io::elem_t* p = row + vector_offset<C, PH, Cc, OUT>(tm, next);
-        if constexpr (OUT && C::kHalf) {
-            const uint2 q = *reinterpret_cast<const uint2*>(p);
-            raw[Cc] = make_uint4(q.x, q.y, 0u, 0u);
-        } else {
-            raw[Cc] = *reinterpret_cast<const uint4*>(p);
-        }
+        const typename C::io::elem_t* p = row + vector_offset<C, PH, Cc>(tm, next);
+        raw[Cc] = *reinterpret_cast<const uint4*>(p);
     });
 }
 
@@ -1322,7 +1291,8 @@ __device__ __forceinline__ void pin(float* r) {
 // the condition.  us per call, without / with: 49152 x 256 10.8 / 9.1 (13.6 / 11.7 on inputs from memory), 100000 x 64
 // 6.6 / 5.5, 4000 x 1024 float32 7.4 / 6.2, 16000 x 1024 11.9 / 11.1, 3001 x 2048 with residual 7.6 / 7.05; one token of
 // 1024 or 2048 1.68 / 1.73 and 1.85 / 1.92.  With one token per workgroup the compiler's own place for these loads,
-// between the products, is the better one (4096 x 1000: 4.45 / 4.74), as it is for rows of 12 * 2^m (6144 x 4: 3.4 / 3.7).
+// between the products, is the better one (4096 x 1000: 4.45 / 4.74; 6144 x 4: 3.4 / 3.7).  Two tokens of 768 in a
+// workgroup of one wave (341 tokens, inputs from memory): 3.16 / 2.97, with the statistic 5.01 / 3.50.
 template <class C, bool RESID, bool STATS = false>
 __global__ __launch_bounds__(C::BT) void forward_once_kernel(const typename C::io::elem_t* x,
                                                              const float* __restrict__ alpha,
@@ -1331,7 +1301,7 @@ __global__ __launch_bounds__(C::BT) void forward_once_kernel(const typename C::i
                                                              typename C::io::elem_t* y,
                                                              float* __restrict__ sumsq, int64_t N) {
     static_assert(!STATS || RESID, "the statistic belongs to the residual-stream output");
-    __shared__ float wave_sums[STATS ? C::kPair * C::BT / 64 : 1];
+    __shared__ float wave_sums[STATS ? C::BT / 64 : 1];
     __shared__ __align__(16) float lds[C::kExchangeBytes / 4];
     constexpr int LAST = C::P - 1;
     const unsigned t = threadIdx.x % C::TPT;
@@ -1341,15 +1311,15 @@ __global__ __launch_bounds__(C::BT) void forward_once_kernel(const typename C::i
     tm.init(t, wk.slot);
     uint4 raw[C::NV], rraw[RESID ? C::NV : 1];
     global_get<C, 0>(raw, x, wk, grp, tm);                      // a ragged group re-reads the last token
-    if constexpr (RESID) global_get<C, LAST, true>(rraw, resid, wk, grp, tm);
+    if constexpr (RESID) global_get<C, LAST>(rraw, resid, wk, grp, tm);
     float a[C::E], b[C::E];
     param_load<C>(a, alpha, tm);
     param_load<C>(b, beta, tm);
-    constexpr bool HOLD = C::G > 1 && !C::kTwelve;
+    constexpr bool HOLD = C::G > 1;
     if constexpr (HOLD) __builtin_amdgcn_sched_barrier(0);
     else scale_alpha<C>(a, tm);
     RoundB<C> hb{};
-    if constexpr (C::kMfma) hb = make_round_b<C>(tm);
+    if constexpr (C::kMfma) hb = make_round_b<C>();
     float r[C::E];
     transform_from_raw<C, false>(r, raw, lds, tm, hb);
     if constexpr (HOLD) scale_alpha<C>(a, tm);                 // here, so that nothing before waits for alpha
@@ -1363,10 +1333,6 @@ __global__ __launch_bounds__(C::BT) void forward_once_kernel(const typename C::i
         for (int i = 0; i < C::E; ++i) r[i] = fmaf(r[i], a[i], b[i]);
     }
     if constexpr (HOLD) pin<C::E>(r);
-    if constexpr (C::kStoreBarrier && !STATS) {             // (STATS: the barrier of token_sumsq)
-        pin<C::E>(r);                                       // x has been read
-        exchange_barrier();
-    }
     if constexpr (STATS) token_sumsq<C>(r, wave_sums, sumsq, wk.token(grp), N, t, wk.slot, tm);
     global_put<C, LAST, false>(r, y, wk, grp, tm);
 }
@@ -1506,7 +1472,7 @@ __global__ __launch_bounds__(C::BT, C::kBwdWavesPerSimd) void backward_kernel(co
 #pragma unroll
         for (int i = 0; i < C::kSums; ++i) { da[i] = 0.0f; db[i] = 0.0f; }
     }
-    const RoundB<C> hb = make_round_b<C>(tm);
+    const RoundB<C> hb = make_round_b<C>();
     wait_vmem<0>();
     for (; grp < wk.groups; grp += step) {
         const bool more = grp + step < wk.groups;
@@ -1854,7 +1820,7 @@ __global__ __launch_bounds__(3 * C::BT) void backward_teams_kernel(const typenam
         // (before the first fetch: with it behind, the compiler waits for the prefetch at every exchange, 284 against
         // 270 us at 32768 x 8192; not so for rows of 12 * 2^m elements)
         if (C::kTwelve && grp < wk.groups) stage_issue<C, 0>(stage_x, x, wk, grp, tm);
-        const RoundB<C> hb = make_round_b<C>(tm);
+        const RoundB<C> hb = make_round_b<C>();
         if (!C::kTwelve && grp < wk.groups) stage_issue<C, 0>(stage_x, x, wk, grp, tm);
         float da[C::E];
 #pragma unroll
@@ -1912,7 +1878,7 @@ __global__ __launch_bounds__(3 * C::BT) void backward_teams_kernel(const typenam
         // the stage buffers are idle now
         write_partial_row<C>(db, reinterpret_cast<float*>(stage_g_buf), sums.row(1), 1.0f, tid, tm);
     } else {
-        const RoundB<C> hb = make_round_b<C>(tm);
+        const RoundB<C> hb = make_round_b<C>();
         int64_t prev = -1;                                      // token group whose Y data is in the exchange region
         auto first_half = [&](float (&g)[C::E], Round1<C>& d1) {
             lds_get<C, 0>(g, lds_g + tm.lds_off[0]);

@@ -247,19 +247,14 @@ constexpr LaneWave twelve_swap(unsigned lane, unsigned wave, int w) {
     }
     return s;
 }
-// Half waves (two waves on the same 1536 elements): both fetch whole vectors, and each stores the half of every
-// vector that it computes.  In place (y = x) a store must therefore stay behind the other wave's fetch: the exchange
-// keeps it there, or a barrier where there is none.
-constexpr bool twelve_store_barrier(int m, bool half) { return half && twelve_wave_bits(m) == 0; }
 // Exchange region of a token: one block of 64 16-byte places per (four registers, wave), and 16 bytes more, so
 // that the lanes of a scattered access differ in their banks.  Every thread puts in the order of one layout and
 // gets in the order of the other.
 constexpr unsigned kTwelveBlockWords = 64u * 4u + 4u;
 constexpr unsigned twelve_place(unsigned lane, unsigned wave) { return wave * kTwelveBlockWords + lane * 4u; }
 constexpr unsigned twelve_exchange_words(int w) { return 6u * (kTwelveBlockWords << w); }
-// Registers I .. I+3 of a thread; half waves: 12 registers, the two halves' blocks in turn.
-constexpr unsigned twelve_exchange_reg(int I, int w, bool half) { return (I / 4) * ((half ? 2u : 1u) * kTwelveBlockWords << w); }
-constexpr unsigned twelve_exchange_half(unsigned half, int w) { return half * (kTwelveBlockWords << w); }
+// Registers I .. I+3 of a thread.
+constexpr unsigned twelve_exchange_reg(int I, int w) { return (I / 4) * (kTwelveBlockWords << w); }
 // Column sums in LDS: 16 words more after every block, for the same reason.
 constexpr unsigned twelve_column(unsigned e, int m) { return e + 16u * (e >> m); }
 

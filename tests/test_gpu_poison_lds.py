@@ -5,12 +5,12 @@ missing wait on a prefetch -- returns NaN there instead of the previous token gr
 values, so the ordinary comparison against the oracle turns a synchronisation mistake into a hard
 failure.  Widths in this build: bf16 4096 and 8192 (matrix-core schedule, one exchange; the three-team
 backward), 16384 (two exchanges in the backward), 768 (two tokens to a wave, a missing one's zeros in the stage),
-3072 (half waves with an exchange), 6144, 12288 (single-team backward with an exchange), 512 (wave schedule, no
+3072, 6144, 12288 (single-team backward with an exchange), 512 (wave schedule, no
 exchange), and float32 512, 4096 and 8192 (wave schedule with a token on part of one wave, on two and
 on four).  Token counts: past the few-token limit of the residual forward (2^24, 2^23, 2^22 or 2^21
 elements), and more token groups than any backward kernel has workgroups, so that every kernel refills
 its stages and re-uses its exchange region; 300 tokens of 512 run the one-pass forward kernel, as do the smaller counts
-of 768, 3072 (half waves, whole waves) and 12288.  Odd counts of 768 leave half a wave without a token."""
+of 768, 3072 and 12288.  Odd counts of 768 leave half a wave without a token."""
 import ctypes
 
 import numpy as np

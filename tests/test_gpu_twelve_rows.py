@@ -13,8 +13,8 @@ from parity import assert_grad_close, assert_io_close, nan_filled, to_gpu
 
 pytestmark = pytest.mark.gpu
 
-# elements per call up to which the one-pass forward kernel runs, with half waves and with whole ones
-FEW = {768: (1 << 20, 3 << 20), 1536: (1 << 20, 3 << 20), 3072: (1 << 21, 3 << 20), 6144: (3 << 20,), 12288: (1 << 23,)}
+# elements per call up to which the one-pass forward kernel runs
+FEW = {768: 3 << 20, 1536: 3 << 20, 3072: 3 << 20, 6144: 3 << 20, 12288: 1 << 23}
 
 
 @pytest.mark.parametrize("d,N", [(768, n) for n in (1, 2, 3, 4, 5, 8, 9, 23, 24, 25, 47, 4099)] +
@@ -44,7 +44,7 @@ def test_every_output_at_partial_waves(d, N):
 @pytest.mark.parametrize("d", [768, 1536, 3072, 6144, 12288])
 def test_rows_are_the_same_on_both_sides_of_every_limit(d):
     # few-token limits; 32 MiB (backward) and 128 MiB (forward, dx alone) a tensor
-    for N, back in (*((limit // d, False) for limit in FEW[d]), ((32 << 20) // (2 * d), True), ((128 << 20) // (2 * d), False)):
+    for N, back in ((FEW[d] // d, False), ((32 << 20) // (2 * d), True), ((128 << 20) // (2 * d), False)):
         print(f"[twelve] d={d} N={N}", flush=True)
         gen = torch.Generator(device="cuda").manual_seed(N)
         x = torch.empty(N + 1, d, dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
@@ -70,7 +70,7 @@ def test_rows_are_the_same_on_both_sides_of_every_limit(d):
 @pytest.mark.parametrize("d,N", [(768, n) for n in (1, 2, 5, 300, 512, 513, 1023, 1024, 1025, 1365, 1366, 4097)] +
                          [(1536, n) for n in (1, 3, 200, 256, 257, 512, 513, 682, 683, 2049)] + [(3072, n) for n in (1, 200, 682, 683, 1025)])
 def test_forward_in_place_is_the_forward_out_of_place(d, N):
-    # two waves that both fetch the whole of a row, of which each stores a part: bit for bit
+    # no wave stores what another has still to fetch: bit for bit
     print(f"[twelve] in place d={d} N={N}", flush=True)
     gen = torch.Generator(device="cuda").manual_seed(d + N)
     x = torch.empty(N, d, dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
