@@ -263,6 +263,17 @@ static int dispatch_d(int logd, Op op, Args& a) {
 // / 52.6, of 32768 x 1536 90.6 / 89.4 / 94.3, backward alone 34.1 / 32.5 / 32.5 and 61.1 / 58.0 / 57.9; three sets in
 // turn: backward of 16384 x 768 18.6 / 21.5 / 21.4, of 8192 x 1536 19.2 / 22.6 / 22.5.  A forward call alone on an
 // input that lies in memory loses 2..4 % to streaming (8192 x 6144 39.4 against 38.4), one of 400 MB 6 %.
+// Backward, rows of 768, up to 512 tokens: workgroups of 128 threads (four tokens), so that twice as many share a call
+// that has few -- unless two passes of one workgroup of 256 threads do for it, which saves the second launch.  us per call
+// under graph replay, 256 / 128 threads, inputs that come back: 1 token 4.21 / 3.92, 8 4.58 / 5.34, 16 5.86 / 6.19, 17 6.74 /
+// 6.23, 64 6.77 / 6.24, 341 7.00 / 6.63, 512 7.09 / 6.99, 683 7.26 / 7.31, 1365 8.22 / 9.87; dx alone 64 3.26 / 2.84, 512 3.33 / 2.95,
+// 1365 3.51 / 3.77.
+constexpr int64_t kSmallBackwardTokens = 512;
+using SmallBackwardCfg = TwelveCfg<6, true, 128>;
+static bool small_backward(int64_t N, bool grads) {
+    return N <= kSmallBackwardTokens && (!grads || N <= SmallBackwardCfg::G || !one_workgroup<TwelveCfg<6>>(N));
+}
+
 template <int M>
 static int run_twelve(Op op, Args& a) {
     const int64_t elems = a.N * TwelveCfg<M>::kRow, bytes = 2 * elems;
@@ -273,7 +284,18 @@ static int run_twelve(Op op, Args& a) {
             return launch_forward<TwelveCfg<M, true>>(a.x, a.alpha, a.beta, a.resid, a.y, a.sumsq, a.N, a.stream);
         return launch_forward<TwelveCfg<M>>(a.x, a.alpha, a.beta, a.resid, a.y, a.sumsq, a.N, a.stream);
     }
-    if (op == Op::Workspace) { a.workspace_out = workspace_for<TwelveCfg<M>>(a.N); return WHT_OK; }
+    if (op == Op::Workspace) {
+        a.workspace_out = workspace_for<TwelveCfg<M>>(a.N);
+        if constexpr (M == 6)
+            if (!one_workgroup<TwelveCfg<M>>(a.N)) {        // what suffices for N tokens suffices for fewer
+                const size_t small = workspace_for<SmallBackwardCfg>(a.N < kSmallBackwardTokens ? a.N : kSmallBackwardTokens);
+                if (a.workspace_out < small) a.workspace_out = small;
+            }
+        return WHT_OK;
+    }
+    if constexpr (M == 6)
+        if (small_backward(a.N, a.dalpha != nullptr))
+            return launch_backward<SmallBackwardCfg>(a.dy, a.x, a.alpha, a.dx, a.dalpha, a.dbeta, a.N, a.workspace, a.stream);
     if (bytes <= (int64_t(a.dalpha ? 32 : 128) << 20))             // dx alone reads dy only
         return launch_backward<TwelveCfg<M, true>>(a.dy, a.x, a.alpha, a.dx, a.dalpha, a.dbeta, a.N, a.workspace, a.stream);
     return launch_backward<TwelveCfg<M>>(a.dy, a.x, a.alpha, a.dx, a.dalpha, a.dbeta, a.N, a.workspace, a.stream);

@@ -26,7 +26,8 @@ MATRIX = [(768, "bf16", 8, 2), (1024, "bf16", 4, 1), (1536, "bf16", 4, 1), (2048
 
 def _counts(G, W, d):
     workgroups = 1024 if d <= 64 else 512
-    return (G + W + 1, 2 * workgroups * G + W + 1)
+    few = (19, 33) if d == 768 else ()                # the backward pass on workgroups of four tokens
+    return (G + W + 1, 2 * workgroups * G + W + 1, *few)
 
 
 def _params(inp):

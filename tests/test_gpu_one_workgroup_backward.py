@@ -20,7 +20,9 @@ SHAPES = [(32, "bf16", 64), (512, "bf16", 8), (768, "bf16", 8), (1024, "bf16", 4
 
 @pytest.mark.parametrize("d,dtype,G", SHAPES)
 def test_few_groups(d, dtype, G):
-    for N in sorted({1, G, G + 1, 2 * G, 2 * G + 1, 3 * G, 3 * G + 1}):
+    # 768: four tokens to a workgroup up to 4 and from 17 to 512
+    more = {4, 5, 511, 512, 513} if d == 768 else set()
+    for N in sorted({1, G, G + 1, 2 * G, 2 * G + 1, 3 * G, 3 * G + 1} | more):
         print(f"[one workgroup] d={d} {dtype} N={N}", flush=True)
         inp = synth.make_inputs(N, d, dtype, seed=11 * d + N)
         x, dy = to_gpu(inp.x, dtype), to_gpu(inp.dy, dtype)

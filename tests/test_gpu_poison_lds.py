@@ -44,7 +44,7 @@ def poison_lib():
 
 @pytest.mark.parametrize("d,dtype,N", [(512, "bf16", 300), (512, "f32", 300), (4096, "bf16", 1031), (4096, "f32", 70),
                                        (8192, "bf16", 700), (8192, "f32", 300), (16384, "bf16", 600), (6144, "bf16", 600),
-                                       (768, "bf16", 9), (768, "bf16", 8197), (3072, "bf16", 301), (3072, "bf16", 701), (3072, "bf16", 1031),
+                                       (768, "bf16", 9), (768, "bf16", 19), (768, "bf16", 8197), (3072, "bf16", 301), (3072, "bf16", 701), (3072, "bf16", 1031),
                                        (12288, "bf16", 259), (12288, "bf16", 701), (512, "bf16", 32805), (512, "f32", 16421), (4096, "f32", 1061), (8192, "f32", 1061)])
 def test_poisoned_lds_build_matches_the_oracle(d, dtype, N):
     print(f"[poison] d={d} {dtype} N={N}", flush=True)

@@ -120,6 +120,11 @@ def test_workspace_query():
     assert q(32768, 8192, 1) <= 64 << 20
     # rows of 12 * 2^m elements: the partial rows have the row's real length
     assert q(1, 6144, 1) == 2 * 6144 * 4
+    # never less for more tokens, so that one buffer serves every shorter call
+    for d, dtype in [(32 << k, t) for k in range(10) for t in (0, 1) if k < 9 or t == 1] + [(768 << k, 1) for k in range(5)]:
+        need = [q(N, d, dtype) for N in range(1, 1100)]
+        assert need == sorted(need) and need[0] > 0, (d, dtype)
+    assert q(17, 768, 1) == 5 * 2 * 768 * 4 and q(512, 768, 1) == q(513, 768, 1) == 128 * 2 * 768 * 4
     # tokens of a workgroup pass, which tests/test_gpu_one_workgroup_backward.py and test_gpu_nonfinite.py rely on
     for d, group in ((768, 8), (1536, 4), (3072, 2), (6144, 1), (12288, 1)):
         assert q(group, d, 1) == 2 * d * 4 and q(group + 1, d, 1) == 2 * (2 * d * 4)
