@@ -37,15 +37,17 @@ static int grid_for(int64_t N, bool backward) {
 // Workgroups per cluster of the forward kernel: the configuration's figure when the grid divides
 // into such clusters and every workgroup has many token groups to walk, else the whole grid.  Clusters spread
 // the loss at unlucky address distances (see MfmaCfg), but each ends with its own ragged last round and their
-// windows make short tensors slower: up to 24 rounds the plain interleave is ahead at every width.  us per call, four
-// clusters / one: 8.5 rounds of 4096 27.5 / 25.7, of 8192 28.2 / 25.8, of 3072 21.0 / 20.2, of float32 1024 26.3 /
-// 24.6, 17 rounds of 8192 51.0 / 48.7, 24 rounds of 4096 68.0 / 66.4; 32 rounds of 4096 91.9 / 94..99, of 8192 94 / 94..96,
-// of 3072 72.3 / 70.4 (rows of 12 * 2^m stay with one up to 48), 64 rounds of 8192 186 / 193..202, of 6144 139 / 137..146.
+// windows make short tensors slower.  us per call over 32 distances between x and y, clustered mean (worst) / plain mean
+// (worst): 16 rounds of 4096 45.7 (48.4) / 45.1 (48.7), of 8192 46.5 (48.2) / 45.8 (49.2); 20 rounds 55.8 (57.0) / 56.9
+// (64.1) and 56.5 (57.8) / 56.8 (64.3); 28 rounds 77.7 (79.0) / 80.6 (93.2) and 78.2 (79.8) / 79.2 (90.4), of float32
+// 1024 76.6 (78.1) / 78.5 (89.4); 40 rounds 111.5 (113.1) / 116.2 (134.4) and 111.8 (113.5) / 117.4 (134.8); 8 rounds 25.1 / 24.2
+// and 24.9 / 24.3.  Rows of 12 * 2^m: 28 rounds of 3072 61.1 (61.9) / 60.3 (62.2), 48 102.7 (104.4) / 103.0 (111.7), of 6144 28
+// 61.0 / 60.9, 48 103.1 (104.5) / 103.5 (112.4).
 template <class C>
 static int forward_cluster(int64_t N, int grid, bool resid) {
     const int64_t groups = (N + C::G - 1) / C::G;
     const int want = resid ? C::kFwdClusterResid : C::kFwdCluster;
-    constexpr int rounds = C::kTwelve ? 48 : 32;
+    constexpr int rounds = C::kTwelve ? 48 : 20;
     if (want > 0 && grid % want == 0 && grid > want && groups >= rounds * (int64_t)grid) return want;
     return grid;
 }

@@ -1,5 +1,5 @@
 """The forward kernel's deal of token groups to clusters of workgroups, on both sides of the number of rounds from
-which it is used (32, for rows of 12 * 2^m elements 48; 512 workgroups), with a last region that is short and one
+which it is used (20, for rows of 12 * 2^m elements 48; 512 workgroups), with a last region that is short and one
 that is ragged: bit for bit the rows of calls that are too short for it, which other tests hold against the oracle."""
 import pytest
 import torch
@@ -10,8 +10,8 @@ pytestmark = pytest.mark.gpu
 
 
 # width, dtype, rounds from which token groups are dealt, tokens of a group
-@pytest.mark.parametrize("d,dtype,rounds,G", [(4096, torch.bfloat16, 32, 2), (8192, torch.bfloat16, 32, 1), (4096, torch.float32, 32, 1),
-                                              (1024, torch.float32, 32, 4), (3072, torch.bfloat16, 48, 2), (6144, torch.bfloat16, 48, 1)])
+@pytest.mark.parametrize("d,dtype,rounds,G", [(4096, torch.bfloat16, 20, 2), (8192, torch.bfloat16, 20, 1), (4096, torch.float32, 20, 1),
+                                              (1024, torch.float32, 20, 4), (3072, torch.bfloat16, 48, 2), (6144, torch.bfloat16, 48, 1)])
 def test_clusters_compute_the_rows_of_the_plain_walk(d, dtype, rounds, G):
     first = (rounds * 512 - 1) * G + 1                    # the first count of that many rounds, its last group ragged where G > 1
     gen = torch.Generator(device="cuda").manual_seed(d)
