@@ -37,11 +37,12 @@
  *   - x, y, dy, dx are row-major [N, d], contiguous (leading dimension d), of type `dtype`.
  *     alpha, beta, dalpha, dbeta are float32 [d] whatever `dtype` is.
  *   - bfloat16 tensors are computed in float32 internally and rounded to nearest-even on store.
- *     For bfloat16 tensors of d >= 1024 (and all 12 * 2^m widths) ten of the log2(d) stages run on
- *     the matrix cores as products with +-1 matrices: exact products, float32 accumulation, and a
- *     float32 value entering such a product is represented as the sum of two bfloat16 terms, which
- *     carries it to a relative error of at most 2^-17 (five hundred times finer than the bfloat16
- *     output's own rounding).  float32 tensors never take this path.
+ *     For bfloat16 tensors of d >= 1024 ten of the log2(d) stages run on the matrix cores as
+ *     products with +-1 matrices (d = 12 * 2^m: six of the Sylvester stages, P12 and, from 1536 on, a
+ *     third of a seventh stage): exact products, float32 accumulation, and a float32 value entering
+ *     such a product is represented as the sum of two bfloat16 terms, which carries it to a relative
+ *     error of at most 2^-17 (five hundred times finer than the bfloat16 output's own rounding).
+ *     float32 tensors never take this path.
  *   - Non-finite inputs: NaN propagates.  An infinite input makes the token's outputs +-Inf or NaN
  *     with float32 tensors and bfloat16 tensors of d <= 512 (Inf - Inf in a butterfly) and NaN with
  *     the other bfloat16 tensors (the two-term representation of Inf is Inf + NaN).  Other tokens'

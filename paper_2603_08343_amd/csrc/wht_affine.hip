@@ -258,13 +258,22 @@ static int dispatch_d(int logd, Op op, Args& a) {
 // 4.21 / 3.51 and 5.36 / 4.76.  One pass / persistent: 3863 x 768 5.47 / 5.36 and 6.01 / 6.38, 5461 x 768 6.70 / 6.01 and 7.14 /
 // 7.86, 965 x 3072 5.93 / 6.85, 1365 x 3072 8.01 / 7.59, 512 x 6144 5.9 / 6.6, 682 x 6144 7.9 / 7.3, 341 x 12288 9.6 / 12.3,
 // 682 x 12288 14.5 / 15.0.
-// Tensors of up to 128 MiB (32 MiB where the backward pass reads both) are read with the default cache policy, larger ones streamed.  What has
-// been read with the default policy stays in the Infinity Cache: a backward call that follows its forward call finds
-// x there, and a caller that comes back to the same small tensors finds them.  us per call, default policy in
-// both directions / in forward alone / in neither, twelve sets of buffers in turn: a step of 32768 x 768 51.7 / 49.5
-// / 52.6, of 32768 x 1536 90.6 / 89.4 / 94.3, backward alone 34.1 / 32.5 / 32.5 and 61.1 / 58.0 / 57.9; three sets in
-// turn: backward of 16384 x 768 18.6 / 21.5 / 21.4, of 8192 x 1536 19.2 / 22.6 / 22.5.  A forward call alone on an
-// input that lies in memory loses 2..4 % to streaming (8192 x 6144 39.4 against 38.4), one of 400 MB 6 %.
+// Tensors of up to 128 MiB (32 MiB where the backward pass reads both) are read with the default cache policy, as
+// these rows always have been, larger ones streamed.  What has been read with the default policy stays in the
+// Infinity Cache: a backward call that follows its forward call finds x there, and a caller that comes back to the
+// same small tensors finds them.  us per call, default policy in both directions / in forward alone / in neither,
+// twelve sets of buffers in turn: a step of 32768 x 768 51.7 / 49.5 / 52.6, of 32768 x 1536 90.6 / 89.4 / 94.3, backward
+// alone 34.1 / 32.5 / 32.5 and 61.1 / 58.0 / 57.9.  A forward call alone on an input that lies in memory loses 2..4 % to
+// streaming (8192 x 6144 39.4 against 38.4), one of 400 MB 6 %.
+// The 32 MiB: backward, default policy / streamed, three sets of buffers in turn and inputs from memory (rows padded to
+// 16 * 2^m, before: always default):
+//     10923 x 768    16.0 / 17.9   18.1 / 18.4   (16.9, 18.0)        1365 x 6144    18.5 / 22.0   20.3 / 22.3   (19.4, 21.3)
+//     16384 x 768    19.2 / 21.3   21.8 / 21.7   (21.0, 22.5)        2048 x 6144    21.9 / 25.4   23.5 / 25.7   (23.9, 25.3)
+//     8192 x 1536    19.8 / 22.7   22.5 / 22.9   (22.8, 23.9)        683 x 12288    25.3 / 31.1   26.4 / 31.4   (39.5, 41.6)
+//     2731 x 3072    16.9 / 18.3   19.7 / 18.7   (18.9, 20.3)        1365 x 12288   35.7 / 39.7   37.3 / 40.8   (56.1, 56.6)
+//     5461 x 3072    24.6 / 26.0   27.0 / 26.0   (28.3, 28.6)
+// So the default policy costs up to 5 % from memory at 768 and 3072 and gains more elsewhere; streamed, calls of 6144 and
+// 768 would be slower than before.  The power-of-two rows have always been streamed and lose by a change.
 // Backward, rows of 768, up to 512 tokens: workgroups of 128 threads (four tokens), so that twice as many share a call
 // that has few -- unless two passes of one workgroup of 256 threads do for it, which saves the second launch.  us per call
 // under graph replay, 256 / 128 threads, inputs that come back: 1 token 4.21 / 3.92, 8 4.58 / 5.34, 16 5.86 / 6.19, 17 6.74 /
