@@ -145,9 +145,9 @@ struct MfmaCfg {
 // large calls were bound by instruction issue there (75 % of the vector slots at 6144) and are bound by memory
 // (forward) or nearly so here.  us per call, before / after: forward 32768 x 6144 153 / 137 (5.9 TB/s; a copy in
 // this layout 130), backward 262 / 229 (5.3 TB/s), a step of 32768 x 768 56.4 / 48.6, of 32768 x 1536 100 / 88,
-// backward of 16384 x 12288 358 / 256 (one exchange per transform instead of two).  A wave computes 24 values per
-// lane where it computed 16, and two tokens of 768: calls of one to a few tokens per CU take up to 0.6 us longer
-// in the backward pass of 768 and 6144 (64 tokens 6.2 / 6.6 and 8.1 / 8.7).
+// backward of 16384 x 12288 358 / 256 (one exchange per transform instead of two).  What is slower than
+// on padded rows: the backward pass of up to 341 tokens of 6144 (64 tokens 8.4 / 8.9; 24 values per lane in dependent
+// rounds with nothing else on the CU), forward calls of some sizes by up to 5 %.
 // LEAST: threads of a workgroup, where a token (two of 768) takes fewer.
 // KEEP: x and dy are read with the default cache policy and so stay in the Infinity Cache (see run_twelve).
 template <int LOGM, bool KEEP = false, int LEAST = 256>
