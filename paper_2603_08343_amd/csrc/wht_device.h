@@ -1285,14 +1285,38 @@ __device__ __forceinline__ void pin(float* r) {
 // long, so everything the group needs -- x, alpha, beta, the residual -- is requested at once,
 // straight into registers, before anything is awaited; there is no token loop, no prefetch stage and
 // no walk over the grid, whose set-up costs the persistent kernel about a microsecond per launch.
-// Where the store is conditional (several tokens per workgroup) the compiler moves the loads of the residual, alpha
-// and beta, with the arithmetic on them, into that condition, behind the transform, and the launch becomes two
-// round trips long.  HOLD: a scheduling barrier keeps them in front and the pinned results keep the arithmetic out of
-// the condition.  us per call, without / with: 49152 x 256 10.8 / 9.1 (13.6 / 11.7 on inputs from memory), 100000 x 64
-// 6.6 / 5.5, 4000 x 1024 float32 7.4 / 6.2, 16000 x 1024 11.9 / 11.1, 3001 x 2048 with residual 7.6 / 7.05; one token of
-// 1024 or 2048 1.68 / 1.73 and 1.85 / 1.92.  With one token per workgroup the compiler's own place for these loads,
-// between the products, is the better one (4096 x 1000: 4.45 / 4.74; 6144 x 4: 3.4 / 3.7).  Two tokens of 768 in a
-// workgroup of one wave (341 tokens, inputs from memory): 3.16 / 2.97, with the statistic 5.01 / 3.50.
+//
+// The compiler places these loads by register pressure and not by time: a part of x behind the first products
+// (d = 8192), the residual behind the transform, and where the store is conditional (several tokens per workgroup)
+// alpha, beta and the arithmetic on them in that condition; each makes the launch another round trip longer.  A
+// scheduling barrier behind x, behind x and the residual or behind all of them keeps them in front, and the results of
+// a conditional store are then pinned in front of the condition.  It costs registers, and so waves, where a CU has
+// several workgroups, and a wait where the products could have covered the loads.  So the place differs; this is the
+// one that is no slower than the others, or by little, at few tokens and at the limit, on inputs that come back and on
+// inputs from memory.  us per call under graph replay, from memory, compiler's own / x / x and residual / all in front:
+//     256 wide, 512 tokens: 2.59 / 2.41 / 2.42 / 2.49, residual 3.70 / 3.04 / 2.84 / 2.95 (but 16384 tokens of 128, float32 6.94 /
+//       6.56 / 7.05 / 7.04), statistic 3.07 / 3.40 / 3.07 / 3.18
+//     1024 wide, 512 tokens: 2.83 / 2.97 / 2.97 / 2.94, residual 3.76 / 3.94 / 3.26 / 3.01, statistic 3.90 / 3.90 / 3.58 / 3.29
+//     4096 wide, 64 tokens, residual: 3.54 / 3.54 / 3.07 / 3.48; 8192 wide, 16 tokens 4.60 / 3.96 / 3.83 / 4.24
+//     6144 wide, 85 tokens: 4.30 / 4.41 / 4.41 / 4.70, residual 4.84 / 4.68 / 4.46 / 5.07; 341 of 768, statistic 5.02 / 4.54 / 3.81 / 3.51
+// (profiles/wht_affine_one_pass_request_order.txt has all).
+enum class Requests { kFree, kX, kInputs, kAll };
+template <class C>
+constexpr Requests requests_first(bool resid, bool stats) {
+    const bool plain_resid = resid && !stats;
+    if constexpr (C::kTwelve) return C::m == 6 ? Requests::kAll : resid && C::m < 10 ? Requests::kInputs : Requests::kFree;
+    else if constexpr (C::kWave) {
+        if (C::v == 3) return stats ? Requests::kFree : plain_resid && C::n == 9 ? Requests::kAll : Requests::kX;
+        if (C::n <= 10) return Requests::kX;
+        if (C::n == 11) return resid ? Requests::kAll : Requests::kFree;
+        return C::n == 13 && plain_resid ? Requests::kInputs : Requests::kFree;
+    } else {
+        if (C::n == 13 || (C::n == 11 && stats)) return Requests::kX;
+        if (C::n <= 11) return resid ? Requests::kAll : Requests::kFree;
+        return plain_resid || (C::n == 14 && resid) ? Requests::kInputs : Requests::kFree;
+    }
+}
+
 template <class C, bool RESID, bool STATS = false>
 __global__ __launch_bounds__(C::BT) void forward_once_kernel(const typename C::io::elem_t* x,
                                                              const float* __restrict__ alpha,
@@ -1310,19 +1334,21 @@ __global__ __launch_bounds__(C::BT) void forward_once_kernel(const typename C::i
     ThreadMap<C> tm;
     tm.init(t, wk.slot);
     uint4 raw[C::NV], rraw[RESID ? C::NV : 1];
+    constexpr Requests FIRST = requests_first<C>(RESID, STATS);
     global_get<C, 0>(raw, x, wk, grp, tm);                      // a ragged group re-reads the last token
+    if constexpr (FIRST == Requests::kX) __builtin_amdgcn_sched_barrier(0);
     if constexpr (RESID) global_get<C, LAST>(rraw, resid, wk, grp, tm);
+    if constexpr (FIRST == Requests::kInputs) __builtin_amdgcn_sched_barrier(0);
     float a[C::E], b[C::E];
     param_load<C>(a, alpha, tm);
     param_load<C>(b, beta, tm);
-    constexpr bool HOLD = C::G > 1;
-    if constexpr (HOLD) __builtin_amdgcn_sched_barrier(0);
+    if constexpr (FIRST == Requests::kAll) __builtin_amdgcn_sched_barrier(0);
     else scale_alpha<C>(a, tm);
     RoundB<C> hb{};
     if constexpr (C::kMfma) hb = make_round_b<C>();
     float r[C::E];
     transform_from_raw<C, false>(r, raw, lds, tm, hb);
-    if constexpr (HOLD) scale_alpha<C>(a, tm);                 // here, so that nothing before waits for alpha
+    if constexpr (FIRST == Requests::kAll) scale_alpha<C>(a, tm);      // here, so that nothing before waits for alpha
     if constexpr (RESID) {
         float res[C::E];
         unpack_all<C>(res, rraw);
@@ -1332,7 +1358,7 @@ __global__ __launch_bounds__(C::BT) void forward_once_kernel(const typename C::i
 #pragma unroll
         for (int i = 0; i < C::E; ++i) r[i] = fmaf(r[i], a[i], b[i]);
     }
-    if constexpr (HOLD) pin<C::E>(r);
+    if constexpr (FIRST != Requests::kFree && C::G > 1) pin<C::E>(r);
     if constexpr (STATS) token_sumsq<C>(r, wave_sums, sumsq, wk.token(grp), N, t, wk.slot, tm);
     global_put<C, LAST, false>(r, y, wk, grp, tm);
 }
