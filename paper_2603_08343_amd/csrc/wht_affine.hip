@@ -19,6 +19,15 @@ namespace wht {
 
 constexpr int kNumCU = 256;             // MI355X
 
+enum class Op { Forward, Backward, Workspace };
+
+struct Args {
+    const void* x; const void* dy; const void* resid; const float* alpha; const float* beta;
+    void* y; void* dx; float* dalpha; float* dbeta; float* sumsq;
+    int64_t N; void* workspace; hipStream_t stream;
+    size_t workspace_out;
+};
+
 // Workgroups launched per CU: the grid is persistent, each workgroup strides over token groups.  The
 // per-configuration figures (C::kFwdGroupsPerCU, C::kBwdGroupsPerCU) are measured optima; the launch
 // shape, and with it the backward workspace size, depends on (N, d, dtype) alone.
@@ -71,23 +80,43 @@ static bool few_tokens(int64_t N, bool resid) {
     return N * C::kRow <= (int64_t(1) << (wide_f32 && resid ? limit + 1 : limit));
 }
 
+// Whether the persistent forward kernels and the backward kernels write y and dx through L2 rather than streaming them
+// past the caches ("nt").  Written through, results stay in the Infinity Cache: the next kernel finds them there, and a
+// program that gets the same output buffers back overwrites them there.  us per call, streamed / through, everything from
+// memory: 32768 x 1024 forward 24.5 / 24.1, backward 39.4 / 38.6; forward, forward on its result with the residual and backward, 32 MiB
+// each, 47.5 / 43.1, 128 MiB each 182 / 172; with two sets of outputs in turn forward 32768 x 2048 44.1 / 40.6, a step of
+// 32768 x 1024 64.4 / 59.3.  Above 136 MiB the three kinds of stream no longer fit together and streaming is ahead
+// (backward of 32768 x 8192 276 / 281, a step of 16384 x 4096 float32 231 / 236).  Where a workgroup of the persistent forward
+// has few rounds, each waits for the stores of the one before it, and those come back from memory, not L2: forward of 16 MiB of
+// 8192 wide 8.6 / 9.3, of 32 MiB of 16384 wide 17.0 / 18.0, dx alone of 16 MiB of 2048 wide 7.6 / 8.5.
+// Rows of 12 * 2^m: run_twelve.
 template <class C>
+static bool write_through(int64_t N, bool backward, bool grads) {
+    constexpr int64_t MiB = 1 << 20;
+    const int64_t bytes = N * C::kRow * (int64_t)sizeof(typename C::io::elem_t);
+    if (!backward && bytes < (C::n >= 13 ? 56 : 24) * MiB) return false;
+    if (backward && !grads && (C::n == 14 ? bytes < 56 * MiB : bytes >= 12 * MiB && bytes < 24 * MiB)) return false;
+    return bytes <= 136 * MiB;
+}
+// f(false type or true type): a choice made at run time as a template argument.
+template <class F>
+static void with_bool(bool b, F&& f) {
+    if (b) f(std::true_type{});
+    else f(std::false_type{});
+}
+
+template <class C, bool THROUGH, int R>
 static int launch_forward_once(const void* x, const float* alpha, const float* beta, const void* resid,
                                void* y, float* sumsq, int64_t N, hipStream_t stream) {
     using T = typename C::io::elem_t;
-    const int grid = (int)((N + C::G - 1) / C::G);
-    if (resid && sumsq)
-        hipLaunchKernelGGL((forward_once_kernel<C, true, true>), dim3(grid), dim3(C::BT), 0, stream,
-                           static_cast<const T*>(x), alpha, beta, static_cast<const T*>(resid), static_cast<T*>(y),
-                           sumsq, N);
-    else if (resid)
-        hipLaunchKernelGGL((forward_once_kernel<C, true>), dim3(grid), dim3(C::BT), 0, stream,
-                           static_cast<const T*>(x), alpha, beta, static_cast<const T*>(resid), static_cast<T*>(y),
-                           static_cast<float*>(nullptr), N);
-    else
-        hipLaunchKernelGGL((forward_once_kernel<C, false>), dim3(grid), dim3(C::BT), 0, stream,
-                           static_cast<const T*>(x), alpha, beta, static_cast<const T*>(nullptr), static_cast<T*>(y),
-                           static_cast<float*>(nullptr), N);
+    const int grid = (int)((N + C::G * R - 1) / (C::G * R));
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(C::BT), 0, stream, static_cast<const T*>(x), alpha, beta,
+                           static_cast<const T*>(resid), static_cast<T*>(y), sumsq, N);
+    };
+    if (resid && sumsq) launch(forward_once_kernel<C, true, true, THROUGH, R>);
+    else if (resid) launch(forward_once_kernel<C, true, false, THROUGH, R>);
+    else launch(forward_once_kernel<C, false, false, THROUGH, R>);
     return hipGetLastError() == hipSuccess ? WHT_OK : WHT_ERR_LAUNCH;
 }
 
@@ -97,19 +126,24 @@ static int launch_forward(const void* x, const float* alpha, const float* beta, 
     using T = typename C::io::elem_t;
     const int grid = grid_for<C>(N, false);
     const int cluster = forward_cluster<C>(N, grid, resid != nullptr);
-    if (resid && sumsq)
-        hipLaunchKernelGGL((forward_kernel<C, true, true>), dim3(grid), dim3(C::BT), 0, stream,
-                           static_cast<const T*>(x), alpha, beta, static_cast<const T*>(resid),
-                           static_cast<T*>(y), sumsq, N, cluster);
-    else if (resid)
-        hipLaunchKernelGGL((forward_kernel<C, true>), dim3(grid), dim3(C::BT), 0, stream,
-                           static_cast<const T*>(x), alpha, beta, static_cast<const T*>(resid),
-                           static_cast<T*>(y), static_cast<float*>(nullptr), N, cluster);
-    else
-        hipLaunchKernelGGL((forward_kernel<C, false>), dim3(grid), dim3(C::BT), 0, stream,
-                           static_cast<const T*>(x), alpha, beta, static_cast<const T*>(nullptr),
-                           static_cast<T*>(y), static_cast<float*>(nullptr), N, cluster);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(C::BT), 0, stream, static_cast<const T*>(x), alpha, beta,
+                           static_cast<const T*>(resid), static_cast<T*>(y), sumsq, N, cluster);
+    };
+    with_bool(!C::kTwelve && write_through<C>(N, false, false), [&](auto b) {
+        constexpr bool THROUGH = !C::kTwelve && decltype(b)::value;
+        if (resid && sumsq) launch(forward_kernel<C, true, true, THROUGH>);
+        else if (resid) launch(forward_kernel<C, true, false, THROUGH>);
+        else launch(forward_kernel<C, false, false, THROUGH>);
+    });
     return hipGetLastError() == hipSuccess ? WHT_OK : WHT_ERR_LAUNCH;
+}
+
+template <class CF, class CO>
+static int forward(const Args& a) {
+    if (few_tokens<CO>(a.N, a.resid != nullptr))
+        return launch_forward_once<CO, false, 1>(a.x, a.alpha, a.beta, a.resid, a.y, a.sumsq, a.N, a.stream);
+    return launch_forward<CF>(a.x, a.alpha, a.beta, a.resid, a.y, a.sumsq, a.N, a.stream);
 }
 
 // A call of a few token groups runs on one workgroup, which writes dalpha and dbeta itself: no partial
@@ -134,34 +168,22 @@ static int launch_backward(const void* dy, const void* x, const float* alpha, vo
     float* ws = static_cast<float*>(workspace);
     const SumRows sums = direct ? SumRows{dalpha, dbeta, 0} : SumRows{ws, ws + C::kRow, 2 * C::kRow};
 
-    if constexpr (C::kWave) {
-        const T *dyp = static_cast<const T*>(dy), *xp = static_cast<const T*>(x);
-        if (grads && dx)
-            hipLaunchKernelGGL((backward_wave_kernel<C, true, true>), dim3(grid), dim3(C::BT), 0, stream, dyp, xp, alpha,
-                               static_cast<T*>(dx), sums, N);
-        else if (grads)
-            hipLaunchKernelGGL((backward_wave_kernel<C, true, false>), dim3(grid), dim3(C::BT), 0, stream, dyp, xp, alpha,
-                               static_cast<T*>(nullptr), sums, N);
-        else
-            hipLaunchKernelGGL((backward_wave_kernel<C, false, true>), dim3(grid), dim3(C::BT), 0, stream, dyp,
-                               static_cast<const T*>(nullptr), alpha, static_cast<T*>(dx), sums, N);
-    } else if (grads && dx) {
-        if constexpr (C::kBwdTeams)
-            hipLaunchKernelGGL((backward_teams_kernel<C>), dim3(grid), dim3(3 * C::BT), 0, stream,
-                               static_cast<const T*>(dy), static_cast<const T*>(x), alpha, static_cast<T*>(dx),
-                               sums, N);
-        else
-            hipLaunchKernelGGL((backward_kernel<C, true, true>), dim3(grid), dim3(C::BT), 0, stream,
-                               static_cast<const T*>(dy), static_cast<const T*>(x), alpha, static_cast<T*>(dx),
-                               sums, N);
-    } else if (grads)
-        hipLaunchKernelGGL((backward_kernel<C, true, false>), dim3(grid), dim3(C::BT), 0, stream,
-                           static_cast<const T*>(dy), static_cast<const T*>(x), alpha, static_cast<T*>(nullptr),
-                           sums, N);
-    else
-        hipLaunchKernelGGL((backward_kernel<C, false, true>), dim3(grid), dim3(C::BT), 0, stream,
-                           static_cast<const T*>(dy), static_cast<const T*>(nullptr), alpha, static_cast<T*>(dx),
-                           sums, N);
+    auto launch = [&](auto kernel, int threads) {
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), 0, stream, static_cast<const T*>(dy), static_cast<const T*>(x),
+                           alpha, static_cast<T*>(dx), sums, N);
+    };
+    with_bool(write_through<C>(N, true, grads), [&](auto b) {
+        constexpr bool THROUGH = C::kTwelve ? C::kKeep : decltype(b)::value;
+        if constexpr (C::kWave) {
+            if (grads && dx) launch(backward_wave_kernel<C, true, true, THROUGH>, C::BT);
+            else if (!grads) launch(backward_wave_kernel<C, false, true, THROUGH>, C::BT);
+            else launch(backward_wave_kernel<C, true, false, false>, C::BT);
+        } else if (grads && dx) {
+            if constexpr (C::kBwdTeams) launch(backward_teams_kernel<C, THROUGH>, 3 * C::BT);
+            else launch(backward_kernel<C, true, true, THROUGH>, C::BT);
+        } else if (!grads) launch(backward_kernel<C, false, true, THROUGH>, C::BT);
+        else launch(backward_kernel<C, true, false, false>, C::BT);
+    });
     if (hipGetLastError() != hipSuccess) return WHT_ERR_LAUNCH;
     if (!grads || direct) return WHT_OK;
     constexpr int CG = reduce_columns(C::kRow);
@@ -173,24 +195,13 @@ static int launch_backward(const void* dy, const void* x, const float* alpha, vo
 template <class C>
 static size_t workspace_for(int64_t N) { return (size_t)grid_for<C>(N, true) * 2 * C::kRow * sizeof(float); }
 
-enum class Op { Forward, Backward, Workspace };
-
-struct Args {
-    const void* x; const void* dy; const void* resid; const float* alpha; const float* beta;
-    void* y; void* dx; float* dalpha; float* dbeta; float* sumsq;
-    int64_t N; void* workspace; hipStream_t stream;
-    size_t workspace_out;
-};
-
 // CF: configuration of the forward kernels, CB: of the backward kernels (and its workspace), CO: of
 // the forward kernel for few tokens.
 template <class CF, class CB = CF, class CO = CF>
 static int run(Op op, Args& a) {
     switch (op) {
     case Op::Forward:
-        if (few_tokens<CO>(a.N, a.resid != nullptr))
-            return launch_forward_once<CO>(a.x, a.alpha, a.beta, a.resid, a.y, a.sumsq, a.N, a.stream);
-        return launch_forward<CF>(a.x, a.alpha, a.beta, a.resid, a.y, a.sumsq, a.N, a.stream);
+        return forward<CF, CO>(a);
     case Op::Backward: return launch_backward<CB>(a.dy, a.x, a.alpha, a.dx, a.dalpha, a.dbeta, a.N,
                                                   a.workspace, a.stream);
     default:           a.workspace_out = workspace_for<CB>(a.N); return WHT_OK;
@@ -272,6 +283,9 @@ static int dispatch_d(int logd, Op op, Args& a) {
 //     8192 x 1536    19.8 / 22.7   22.5 / 22.9   (22.8, 23.9)        683 x 12288    25.3 / 31.1   26.4 / 31.4   (39.5, 41.6)
 //     2731 x 3072    16.9 / 18.3   19.7 / 18.7   (18.9, 20.3)        1365 x 12288   35.7 / 39.7   37.3 / 40.8   (56.1, 56.6)
 //     5461 x 3072    24.6 / 26.0   27.0 / 26.0   (28.3, 28.6)
+// y is streamed and dx written through only where x or dy is read with the default policy: written through, y and dx would
+// push x out of the Infinity Cache before the backward call reads it (a step of 43691 x 768, y / dx streamed or through: both
+// streamed 62.8, dx through 66.2, both through 73.6; 10923 x 768 26.5 and 25.7 with dx through).
 // So the default policy costs up to 5 % from memory at 768 and 3072 and gains more elsewhere; streamed, calls of 6144 and
 // 768 would be slower than before.  The power-of-two rows have always been streamed and lose by a change.
 // Backward, rows of 768, up to 512 tokens: workgroups of 128 threads (four tokens), so that twice as many share a call
@@ -290,9 +304,8 @@ static int run_twelve(Op op, Args& a) {
     const int64_t elems = a.N * TwelveCfg<M>::kRow, bytes = 2 * elems;
     if (op == Op::Forward) {
         if (elems <= (M <= 9 ? int64_t(3) << 20 : int64_t(1) << 23))
-            return launch_forward_once<TwelveCfg<M, false, 64>>(a.x, a.alpha, a.beta, a.resid, a.y, a.sumsq, a.N, a.stream);
-        if (bytes <= (int64_t(128) << 20))
-            return launch_forward<TwelveCfg<M, true>>(a.x, a.alpha, a.beta, a.resid, a.y, a.sumsq, a.N, a.stream);
+            return launch_forward_once<TwelveCfg<M, false, 64>, false, 1>(a.x, a.alpha, a.beta, a.resid, a.y, a.sumsq, a.N, a.stream);
+        if (bytes <= (int64_t(128) << 20)) return launch_forward<TwelveCfg<M, true>>(a.x, a.alpha, a.beta, a.resid, a.y, a.sumsq, a.N, a.stream);
         return launch_forward<TwelveCfg<M>>(a.x, a.alpha, a.beta, a.resid, a.y, a.sumsq, a.N, a.stream);
     }
     if (op == Op::Workspace) {

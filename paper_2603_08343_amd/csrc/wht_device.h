@@ -31,12 +31,25 @@ __device__ __forceinline__ void static_for(F&& f) {
     }
 }
 
-constexpr int kStreamPolicy = 2;   // cache-policy operand of a load: "nt" (read once, do not retain)
+// Cache-policy operands of loads and stores:
+//   kStreamPolicy   "nt": read or written once, retained nowhere;
+//   kThroughPolicy  "sc1" (device scope): a store passes through L2 at once instead of lying there dirty until the end of
+//                   the kernel writes it back, and stays in the Infinity Cache for the kernel that reads it.
+constexpr int kStreamPolicy = 2, kThroughPolicy = 16;
 
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
-// x, dy are read once and y, dx written once: stream them past the caches (non-temporal).
+// Stores through L2 go through a buffer resource: the compiler has no other 16-byte store with a device scope.  Its base is
+// the same for a wave, a lane's part of the address is 32 bits, and what lies past its end is dropped.
+typedef __amdgpu_buffer_rsrc_t rsrc_t;
+__device__ __forceinline__ rsrc_t make_rsrc(const void* base, unsigned bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, 0x00027000);
+}
+__device__ __forceinline__ void store16_through(rsrc_t to, unsigned offset, const uint4& q) {
+    const u32x4 v = {q.x, q.y, q.z, q.w};
+    __builtin_amdgcn_raw_buffer_store_b128(v, to, offset, 0, kThroughPolicy);
+}
 __device__ __forceinline__ void stream_store16(void* p, const uint4& q) {
     const u32x4 v = {q.x, q.y, q.z, q.w};
     __builtin_nontemporal_store(v, static_cast<u32x4*>(p));
@@ -767,22 +780,55 @@ __device__ __forceinline__ void unpack_all(float (&r)[C::E], const uint4 (&raw)[
     });
 }
 
-// STREAM: non-temporal stores.  Stores the vectors of the tokens that exist.
-template <class C, int PH, bool STREAM = true>
+// The rows that a wave stores: up to PER tokens from its first one on, none past the last token.
+template <class C>
+struct OutRows {
+    static constexpr int PER = C::TPT < 64 ? 64 / C::TPT : C::kPair;
+    static constexpr unsigned kRowBytes = C::kRow * (unsigned)sizeof(typename C::io::elem_t);
+    rsrc_t to;
+    unsigned lane_row;              // this lane's row from there, in elements
+    __device__ __forceinline__ OutRows(typename C::io::elem_t* tensor, int64_t grp, int64_t N, unsigned slot) {
+        const unsigned first_slot = __builtin_amdgcn_readfirstlane(slot);
+        const int64_t first = grp * C::G + first_slot * C::kPair, left = N - first;
+        to = make_rsrc(tensor + first * C::kRow, (left < 0 ? 0u : left < PER ? (unsigned)left : (unsigned)PER) * kRowBytes);
+        lane_row = C::TPT < 64 ? (slot - first_slot) * C::kRow : 0u;
+    }
+};
+
+// Registers in the layout of phase PH -> the rows of the tokens that exist, through L2 ...
+template <class C, int PH>
+__device__ __forceinline__ void global_put_through(const float (&r)[C::E], typename C::io::elem_t* tensor,
+                                                   unsigned slot, int64_t N, int64_t grp, const ThreadMap<C>& tm) {
+    const OutRows<C> rows(tensor, grp, N, slot);
+    static_for<0, C::NV>([&](auto c) {
+        constexpr int Cc = decltype(c)::value;
+        const unsigned at = rows.lane_row + vector_offset<C, PH, Cc>(tm, C::kRow);
+        store16_through(rows.to, at * (unsigned)sizeof(typename C::io::elem_t), C::io::pack(&r[Cc * C::V]));
+    });
+}
+// ... or with plain or (STREAM) non-temporal stores.
+template <class C, int PH, bool STREAM>
 __device__ __forceinline__ void global_put(const float (&r)[C::E], typename C::io::elem_t* tensor,
-                                           const Walker<C>& wk, int64_t grp, const ThreadMap<C>& tm) {
-    const int64_t tok = wk.token(grp);
+                                           unsigned slot, int64_t N, int64_t grp, const ThreadMap<C>& tm) {
+    const int64_t tok = grp * C::G + slot * C::kPair;
     typename C::io::elem_t* row = tensor + tok * C::kRow;
     static_for<0, C::NV>([&](auto c) {
         constexpr int Cc = decltype(c)::value;
-        bool active = C::G == 1 || tok < wk.N;
-        if constexpr (C::kPair == 2) active = tok + (Cc == 2 ? (tm.second ? 1 : 0) : Cc) < wk.N;
+        bool active = C::G == 1 || tok < N;
+        if constexpr (C::kPair == 2) active = tok + (Cc == 2 ? (tm.second ? 1 : 0) : Cc) < N;
         if (active) {
             typename C::io::elem_t* p = row + vector_offset<C, PH, Cc>(tm, C::kRow);
             if constexpr (STREAM) stream_store16(p, C::io::pack(&r[Cc * C::V]));
             else *reinterpret_cast<uint4*>(p) = C::io::pack(&r[Cc * C::V]);
         }
     });
+}
+// The persistent kernels' y and dx.
+template <class C, int PH, bool THROUGH>
+__device__ __forceinline__ void put_output(const float (&r)[C::E], typename C::io::elem_t* tensor, unsigned slot,
+                                           int64_t N, int64_t grp, const ThreadMap<C>& tm) {
+    if constexpr (THROUGH) global_put_through<C, PH>(r, tensor, slot, N, grp, tm);
+    else global_put<C, PH, true>(r, tensor, slot, N, grp, tm);
 }
 
 template <class C>
@@ -1096,16 +1142,12 @@ __device__ __forceinline__ void transform_back(float (&r)[C::E], float* lds, con
 // nothing where dx could be stored over that row meanwhile; its stores and its sums are left out.
 
 // Four sums of a partial row.  Every workgroup writes its row at the end of the kernel, and rows that lie
-// dirty in L2 are written back before the next kernel adds them up: rows of 2048 to 4096 columns are streamed
-// past the caches instead.  Graph replay, plain / streamed, us per call: 256 rows of 4096 columns 12.7 / 11.1,
-// of 2048 10.1 / 9.5, of 3072 10.8 / 10.2.  Fewer rows lose: 3 to 128 rows of 4096 columns 6.5..8.8 / 6.8..9.2,
-// of 2048 6.8..8.6 / 7.0..8.9; a single workgroup's row takes the same time either way (4.2 / 4.2).  Shorter
-// rows and rows of 8192 measured no gain.
-template <int ROW>
-__device__ __forceinline__ void put_sums(float* out, const float4& q) {
-    const u32x4 v = {__float_as_uint(q.x), __float_as_uint(q.y), __float_as_uint(q.z), __float_as_uint(q.w)};
-    if constexpr (ROW >= 2048 && ROW <= 4096) __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(out));
-    else *reinterpret_cast<u32x4*>(out) = v;
+// dirty in L2 are written back before the next kernel adds them up; written through L2 they are on their way at once and
+// wait in the Infinity Cache.  us per call under graph replay, before (plain stores, from 2048 to 4096 columns streamed) /
+// through: dalpha and dbeta of 8192 x 1024 12.3 / 11.4, backward of 2000 x 2048 11.4 / 10.8; over all widths the call for the
+// parameters alone gains 5 to 8 % from 1 to 16 MiB, the whole backward pass 1 to 3 %.
+__device__ __forceinline__ void put_sums(rsrc_t row, unsigned column, const float4& q) {
+    store16_through(row, column * 4u, make_uint4(__float_as_uint(q.x), __float_as_uint(q.y), __float_as_uint(q.z), __float_as_uint(q.w)));
 }
 
 __device__ __forceinline__ float4 add4(const float4& a, const float4& b) {
@@ -1118,8 +1160,9 @@ struct SumRows {
     float* dalpha;
     float* dbeta;
     int stride;                     // floats between the rows of consecutive workgroups
-    __device__ __forceinline__ float* row(int which) const {
-        return (which == 0 ? dalpha : dbeta) + (size_t)blockIdx.x * stride;
+    template <class C>
+    __device__ __forceinline__ rsrc_t row(int which) const {
+        return make_rsrc((which == 0 ? dalpha : dbeta) + (size_t)blockIdx.x * stride, C::kRow * 4u);
     }
 };
 
@@ -1186,7 +1229,7 @@ __device__ __forceinline__ void token_sumsq(const float (&r)[C::E], float* wave_
 // shuffles, and a token that spans several waves adds the wave sums through LDS in a fixed order
 // (one more workgroup barrier per token; the next write to that LDS array is behind the next
 // token's exchange barriers, so nothing else is needed).
-template <class C, bool RESID, bool STATS = false>
+template <class C, bool RESID, bool STATS, bool THROUGH>
 __global__ __launch_bounds__(C::BT) void forward_kernel(const typename C::io::elem_t* x,
                                                         const float* __restrict__ alpha,
                                                         const float* __restrict__ beta,
@@ -1255,7 +1298,7 @@ __global__ __launch_bounds__(C::BT) void forward_kernel(const typename C::io::el
         }
         if constexpr (STATS) token_sumsq<C>(r, wave_sums, sumsq, wk.token(grp), N, t, wk.slot, tm);
         if (more) wait_vmem<0>();
-        global_put<C, LAST>(r, y, wk, grp, tm);
+        put_output<C, LAST, THROUGH>(r, y, wk.slot, N, grp, tm);
     }
 }
 
@@ -1281,7 +1324,7 @@ __device__ __forceinline__ void pin(float* r) {
 }
 
 // forward for a few tokens (decoding, paper Sec. 5: one token per sequence and step): one token
-// group per workgroup and nothing else.  With so little work a launch is one memory round trip
+// group (R = 2: two) per workgroup and nothing else.  With so little work a launch is one memory round trip
 // long, so everything the group needs -- x, alpha, beta, the residual -- is requested at once,
 // straight into registers, before anything is awaited; there is no token loop, no prefetch stage and
 // no walk over the grid, whose set-up costs the persistent kernel about a microsecond per launch.
@@ -1316,8 +1359,26 @@ constexpr Requests requests_first(bool resid, bool stats) {
         return plain_resid || (C::n == 14 && resid) ? Requests::kInputs : Requests::kFree;
     }
 }
+// The same where the results are written through (1 MiB and more) by R token groups per workgroup; mean over 1.5 to 6 MiB (one
+// group) and 6 to 24 MiB (two) of the time before over the time with kFree / kX / kInputs / kAll: 1024 wide 0.98 0.98 0.97 1.07 and
+// 1.15 1.16 1.16 1.16; 2048 wide, residual, 0.98 0.98 1.10 1.06 and 1.06 1.05 1.02 0.99; 4096 1.09 1.08 1.08 1.00; 256 wide 1.05 1.10 1.10
+// 1.02; 3072 wide, two groups, 1.15 1.15 1.15 1.07, with the statistic 1.04 1.01 0.97 0.99.
+template <class C>
+constexpr Requests requests_first_through(bool resid, bool stats, int R) {
+    if constexpr (C::kTwelve) {
+        if (R == 2) return stats ? Requests::kFree : Requests::kX;
+        return C::m == 6 ? Requests::kAll : C::m == 10 && !resid ? Requests::kFree : Requests::kInputs;
+    } else if constexpr (C::kWave) {
+        if (C::v == 3) return resid && !stats ? Requests::kInputs : Requests::kX;
+        if (C::n == 11 && !resid) return Requests::kAll;
+        return C::n >= 11 && resid ? Requests::kInputs : Requests::kX;
+    } else {
+        if (C::n == 10 && (R == 1 || !resid)) return Requests::kAll;
+        return R == 1 && resid ? Requests::kInputs : Requests::kX;
+    }
+}
 
-template <class C, bool RESID, bool STATS = false>
+template <class C, bool RESID, bool STATS, bool THROUGH, int R>
 __global__ __launch_bounds__(C::BT) void forward_once_kernel(const typename C::io::elem_t* x,
                                                              const float* __restrict__ alpha,
                                                              const float* __restrict__ beta,
@@ -1330,14 +1391,17 @@ __global__ __launch_bounds__(C::BT) void forward_once_kernel(const typename C::i
     constexpr int LAST = C::P - 1;
     const unsigned t = threadIdx.x % C::TPT;
     const Walker<C> wk{N, (N + C::G - 1) / C::G, threadIdx.x / C::TPT};
-    const int64_t grp = blockIdx.x;
     ThreadMap<C> tm;
     tm.init(t, wk.slot);
-    uint4 raw[C::NV], rraw[RESID ? C::NV : 1];
-    constexpr Requests FIRST = requests_first<C>(RESID, STATS);
-    global_get<C, 0>(raw, x, wk, grp, tm);                      // a ragged group re-reads the last token
+    uint4 raw[R][C::NV], rraw[R][RESID ? C::NV : 1];
+    constexpr Requests FIRST = THROUGH ? requests_first_through<C>(RESID, STATS, R) : requests_first<C>(RESID, STATS);
+    auto group = [&](int i) { return (int64_t)blockIdx.x + (int64_t)i * gridDim.x; };
+#pragma unroll
+    for (int i = 0; i < R; ++i) global_get<C, 0>(raw[i], x, wk, group(i), tm);      // a ragged group re-reads the last token
     if constexpr (FIRST == Requests::kX) __builtin_amdgcn_sched_barrier(0);
-    if constexpr (RESID) global_get<C, LAST>(rraw, resid, wk, grp, tm);
+    if constexpr (RESID)
+#pragma unroll
+        for (int i = 0; i < R; ++i) global_get<C, LAST>(rraw[i], resid, wk, group(i), tm);
     if constexpr (FIRST == Requests::kInputs) __builtin_amdgcn_sched_barrier(0);
     float a[C::E], b[C::E];
     param_load<C>(a, alpha, tm);
@@ -1346,21 +1410,25 @@ __global__ __launch_bounds__(C::BT) void forward_once_kernel(const typename C::i
     else scale_alpha<C>(a, tm);
     RoundB<C> hb{};
     if constexpr (C::kMfma) hb = make_round_b<C>();
-    float r[C::E];
-    transform_from_raw<C, false>(r, raw, lds, tm, hb);
-    if constexpr (FIRST == Requests::kAll) scale_alpha<C>(a, tm);      // here, so that nothing before waits for alpha
-    if constexpr (RESID) {
-        float res[C::E];
-        unpack_all<C>(res, rraw);
+    static_for<0, R>([&](auto rr) {
+        constexpr int I = decltype(rr)::value;
+        float r[C::E];
+        transform_from_raw<C, I + 1 < R>(r, raw[I], lds, tm, hb);
+        if constexpr (FIRST == Requests::kAll && I == 0) scale_alpha<C>(a, tm);      // here, so that nothing before waits for alpha
+        if constexpr (RESID) {
+            float res[C::E];
+            unpack_all<C>(res, rraw[I]);
 #pragma unroll
-        for (int i = 0; i < C::E; ++i) r[i] = res[i] + fmaf(r[i], a[i], b[i]);
-    } else {
+            for (int i = 0; i < C::E; ++i) r[i] = res[i] + fmaf(r[i], a[i], b[i]);
+        } else {
 #pragma unroll
-        for (int i = 0; i < C::E; ++i) r[i] = fmaf(r[i], a[i], b[i]);
-    }
-    if constexpr (FIRST != Requests::kFree && C::G > 1) pin<C::E>(r);
-    if constexpr (STATS) token_sumsq<C>(r, wave_sums, sumsq, wk.token(grp), N, t, wk.slot, tm);
-    global_put<C, LAST, false>(r, y, wk, grp, tm);
+            for (int i = 0; i < C::E; ++i) r[i] = fmaf(r[i], a[i], b[i]);
+        }
+        if constexpr (!THROUGH && FIRST != Requests::kFree && C::G > 1) pin<C::E>(r);
+        if constexpr (STATS) token_sumsq<C>(r, wave_sums, sumsq, wk.token(group(I)), N, t, wk.slot, tm);
+        if constexpr (THROUGH) global_put_through<C, LAST>(r, y, wk.slot, N, group(I), tm);
+        else global_put<C, LAST, false>(r, y, wk.slot, N, group(I), tm);
+    });
 }
 
 // The sums of a workgroup's G token slots (in LDS, one region of kTokenWords floats each) added up, times
@@ -1369,7 +1437,7 @@ __global__ __launch_bounds__(C::BT) void forward_once_kernel(const typename C::i
 // flight).  Four columns against one, and 16-byte stores against 4-byte ones, at 32768 x 1536: 63.4 against
 // 68.7 us for the call.
 template <class C>
-__device__ __forceinline__ void add_token_slots(float* out, const float* slots, unsigned tid, float scale) {
+__device__ __forceinline__ void add_token_slots(rsrc_t out, const float* slots, unsigned tid, float scale) {
     constexpr int SLOTS = C::G / C::kPair, CHAINS = SLOTS < 8 ? SLOTS : 8;
     if constexpr (C::D >= 4 * C::BT || C::kTwelve) {
         // unrolled: the reads of one pass do not wait for the stores of the one before
@@ -1388,7 +1456,7 @@ __device__ __forceinline__ void add_token_slots(float* out, const float* slots, 
             for (int half = CHAINS / 2; half >= 1; half /= 2)
 #pragma unroll
                 for (int c = 0; c < half; ++c) acc[c] = add4(acc[c], acc[c + half]);
-            put_sums<C::kRow>(out + j, make_float4(acc[0].x * scale, acc[0].y * scale, acc[0].z * scale, acc[0].w * scale));
+            put_sums(out, j, make_float4(acc[0].x * scale, acc[0].y * scale, acc[0].z * scale, acc[0].w * scale));
         }
     } else {
         for (unsigned j = tid; j < (unsigned)C::D; j += C::BT) {
@@ -1402,7 +1470,7 @@ __device__ __forceinline__ void add_token_slots(float* out, const float* slots, 
             for (int half = CHAINS / 2; half >= 1; half /= 2)
 #pragma unroll
                 for (int c = 0; c < half; ++c) acc[c] += acc[c + half];
-            out[j] = acc[0] * scale;
+            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc[0] * scale), out, j * 4u, 0, kThroughPolicy);
         }
     }
 }
@@ -1435,10 +1503,10 @@ __device__ __forceinline__ void sums_to_slot(const float (&acc)[C::kSums], float
 
 // A thread's sums (last layout) times `scale` straight to the row, where the workgroup has one token.
 template <class C>
-__device__ __forceinline__ void put_thread_sums(const float (&acc)[C::E], float* out, float scale, const ThreadMap<C>& tm) {
+__device__ __forceinline__ void put_thread_sums(const float (&acc)[C::E], rsrc_t out, float scale, const ThreadMap<C>& tm) {
     static_for<0, C::E / 4>([&](auto i) {
         constexpr int I = decltype(i)::value * 4;
-        put_sums<C::kRow>(out + vector_offset<C, C::P - 1, I / C::V>(tm, 0u) + I % C::V,
+        put_sums(out, vector_offset<C, C::P - 1, I / C::V>(tm, 0u) + I % C::V,
                           make_float4(acc[I] * scale, acc[I + 1] * scale, acc[I + 2] * scale, acc[I + 3] * scale));
     });
 }
@@ -1465,7 +1533,7 @@ __device__ __forceinline__ void unsign_sums(float (&da)[C::kSums], const ThreadM
 // GRADS / DX select the outputs: without GRADS x is never read and no sums are kept (dx only, the
 // traffic of a forward pass); without DX nothing is transformed back or stored.  With only one of
 // the two, consecutive transforms run in the same order and need the trailing barrier again.
-template <class C, bool GRADS, bool DX>
+template <class C, bool GRADS, bool DX, bool THROUGH>
 __global__ __launch_bounds__(C::BT, C::kBwdWavesPerSimd) void backward_kernel(const typename C::io::elem_t* dy,
                                                          const typename C::io::elem_t* x,
                                                          const float* __restrict__ alpha,
@@ -1539,7 +1607,7 @@ __global__ __launch_bounds__(C::BT, C::kBwdWavesPerSimd) void backward_kernel(co
             for (int i = 0; i < C::E; ++i) g[i] *= a[i];
             transform_back<C, !BOTH>(g, lds, tm, hb);    // g = H_raw(alpha' dy), first layout
             if (more) wait_vmem<0>();
-            global_put<C, 0>(g, dx, wk, grp, tm);
+            put_output<C, 0, THROUGH>(g, dx, wk.slot, N, grp, tm);
         } else {
             if (more) wait_vmem<0>();
         }
@@ -1553,7 +1621,7 @@ __global__ __launch_bounds__(C::BT, C::kBwdWavesPerSimd) void backward_kernel(co
         __syncthreads();                          // the last exchange, or the first sums, have been read everywhere
         sums_to_slot<C>(which == 0 ? da : db, lds, tm);
         __syncthreads();
-        add_token_slots<C>(sums.row(which), lds, threadIdx.x, which == 0 ? s : 1.0f);
+        add_token_slots<C>(sums.row<C>(which), lds, threadIdx.x, which == 0 ? s : 1.0f);
     }
     }   // GRADS
 }
@@ -1651,7 +1719,7 @@ __device__ __forceinline__ void zero_stage(const unsigned char* wave_slot) {
 //   sums, and r <- alpha' dy (and its first stage) in place of the z that has been used;  issue dy(k+1);  transform back;
 //   wait for everything pending;  store dx(k).
 // Taking dy in pieces keeps one set of 2^e values live besides the sums and alpha'.
-template <class C, bool GRADS, bool DX>
+template <class C, bool GRADS, bool DX, bool THROUGH>
 __global__ __launch_bounds__(C::BT, C::kBwdWavesPerSimd)
 void backward_wave_kernel(const typename C::io::elem_t* dy, const typename C::io::elem_t* x,
                           const float* __restrict__ alpha, typename C::io::elem_t* dx,
@@ -1751,14 +1819,7 @@ void backward_wave_kernel(const typename C::io::elem_t* dy, const typename C::io
         if constexpr (C::w > 0 && GRADS != DX) exchange_barrier();
         if (more) wait_vmem<0>();
         if constexpr (DX) {
-            unsigned char* base = reinterpret_cast<unsigned char*>(dx + rows.base);
-            const unsigned off = (rows.rel + tm.first_elem) * (unsigned)sizeof(typename C::io::elem_t);
-            if (rows.active)
-                static_for<0, C::NV>([&](auto c) {
-                    constexpr int Cc = decltype(c)::value;
-                    constexpr unsigned elem = reg_elem_offset(C::plan.ph[0], C::e, Cc * C::V);
-                    stream_store16(base + elem * sizeof(typename C::io::elem_t) + off, C::io::pack(&r[Cc * C::V]));
-                });
+            put_output<C, 0, THROUGH>(r, dx, threadIdx.x / C::TPT, N, grp, tm);
         }
     }
     if constexpr (GRADS) {
@@ -1767,7 +1828,7 @@ void backward_wave_kernel(const typename C::io::elem_t* dy, const typename C::io
         const float s = inv_sqrt_d<C>();
 #pragma unroll
         for (int which = 0; which < 2; ++which) {
-            float* row = sums.row(which);
+            const rsrc_t row = sums.row<C>(which);
             if (which == 0) unsign_sums<C>(da, tm);
             if constexpr (C::G == 1) {                         // one token per workgroup: straight to the row
                 put_thread_sums<C>(which == 0 ? da : db, row, which == 0 ? s : 1.0f, tm);
@@ -1784,7 +1845,7 @@ void backward_wave_kernel(const typename C::io::elem_t* dy, const typename C::io
 // One team's per-thread sums (last layout) -> the workgroup's row out[kRow], times `scale`, through `slots`
 // (an idle region of G * kTokenWords floats): with one workgroup barrier, which every wave passes.
 template <class C>
-__device__ __forceinline__ void write_partial_row(const float (&acc)[C::E], float* slots, float* out,
+__device__ __forceinline__ void write_partial_row(const float (&acc)[C::E], float* slots, rsrc_t out,
                                                   float scale, unsigned tid, const ThreadMap<C>& tm) {
     sums_to_slot<C>(acc, slots, tm);
     __syncthreads();
@@ -1812,7 +1873,7 @@ __device__ __forceinline__ void write_partial_row(const float (&acc)[C::E], floa
 //   between B1(k) and B2(k), refilled with dy(k+2) after B2(k).
 // All teams run the same number of iterations, so they pass the same number of barriers.
 // dx(k) is stored after x(k) and dy(k) have been read in full, so dx may alias either exactly.
-template <class C>
+template <class C, bool THROUGH>
 __global__ __launch_bounds__(3 * C::BT) void backward_teams_kernel(const typename C::io::elem_t* dy,
                                                                    const typename C::io::elem_t* x,
                                                                    const float* __restrict__ alpha,
@@ -1874,7 +1935,7 @@ __global__ __launch_bounds__(3 * C::BT) void backward_teams_kernel(const typenam
             exchange_barrier();                                 // B2(k)
         }
         unsign_sums<C>(da, tm);
-        write_partial_row<C>(da, lds_x, sums.row(0), inv_sqrt_d<C>(), tid, tm);
+        write_partial_row<C>(da, lds_x, sums.row<C>(0), inv_sqrt_d<C>(), tid, tm);
     } else if (team == 1) {
         if (grp < wk.groups) stage_issue<C, LAST>(stage_g0, dy, wk, grp, tm);
         float a[C::E], db[C::E];
@@ -1902,7 +1963,7 @@ __global__ __launch_bounds__(3 * C::BT) void backward_teams_kernel(const typenam
             exchange_barrier();                                 // B2(k)
         }
         // the stage buffers are idle now
-        write_partial_row<C>(db, reinterpret_cast<float*>(stage_g_buf), sums.row(1), 1.0f, tid, tm);
+        write_partial_row<C>(db, reinterpret_cast<float*>(stage_g_buf), sums.row<C>(1), 1.0f, tid, tm);
     } else {
         const RoundB<C> hb = make_round_b<C>();
         int64_t prev = -1;                                      // token group whose Y data is in the exchange region
@@ -1913,7 +1974,7 @@ __global__ __launch_bounds__(3 * C::BT) void backward_teams_kernel(const typenam
         };
         auto second_half = [&](float (&g)[C::E], const Round1<C>& d1, int64_t grp_done) {
             mfma_round2<C>(g, d1, hb, tm);
-            global_put<C, 0>(g, dx, wk, grp_done, tm);
+            put_output<C, 0, THROUGH>(g, dx, wk.slot, N, grp_done, tm);
         };
         for (; grp < wk.groups; grp += step) {
             float g[C::E];
