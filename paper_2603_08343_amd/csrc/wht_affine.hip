@@ -61,23 +61,49 @@ static int forward_cluster(int64_t N, int grid, bool resid) {
     return grid;
 }
 
-// Few tokens (decoding, short prefills): one token group per workgroup and no token loop.  Measured
-// under HIP-graph replay, bfloat16: 2.1 against 3.2 us per call for one token of 4096 elements.  The
-// persistent kernel takes over where the two break even:
-//   matrix-core schedule: 2^24 elements per call at d = 1024 and 2048 (16384 tokens of 1024 elements:
-//     11.2 against 13.4 us), 2^22 above;
-//   wave schedule: bfloat16 2^24 (65536 tokens of 256 elements: 11.2 against 13.0 us), float32 2^23 up to
-//     d = 2048 (8192 tokens of 1024: 10.8 against 13.2) and 2^21 above (1024 tokens of 4096: 8.4 against
-//     7.6), 2^22 there with the residual add (600 tokens of 4096 with the statistic: 8.0 against 8.7).
-// Those are times on inputs that earlier calls left in the Infinity Cache; on inputs from memory the two break even
-// at the 2^24 and 2^23 (65601 tokens of 256: 14.3 against 13.7 us).  Rows of 12 * 2^m elements: run_twelve.
-// Both kernels do the same arithmetic on a token in the same order, so the switch is invisible in y
+// Forward calls by the size of x in bytes.  Few tokens (decoding, short prefills): one token group per workgroup and no
+// token loop (forward_once_kernel), with plain stores up to `through`, through L2 from there on, and from `pair` on with
+// two token groups per workgroup, both requested at once: alpha and beta, two to four times as many bytes as a thread's
+// part of x, are then read half as often.  From `limit` on the persistent kernel.
+// What each is worth, us per call under graph replay, three sets of inputs and two of outputs in turn / everything from memory:
+//   plain against through: 4097 x 1024 4.53 / 5.41 and 4.02 / 5.04, 1024 x 4096 4.68 / 5.66 and 3.74 / 4.75, 16385 x 256 4.36 / 5.46
+//     and 3.62 / 5.53; one token of 4096 with the statistic 2.65 and 2.77 (the kernel ends when memory, not L2, has the results);
+//   one group against two, 2048 wide: 1025 tokens 3.05 / 3.86 and 3.03 / 3.76, 4097 6.9 / 9.8 and 6.3 / 8.0; 8 MiB of 1536 wide
+//     7.0 / 7.7 and 5.6 / 6.3, of 12288 wide 10.6 / 11.4 and 7.9 / 8.8 (there the persistent kernel took over from 2^22 elements on);
+//     below, half the workgroups leave CUs idle: 1 MiB of 2048 wide 2.8 and 3.2;
+//   persistent against one pass: 32 MiB of 256 wide (bfloat16) 13.4 / 14.4 and 11.1 / 14.4, of 2048 13.1 / 15.3 and 11.4 / 18.0 (so 24 there), 8 MiB
+//     of 16384 9.9 / 10.8 and 6.0 / 8.6, 32 MiB of 1536 11.5 / 13.5 and 14.2 / 15.3.
+// Rows of 12 * 2^m elements have workgroups of one token (two of 768): workgroups of 256 threads, with up to eight tokens,
+// leave CUs without any, and from 257 of them on put two on one CU beside others with one (341 x 768 3.33 / 2.34, 1365 x
+// 1536 5.60 / 4.80, 683 x 3072 6.01 / 4.83).
+// The kernels do the same arithmetic on a token in the same order, so the switches are invisible in y
 // (the norm statistic is summed in the order of the launch shape: its last bits may differ).
+struct OnceSizes { int64_t through, pair, limit; };
 template <class C>
-static bool few_tokens(int64_t N, bool resid) {
-    constexpr int limit = C::kMfma ? (C::n <= 11 ? 24 : 22) : C::v == 3 ? 24 : (C::n <= 11 ? 23 : 21);
-    constexpr bool wide_f32 = C::kWave && C::v == 2 && C::n >= 12;
-    return N * C::kRow <= (int64_t(1) << (wide_f32 && resid ? limit + 1 : limit));
+constexpr OnceSizes once_sizes(bool resid, bool stats) {
+    constexpr int64_t MiB = 1 << 20, none = INT64_MAX;
+    const int64_t through = stats ? 5 * MiB / 2 : MiB;
+    if constexpr (C::kTwelve) {
+        switch (C::m) {
+        case 6:  return {through, resid ? 5 * MiB : 7 * MiB, 22 * MiB};
+        case 7:  return {resid ? 7 * MiB / 2 : 5 * MiB / 2, resid ? 7 * MiB / 2 : 5 * MiB / 2, resid ? 22 * MiB : 17 * MiB};
+        case 8:  return {through, stats ? 3 * MiB : 2 * MiB, resid ? 14 * MiB : 17 * MiB};
+        case 9:  return {resid ? 7 * MiB / 2 : MiB, 7 * MiB / 2, stats ? 7 * MiB : resid ? 12 * MiB : 17 * MiB};
+        default: return {4 * MiB, 7 * MiB, 34 * MiB};
+        }
+    } else if constexpr (C::kWave) {
+        const int64_t from = resid && C::v == 2 && C::n <= 10 ? 6 * MiB : through;
+        if (C::v == 3 || C::n <= 10) return {from, none, (resid ? 33 : 48) * MiB};
+        return {from, none, (C::n == 11 ? (resid ? 28 : 20) : C::n == 12 || resid ? 17 : 9) * MiB};
+    } else {
+        switch (C::n) {
+        case 10: return {through, resid ? none : 5 * MiB / 2, 24 * MiB};
+        case 11: return {through, stats ? 10 * MiB : resid ? 7 * MiB : 7 * MiB / 2, 24 * MiB};
+        case 12: return {through, resid ? 7 * MiB : 10 * MiB, (stats ? 9 : 17) * MiB};
+        case 13: return {through, none, (resid ? 7 : 13) * MiB};
+        default: return {4 * MiB, none, 24 * MiB};
+        }
+    }
 }
 
 // Whether the persistent forward kernels and the backward kernels write y and dx through L2 rather than streaming them
@@ -141,9 +167,15 @@ static int launch_forward(const void* x, const float* alpha, const float* beta, 
 
 template <class CF, class CO>
 static int forward(const Args& a) {
-    if (few_tokens<CO>(a.N, a.resid != nullptr))
-        return launch_forward_once<CO, false, 1>(a.x, a.alpha, a.beta, a.resid, a.y, a.sumsq, a.N, a.stream);
-    return launch_forward<CF>(a.x, a.alpha, a.beta, a.resid, a.y, a.sumsq, a.N, a.stream);
+    const int64_t bytes = a.N * CO::kRow * (int64_t)sizeof(typename CO::io::elem_t);
+    const OnceSizes at = once_sizes<CO>(a.resid != nullptr, a.sumsq != nullptr);
+    if (bytes >= at.limit) return launch_forward<CF>(a.x, a.alpha, a.beta, a.resid, a.y, a.sumsq, a.N, a.stream);
+    if constexpr (CO::kMfma && once_sizes<CO>(false, false).pair < INT64_MAX)
+        if (bytes >= at.pair)
+            return launch_forward_once<CO, true, 2>(a.x, a.alpha, a.beta, a.resid, a.y, a.sumsq, a.N, a.stream);
+    if (bytes >= at.through)
+        return launch_forward_once<CO, true, 1>(a.x, a.alpha, a.beta, a.resid, a.y, a.sumsq, a.N, a.stream);
+    return launch_forward_once<CO, false, 1>(a.x, a.alpha, a.beta, a.resid, a.y, a.sumsq, a.N, a.stream);
 }
 
 // A call of a few token groups runs on one workgroup, which writes dalpha and dbeta itself: no partial
@@ -261,14 +293,6 @@ static int dispatch_d(int logd, Op op, Args& a) {
 }
 
 // Rows of 12 * 2^m elements (bfloat16); logd = m + 4.
-// Few tokens: one pass, in workgroups of one token (two of 768), up to 3 * 2^20 elements (2^23 at m = 10), then the
-// persistent kernel.  Workgroups of 256 threads, with up to eight tokens, leave CUs without any, and from 257 of them
-// on put two on one CU beside others with one.  us per call under graph replay, 256 threads / one token per
-// workgroup, inputs that come back and inputs from memory: 341 x 768 3.33 / 2.34 and 3.95 / 2.97, 1365 x 768 3.56 / 3.14 and
-// 4.25 / 3.77, 1365 x 1536 5.60 / 4.80 and 6.31 / 5.50, 683 x 3072 6.01 / 4.83 and 6.76 / 5.70, 483 x 1536 with the statistic
-// 4.21 / 3.51 and 5.36 / 4.76.  One pass / persistent: 3863 x 768 5.47 / 5.36 and 6.01 / 6.38, 5461 x 768 6.70 / 6.01 and 7.14 /
-// 7.86, 965 x 3072 5.93 / 6.85, 1365 x 3072 8.01 / 7.59, 512 x 6144 5.9 / 6.6, 682 x 6144 7.9 / 7.3, 341 x 12288 9.6 / 12.3,
-// 682 x 12288 14.5 / 15.0.
 // Tensors of up to 128 MiB (32 MiB where the backward pass reads both) are read with the default cache policy, as
 // these rows always have been, larger ones streamed.  What has been read with the default policy stays in the
 // Infinity Cache: a backward call that follows its forward call finds x there, and a caller that comes back to the
@@ -303,10 +327,8 @@ template <int M>
 static int run_twelve(Op op, Args& a) {
     const int64_t elems = a.N * TwelveCfg<M>::kRow, bytes = 2 * elems;
     if (op == Op::Forward) {
-        if (elems <= (M <= 9 ? int64_t(3) << 20 : int64_t(1) << 23))
-            return launch_forward_once<TwelveCfg<M, false, 64>, false, 1>(a.x, a.alpha, a.beta, a.resid, a.y, a.sumsq, a.N, a.stream);
-        if (bytes <= (int64_t(128) << 20)) return launch_forward<TwelveCfg<M, true>>(a.x, a.alpha, a.beta, a.resid, a.y, a.sumsq, a.N, a.stream);
-        return launch_forward<TwelveCfg<M>>(a.x, a.alpha, a.beta, a.resid, a.y, a.sumsq, a.N, a.stream);
+        if (bytes <= (int64_t(128) << 20)) return forward<TwelveCfg<M, true>, TwelveCfg<M, false, 64>>(a);
+        return forward<TwelveCfg<M>, TwelveCfg<M, false, 64>>(a);
     }
     if (op == Op::Workspace) {
         a.workspace_out = workspace_for<TwelveCfg<M>>(a.N);
