@@ -135,7 +135,7 @@ _native_module = None
 
 class _NoNative:
     """Stands in for the extension module where it cannot be used: declines every call."""
-    forward = backward = staticmethod(lambda *args: None)
+    forward = backward = layer = staticmethod(lambda *args: None)
 
 
 def _load_native(torch, lib):
@@ -151,7 +151,8 @@ def _load_native(torch, lib):
         return _NoNative
     names = ("wht_affine_forward", "wht_affine_forward_residual", "wht_affine_forward_residual_stats",
              "wht_affine_backward_workspace_bytes", "wht_affine_backward", "wht_affine_backward_static")
-    _torch_marshal.bind(*(ctypes.cast(getattr(lib, n), ctypes.c_void_p).value for n in names), current_stream)
+    _torch_marshal.bind(*(ctypes.cast(getattr(lib, n), ctypes.c_void_p).value for n in names), current_stream,
+                        wht_affine_backward)
     return _torch_marshal
 
 

@@ -51,9 +51,10 @@ def _compile_marshal(verbose: bool) -> None:
     torch_dir = os.path.dirname(importlib.util.find_spec("torch").origin)
     lib_dir = os.path.join(torch_dir, "lib")
     cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
-           "-isystem", os.path.join(torch_dir, "include"), "-isystem", sysconfig.get_paths()["include"],
+           "-isystem", os.path.join(torch_dir, "include"),
+           "-isystem", os.path.join(torch_dir, "include", "torch", "csrc", "api", "include"), "-isystem", sysconfig.get_paths()["include"],
            f'-DWHT_TORCH_VERSION="{importlib.metadata.version("torch")}"',
-           "-o", MARSHAL_LIB, MARSHAL_SRC, "-L" + lib_dir, "-ltorch_python", "-ltorch_cpu", "-lc10"]
+           "-o", MARSHAL_LIB, MARSHAL_SRC, "-L" + lib_dir, "-ltorch_python", "-ltorch_hip", "-ltorch_cpu", "-lc10"]
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.run(cmd, check=True)
