@@ -178,16 +178,30 @@ static int forward(const Args& a) {
     return launch_forward_once<CO, false, 1>(a.x, a.alpha, a.beta, a.resid, a.y, a.sumsq, a.N, a.stream);
 }
 
-// A call of a few token groups runs on one workgroup, which writes dalpha and dbeta itself: no partial
-// rows and no second launch, which costs the stream 2.5 us and the host 3.3.  The groups then run one
-// after the other; up to here that is no slower (us per call under graph replay, two launches / one):
-// 3 groups at d = 256 6.0 / 5.7, at d = 1024 6.1 / 4.9, at float32 d = 1024 6.6 / 6.4; 2 groups at
-// d = 4096 7.6 / 6.5, at d = 8192 6.6 / 5.4; 1 at d = 16384 11.0 / 8.1 and at float32 d = 4096 7.7 / 5.2,
-// where 2 already are 11.1 / 12.3 and 7.7 / 8.3; 2 at d = 768 5.8 (3: 6.6 / 7.1), 1 at d = 12288 9.1 (2: 11.4 / 12.2).
+// Rows that backward_few_kernel does not take (shorter than 8 slices, float32 4): a call of up to three token groups runs on one
+// workgroup, which writes dalpha and dbeta itself: no partial rows and no second launch, which costs the stream
+// 2.5 us and the host 3.3.  The groups then run one after the other; up to here that is no slower (us per call under graph
+// replay, two launches / one: 3 groups at d = 256 6.0 / 5.7).
 template <class C>
-static bool one_workgroup(int64_t N) {
-    constexpr int most = C::kRow >= 12288 ? 1 : (C::kRow <= 1024 && !C::kTwelve ? 3 : (C::kMfma && C::P <= 2 ? 2 : 1));
-    return N <= (int64_t)most * C::G;
+static bool one_workgroup(int64_t N) { return N <= 3 * (int64_t)C::G; }
+
+// A call of few elements runs on backward_few_kernel: no partial rows and no second launch, which cost the stream 2.5 us and
+// the host 3.3, and a workgroup for every 64 columns where one_workgroup has a single one.  Rows must have 8 slices of 64
+// columns (float32: 4).  Its workgroups read x and dy while others write dx: where dx lies over one of them, dx is a launch of its own, and a call that
+// writes dalpha or dbeta over alpha stays on the other kernels.
+// us per call under graph replay, before / this kernel, backward: 1 x 512 3.8 / 2.2, 64 x 512 6.1 / 3.4, 64 x 1024 5.7 / 3.9 (91: 5.8 /
+// 5.9), 60 x 1536 7.5 / 4.6 (85: 7.6 / 7.1), 16 x 4096 6.3 / 3.1, 32 6.3 / 4.3 (45: 6.4 / 5.5, from memory 6.9 / 7.2), 16 x 8192 6.7 / 4.4 (23: 6.8 / 5.3,
+// from memory 7.2 / 6.8), 12 x 16384 12.0 / 9.4 (16: 12.1 / 10.5), 64 x 768 6.5 / 3.9 (121: 6.5 / 6.0), 16 x 12288 12.2 / 5.8; float32
+// 64 x 512 6.3 / 3.7 (128: 6.4 / 5.6), 64 x 1024 6.1 / 4.5, 32 x 2048 8.0 / 4.0 (64: 8.0 / 6.1), 12 x 8192 8.9 / 5.1 (16: 9.0 / 6.0).
+template <class C>
+constexpr bool has_few_backward() {
+    if (C::kTwelve) return C::kKeep && (C::kRow > 768 || C::BT == 128);         // what calls of so few elements run on
+    return C::kRow % 64 == 0 && C::kRow / 64 >= 16 / (int)sizeof(typename C::io::elem_t);
+}
+template <class C>
+constexpr int64_t few_backward_elements() {
+    if (sizeof(typename C::io::elem_t) == 4) return C::kRow <= 512 ? 3 << 14 : C::kRow == 1024 ? 1 << 16 : 3 << 15;
+    return C::kRow <= 1024 ? 1 << 16 : C::kRow < 2048 ? 3 << 15 : C::kRow < 12288 ? 1 << 17 : 3 << 16;
 }
 
 template <class C>
@@ -195,7 +209,16 @@ static int launch_backward(const void* dy, const void* x, const float* alpha, vo
                            float* dbeta, int64_t N, void* workspace, hipStream_t stream) {
     using T = typename C::io::elem_t;
     const bool grads = dalpha != nullptr;
-    const bool direct = grads && one_workgroup<C>(N);
+    if constexpr (has_few_backward<C>())
+        if (grads && N * C::kRow <= few_backward_elements<C>() && dalpha != alpha && dbeta != alpha) {
+            const bool apart = dx && (dx == dy || dx == x);
+            const int64_t groups = dx && !apart ? (N + C::G - 1) / C::G : 0;
+            hipLaunchKernelGGL(backward_few_kernel<C>, dim3((unsigned)(FewSlices<C>::A + groups)), dim3(kFewThreads), 0, stream,
+                               static_cast<const T*>(dy), static_cast<const T*>(x), alpha, static_cast<T*>(dx), dalpha, dbeta, N);
+            if (hipGetLastError() != hipSuccess) return WHT_ERR_LAUNCH;
+            return apart ? launch_backward<C>(dy, nullptr, alpha, dx, nullptr, nullptr, N, nullptr, stream) : WHT_OK;
+        }
+    const bool direct = !has_few_backward<C>() && grads && one_workgroup<C>(N);
     const int grid = direct ? 1 : grid_for<C>(N, grads);      // dx alone streams like a forward pass
     float* ws = static_cast<float*>(workspace);
     const SumRows sums = direct ? SumRows{dalpha, dbeta, 0} : SumRows{ws, ws + C::kRow, 2 * C::kRow};
@@ -313,15 +336,10 @@ static int dispatch_d(int logd, Op op, Args& a) {
 // So the default policy costs up to 5 % from memory at 768 and 3072 and gains more elsewhere; streamed, calls of 6144 and
 // 768 would be slower than before.  The power-of-two rows have always been streamed and lose by a change.
 // Backward, rows of 768, up to 512 tokens: workgroups of 128 threads (four tokens), so that twice as many share a call
-// that has few -- unless two passes of one workgroup of 256 threads do for it, which saves the second launch.  us per call
-// under graph replay, 256 / 128 threads, inputs that come back: 1 token 4.21 / 3.92, 8 4.58 / 5.34, 16 5.86 / 6.19, 17 6.74 /
-// 6.23, 64 6.77 / 6.24, 341 7.00 / 6.63, 512 7.09 / 6.99, 683 7.26 / 7.31, 1365 8.22 / 9.87; dx alone 64 3.26 / 2.84, 512 3.33 / 2.95,
-// 1365 3.51 / 3.77.
+// that has few.  us per call under graph replay, 256 / 128 threads, inputs that come back: 341 7.00 / 6.63, 512 7.09 / 6.99, 683 7.26 /
+// 7.31, 1365 8.22 / 9.87; dx alone 64 3.26 / 2.84, 512 3.33 / 2.95, 1365 3.51 / 3.77.
 constexpr int64_t kSmallBackwardTokens = 512;
 using SmallBackwardCfg = TwelveCfg<6, true, 128>;
-static bool small_backward(int64_t N, bool grads) {
-    return N <= kSmallBackwardTokens && (!grads || N <= SmallBackwardCfg::G || !one_workgroup<TwelveCfg<6>>(N));
-}
 
 template <int M>
 static int run_twelve(Op op, Args& a) {
@@ -333,14 +351,14 @@ static int run_twelve(Op op, Args& a) {
     if (op == Op::Workspace) {
         a.workspace_out = workspace_for<TwelveCfg<M>>(a.N);
         if constexpr (M == 6)
-            if (!one_workgroup<TwelveCfg<M>>(a.N)) {        // what suffices for N tokens suffices for fewer
+            if (a.N > 2 * TwelveCfg<M>::G) {                // what suffices for N tokens suffices for fewer
                 const size_t small = workspace_for<SmallBackwardCfg>(a.N < kSmallBackwardTokens ? a.N : kSmallBackwardTokens);
                 if (a.workspace_out < small) a.workspace_out = small;
             }
         return WHT_OK;
     }
     if constexpr (M == 6)
-        if (small_backward(a.N, a.dalpha != nullptr))
+        if (a.N <= kSmallBackwardTokens)
             return launch_backward<SmallBackwardCfg>(a.dy, a.x, a.alpha, a.dx, a.dalpha, a.dbeta, a.N, a.workspace, a.stream);
     if (bytes <= (int64_t(a.dalpha ? 32 : 128) << 20))             // dx alone reads dy only
         return launch_backward<TwelveCfg<M, true>>(a.dy, a.x, a.alpha, a.dx, a.dalpha, a.dbeta, a.N, a.workspace, a.stream);

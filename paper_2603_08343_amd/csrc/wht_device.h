@@ -1703,6 +1703,21 @@ __device__ __forceinline__ void zero_stage(const unsigned char* wave_slot) {
         asm volatile("ds_write_b128 %0, %1 offset:%2" : : "v"(addr), "v"(zero), "n"(c * 1024) : "memory");
 }
 
+// alpha' dy and the first stage back in one, on COUNT of a thread's values: a product and two multiply-adds per pair.
+template <class C, int COUNT>
+__device__ __forceinline__ void first_stage_back(float* r, const float* g, const float* a) {
+    constexpr int Q = wave_first_back_reg<C>();
+    static_assert((2 << Q) <= COUNT, "a pair lies in one piece");
+#pragma unroll
+    for (int i = 0; i < COUNT; ++i)
+        if (!((i >> Q) & 1)) {
+            const int j = i | (1 << Q);
+            const float p = g[j] * a[j], q = g[i];
+            r[i] = fmaf(q, a[i], p);
+            r[j] = fmaf(q, a[i], -p);
+        }
+}
+
 // backward of the wave schedule, which took the place of butterflies re-dealt two or three times through
 // LDS per transform (two one-word passes at d = 256; one wave per SIMD waiting on conflicting LDS accesses
 // at float32 d = 4096).  Bound by memory (vector issue 41 and 39 % of the SIMD cycles, no bank conflict in
@@ -1796,16 +1811,7 @@ void backward_wave_kernel(const typename C::io::elem_t* dy, const typename C::io
                 pin<COUNT>(db + B);
             }
             if constexpr (DX) {
-                // alpha' dy and the first stage in one: a product and two multiply-adds per pair
-                static_assert((2 << Q) <= COUNT, "a pair lies in one piece");
-#pragma unroll
-                for (int i = 0; i < COUNT; ++i)
-                    if (!((i >> Q) & 1)) {
-                        const int j = i | (1 << Q);
-                        const float p = g[j] * a[B + j];
-                        r[B + i] = fmaf(g[i], a[B + i], p);
-                        r[B + j] = fmaf(g[i], a[B + i], -p);
-                    }
+                first_stage_back<C, COUNT>(r + B, g, a + B);
                 pin<COUNT>(r + B);
             }
         });
@@ -1993,6 +1999,184 @@ __global__ __launch_bounds__(3 * C::BT) void backward_teams_kernel(const typenam
             second_half(g, d1, prev);
         }
     }
+}
+
+// ------------------------------------------------------------------------------------------------
+// backward for a few tokens: one launch, no partial rows
+//
+// dalpha and dbeta are sums over all tokens, so the other kernels end in rows of partial sums and a second launch.
+// Here a workgroup has 64 columns instead (a "slice") and takes every token: of z it needs the 64 values of its slice,
+//     z[64 j + lo] = H_64 along lo of  sum over k of +-x[64 k + lo],   the sign that of row j, column k of H_raw's upper factor,
+// one multiply-add per element of x and 64-point butterflies, and nothing of what other workgroups compute.  Every such
+// workgroup reads all of x; that is the price, and why this is for calls of few elements.  Further workgroups make dx,
+// one token group each.
+// A wave takes every 16th token.  Its lanes hold 16-byte vectors of V elements, 64 / V lanes to the 64 columns of one k
+// and V consecutive k to a load; the V k's sums of each column are then brought together, half of the values at a time, by
+// lane swaps, which leaves one column per lane.
+// Bound by vector issue: 18 instructions per load (8 values: widen, multiply-add, sign) and about 36 per token behind them,
+// on the 16 waves of one CU, 1.1 to 2 us per 2^15 to 2^16 elements; 64 columns because a line of dy has them.  The table at
+// few_backward_elements (wht_affine.hip) has the times.
+constexpr int kFewThreads = 1024, kFewWaves = kFewThreads / 64;
+
+template <class C>
+struct FewSlices {
+    static constexpr int V = 16 / (int)sizeof(typename C::io::elem_t), LANES = 64 / V;
+    static constexpr int A = C::kRow / 64;                          // slices, and values of k
+    static constexpr int LOADS = (A + V - 1) / V;
+    static constexpr int TOKENS = LOADS >= 8 ? 1 : LOADS >= 4 ? 2 : 4, CHUNK = LOADS < 8 ? LOADS : LOADS % 8 == 0 ? 8 : 6;
+    static_assert(C::kRow % 64 == 0 && A >= V && LOADS <= 32 && LOADS % CHUNK == 0, "a load is V values of k, one sign bit each");
+    // whether row j, column k of the upper factor is -1
+    static __device__ __forceinline__ unsigned minus(unsigned j, unsigned k) {
+        if constexpr (C::kTwelve) {
+            constexpr unsigned mid = C::m - 6;
+            return ((paley12_minus_row(j >> mid) >> (k >> mid)) ^ __popc(j & k & ((1u << mid) - 1u))) & 1u;
+        } else return __popc(j & k) & 1u;
+    }
+};
+
+// z <- its 64-point transform across the lanes of the wave.
+__device__ __forceinline__ float lanes_transform(float z, unsigned lane) {
+    auto dpp = [](float v, auto ctrl) {
+        return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), decltype(ctrl)::value, 0xf, 0xf, false));
+    };
+    auto stage = [&](float partner, unsigned bit) { z = fmaf(z, lane & bit ? -1.0f : 1.0f, partner); };
+    stage(dpp(z, std::integral_constant<int, 0xB1>{}), 1u);                                     // quad_perm [1,0,3,2]
+    stage(dpp(z, std::integral_constant<int, 0x4E>{}), 2u);                                     // quad_perm [2,3,0,1]
+    stage(dpp(dpp(z, std::integral_constant<int, 0x141>{}), std::integral_constant<int, 0x1B>{}), 4u);     // l ^ 7, then ^ 3
+    stage(dpp(z, std::integral_constant<int, 0x128>{}), 8u);                                    // row_ror:8
+    const auto s16 = __builtin_amdgcn_permlane16_swap(__float_as_uint(z), __float_as_uint(z), false, false);
+    z = fmaf(__uint_as_float(s16[1]), lane & 16u ? -1.0f : 1.0f, __uint_as_float(s16[0]));
+    const auto s32 = __builtin_amdgcn_permlane32_swap(__float_as_uint(z), __float_as_uint(z), false, false);
+    return fmaf(__uint_as_float(s32[1]), lane & 32u ? -1.0f : 1.0f, __uint_as_float(s32[0]));
+}
+
+// dalpha and dbeta of slice j.
+template <class C>
+__device__ __forceinline__ void few_sums(const typename C::io::elem_t* dy, const typename C::io::elem_t* x, float* dalpha,
+                                         float* dbeta, int64_t N, unsigned j) {
+    using F = FewSlices<C>;
+    using T = typename C::io::elem_t;
+    __shared__ float part[2][kFewWaves][64];
+    const unsigned wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63u;
+    const unsigned group = lane / F::LANES;
+    uint32_t minus = 0;
+#pragma unroll
+    for (int l = 0; l < F::LOADS; ++l) minus |= F::minus(j, l * F::V + group) << l;
+    // the column that ends up in this lane
+    const unsigned value = F::V == 8 ? ((lane >> 5) << 2) | (((lane >> 4) & 1u) << 1) | ((lane >> 3) & 1u)
+                                     : ((lane >> 5) << 1) | ((lane >> 4) & 1u);
+    const unsigned column = 64u * j + (lane % F::LANES) * F::V + value;
+    float da = 0.0f, db = 0.0f;
+    for (int64_t n = wave; n < N; n += kFewWaves * F::TOKENS) {
+        float acc[F::TOKENS][F::V], g[F::TOKENS];
+#pragma unroll
+        for (int u = 0; u < F::TOKENS; ++u) {
+            const int64_t tok = n + u * kFewWaves, row = (tok < N ? tok : N - 1) * C::kRow;
+            if constexpr (sizeof(T) == 2) g[u] = __uint_as_float((uint32_t)dy[row + column] << 16);
+            else g[u] = dy[row + column];
+#pragma unroll
+            for (int i = 0; i < F::V; ++i) acc[u][i] = 0.0f;
+        }
+#pragma unroll 1
+        for (int l0 = 0; l0 < F::LOADS; l0 += F::CHUNK) {
+            uint4 raw[F::TOKENS][F::CHUNK];
+#pragma unroll
+            for (int u = 0; u < F::TOKENS; ++u) {
+                const int64_t tok = n + u * kFewWaves;
+                const T* row = x + (tok < N ? tok : N - 1) * C::kRow;
+#pragma unroll
+                for (int l = 0; l < F::CHUNK; ++l) {
+                    const unsigned at = ((l0 + l) * 64u + lane) * F::V;
+                    // rows of 768: the second half of the last load lies past the row
+                    raw[u][l] = F::A % F::V == 0 || at < (unsigned)C::kRow ? *reinterpret_cast<const uint4*>(row + at) : make_uint4(0u, 0u, 0u, 0u);
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < F::TOKENS; ++u)
+#pragma unroll
+                for (int l = 0; l < F::CHUNK; ++l) {
+                    float v[F::V];
+                    C::io::unpack(raw[u][l], v);
+                    const float s = __uint_as_float(0x3F800000u | ((minus >> (l0 + l)) << 31));
+#pragma unroll
+                    for (int i = 0; i < F::V; ++i) acc[u][i] = fmaf(v[i], s, acc[u][i]);
+                }
+        }
+#pragma unroll
+        for (int u = 0; u < F::TOKENS; ++u) {
+            float (&r)[F::V] = acc[u];
+#pragma unroll
+            for (int i = 0; i < F::V / 2; ++i) {
+                const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(r[i]), __float_as_uint(r[i + F::V / 2]), false, false);
+                r[i] = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
+            }
+#pragma unroll
+            for (int i = 0; i < F::V / 4; ++i) {
+                const auto sw = __builtin_amdgcn_permlane16_swap(__float_as_uint(r[i]), __float_as_uint(r[i + F::V / 4]), false, false);
+                r[i] = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
+            }
+            if constexpr (F::V == 8) {
+                const bool upper = (lane & 8u) != 0u;
+                const float keep = upper ? r[1] : r[0], send = upper ? r[0] : r[1];
+                r[0] = keep + __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(send), 0x128, 0xf, 0xf, false));   // row_ror:8
+            }
+            const float z = lanes_transform(r[0], lane);
+            if (n + u * kFewWaves < N) {
+                da = fmaf(g[u], z, da);
+                db += g[u];
+            }
+        }
+    }
+    part[0][wave][lane] = da;
+    part[1][wave][lane] = db;
+    __syncthreads();
+    if (wave < 2) {
+        float s[kFewWaves];
+#pragma unroll
+        for (int w = 0; w < kFewWaves; ++w) s[w] = part[wave][w][lane];
+#pragma unroll
+        for (int half = kFewWaves / 2; half >= 1; half /= 2)
+#pragma unroll
+            for (int w = 0; w < half; ++w) s[w] += s[w + half];
+        if (wave == 0) dalpha[column] = s[0] * inv_sqrt_d<C>();
+        else dbeta[column] = s[0];
+    }
+}
+
+// dx of token group grp, by the first C::BT threads: the arithmetic of the other backward kernels.
+template <class C>
+__device__ __forceinline__ void few_dx(const typename C::io::elem_t* dy, const float* __restrict__ alpha, typename C::io::elem_t* dx,
+                                       int64_t N, int64_t grp) {
+    __shared__ __align__(16) float lds[C::kExchangeBytes / 4];
+    constexpr int LAST = C::P - 1;
+    if (threadIdx.x >= C::BT) return;               // whole waves; a barrier counts the waves that are left
+    const Walker<C> wk{N, (N + C::G - 1) / C::G, threadIdx.x / C::TPT};
+    ThreadMap<C> tm;
+    tm.init(threadIdx.x % C::TPT, wk.slot);
+    uint4 graw[C::NV];
+    global_get<C, LAST>(graw, dy, wk, grp, tm);     // a ragged group re-reads the last token
+    float a[C::E], r[C::E];
+    alpha_get<C>(a, alpha, tm);
+    unpack_all<C>(r, graw);
+    if constexpr (C::kMfma) {
+        const RoundB<C> hb = make_round_b<C>();
+#pragma unroll
+        for (int i = 0; i < C::E; ++i) r[i] *= a[i];
+        transform_back<C>(r, lds, tm, hb);
+    } else {
+        first_stage_back<C, C::E>(r, r, a);
+        wave_transform<C, false, wave_first_back_bit<C>()>(r, lds, tm);
+    }
+    global_put<C, 0, false>(r, dx, wk.slot, N, grp, tm);
+}
+
+// Workgroups 0 .. slices - 1: dalpha and dbeta; the others, where dx is wanted: its token groups.  dx must not lie over x or dy.
+template <class C>
+__global__ __launch_bounds__(kFewThreads) void backward_few_kernel(const typename C::io::elem_t* dy, const typename C::io::elem_t* x,
+                                                                   const float* __restrict__ alpha, typename C::io::elem_t* dx,
+                                                                   float* dalpha, float* dbeta, int64_t N) {
+    if (blockIdx.x < (unsigned)FewSlices<C>::A) few_sums<C>(dy, x, dalpha, dbeta, N, blockIdx.x);
+    else few_dx<C>(dy, alpha, dx, N, blockIdx.x - FewSlices<C>::A);
 }
 
 // out[which][j] = sum over rows of partials[row][which][j].  Workgroup = CG float4 columns x

@@ -1,0 +1,86 @@
+"""The backward pass of a few tokens in one launch (backward_few_kernel): a slice of 64 columns per workgroup for dalpha and
+dbeta, a wave for every 16th token, up to four tokens of a wave at a time.  Every output against the oracle at token
+counts around those steps and on both sides of the size up to which the kernel runs; dx bit for bit what the other
+kernels give (alone, and in the place of dy or x, where the call takes them)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2603_08343_amd as wht
+from paper_2603_08343_amd import synth
+from parity import assert_grad_close, assert_io_close, nan_filled, to_gpu
+
+pytestmark = pytest.mark.gpu
+
+LIMITS = {("bf16", 512): 1 << 16, ("bf16", 1024): 1 << 16, ("bf16", 2048): 1 << 17, ("bf16", 4096): 1 << 17, ("bf16", 8192): 1 << 17,
+          ("bf16", 16384): 3 << 16, ("bf16", 768): 1 << 16, ("bf16", 1536): 3 << 15, ("bf16", 3072): 1 << 17, ("bf16", 6144): 1 << 17,
+          ("bf16", 12288): 3 << 16, ("f32", 256): 3 << 14, ("f32", 512): 3 << 14, ("f32", 1024): 1 << 16, ("f32", 2048): 3 << 15,
+          ("f32", 4096): 3 << 15, ("f32", 8192): 3 << 15}
+
+
+@pytest.mark.parametrize("dtype,d", list(LIMITS))
+def test_every_output_around_the_steps_and_the_limit(dtype, d):
+    top = LIMITS[dtype, d] // d
+    for N in sorted({1, 2, 3, 16, 17, 31, 33, 64, 65, top - 1, top, top + 1} & set(range(1, top + 2))):
+        print(f"[few] d={d} {dtype} N={N}", flush=True)
+        inp = synth.make_inputs(N, d, dtype, seed=d + N)
+        x, dy = to_gpu(inp.x, dtype), to_gpu(inp.dy, dtype)
+        a = torch.from_numpy(inp.alpha).cuda()
+        buf = nan_filled(N + 1, d, dtype)
+        dx, da, db = wht.wht_affine_backward(dy, x, a, dx=buf[:N])
+        again = wht.wht_affine_backward(dy, x, a)
+        only_dx = wht.wht_affine_backward(dy, None, a, want_param_grads=False)[0]
+        only = wht.wht_affine_backward(dy, x, a, want_dx=False)[1:]
+        onto_dy, onto_x = dy.clone(), x.clone()
+        in_place = wht.wht_affine_backward(onto_dy, x, a, dx=onto_dy), wht.wht_affine_backward(dy, onto_x, a, dx=onto_x)
+        torch.cuda.synchronize()
+        rdx, rda, rdb = oracle.backward(inp.dy, inp.x, inp.alpha, "fast")
+        assert_io_close(dx, rdx, dtype, "dx")
+        for ga, gb in ((da, db), in_place[0][1:], in_place[1][1:]):
+            assert_grad_close(ga, rda, "dalpha")
+            assert_grad_close(gb, rdb, "dbeta")
+        assert bool(torch.isnan(buf[N].float()).all())
+        assert all(torch.equal(p, q) for p, q in zip((dx, da, db), again))
+        assert torch.equal(only[0], da) and torch.equal(only[1], db)
+        assert all(torch.equal(dx, t) for t in (only_dx, onto_dy, onto_x))
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 512), ("bf16", 768), ("bf16", 4096), ("bf16", 6144), ("f32", 256), ("f32", 8192)])
+def test_one_hot_rows_reach_every_column(dtype, d):
+    """x one-hot at column k: z = +-1/sqrt(d), so dalpha is that row of H times dy; one token at a time and all at once."""
+    N = min(LIMITS[dtype, d] // d, 48)
+    print(f"[few] one-hot d={d} {dtype} N={N}", flush=True)
+    rng = np.random.RandomState(d)
+    at = np.concatenate(([0, 1, 63, 64, d - 1], rng.randint(0, d, N)))[:N]
+    x = torch.zeros(N, d, dtype=torch.bfloat16 if dtype == "bf16" else torch.float32, device="cuda")
+    x[torch.arange(N), torch.from_numpy(at).cuda()] = 1.0
+    dy = torch.ones_like(x)
+    a, zero = torch.ones(d, device="cuda"), torch.zeros(d, device="cuda")
+    rows = wht.wht_affine_forward(x.float() if dtype == "f32" else x, a, zero).double()          # +-1/sqrt(d), rounded
+    da, db = wht.wht_affine_backward(dy, x, a)[1:]
+    signs = torch.sign(rows).sum(0)                                                              # exact
+    assert torch.equal(torch.round(da.double() * d ** 0.5), signs) and torch.equal(db, torch.full_like(db, float(N)))
+
+
+@pytest.mark.parametrize("value", [float("inf"), float("nan")])
+@pytest.mark.parametrize("dtype,d", [("bf16", 512), ("bf16", 768), ("bf16", 8192), ("f32", 1024)])
+def test_non_finite_values_stay_where_they_belong(dtype, d, value):
+    N = 11
+    print(f"[few] non-finite d={d} {dtype} {value}", flush=True)
+    inp = synth.make_inputs(N, d, dtype, seed=d)
+    x, dy = to_gpu(inp.x, dtype), to_gpu(inp.dy, dtype)
+    a = torch.from_numpy(inp.alpha).cuda()
+    _, rda, rdb = oracle.backward(inp.dy, inp.x, inp.alpha, "fast")
+    bad_x = x.clone()
+    bad_x[10, 3] = value                                       # every z of the row, so every dalpha; no dbeta
+    dx, da, db = wht.wht_affine_backward(dy, bad_x, a)
+    assert not bool(torch.isfinite(da).any()) and bool(torch.isfinite(dx.float()).all())
+    assert_grad_close(db, rdb, "dbeta")
+    bad_dy = dy.clone()
+    bad_dy[10, 3] = value                                      # one column of the sums, one row of dx
+    dx, da, db = wht.wht_affine_backward(bad_dy, x, a)
+    keep = torch.arange(d, device="cuda") != 3
+    assert not bool(torch.isfinite(da[3])) and not bool(torch.isfinite(db[3]))
+    assert bool(torch.isfinite(da[keep]).all()) and bool(torch.isfinite(db[keep]).all())
+    assert not bool(torch.isfinite(dx[10].float()).any()) and bool(torch.isfinite(dx[:10].float()).all())
