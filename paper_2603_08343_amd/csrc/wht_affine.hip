@@ -357,9 +357,13 @@ static int run_twelve(Op op, Args& a) {
             }
         return WHT_OK;
     }
-    if constexpr (M == 6)
-        if (a.N <= kSmallBackwardTokens)
+    if constexpr (M == 6) {
+        // Up to two token groups of 256 threads the workspace has a row for each of those and none for groups of four tokens:
+        // a call that backward_few_kernel declines there runs on one workgroup of 256 threads, without partial rows.
+        const bool over_alpha = a.dalpha && (a.dalpha == a.alpha || a.dbeta == a.alpha);
+        if (a.N <= kSmallBackwardTokens && !(over_alpha && a.N <= 2 * TwelveCfg<M>::G))
             return launch_backward<SmallBackwardCfg>(a.dy, a.x, a.alpha, a.dx, a.dalpha, a.dbeta, a.N, a.workspace, a.stream);
+    }
     if (bytes <= (int64_t(a.dalpha ? 32 : 128) << 20))             // dx alone reads dy only
         return launch_backward<TwelveCfg<M, true>>(a.dy, a.x, a.alpha, a.dx, a.dalpha, a.dbeta, a.N, a.workspace, a.stream);
     return launch_backward<TwelveCfg<M>>(a.dy, a.x, a.alpha, a.dx, a.dalpha, a.dbeta, a.N, a.workspace, a.stream);

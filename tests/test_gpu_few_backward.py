@@ -84,3 +84,24 @@ def test_non_finite_values_stay_where_they_belong(dtype, d, value):
     assert not bool(torch.isfinite(da[3])) and not bool(torch.isfinite(db[3]))
     assert bool(torch.isfinite(da[keep]).all()) and bool(torch.isfinite(db[keep]).all())
     assert not bool(torch.isfinite(dx[10].float()).any()) and bool(torch.isfinite(dx[:10].float()).all())
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 768), ("bf16", 512), ("bf16", 4096), ("f32", 1024)])
+def test_sums_in_the_place_of_alpha(dtype, d):
+    """dalpha or dbeta over alpha itself: another kernel's call, in a workspace of the size asked for and not a byte more."""
+    code = wht.DTYPE_BF16 if dtype == "bf16" else wht.DTYPE_F32
+    for N in (1, 4, 5, 8, 9, 16, 17, 32):
+        inp = synth.make_inputs(N, d, dtype, seed=3 * d + N)
+        x, dy = to_gpu(inp.x, dtype), to_gpu(inp.dy, dtype)
+        rdx, rda, rdb = oracle.backward(inp.dy, inp.x, inp.alpha, "fast")
+        need = max(16, wht.wht_affine_backward_workspace_bytes(N, d, code))
+        for over in ("dalpha", "dbeta"):
+            print(f"[few] over alpha d={d} {dtype} N={N} {over}", flush=True)
+            a = torch.from_numpy(inp.alpha).cuda()
+            room = torch.full((need + (1 << 16),), 77, dtype=torch.uint8, device="cuda")
+            dx, da, db = wht.wht_affine_backward(dy, x, a, workspace=room[:need], **{over: a})
+            assert (da if over == "dalpha" else db).data_ptr() == a.data_ptr()
+            assert bool((room[need:] == 77).all())
+            assert_io_close(dx, rdx, dtype, "dx")
+            assert_grad_close(da, rda, "dalpha")
+            assert_grad_close(db, rdb, "dbeta")
