@@ -115,11 +115,14 @@ constexpr OnceSizes once_sizes(bool resid, bool stats) {
 // (backward of 32768 x 8192 276 / 281, a step of 16384 x 4096 float32 231 / 236).  Where a workgroup of the persistent forward
 // has few rounds, each waits for the stores of the one before it, and those come back from memory, not L2: forward of 16 MiB of
 // 8192 wide 8.6 / 9.3, of 32 MiB of 16384 wide 17.0 / 18.0, dx alone of 16 MiB of 2048 wide 7.6 / 8.5.
-// Rows of 12 * 2^m: run_twelve.
+// Rows of 12 * 2^m: where x or dy is read with the default policy (kKeep) dx always and y never, elsewhere by the limits at
+// run_twelve.
 template <class C>
 static bool write_through(int64_t N, bool backward, bool grads) {
     constexpr int64_t MiB = 1 << 20;
     const int64_t bytes = N * C::kRow * (int64_t)sizeof(typename C::io::elem_t);
+    if constexpr (C::kTwelve)
+        return C::kKeep ? backward : bytes <= 136 * MiB && (!backward || (C::m < 10 && (bytes < 56 * MiB || bytes >= 80 * MiB)));
     if (!backward && bytes < (C::n >= 13 ? 56 : 24) * MiB) return false;
     if (backward && !grads && (C::n == 14 ? bytes < 56 * MiB : bytes >= 12 * MiB && bytes < 24 * MiB)) return false;
     return bytes <= 136 * MiB;
@@ -156,8 +159,8 @@ static int launch_forward(const void* x, const float* alpha, const float* beta, 
         hipLaunchKernelGGL(kernel, dim3(grid), dim3(C::BT), 0, stream, static_cast<const T*>(x), alpha, beta,
                            static_cast<const T*>(resid), static_cast<T*>(y), sumsq, N, cluster);
     };
-    with_bool(!C::kTwelve && write_through<C>(N, false, false), [&](auto b) {
-        constexpr bool THROUGH = !C::kTwelve && decltype(b)::value;
+    with_bool(write_through<C>(N, false, false), [&](auto b) {
+        constexpr bool THROUGH = !(C::kTwelve && C::kKeep) && decltype(b)::value;
         if (resid && sumsq) launch(forward_kernel<C, true, true, THROUGH>);
         else if (resid) launch(forward_kernel<C, true, false, THROUGH>);
         else launch(forward_kernel<C, false, false, THROUGH>);
@@ -228,7 +231,7 @@ static int launch_backward(const void* dy, const void* x, const float* alpha, vo
                            alpha, static_cast<T*>(dx), sums, N);
     };
     with_bool(write_through<C>(N, true, grads), [&](auto b) {
-        constexpr bool THROUGH = C::kTwelve ? C::kKeep : decltype(b)::value;
+        constexpr bool THROUGH = (C::kTwelve && C::kKeep) || decltype(b)::value;
         if constexpr (C::kWave) {
             if (grads && dx) launch(backward_wave_kernel<C, true, true, THROUGH>, C::BT);
             else if (!grads) launch(backward_wave_kernel<C, false, true, THROUGH>, C::BT);
@@ -316,13 +319,20 @@ static int dispatch_d(int logd, Op op, Args& a) {
 }
 
 // Rows of 12 * 2^m elements (bfloat16); logd = m + 4.
-// Tensors of up to 128 MiB (32 MiB where the backward pass reads both) are read with the default cache policy, as
-// these rows always have been, larger ones streamed.  What has been read with the default policy stays in the
-// Infinity Cache: a backward call that follows its forward call finds x there, and a caller that comes back to the
-// same small tensors finds them.  us per call, default policy in both directions / in forward alone / in neither,
-// twelve sets of buffers in turn: a step of 32768 x 768 51.7 / 49.5 / 52.6, of 32768 x 1536 90.6 / 89.4 / 94.3, backward
-// alone 34.1 / 32.5 / 32.5 and 61.1 / 58.0 / 57.9.  A forward call alone on an input that lies in memory loses 2..4 % to
-// streaming (8192 x 6144 39.4 against 38.4), one of 400 MB 6 %.
+// Small tensors are read with the default cache policy, as these rows always have been, larger ones streamed: x of a forward
+// call below 80 MiB (with the residual, 48 MiB up to m = 8 and 56 above), x and dy of a backward call up to 32 MiB, dy where dx
+// is made alone up to 128.  What has been read with the default policy stays in the Infinity Cache: a backward call that
+// follows its forward call finds x there, and a caller that comes back to the same small tensors finds them.
+// y is streamed where x is kept (through L2, y and dx would push x out before the backward call reads it) and goes through
+// L2 where x is streamed, both up to 136 MiB.  us per call, kept and streamed y / streamed x and y through, three sets of
+// inputs in turn and inputs from memory:
+//     forward     64 MiB of 768 22.0 / 23.5 and 26.2 / 23.6, 96 36.7 / 32.3 and 36.7 / 32.4, 128 47.6 / 41.5; 96 of 3072 38.4 / 34.1, of 12288 43.0 / 40.5;
+//     residual    40 MiB of 768 21.6 / 22.5 and 25.8 / 22.6, 48 26.9 / 25.6 and 29.9 / 25.6, 128 72.3 / 60.2; 48 of 6144 27.8 / 28.8 and 30.6 / 29.4,
+//                 64 39.4 / 35.1; 64 of 12288 41.8 / 39.7.
+// dx of a backward call above 32 MiB goes through L2 up to 136 MiB but for 56 to 80 MiB, where x, y, dy and dx of a step just
+// fill the Infinity Cache, and for m = 10.  us per call, streamed / through, backward and a step: 48 MiB of 768 32.6 / 31.4 and
+// 48.6 / 48.7 (from memory 50.2 / 49.4), 64 41.6 / 39.4 and 62.9 / 63.5, 128 73.8 / 67.9 and 112.2 / 110.6; 48 of 6144 36.2 / 34.8 and 54.7 / 53.9,
+// 128 of 1536 75.0 / 68.5 and 121.6 / 111.3; 48 of 12288 47.1 / 44.1 and 67.5 / 69.6.
 // The 32 MiB: backward, default policy / streamed, three sets of buffers in turn and inputs from memory (rows padded to
 // 16 * 2^m, before: always default):
 //     10923 x 768    16.0 / 17.9   18.1 / 18.4   (16.9, 18.0)        1365 x 6144    18.5 / 22.0   20.3 / 22.3   (19.4, 21.3)
@@ -330,9 +340,6 @@ static int dispatch_d(int logd, Op op, Args& a) {
 //     8192 x 1536    19.8 / 22.7   22.5 / 22.9   (22.8, 23.9)        683 x 12288    25.3 / 31.1   26.4 / 31.4   (39.5, 41.6)
 //     2731 x 3072    16.9 / 18.3   19.7 / 18.7   (18.9, 20.3)        1365 x 12288   35.7 / 39.7   37.3 / 40.8   (56.1, 56.6)
 //     5461 x 3072    24.6 / 26.0   27.0 / 26.0   (28.3, 28.6)
-// y is streamed and dx written through only where x or dy is read with the default policy: written through, y and dx would
-// push x out of the Infinity Cache before the backward call reads it (a step of 43691 x 768, y / dx streamed or through: both
-// streamed 62.8, dx through 66.2, both through 73.6; 10923 x 768 26.5 and 25.7 with dx through).
 // So the default policy costs up to 5 % from memory at 768 and 3072 and gains more elsewhere; streamed, calls of 6144 and
 // 768 would be slower than before.  The power-of-two rows have always been streamed and lose by a change.
 // Backward, rows of 768, up to 512 tokens: workgroups of 128 threads (four tokens), so that twice as many share a call
@@ -345,7 +352,7 @@ template <int M>
 static int run_twelve(Op op, Args& a) {
     const int64_t elems = a.N * TwelveCfg<M>::kRow, bytes = 2 * elems;
     if (op == Op::Forward) {
-        if (bytes <= (int64_t(128) << 20)) return forward<TwelveCfg<M, true>, TwelveCfg<M, false, 64>>(a);
+        if (bytes < (int64_t(!a.resid ? 80 : M <= 8 ? 48 : 56) << 20)) return forward<TwelveCfg<M, true>, TwelveCfg<M, false, 64>>(a);
         return forward<TwelveCfg<M>, TwelveCfg<M, false, 64>>(a);
     }
     if (op == Op::Workspace) {

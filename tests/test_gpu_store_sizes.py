@@ -15,7 +15,7 @@ CASES = [(d, "bf16") for d in (32, 64, 128, 256, 512, 1024, 2048, 4096, 8192, 16
 # MiB of x at which some width changes its forward route
 ONCE = (1, 2, 2.5, 3, 3.5, 4, 5, 6, 7, 9, 10, 12, 13, 14, 17, 20, 22, 24, 28, 33, 34, 48)
 # MiB at which the persistent forward and the backward kernels do
-PERSISTENT = (12, 24, 32, 56, 128, 136)
+PERSISTENT = (12, 24, 32, 56, 80, 128, 136)
 
 
 def _inputs(N, d, dtype):
@@ -97,3 +97,24 @@ def test_large_rows_on_both_sides_of_every_size(d, dtype):
         onto = g[:N].clone()
         wht.wht_affine_backward(onto, x[:N], a, dx=onto)
         assert torch.equal(onto, ref_dx[:N])
+
+
+@pytest.mark.parametrize("d", [768, 1536, 3072, 6144, 12288])
+def test_large_residual_rows_of_twelve(d):
+    """The residual calls of rows of 12 * 2^m where x stops being kept in the cache and where y stops going through L2."""
+    row = 2 * d
+    top = max(_around(136, row, 16))
+    x, r, a, b = _inputs(top, d, "bf16")
+    ref = torch.empty_like(x)
+    for part in _pieces(top, row):
+        ref[part] = wht.wht_affine_forward_residual(x[part], a, b, r[part])
+    for mib in (48, 56, 136):
+        for N in _around(mib, row, 16):
+            print(f"[sizes] residual d={d} N={N} ({N * row / MIB:.2f} MiB)", flush=True)
+            for call in (wht.wht_affine_forward_residual, wht.wht_affine_forward_residual_stats):
+                buf, y = _guarded(x, N)
+                call(x[:N], a, b, r[:N], y=y)
+                assert torch.equal(y, ref[:N]) and bool(torch.isnan(buf[N]).all())
+        onto = r[:N].clone()
+        wht.wht_affine_forward_residual(x[:N], a, b, onto, y=onto)
+        assert torch.equal(onto, ref[:N])
