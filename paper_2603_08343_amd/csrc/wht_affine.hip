@@ -72,7 +72,9 @@ static int forward_cluster(int64_t N, int grid, bool resid) {
 //     7.0 / 7.7 and 5.6 / 6.3, of 12288 wide 10.6 / 11.4 and 7.9 / 8.8 (there the persistent kernel took over from 2^22 elements on);
 //     below, half the workgroups leave CUs idle: 1 MiB of 2048 wide 2.8 and 3.2;
 //   persistent against one pass: 32 MiB of 256 wide (bfloat16) 13.4 / 14.4 and 11.1 / 14.4, of 2048 13.1 / 15.3 and 11.4 / 18.0 (so 24 there), 8 MiB
-//     of 16384 9.9 / 10.8 and 6.0 / 8.6, 32 MiB of 1536 11.5 / 13.5 and 14.2 / 15.3.
+//     of 16384 9.9 / 10.8 and 6.0 / 8.6, 32 MiB of 1536 11.5 / 13.5 and 14.2 / 15.3; with the residual 25 MiB of 1024 14.6 / 14.7 and 12.5 /
+//     14.6, 29 of 2048 17.5 / 17.5 and 14.8 / 19.1, of float32 2048 17.0 / 17.4 and 14.2 / 17.5 (so 33 there);
+//   two groups with the statistic, 2048 wide: 18 MiB 10.9 / 14.0, one 10.3 / 13.8, so one.
 // Rows of 12 * 2^m elements have workgroups of one token (two of 768): workgroups of 256 threads, with up to eight tokens,
 // leave CUs without any, and from 257 of them on put two on one CU beside others with one (341 x 768 3.33 / 2.34, 1365 x
 // 1536 5.60 / 4.80, 683 x 3072 6.01 / 4.83).
@@ -94,11 +96,11 @@ constexpr OnceSizes once_sizes(bool resid, bool stats) {
     } else if constexpr (C::kWave) {
         const int64_t from = resid && C::v == 2 && C::n <= 10 ? 6 * MiB : through;
         if (C::v == 3 || C::n <= 10) return {from, none, (resid ? 33 : 48) * MiB};
-        return {from, none, (C::n == 11 ? (resid ? 28 : 20) : C::n == 12 || resid ? 17 : 9) * MiB};
+        return {from, none, (C::n == 11 ? (resid ? 33 : 20) : C::n == 12 || resid ? 17 : 9) * MiB};
     } else {
         switch (C::n) {
-        case 10: return {through, resid ? none : 5 * MiB / 2, 24 * MiB};
-        case 11: return {through, stats ? 10 * MiB : resid ? 7 * MiB : 7 * MiB / 2, 24 * MiB};
+        case 10: return {through, resid ? none : 5 * MiB / 2, (resid ? 33 : 24) * MiB};
+        case 11: return {through, stats ? none : resid ? 7 * MiB : 7 * MiB / 2, (resid ? 33 : 24) * MiB};
         case 12: return {through, resid ? 7 * MiB : 10 * MiB, (stats ? 9 : 17) * MiB};
         case 13: return {through, none, (resid ? 7 : 13) * MiB};
         default: return {4 * MiB, none, 24 * MiB};
