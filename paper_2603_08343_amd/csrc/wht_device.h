@@ -2013,7 +2013,7 @@ __global__ __launch_bounds__(3 * C::BT) void backward_teams_kernel(const typenam
 // A wave takes every 16th token.  Its lanes hold 16-byte vectors of V elements, 64 / V lanes to the 64 columns of one k
 // and V consecutive k to a load; the V k's sums of each column are then brought together, half of the values at a time, by
 // lane swaps, which leaves one column per lane.
-// Bound by vector issue: 18 instructions per load (8 values: widen, multiply-add, sign) and about 36 per token behind them,
+// Bound by vector issue: 18 instructions per load (bfloat16: 8 values, widen, multiply-add, sign) and about 36 per token behind them,
 // on the 16 waves of one CU, 1.1 to 2 us per 2^15 to 2^16 elements; 64 columns because a line of dy has them.  The table at
 // few_backward_elements (wht_affine.hip) has the times.
 constexpr int kFewThreads = 1024, kFewWaves = kFewThreads / 64;
@@ -2025,6 +2025,12 @@ struct FewSlices {
     static constexpr int LOADS = (A + V - 1) / V;
     static constexpr int TOKENS = LOADS >= 8 ? 1 : LOADS >= 4 ? 2 : 4, CHUNK = LOADS < 8 ? LOADS : LOADS % 8 == 0 ? 8 : 6;
     static_assert(C::kRow % 64 == 0 && A >= V && LOADS <= 32 && LOADS % CHUNK == 0, "a load is V values of k, one sign bit each");
+    // float32 rows of 2048 on add the loads of a chunk in pairs, as the butterflies do.  dalpha of one token against 64 bits, in one
+    // chain over the loads / in pairs / by butterflies: 8192 wide 1.37e-7 / 1.07e-7 / 1.07e-7, 4096 1.11e-7 / 0.97e-7 / 0.97e-7, 2048
+    // 1.04e-7 / 0.99e-7 / 0.98e-7; up to 1024 the chain is short (0.90e-7).  It takes half as many instructions again per load: 0.04 to 0.1 us
+    // of a call.  bfloat16 keeps the chain: the kernels of more tokens carry z in two bfloat16 terms (2^-17).
+    static constexpr bool PAIRS = V == 4 && LOADS >= 8;
+    static_assert(!PAIRS || (CHUNK & (CHUNK - 1)) == 0, "pairs of pairs");
     // whether row j, column k of the upper factor is -1
     static __device__ __forceinline__ unsigned minus(unsigned j, unsigned k) {
         if constexpr (C::kTwelve) {
@@ -2091,16 +2097,35 @@ __device__ __forceinline__ void few_sums(const typename C::io::elem_t* dy, const
                     raw[u][l] = F::A % F::V == 0 || at < (unsigned)C::kRow ? *reinterpret_cast<const uint4*>(row + at) : make_uint4(0u, 0u, 0u, 0u);
                 }
             }
+            auto sign = [&](int l) { return __uint_as_float(0x3F800000u | ((minus >> (l0 + l)) << 31)); };
 #pragma unroll
-            for (int u = 0; u < F::TOKENS; ++u)
+            for (int u = 0; u < F::TOKENS; ++u) {
+                if constexpr (F::PAIRS) {
+                    float v[F::CHUNK][F::V];
 #pragma unroll
-                for (int l = 0; l < F::CHUNK; ++l) {
-                    float v[F::V];
-                    C::io::unpack(raw[u][l], v);
-                    const float s = __uint_as_float(0x3F800000u | ((minus >> (l0 + l)) << 31));
+                    for (int l = 0; l < F::CHUNK; ++l) C::io::unpack(raw[u][l], v[l]);
 #pragma unroll
-                    for (int i = 0; i < F::V; ++i) acc[u][i] = fmaf(v[i], s, acc[u][i]);
+                    for (int l = 0; l < F::CHUNK; l += 2)
+#pragma unroll
+                        for (int i = 0; i < F::V; ++i) v[l][i] = fmaf(v[l + 1][i], sign(l + 1), v[l][i] * sign(l));
+#pragma unroll
+                    for (int step = 2; step < F::CHUNK; step *= 2)
+#pragma unroll
+                        for (int l = 0; l < F::CHUNK; l += 2 * step)
+#pragma unroll
+                            for (int i = 0; i < F::V; ++i) v[l][i] += v[l + step][i];
+#pragma unroll
+                    for (int i = 0; i < F::V; ++i) acc[u][i] += v[0][i];
+                } else {
+#pragma unroll
+                    for (int l = 0; l < F::CHUNK; ++l) {
+                        float v[F::V];
+                        C::io::unpack(raw[u][l], v);
+#pragma unroll
+                        for (int i = 0; i < F::V; ++i) acc[u][i] = fmaf(v[i], sign(l), acc[u][i]);
+                    }
                 }
+            }
         }
 #pragma unroll
         for (int u = 0; u < F::TOKENS; ++u) {
