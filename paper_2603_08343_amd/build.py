@@ -26,6 +26,10 @@ POISON_LIB = os.path.join(HERE, "libwht_affine_poison.so")
 MARSHAL_SRC = os.path.join(HERE, "csrc", "torch_marshal.cpp")
 MARSHAL_LIB = os.path.join(HERE, "_torch_marshal.so")
 
+# host code only, loaded by tests: the rules of dispatch, so that a test finds the sizes at which the kernels change
+ROUTE_SRC = os.path.join(HERE, "csrc", "route_query.cpp")
+ROUTE_LIB = os.path.join(HERE, "libwht_route.so")
+
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
     # packed float32 VALU forms are kept out of the generated code on the test machines.  The
@@ -37,13 +41,14 @@ HIPCC_FLAGS = [
     "-Wall", "-Wno-unused-function",
 ]
 HEADER = os.path.join(os.path.dirname(HERE), "include", "wht_affine.h")
-SOURCES = [SRC, HEADER] + [os.path.join(HERE, "csrc", f) for f in ("wht_device.h", "wht_plan.h", "wht_validate.h")]
+SOURCES = [SRC, HEADER] + [os.path.join(HERE, "csrc", f) for f in ("wht_device.h", "wht_plan.h", "wht_route.h", "wht_validate.h")]
 
 
 def build(verbose: bool = False, extra=()) -> str:
     _compile(COPY_SRC, COPY_LIB, verbose, extra)
     _compile(SRC, POISON_LIB, verbose, (*extra, "-DWHT_POISON_LDS"))
     _compile_marshal(verbose)
+    _compile_route(verbose)
     return _compile(SRC, LIB, verbose, extra)
 
 
@@ -55,6 +60,13 @@ def _compile_marshal(verbose: bool) -> None:
            "-isystem", os.path.join(torch_dir, "include", "torch", "csrc", "api", "include"), "-isystem", sysconfig.get_paths()["include"],
            f'-DWHT_TORCH_VERSION="{importlib.metadata.version("torch")}"',
            "-o", MARSHAL_LIB, MARSHAL_SRC, "-L" + lib_dir, "-ltorch_python", "-ltorch_hip", "-ltorch_cpu", "-lc10"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+
+
+def _compile_route(verbose: bool) -> None:
+    cmd = [os.environ.get("CXX", "g++"), "-O1", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wextra", "-o", ROUTE_LIB, ROUTE_SRC]
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.run(cmd, check=True)
@@ -78,10 +90,13 @@ def _compile(src: str, lib: str, verbose: bool, extra=()) -> str:
 def ensure_built(verbose: bool = False) -> str:
     """For harnesses (tests, smoke check, benchmark): compile only if nothing has been built yet.
     The binding itself never builds: a missing library is an error there."""
-    if not all(os.path.exists(lib) for lib in (LIB, COPY_LIB, POISON_LIB, MARSHAL_LIB)):
+    if not all(os.path.exists(lib) for lib in (LIB, COPY_LIB, POISON_LIB, MARSHAL_LIB, ROUTE_LIB)):
         build(verbose=verbose)
     elif any(os.path.getmtime(f) > os.path.getmtime(MARSHAL_LIB) for f in (MARSHAL_SRC, HEADER)):
         raise RuntimeError(f"{MARSHAL_LIB} is older than its source: run `python -m paper_2603_08343_amd.build`")
+    elif any(os.path.getmtime(f) > os.path.getmtime(ROUTE_LIB)
+             for f in (ROUTE_SRC, os.path.join(HERE, "csrc", "wht_route.h"), os.path.join(HERE, "csrc", "wht_validate.h"), HEADER)):
+        raise RuntimeError(f"{ROUTE_LIB} is older than its sources: run `python -m paper_2603_08343_amd.build`")
     elif any(os.path.getmtime(f) > min(os.path.getmtime(LIB), os.path.getmtime(POISON_LIB))
              for f in SOURCES if os.path.exists(f)):
         # a stale binary would be validated and recorded under the new sources' name

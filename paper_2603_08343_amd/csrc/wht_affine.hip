@@ -10,6 +10,7 @@
 
 #include "../../include/wht_affine.h"
 #include "wht_device.h"
+#include "wht_route.h"
 #include "wht_validate.h"
 
 namespace wht {
@@ -61,74 +62,14 @@ static int forward_cluster(int64_t N, int grid, bool resid) {
     return grid;
 }
 
-// Forward calls by the size of x in bytes.  Few tokens (decoding, short prefills): one token group per workgroup and no
-// token loop (forward_once_kernel), with plain stores up to `through`, through L2 from there on, and from `pair` on with
-// two token groups per workgroup, both requested at once: alpha and beta, two to four times as many bytes as a thread's
-// part of x, are then read half as often.  From `limit` on the persistent kernel.
-// What each is worth, us per call under graph replay, three sets of inputs and two of outputs in turn / everything from memory:
-//   plain against through: 4097 x 1024 4.53 / 5.41 and 4.02 / 5.04, 1024 x 4096 4.68 / 5.66 and 3.74 / 4.75, 16385 x 256 4.36 / 5.46
-//     and 3.62 / 5.53; one token of 4096 with the statistic 2.65 and 2.77 (the kernel ends when memory, not L2, has the results);
-//   one group against two, 2048 wide: 1025 tokens 3.05 / 3.86 and 3.03 / 3.76, 4097 6.9 / 9.8 and 6.3 / 8.0; 8 MiB of 1536 wide
-//     7.0 / 7.7 and 5.6 / 6.3, of 12288 wide 10.6 / 11.4 and 7.9 / 8.8 (there the persistent kernel took over from 2^22 elements on);
-//     below, half the workgroups leave CUs idle: 1 MiB of 2048 wide 2.8 and 3.2;
-//   persistent against one pass: 32 MiB of 256 wide (bfloat16) 13.4 / 14.4 and 11.1 / 14.4, of 2048 13.1 / 15.3 and 11.4 / 18.0 (so 24 there), 8 MiB
-//     of 16384 9.9 / 10.8 and 6.0 / 8.6, 32 MiB of 1536 11.5 / 13.5 and 14.2 / 15.3; with the residual 25 MiB of 1024 14.6 / 14.7 and 12.5 /
-//     14.6, 29 of 2048 17.5 / 17.5 and 14.8 / 19.1, of float32 2048 17.0 / 17.4 and 14.2 / 17.5 (so 33 there);
-//   two groups with the statistic, 2048 wide: 18 MiB 10.9 / 14.0, one 10.3 / 13.8, so one.
-// Rows of 12 * 2^m elements have workgroups of one token (two of 768): workgroups of 256 threads, with up to eight tokens,
-// leave CUs without any, and from 257 of them on put two on one CU beside others with one (341 x 768 3.33 / 2.34, 1365 x
-// 1536 5.60 / 4.80, 683 x 3072 6.01 / 4.83).
-// The kernels do the same arithmetic on a token in the same order, so the switches are invisible in y
-// (the norm statistic is summed in the order of the launch shape: its last bits may differ).
-struct OnceSizes { int64_t through, pair, limit; };
 template <class C>
-constexpr OnceSizes once_sizes(bool resid, bool stats) {
-    constexpr int64_t MiB = 1 << 20, none = INT64_MAX;
-    const int64_t through = stats ? 5 * MiB / 2 : MiB;
-    if constexpr (C::kTwelve) {
-        switch (C::m) {
-        case 6:  return {through, resid ? 5 * MiB : 7 * MiB, 22 * MiB};
-        case 7:  return {resid ? 7 * MiB / 2 : 5 * MiB / 2, resid ? 7 * MiB / 2 : 5 * MiB / 2, resid ? 22 * MiB : 17 * MiB};
-        case 8:  return {through, stats ? 3 * MiB : 2 * MiB, resid ? 14 * MiB : 17 * MiB};
-        case 9:  return {resid ? 7 * MiB / 2 : MiB, 7 * MiB / 2, stats ? 7 * MiB : resid ? 12 * MiB : 17 * MiB};
-        default: return {4 * MiB, 7 * MiB, 34 * MiB};
-        }
-    } else if constexpr (C::kWave) {
-        const int64_t from = resid && C::v == 2 && C::n <= 10 ? 6 * MiB : through;
-        if (C::v == 3 || C::n <= 10) return {from, none, (resid ? 33 : 48) * MiB};
-        return {from, none, (C::n == 11 ? (resid ? 33 : 20) : C::n == 12 || resid ? 17 : 9) * MiB};
-    } else {
-        switch (C::n) {
-        case 10: return {through, resid ? none : 5 * MiB / 2, (resid ? 33 : 24) * MiB};
-        case 11: return {through, stats ? none : resid ? 7 * MiB : 7 * MiB / 2, (resid ? 33 : 24) * MiB};
-        case 12: return {through, resid ? 7 * MiB : 10 * MiB, (stats ? 9 : 17) * MiB};
-        case 13: return {through, none, (resid ? 7 : 13) * MiB};
-        default: return {4 * MiB, none, 24 * MiB};
-        }
-    }
+constexpr Rows rows_of() {
+    if constexpr (C::kTwelve) return {Sched::Twelve, C::m, 2};
+    else return {C::kWave ? Sched::Wave : Sched::Matrix, C::n, (int)sizeof(typename C::io::elem_t)};
 }
+template <class C>
+static int64_t bytes_of(int64_t N) { return N * C::kRow * (int64_t)sizeof(typename C::io::elem_t); }
 
-// Whether the persistent forward kernels and the backward kernels write y and dx through L2 rather than streaming them
-// past the caches ("nt").  Written through, results stay in the Infinity Cache: the next kernel finds them there, and a
-// program that gets the same output buffers back overwrites them there.  us per call, streamed / through, everything from
-// memory: 32768 x 1024 forward 24.5 / 24.1, backward 39.4 / 38.6; forward, forward on its result with the residual and backward, 32 MiB
-// each, 47.5 / 43.1, 128 MiB each 182 / 172; with two sets of outputs in turn forward 32768 x 2048 44.1 / 40.6, a step of
-// 32768 x 1024 64.4 / 59.3.  Above 136 MiB the three kinds of stream no longer fit together and streaming is ahead
-// (backward of 32768 x 8192 276 / 281, a step of 16384 x 4096 float32 231 / 236).  Where a workgroup of the persistent forward
-// has few rounds, each waits for the stores of the one before it, and those come back from memory, not L2: forward of 16 MiB of
-// 8192 wide 8.6 / 9.3, of 32 MiB of 16384 wide 17.0 / 18.0, dx alone of 16 MiB of 2048 wide 7.6 / 8.5.
-// Rows of 12 * 2^m: where x or dy is read with the default policy (kKeep) dx always and y never, elsewhere by the limits at
-// run_twelve.
-template <class C>
-static bool write_through(int64_t N, bool backward, bool grads) {
-    constexpr int64_t MiB = 1 << 20;
-    const int64_t bytes = N * C::kRow * (int64_t)sizeof(typename C::io::elem_t);
-    if constexpr (C::kTwelve)
-        return C::kKeep ? backward : bytes <= 136 * MiB && (!backward || (C::m < 10 && (bytes < 56 * MiB || bytes >= 80 * MiB)));
-    if (!backward && bytes < (C::n >= 13 ? 56 : 24) * MiB) return false;
-    if (backward && !grads && (C::n == 14 ? bytes < 56 * MiB : bytes >= 12 * MiB && bytes < 24 * MiB)) return false;
-    return bytes <= 136 * MiB;
-}
 // f(false type or true type): a choice made at run time as a template argument.
 template <class F>
 static void with_bool(bool b, F&& f) {
@@ -136,51 +77,45 @@ static void with_bool(bool b, F&& f) {
     else f(std::false_type{});
 }
 
-template <class C, bool THROUGH, int R>
-static int launch_forward_once(const void* x, const float* alpha, const float* beta, const void* resid,
-                               void* y, float* sumsq, int64_t N, hipStream_t stream) {
+template <class C, Out OUT, bool THROUGH, int R>
+static void launch_forward_once(const Args& a) {
     using T = typename C::io::elem_t;
-    const int grid = (int)((N + C::G * R - 1) / (C::G * R));
-    auto launch = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3(grid), dim3(C::BT), 0, stream, static_cast<const T*>(x), alpha, beta,
-                           static_cast<const T*>(resid), static_cast<T*>(y), sumsq, N);
-    };
-    if (resid && sumsq) launch(forward_once_kernel<C, true, true, THROUGH, R>);
-    else if (resid) launch(forward_once_kernel<C, true, false, THROUGH, R>);
-    else launch(forward_once_kernel<C, false, false, THROUGH, R>);
-    return hipGetLastError() == hipSuccess ? WHT_OK : WHT_ERR_LAUNCH;
+    const int grid = (int)((a.N + C::G * R - 1) / (C::G * R));
+    hipLaunchKernelGGL((forward_once_kernel<C, OUT != Out::Y, OUT == Out::Stats, THROUGH, R>), dim3(grid), dim3(C::BT), 0, a.stream,
+                       static_cast<const T*>(a.x), a.alpha, a.beta, static_cast<const T*>(a.resid), static_cast<T*>(a.y), a.sumsq, a.N);
 }
 
-template <class C>
-static int launch_forward(const void* x, const float* alpha, const float* beta, const void* resid, void* y,
-                          float* sumsq, int64_t N, hipStream_t stream) {
+template <class C, Out OUT, bool THROUGH>
+static void launch_forward(const Args& a) {
     using T = typename C::io::elem_t;
-    const int grid = grid_for<C>(N, false);
-    const int cluster = forward_cluster<C>(N, grid, resid != nullptr);
-    auto launch = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3(grid), dim3(C::BT), 0, stream, static_cast<const T*>(x), alpha, beta,
-                           static_cast<const T*>(resid), static_cast<T*>(y), sumsq, N, cluster);
-    };
-    with_bool(write_through<C>(N, false, false), [&](auto b) {
-        constexpr bool THROUGH = !(C::kTwelve && C::kKeep) && decltype(b)::value;
-        if (resid && sumsq) launch(forward_kernel<C, true, true, THROUGH>);
-        else if (resid) launch(forward_kernel<C, true, false, THROUGH>);
-        else launch(forward_kernel<C, false, false, THROUGH>);
-    });
+    const int grid = grid_for<C>(a.N, false);
+    const int cluster = forward_cluster<C>(a.N, grid, OUT != Out::Y);
+    hipLaunchKernelGGL((forward_kernel<C, OUT != Out::Y, OUT == Out::Stats, THROUGH>), dim3(grid), dim3(C::BT), 0, a.stream,
+                       static_cast<const T*>(a.x), a.alpha, a.beta, static_cast<const T*>(a.resid), static_cast<T*>(a.y), a.sumsq, a.N,
+                       cluster);
+}
+
+// CF: configuration of the persistent kernel, CO: of the one-pass kernel.
+template <class CF, class CO, Out OUT>
+static int forward_out(const Args& a) {
+    const Way way = forward_way(rows_of<CO>(), OUT, bytes_of<CO>(a.N));
+    constexpr auto reaches = [](Way w) { return forward_reaches(rows_of<CO>(), OUT, w); };
+    static_assert(reaches(Way::Plain) && reaches(Way::Stream) && (CO::kMfma || !reaches(Way::Pair)));
+    if (way == Way::Plain) launch_forward_once<CO, OUT, false, 1>(a);
+    if constexpr (reaches(Way::Through))
+        if (way == Way::Through) launch_forward_once<CO, OUT, true, 1>(a);
+    if constexpr (reaches(Way::Pair))
+        if (way == Way::Pair) launch_forward_once<CO, OUT, true, 2>(a);
+    if (way == Way::Stream) launch_forward<CF, OUT, false>(a);
+    if constexpr (reaches(Way::Flow) && !CF::kKeep)                 // x that is kept lies below the sizes of Flow
+        if (way == Way::Flow) launch_forward<CF, OUT, true>(a);
     return hipGetLastError() == hipSuccess ? WHT_OK : WHT_ERR_LAUNCH;
 }
 
 template <class CF, class CO>
 static int forward(const Args& a) {
-    const int64_t bytes = a.N * CO::kRow * (int64_t)sizeof(typename CO::io::elem_t);
-    const OnceSizes at = once_sizes<CO>(a.resid != nullptr, a.sumsq != nullptr);
-    if (bytes >= at.limit) return launch_forward<CF>(a.x, a.alpha, a.beta, a.resid, a.y, a.sumsq, a.N, a.stream);
-    if constexpr (CO::kMfma && once_sizes<CO>(false, false).pair < INT64_MAX)
-        if (bytes >= at.pair)
-            return launch_forward_once<CO, true, 2>(a.x, a.alpha, a.beta, a.resid, a.y, a.sumsq, a.N, a.stream);
-    if (bytes >= at.through)
-        return launch_forward_once<CO, true, 1>(a.x, a.alpha, a.beta, a.resid, a.y, a.sumsq, a.N, a.stream);
-    return launch_forward_once<CO, false, 1>(a.x, a.alpha, a.beta, a.resid, a.y, a.sumsq, a.N, a.stream);
+    if (!a.resid) return forward_out<CF, CO, Out::Y>(a);
+    return a.sumsq ? forward_out<CF, CO, Out::Stats>(a) : forward_out<CF, CO, Out::Resid>(a);
 }
 
 // Rows that backward_few_kernel does not take (shorter than 8 slices, float32 4): a call of up to three token groups runs on one
@@ -190,32 +125,17 @@ static int forward(const Args& a) {
 template <class C>
 static bool one_workgroup(int64_t N) { return N <= 3 * (int64_t)C::G; }
 
-// A call of few elements runs on backward_few_kernel: no partial rows and no second launch, which cost the stream 2.5 us and
-// the host 3.3, and a workgroup for every 64 columns where one_workgroup has a single one.  Rows must have 8 slices of 64
-// columns (float32: 4).  Its workgroups read x and dy while others write dx: where dx lies over one of them, dx is a launch of its own, and a call that
-// writes dalpha or dbeta over alpha stays on the other kernels.
-// us per call under graph replay, before / this kernel, backward: 1 x 512 3.8 / 2.2, 64 x 512 6.1 / 3.4, 64 x 1024 5.7 / 3.9 (91: 5.8 /
-// 5.9), 60 x 1536 7.5 / 4.6 (85: 7.6 / 7.1), 16 x 4096 6.3 / 3.1, 32 6.3 / 4.3 (45: 6.4 / 5.5, from memory 6.9 / 7.2), 16 x 8192 6.7 / 4.4 (23: 6.8 / 5.3,
-// from memory 7.2 / 6.8), 12 x 16384 12.0 / 9.4 (16: 12.1 / 10.5), 64 x 768 6.5 / 3.9 (121: 6.5 / 6.0), 16 x 12288 12.2 / 5.8; float32
-// 64 x 512 6.3 / 3.7 (128: 6.4 / 5.6), 64 x 1024 6.1 / 4.5, 32 x 2048 8.0 / 4.0 (64: 8.0 / 6.1), 12 x 8192 8.9 / 5.1 (16: 9.0 / 6.0).
+// Configurations whose calls of few elements run on backward_few_kernel; of rows of 768, the one of small calls.
 template <class C>
-constexpr bool has_few_backward() {
-    if (C::kTwelve) return C::kKeep && (C::kRow > 768 || C::BT == 128);         // what calls of so few elements run on
-    return C::kRow % 64 == 0 && C::kRow / 64 >= 16 / (int)sizeof(typename C::io::elem_t);
-}
-template <class C>
-constexpr int64_t few_backward_elements() {
-    if (sizeof(typename C::io::elem_t) == 4) return C::kRow <= 512 ? 3 << 14 : C::kRow == 1024 ? 1 << 16 : 3 << 15;
-    return C::kRow <= 1024 ? 1 << 16 : C::kRow < 2048 ? 3 << 15 : C::kRow < 12288 ? 1 << 17 : 3 << 16;
-}
+constexpr bool has_few() { return has_few_backward(rows_of<C>()) && (!C::kTwelve || (C::kKeep && (C::kRow > 768 || C::BT == 128))); }
 
 template <class C>
 static int launch_backward(const void* dy, const void* x, const float* alpha, void* dx, float* dalpha,
                            float* dbeta, int64_t N, void* workspace, hipStream_t stream) {
     using T = typename C::io::elem_t;
     const bool grads = dalpha != nullptr;
-    if constexpr (has_few_backward<C>())
-        if (grads && N * C::kRow <= few_backward_elements<C>() && dalpha != alpha && dbeta != alpha) {
+    if constexpr (has_few<C>())
+        if (grads && N * C::kRow <= few_backward_elements(rows_of<C>()) && dalpha != alpha && dbeta != alpha) {
             const bool apart = dx && (dx == dy || dx == x);
             const int64_t groups = dx && !apart ? (N + C::G - 1) / C::G : 0;
             hipLaunchKernelGGL(backward_few_kernel<C>, dim3((unsigned)(FewSlices<C>::A + groups)), dim3(kFewThreads), 0, stream,
@@ -223,7 +143,7 @@ static int launch_backward(const void* dy, const void* x, const float* alpha, vo
             if (hipGetLastError() != hipSuccess) return WHT_ERR_LAUNCH;
             return apart ? launch_backward<C>(dy, nullptr, alpha, dx, nullptr, nullptr, N, nullptr, stream) : WHT_OK;
         }
-    const bool direct = !has_few_backward<C>() && grads && one_workgroup<C>(N);
+    const bool direct = !has_few<C>() && grads && one_workgroup<C>(N);
     const int grid = direct ? 1 : grid_for<C>(N, grads);      // dx alone streams like a forward pass
     float* ws = static_cast<float*>(workspace);
     const SumRows sums = direct ? SumRows{dalpha, dbeta, 0} : SumRows{ws, ws + C::kRow, 2 * C::kRow};
@@ -232,7 +152,7 @@ static int launch_backward(const void* dy, const void* x, const float* alpha, vo
         hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), 0, stream, static_cast<const T*>(dy), static_cast<const T*>(x),
                            alpha, static_cast<T*>(dx), sums, N);
     };
-    with_bool(write_through<C>(N, true, grads), [&](auto b) {
+    with_bool(dx_through(rows_of<C>(), grads, bytes_of<C>(N)), [&](auto b) {
         constexpr bool THROUGH = (C::kTwelve && C::kKeep) || decltype(b)::value;
         if constexpr (C::kWave) {
             if (grads && dx) launch(backward_wave_kernel<C, true, true, THROUGH>, C::BT);
@@ -321,40 +241,13 @@ static int dispatch_d(int logd, Op op, Args& a) {
 }
 
 // Rows of 12 * 2^m elements (bfloat16); logd = m + 4.
-// Small tensors are read with the default cache policy, as these rows always have been, larger ones streamed: x of a forward
-// call below 80 MiB (with the residual, 48 MiB up to m = 8 and 56 above), x and dy of a backward call up to 32 MiB, dy where dx
-// is made alone up to 128.  What has been read with the default policy stays in the Infinity Cache: a backward call that
-// follows its forward call finds x there, and a caller that comes back to the same small tensors finds them.
-// y is streamed where x is kept (through L2, y and dx would push x out before the backward call reads it) and goes through
-// L2 where x is streamed, both up to 136 MiB.  us per call, kept and streamed y / streamed x and y through, three sets of
-// inputs in turn and inputs from memory:
-//     forward     64 MiB of 768 22.0 / 23.5 and 26.2 / 23.6, 96 36.7 / 32.3 and 36.7 / 32.4, 128 47.6 / 41.5; 96 of 3072 38.4 / 34.1, of 12288 43.0 / 40.5;
-//     residual    40 MiB of 768 21.6 / 22.5 and 25.8 / 22.6, 48 26.9 / 25.6 and 29.9 / 25.6, 128 72.3 / 60.2; 48 of 6144 27.8 / 28.8 and 30.6 / 29.4,
-//                 64 39.4 / 35.1; 64 of 12288 41.8 / 39.7.
-// dx of a backward call above 32 MiB goes through L2 up to 136 MiB but for 56 to 80 MiB, where x, y, dy and dx of a step just
-// fill the Infinity Cache, and for m = 10.  us per call, streamed / through, backward and a step: 48 MiB of 768 32.6 / 31.4 and
-// 48.6 / 48.7 (from memory 50.2 / 49.4), 64 41.6 / 39.4 and 62.9 / 63.5, 128 73.8 / 67.9 and 112.2 / 110.6; 48 of 6144 36.2 / 34.8 and 54.7 / 53.9,
-// 128 of 1536 75.0 / 68.5 and 121.6 / 111.3; 48 of 12288 47.1 / 44.1 and 67.5 / 69.6.
-// The 32 MiB: backward, default policy / streamed, three sets of buffers in turn and inputs from memory (rows padded to
-// 16 * 2^m, before: always default):
-//     10923 x 768    16.0 / 17.9   18.1 / 18.4   (16.9, 18.0)        1365 x 6144    18.5 / 22.0   20.3 / 22.3   (19.4, 21.3)
-//     16384 x 768    19.2 / 21.3   21.8 / 21.7   (21.0, 22.5)        2048 x 6144    21.9 / 25.4   23.5 / 25.7   (23.9, 25.3)
-//     8192 x 1536    19.8 / 22.7   22.5 / 22.9   (22.8, 23.9)        683 x 12288    25.3 / 31.1   26.4 / 31.4   (39.5, 41.6)
-//     2731 x 3072    16.9 / 18.3   19.7 / 18.7   (18.9, 20.3)        1365 x 12288   35.7 / 39.7   37.3 / 40.8   (56.1, 56.6)
-//     5461 x 3072    24.6 / 26.0   27.0 / 26.0   (28.3, 28.6)
-// So the default policy costs up to 5 % from memory at 768 and 3072 and gains more elsewhere; streamed, calls of 6144 and
-// 768 would be slower than before.  The power-of-two rows have always been streamed and lose by a change.
-// Backward, rows of 768, up to 512 tokens: workgroups of 128 threads (four tokens), so that twice as many share a call
-// that has few.  us per call under graph replay, 256 / 128 threads, inputs that come back: 341 7.00 / 6.63, 512 7.09 / 6.99, 683 7.26 /
-// 7.31, 1365 8.22 / 9.87; dx alone 64 3.26 / 2.84, 512 3.33 / 2.95, 1365 3.51 / 3.77.
-constexpr int64_t kSmallBackwardTokens = 512;
 using SmallBackwardCfg = TwelveCfg<6, true, 128>;
 
 template <int M>
 static int run_twelve(Op op, Args& a) {
-    const int64_t elems = a.N * TwelveCfg<M>::kRow, bytes = 2 * elems;
+    const int64_t bytes = bytes_of<TwelveCfg<M>>(a.N);
     if (op == Op::Forward) {
-        if (bytes < (int64_t(!a.resid ? 80 : M <= 8 ? 48 : 56) << 20)) return forward<TwelveCfg<M, true>, TwelveCfg<M, false, 64>>(a);
+        if (forward_keeps(M, a.resid != nullptr, bytes)) return forward<TwelveCfg<M, true>, TwelveCfg<M, false, 64>>(a);
         return forward<TwelveCfg<M>, TwelveCfg<M, false, 64>>(a);
     }
     if (op == Op::Workspace) {
@@ -373,7 +266,7 @@ static int run_twelve(Op op, Args& a) {
         if (a.N <= kSmallBackwardTokens && !(over_alpha && a.N <= 2 * TwelveCfg<M>::G))
             return launch_backward<SmallBackwardCfg>(a.dy, a.x, a.alpha, a.dx, a.dalpha, a.dbeta, a.N, a.workspace, a.stream);
     }
-    if (bytes <= (int64_t(a.dalpha ? 32 : 128) << 20))             // dx alone reads dy only
+    if (backward_keeps(a.dalpha != nullptr, bytes))
         return launch_backward<TwelveCfg<M, true>>(a.dy, a.x, a.alpha, a.dx, a.dalpha, a.dbeta, a.N, a.workspace, a.stream);
     return launch_backward<TwelveCfg<M>>(a.dy, a.x, a.alpha, a.dx, a.dalpha, a.dbeta, a.N, a.workspace, a.stream);
 }

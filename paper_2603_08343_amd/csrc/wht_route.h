@@ -1,0 +1,168 @@
+// Which kernel a call runs on, by the schedule and width of its rows, what it asks for and its size -- never by what is in
+// the tensors or where they lie.  No GPU call and no HIP header: wht_affine.hip takes its launches from here, and
+// route_query.cpp, which a host compiler builds, tells the tests which kernel a size reaches.
+//
+// Sizes are bytes of one [N, d] tensor.  The figures beside the rules are us per call under graph replay, in three settings:
+//   again   three sets of inputs and two of outputs in turn, which stay in the Infinity Cache while they are small;
+//   inputs  inputs from memory, two sets of outputs in turn: what a program sees whose allocator hands buffers back;
+//   memory  inputs and outputs all from memory.
+#pragma once
+#include <stdint.h>
+
+namespace wht {
+
+enum class Sched { Matrix, Wave, Twelve };
+
+// n: log2 d, or m for rows of 12 * 2^m; bytes: of an element.
+struct Rows { Sched sched; int n; int bytes; };
+
+// ---- forward -------------------------------------------------------------------------------------------------------------------
+
+// What a forward call returns: y, y with the residual added, that and the norm statistic.
+enum class Out { Y, Resid, Stats };
+
+// Few tokens (decoding, short prefills): one token group per workgroup and no token loop (forward_once_kernel), with plain
+// stores (Plain), with stores through L2 (Through), and with two token groups per workgroup and stores through L2 (Pair): both
+// are requested at once, and alpha and beta, two to four times as many bytes as a thread's part of x, are read half as often.
+// Then the persistent kernel (forward_kernel), with y streamed past the caches (Stream) or through L2 (Flow).
+// The kernels do the same arithmetic on a token in the same order, so the switches are invisible in y
+// (the norm statistic is summed in the order of the launch shape: its last bits may differ).
+enum class Way { Plain, Through, Pair, Stream, Flow };
+
+struct Step { double mib; Way way; };       // from this many MiB on
+struct Route { Step step[8]; };             // ends with the first step of 0 MiB behind the first one
+
+//   plain against through: 4097 x 1024 4.53 / 5.41 and 4.02 / 5.04, 1024 x 4096 4.68 / 5.66 and 3.74 / 4.75, 16385 x 256 4.36 / 5.46
+//     and 3.62 / 5.53 (again / memory); one token of 4096 with the statistic 2.65 and 2.77 (the kernel ends when memory, not L2, has the results);
+//   one group against two, 2048 wide: 1025 tokens 3.05 / 3.86 and 3.03 / 3.76, 4097 6.9 / 9.8 and 6.3 / 8.0; 8 MiB of 1536 wide
+//     7.0 / 7.7 and 5.6 / 6.3, of 12288 wide 10.6 / 11.4 and 7.9 / 8.8 (there the persistent kernel took over from 2^22 elements on);
+//     below, half the workgroups leave CUs idle: 1 MiB of 2048 wide 2.8 and 3.2;
+//   persistent against one pass: 32 MiB of 256 wide (bfloat16) 13.4 / 14.4 and 11.1 / 14.4, of 2048 13.1 / 15.3 and 11.4 / 18.0 (so 24 there), 8 MiB
+//     of 16384 9.9 / 10.8 and 6.0 / 8.6, 32 MiB of 1536 11.5 / 13.5 and 14.2 / 15.3; with the residual 25 MiB of 1024 14.6 / 14.7 and 12.5 /
+//     14.6, 29 of 2048 17.5 / 17.5 and 14.8 / 19.1, of float32 2048 17.0 / 17.4 and 14.2 / 17.5 (so 33 there);
+//   two groups with the statistic, 2048 wide: 18 MiB 10.9 / 14.0, one 10.3 / 13.8, so one.
+// Rows of 12 * 2^m elements have workgroups of one token (two of 768): workgroups of 256 threads, with up to eight tokens,
+// leave CUs without any, and from 257 of them on put two on one CU beside others with one (341 x 768 3.33 / 2.34, 1365 x
+// 1536 5.60 / 4.80, 683 x 3072 6.01 / 4.83).
+// Stream and Flow: see dx_through.  Where a workgroup of the persistent forward kernel has few rounds, each waits for the stores
+// of the one before it, and those come back from memory, not L2: forward of 16 MiB of 8192 wide 8.6 / 9.3, of 32 MiB of 16384
+// wide 17.0 / 18.0.  Rows of 12 * 2^m whose x is kept (forward_keeps) are streamed: through L2, y and dx would push x out before
+// the backward call reads it.
+constexpr Route forward_route(Rows rows, Out out) {
+    constexpr Way P = Way::Plain, T = Way::Through, R = Way::Pair, S = Way::Stream, F = Way::Flow;
+    const bool resid = out != Out::Y, stats = out == Out::Stats;
+    const double through = stats ? 2.5 : 1;
+    if (rows.sched == Sched::Twelve) {
+        const double keep = !resid ? 80 : rows.n <= 8 ? 48 : 56;
+        switch (rows.n) {
+        case 6:  return {{{0, P}, {through, T}, {resid ? 5.0 : 7.0, R}, {22, S}, {keep, F}, {136, S}}};
+        case 7:  return {{{0, P}, {resid ? 3.5 : 2.5, R}, {resid ? 22.0 : 17.0, S}, {keep, F}, {136, S}}};
+        case 8:  return {{{0, P}, {through, T}, {stats ? 3.0 : 2.0, R}, {resid ? 14.0 : 17.0, S}, {keep, F}, {136, S}}};
+        case 9:
+            if (resid) return {{{0, P}, {3.5, R}, {stats ? 7.0 : 12.0, S}, {keep, F}, {136, S}}};
+            return {{{0, P}, {1, T}, {3.5, R}, {17, S}, {keep, F}, {136, S}}};
+        default: return {{{0, P}, {4, T}, {7, R}, {34, S}, {keep, F}, {136, S}}};
+        }
+    }
+    if (rows.sched == Sched::Wave) {
+        const double from = resid && rows.bytes == 4 && rows.n <= 10 ? 6.0 : through;
+        if (rows.bytes == 2 || rows.n <= 10) return {{{0, P}, {from, T}, {resid ? 33.0 : 48.0, F}, {136, S}}};
+        if (rows.n == 11 && !resid) return {{{0, P}, {from, T}, {20, S}, {24, F}, {136, S}}};
+        if (rows.n == 11) return {{{0, P}, {from, T}, {33, F}, {136, S}}};
+        if (rows.n == 12) return {{{0, P}, {from, T}, {17, S}, {24, F}, {136, S}}};
+        return {{{0, P}, {from, T}, {resid ? 17.0 : 9.0, S}, {56, F}, {136, S}}};
+    }
+    switch (rows.n) {
+    case 10:
+        if (resid) return {{{0, P}, {through, T}, {33, F}, {136, S}}};
+        return {{{0, P}, {1, T}, {2.5, R}, {24, F}, {136, S}}};
+    case 11:
+        if (stats) return {{{0, P}, {through, T}, {33, F}, {136, S}}};
+        return {{{0, P}, {1, T}, {resid ? 7.0 : 3.5, R}, {resid ? 33.0 : 24.0, F}, {136, S}}};
+    case 12: return {{{0, P}, {through, T}, {resid ? 7.0 : 10.0, R}, {stats ? 9.0 : 17.0, S}, {24, F}, {136, S}}};
+    case 13: return {{{0, P}, {through, T}, {resid ? 7.0 : 13.0, S}, {56, F}, {136, S}}};
+    default: return {{{0, P}, {4, T}, {24, S}, {56, F}, {136, S}}};
+    }
+}
+
+constexpr Way forward_way(Rows rows, Out out, int64_t bytes) {
+    const Route r = forward_route(rows, out);
+    int i = 0;
+    while (i < 7 && r.step[i + 1].mib > 0 && (double)bytes >= r.step[i + 1].mib * (1 << 20)) ++i;
+    return r.step[i].way;
+}
+// Whether some size takes this way: the others are not compiled.
+constexpr bool forward_reaches(Rows rows, Out out, Way way) {
+    const Route r = forward_route(rows, out);
+    for (int i = 0; i < 8 && (i == 0 || r.step[i].mib > 0); ++i)
+        if (r.step[i].way == way) return true;
+    return false;
+}
+
+// Rows of 12 * 2^m: x of calls below this is read with the default cache policy, as these rows always have been, and streamed
+// from there on.  What has been read with the default policy stays in the Infinity Cache: a backward call that
+// follows its forward call finds x there, and a caller that comes back to the same small tensors finds them.
+// us per call, kept and streamed y / streamed x and y through L2, again and memory:
+//     forward     64 MiB of 768 22.0 / 23.5 and 26.2 / 23.6, 96 36.7 / 32.3 and 36.7 / 32.4, 128 47.6 / 41.5; 96 of 3072 38.4 / 34.1, of 12288 43.0 / 40.5;
+//     residual    40 MiB of 768 21.6 / 22.5 and 25.8 / 22.6, 48 26.9 / 25.6 and 29.9 / 25.6, 128 72.3 / 60.2; 48 of 6144 27.8 / 28.8 and 30.6 / 29.4,
+//                 64 39.4 / 35.1; 64 of 12288 41.8 / 39.7.
+constexpr bool forward_keeps(int m, bool resid, int64_t bytes) {
+    return bytes < (int64_t(!resid ? 80 : m <= 8 ? 48 : 56) << 20);
+}
+
+// ---- backward ------------------------------------------------------------------------------------------------------------------
+
+// Rows of 12 * 2^m: x and dy of a backward call up to 32 MiB are read with the default cache policy, dy where dx is made alone
+// up to 128.  The 32 MiB: backward, default policy / streamed, three sets of buffers in turn and inputs from memory (rows padded to
+// 16 * 2^m, before: always default):
+//     10923 x 768    16.0 / 17.9   18.1 / 18.4   (16.9, 18.0)        1365 x 6144    18.5 / 22.0   20.3 / 22.3   (19.4, 21.3)
+//     21845 x 768    22.6 / 25.5   27.1 / 26.1   (24.9, 27.3)        2731 x 6144    27.0 / 29.4   28.9 / 30.1   (27.9, 29.2)
+//     1365 x 3072    14.5 / 15.9   15.6 / 15.9   (15.0, 16.0)        1365 x 12288   37.6 / 40.6   37.5 / 40.9   (49.5, 50.8)
+//     2731 x 3072    16.0 / 18.6   19.7 / 18.7   (20.2, 22.1)
+//     32768 x 768    36.2 / 33.2   37.1 / 33.2   (38.7, 39.7)        4096 x 6144    41.0 / 36.8   41.3 / 36.8   (43.7, 44.0)
+// So the default policy costs up to 5 % from memory at 768 and 3072 and gains more elsewhere; streamed, calls of 6144 and
+// 768 would be slower than before.  The power-of-two rows have always been streamed and lose by a change.
+constexpr bool backward_keeps(bool grads, int64_t bytes) { return bytes <= (int64_t(grads ? 32 : 128) << 20); }
+
+// Whether dx goes through L2 (and y, in the table above) rather than being streamed past the caches ("nt").  Written through,
+// results stay in the Infinity Cache: the next kernel finds them there, and a
+// program that gets the same output buffers back overwrites them there.  us per call, streamed / through, everything from
+// memory: 32768 x 1024 forward 24.5 / 24.1, backward 39.4 / 38.6; forward, forward on its result with the residual and backward, 32 MiB
+// each, 47.5 / 43.1, 128 MiB each 182 / 172; with two sets of outputs in turn forward 32768 x 2048 44.1 / 40.6, a step of
+// 32768 x 1024 64.4 / 59.3.  Above 136 MiB the three kinds of stream no longer fit together and streaming is ahead
+// (backward of 32768 x 8192 276 / 281, a step of 16384 x 4096 float32 231 / 236).  dx alone of 16 MiB of 2048 wide 7.6 / 8.5.
+// Rows of 12 * 2^m: where x or dy is read with the default policy always; above, up to 136 MiB but for 56 to 80 MiB, where x, y, dy
+// and dx of a step just fill the Infinity Cache, and for m = 10: streamed / through, backward and a step: 48 MiB of 768 32.6 / 31.4 and
+// 48.6 / 48.7 (from memory 50.2 / 49.4), 64 41.6 / 39.4 and 62.9 / 63.5, 128 73.8 / 67.9 and 112.2 / 110.6; 48 of 6144 36.2 / 34.8 and 54.7 / 53.9,
+// 128 of 1536 75.0 / 68.5 and 121.6 / 111.3; 48 of 12288 47.1 / 44.1 and 67.5 / 69.6.
+constexpr bool dx_through(Rows rows, bool grads, int64_t bytes) {
+    constexpr int64_t MiB = 1 << 20;
+    if (rows.sched == Sched::Twelve)
+        return backward_keeps(grads, bytes) || (bytes <= 136 * MiB && rows.n < 10 && (bytes < 56 * MiB || bytes >= 80 * MiB));
+    if (!grads && (rows.n == 14 ? bytes < 56 * MiB : bytes >= 12 * MiB && bytes < 24 * MiB)) return false;
+    return bytes <= 136 * MiB;
+}
+
+// A call of few elements runs on backward_few_kernel: no partial rows and no second launch, which cost the stream 2.5 us and
+// the host 3.3, and a workgroup for every 64 columns where a launch of one workgroup has a single one.  Rows must have 8 slices of 64
+// columns (float32: 4).  Its workgroups read x and dy while others write dx: where dx lies over one of them, dx is a launch of its own,
+// and a call that writes dalpha or dbeta over alpha stays on the other kernels.
+// us per call under graph replay, before / this kernel, backward: 1 x 512 3.8 / 2.2, 64 x 512 6.1 / 3.4, 64 x 1024 5.7 / 3.9 (91: 5.8 /
+// 5.9), 60 x 1536 7.5 / 4.6 (85: 7.6 / 7.1), 16 x 4096 6.3 / 3.1, 32 6.3 / 4.3 (45: 6.4 / 5.5, from memory 6.9 / 7.2), 16 x 8192 6.7 / 4.4 (23: 6.8 / 5.3,
+// from memory 7.2 / 6.8), 12 x 16384 12.0 / 9.4 (16: 12.1 / 10.5), 64 x 768 6.5 / 3.9 (121: 6.5 / 6.0), 16 x 12288 12.2 / 5.8; float32
+// 64 x 512 6.3 / 3.7 (128: 6.4 / 5.6), 64 x 1024 6.1 / 4.5, 32 x 2048 8.0 / 4.0 (64: 8.0 / 6.1), 12 x 8192 8.9 / 5.1 (16: 9.0 / 6.0).
+constexpr int row_length(Rows rows) { return rows.sched == Sched::Twelve ? 12 << rows.n : 1 << rows.n; }
+constexpr bool has_few_backward(Rows rows) { return row_length(rows) % 64 == 0 && row_length(rows) / 64 >= 16 / rows.bytes; }
+constexpr int64_t few_backward_elements(Rows rows) {
+    const int row = row_length(rows);
+    if (!has_few_backward(rows)) return 0;
+    if (rows.bytes == 4) return row <= 512 ? 3 << 14 : row == 1024 ? 1 << 16 : 3 << 15;
+    return row <= 1024 ? 1 << 16 : row < 2048 ? 3 << 15 : row < 12288 ? 1 << 17 : 3 << 16;
+}
+
+// Rows of 768: a backward call of up to this many tokens has workgroups of 128 threads (four tokens), so that twice as many share it.
+// us per call under graph replay, 256 / 128 threads, inputs that come back: 341 7.00 / 6.63, 512 7.09 / 6.99, 683 7.26 /
+// 7.31, 1365 8.22 / 9.87; dx alone 64 3.26 / 2.84, 512 3.33 / 2.95, 1365 3.51 / 3.77.
+constexpr int64_t kSmallBackwardTokens = 512;
+
+}  // namespace wht
