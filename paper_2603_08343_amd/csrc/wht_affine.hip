@@ -118,13 +118,6 @@ static int forward(const Args& a) {
     return a.sumsq ? forward_out<CF, CO, Out::Stats>(a) : forward_out<CF, CO, Out::Resid>(a);
 }
 
-// Rows that backward_few_kernel does not take (shorter than 8 slices, float32 4): a call of up to three token groups runs on one
-// workgroup, which writes dalpha and dbeta itself: no partial rows and no second launch, which costs the stream
-// 2.5 us and the host 3.3.  The groups then run one after the other; up to here that is no slower (us per call under graph
-// replay, two launches / one: 3 groups at d = 256 6.0 / 5.7).
-template <class C>
-static bool one_workgroup(int64_t N) { return N <= 3 * (int64_t)C::G; }
-
 // Configurations whose calls of few elements run on backward_few_kernel; of rows of 768, the one of small calls.
 template <class C>
 constexpr bool has_few() { return has_few_backward(rows_of<C>()) && (!C::kTwelve || (C::kKeep && (C::kRow > 768 || C::BT == 128))); }
@@ -134,16 +127,17 @@ static int launch_backward(const void* dy, const void* x, const float* alpha, vo
                            float* dbeta, int64_t N, void* workspace, hipStream_t stream) {
     using T = typename C::io::elem_t;
     const bool grads = dalpha != nullptr;
-    if constexpr (has_few<C>())
-        if (grads && N * C::kRow <= few_backward_elements(rows_of<C>()) && dalpha != alpha && dbeta != alpha) {
-            const bool apart = dx && (dx == dy || dx == x);
-            const int64_t groups = dx && !apart ? (N + C::G - 1) / C::G : 0;
+    if constexpr (has_few<C>()) {
+        const bool in_place = dx && (dx == dy || dx == x);
+        if (grads && takes_few_backward(rows_of<C>(), N, C::G, in_place, dalpha == alpha || dbeta == alpha)) {
+            const int64_t groups = dx && !in_place ? (N + C::G - 1) / C::G : 0;
             hipLaunchKernelGGL(backward_few_kernel<C>, dim3((unsigned)(FewSlices<C>::A + groups)), dim3(kFewThreads), 0, stream,
                                static_cast<const T*>(dy), static_cast<const T*>(x), alpha, static_cast<T*>(dx), dalpha, dbeta, N);
             if (hipGetLastError() != hipSuccess) return WHT_ERR_LAUNCH;
-            return apart ? launch_backward<C>(dy, nullptr, alpha, dx, nullptr, nullptr, N, nullptr, stream) : WHT_OK;
+            return in_place ? launch_backward<C>(dy, nullptr, alpha, dx, nullptr, nullptr, N, nullptr, stream) : WHT_OK;
         }
-    const bool direct = !has_few<C>() && grads && one_workgroup<C>(N);
+    }
+    const bool direct = grads && N <= one_workgroup_groups(rows_of<C>()) * C::G;
     const int grid = direct ? 1 : grid_for<C>(N, grads);      // dx alone streams like a forward pass
     float* ws = static_cast<float*>(workspace);
     const SumRows sums = direct ? SumRows{dalpha, dbeta, 0} : SumRows{ws, ws + C::kRow, 2 * C::kRow};
@@ -260,10 +254,13 @@ static int run_twelve(Op op, Args& a) {
         return WHT_OK;
     }
     if constexpr (M == 6) {
-        // Up to two token groups of 256 threads the workspace has a row for each of those and none for groups of four tokens:
-        // a call that backward_few_kernel declines there runs on one workgroup of 256 threads, without partial rows.
-        const bool over_alpha = a.dalpha && (a.dalpha == a.alpha || a.dbeta == a.alpha);
-        if (a.N <= kSmallBackwardTokens && !(over_alpha && a.N <= 2 * TwelveCfg<M>::G))
+        // What is neither few elements nor up to four tokens, and fits one workgroup of 256 threads, runs there: it saves the second
+        // launch, and the workspace of so few tokens has no rows for groups of four.
+        const bool in_place = a.dx && (a.dx == a.dy || a.dx == a.x), over_alpha = a.dalpha == a.alpha || a.dbeta == a.alpha;
+        constexpr Rows rows = rows_of<SmallBackwardCfg>();
+        const bool few = takes_few_backward(rows, a.N, SmallBackwardCfg::G, in_place, over_alpha);
+        if (a.N <= kSmallBackwardTokens &&
+            (!a.dalpha || few || a.N <= SmallBackwardCfg::G || a.N > one_workgroup_groups(rows) * TwelveCfg<M>::G))
             return launch_backward<SmallBackwardCfg>(a.dy, a.x, a.alpha, a.dx, a.dalpha, a.dbeta, a.N, a.workspace, a.stream);
     }
     if (backward_keeps(a.dalpha != nullptr, bytes))

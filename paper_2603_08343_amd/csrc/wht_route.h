@@ -145,8 +145,7 @@ constexpr bool dx_through(Rows rows, bool grads, int64_t bytes) {
 
 // A call of few elements runs on backward_few_kernel: no partial rows and no second launch, which cost the stream 2.5 us and
 // the host 3.3, and a workgroup for every 64 columns where a launch of one workgroup has a single one.  Rows must have 8 slices of 64
-// columns (float32: 4).  Its workgroups read x and dy while others write dx: where dx lies over one of them, dx is a launch of its own,
-// and a call that writes dalpha or dbeta over alpha stays on the other kernels.
+// columns (float32: 4).  Its workgroups read x, dy and alpha while others write dx, dalpha and dbeta: takes_few_backward.
 // us per call under graph replay, before / this kernel, backward: 1 x 512 3.8 / 2.2, 64 x 512 6.1 / 3.4, 64 x 1024 5.7 / 3.9 (91: 5.8 /
 // 5.9), 60 x 1536 7.5 / 4.6 (85: 7.6 / 7.1), 16 x 4096 6.3 / 3.1, 32 6.3 / 4.3 (45: 6.4 / 5.5, from memory 6.9 / 7.2), 16 x 8192 6.7 / 4.4 (23: 6.8 / 5.3,
 // from memory 7.2 / 6.8), 12 x 16384 12.0 / 9.4 (16: 12.1 / 10.5), 64 x 768 6.5 / 3.9 (121: 6.5 / 6.0), 16 x 12288 12.2 / 5.8; float32
@@ -158,6 +157,29 @@ constexpr int64_t few_backward_elements(Rows rows) {
     if (!has_few_backward(rows)) return 0;
     if (rows.bytes == 4) return row <= 512 ? 3 << 14 : row == 1024 ? 1 << 16 : 3 << 15;
     return row <= 1024 ? 1 << 16 : row < 2048 ? 3 << 15 : row < 12288 ? 1 << 17 : 3 << 16;
+}
+
+// Other calls of up to this many token groups run on one workgroup, which writes dalpha and dbeta itself: no partial rows and no
+// second launch.  The groups then run one after the other; up to here that is no slower (us per call, two launches / one: 3 groups
+// at d = 256 6.0 / 5.7, at d = 1024 6.1 / 4.9, at float32 d = 1024 6.6 / 6.4; 2 groups at d = 4096 7.6 / 6.5, at d = 8192 6.6 / 5.4; 1 at d =
+// 16384 11.0 / 8.1 and at float32 d = 4096 7.7 / 5.2, where 2 already are 11.1 / 12.3 and 7.7 / 8.3; 2 at d = 768 5.8 (3: 6.6 / 7.1), 1 at d =
+// 12288 9.1 (2: 11.4 / 12.2)).
+constexpr int64_t one_workgroup_groups(Rows rows) {
+    const int row = row_length(rows);
+    return row >= 12288 ? 1 : row <= 1024 && rows.sched != Sched::Twelve ? 3 : rows.sched != Sched::Wave ? 2 : 1;
+}
+
+// Whether a backward call with parameter gradients runs on backward_few_kernel; group: tokens of a workgroup of the other kernels.
+// With dalpha or dbeta over alpha it cannot.  With dx over dy or x (in_place), dx is a launch of its own behind the sums, which pays
+// for wide rows only, beyond what one workgroup does and while the sums are short.  us per call, in place, other kernels / few and dx:
+// 4 x 1024 3.4 / 5.0, 64 x 1024 5.6 / 6.7, 96 x 512 6.0 / 8.1, 2 x 4096 4.3 / 5.8, 8 x 4096 6.8 / 6.2, 24 x 4096 6.9 / 7.4, 12 x 2048 6.9 / 6.1, 48 x
+// 2048 7.0 / 8.2, 2 x 16384 10.8 / 8.9, 12 x 16384 11.3 / 11.9, 8 x 12288 11.7 / 10.0, 64 x 768 6.3 / 7.1; float32 8 x 1024 5.0 / 5.3, 16 x 2048 8.1 / 6.9,
+// 48 x 2048 8.2 / 9.4, 4 x 4096 7.9 / 6.2, 24 x 4096 8.1 / 8.9, 1 x 8192 6.2 / 7.1, 4 x 8192 8.5 / 7.6, 12 x 8192 8.7 / 9.6.
+constexpr bool takes_few_backward(Rows rows, int64_t N, int64_t group, bool in_place, bool over_alpha) {
+    const int row = row_length(rows);
+    const int64_t elements = N * row;
+    if (over_alpha || elements > few_backward_elements(rows)) return false;
+    return !in_place || (row >= 2048 && N > one_workgroup_groups(rows) * group && elements <= (row >= 12288 ? 3 << 15 : 1 << 15));
 }
 
 // Rows of 768: a backward call of up to this many tokens has workgroups of 128 threads (four tokens), so that twice as many share it.

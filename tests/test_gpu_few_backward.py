@@ -2,6 +2,8 @@
 dbeta, a wave for every 16th token, up to four tokens of a wave at a time.  Every output against the oracle at token
 counts around those steps and on both sides of the size up to which the kernel runs; dx bit for bit what the other
 kernels give (alone, and in the place of dy or x, where the call takes them)."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -132,3 +134,55 @@ def test_float32_sums_are_as_exact_as_the_butterflies(d):
     off = lambda t: float(((t.double() - exact).norm(dim=1) / exact.norm(dim=1)).mean())
     print(f"[few] d={d} off by {off(got):.3e}, butterflies {off(plain):.3e}", flush=True)
     assert off(got) <= 1.05 * off(plain)
+
+
+def _launches(call):
+    """Kernels that a call launches, counted in a captured graph."""
+    hip = ctypes.CDLL("libamdhip64.so")
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        call()
+    count = ctypes.c_size_t(0)
+    assert hip.hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(count)) == 0
+    return count.value
+
+
+# tokens of a workgroup of the other kernels, and how many such groups one workgroup takes
+@pytest.mark.parametrize("dtype,d,group,groups", [("bf16", 512, 8, 3), ("bf16", 1024, 4, 3), ("bf16", 2048, 4, 2), ("bf16", 4096, 2, 2),
+                                                  ("bf16", 8192, 1, 2), ("bf16", 768, 8, 2), ("bf16", 1536, 4, 2), ("bf16", 12288, 1, 1),
+                                                  ("f32", 256, 16, 3), ("f32", 512, 8, 3), ("f32", 1024, 4, 3), ("f32", 8192, 1, 1)])
+def test_few_groups_are_one_launch_in_place_too(dtype, d, group, groups):
+    """dx over dy or x, dalpha or dbeta over alpha: up to as many groups as one workgroup takes in a single launch, with the sums and
+    the dx of a call on buffers of its own."""
+    code = wht.DTYPE_BF16 if dtype == "bf16" else wht.DTYPE_F32
+    for N in (1, group, group * groups):
+        print(f"[few] in place d={d} {dtype} N={N}", flush=True)
+        inp = synth.make_inputs(N, d, dtype, seed=5 * d + N)
+        rdx, rda, rdb = oracle.backward(inp.dy, inp.x, inp.alpha, "fast")
+        ws = torch.empty(max(16, wht.wht_affine_backward_workspace_bytes(N, d, code)), dtype=torch.uint8, device="cuda")
+        for over in ("dy", "x", "dalpha", "dbeta", None):
+            x, dy, a = to_gpu(inp.x, dtype), to_gpu(inp.dy, dtype), torch.from_numpy(inp.alpha).cuda()
+            dx, da, db = torch.empty_like(x), torch.empty_like(a), torch.empty_like(a)
+            out = {"dx": {"dy": dy, "x": x}.get(over, dx), "dalpha": a if over == "dalpha" else da, "dbeta": a if over == "dbeta" else db}
+            assert _launches(lambda: wht.wht_affine_backward(dy, x, a, workspace=ws, **out)) == 1, over     # captured, not run
+            wht.wht_affine_backward(dy, x, a, workspace=ws, **out)
+            assert_io_close(out["dx"], rdx, dtype, f"dx over {over}")
+            assert_grad_close(out["dalpha"], rda, f"dalpha over {over}")
+            assert_grad_close(out["dbeta"], rdb, f"dbeta over {over}")
+
+
+@pytest.mark.parametrize("dtype,d", list(LIMITS))
+def test_in_place_calls_around_their_limits(dtype, d):
+    """dx over dy at sizes on both sides of every change of kernel that takes_few_backward makes for it."""
+    sizes = {1, 2, 3, 4, 5, 8, 9, 12, 13, 16, 17, 24, 25, (1 << 15) // d, (1 << 15) // d + 1, (3 << 15) // d, (3 << 15) // d + 1}
+    for N in sorted(n for n in sizes if 0 < n * d <= 3 << 16):
+        print(f"[few] limits in place d={d} {dtype} N={N}", flush=True)
+        inp = synth.make_inputs(N, d, dtype, seed=7 * d + N)
+        x, dy, a = to_gpu(inp.x, dtype), to_gpu(inp.dy, dtype), torch.from_numpy(inp.alpha).cuda()
+        dx = wht.wht_affine_backward(dy, x, a)[0]
+        _, da, db = wht.wht_affine_backward(dy, x, a, dx=dy)
+        rdx, rda, rdb = oracle.backward(inp.dy, inp.x, inp.alpha, "fast")
+        assert torch.equal(dy, dx)
+        assert_io_close(dx, rdx, dtype, "dx")
+        assert_grad_close(da, rda, "dalpha")
+        assert_grad_close(db, rdb, "dbeta")
