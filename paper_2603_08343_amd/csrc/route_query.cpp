@@ -42,10 +42,10 @@ int wht_query_dx_through(int32_t dtype, int32_t d, int32_t grads, int64_t N) {
     if (!rows_for(dtype, d, 0, &rows)) return -1;
     return dx_through(rows, grads != 0, N * d * rows.bytes);
 }
-int wht_query_takes_few(int32_t dtype, int32_t d, int64_t N, int64_t group, int32_t in_place, int32_t over_alpha) {
+int wht_query_takes_few(int32_t dtype, int32_t d, int64_t N, int32_t over_alpha) {
     Rows rows{};
     if (!rows_for(dtype, d, 0, &rows)) return -1;
-    return takes_few_backward(rows, N, group, in_place != 0, over_alpha != 0);
+    return takes_few_backward(rows, N, over_alpha != 0);
 }
 int64_t wht_query_few_elements(int32_t dtype, int32_t d) {
     Rows rows{};

@@ -129,7 +129,7 @@ static int launch_backward(const void* dy, const void* x, const float* alpha, vo
     const bool grads = dalpha != nullptr;
     if constexpr (has_few<C>()) {
         const bool in_place = dx && (dx == dy || dx == x);
-        if (grads && takes_few_backward(rows_of<C>(), N, C::G, in_place, dalpha == alpha || dbeta == alpha)) {
+        if (grads && takes_few_backward(rows_of<C>(), N, dalpha == alpha || dbeta == alpha)) {
             const int64_t groups = dx && !in_place ? (N + C::G - 1) / C::G : 0;
             hipLaunchKernelGGL(backward_few_kernel<C>, dim3((unsigned)(FewSlices<C>::A + groups)), dim3(kFewThreads), 0, stream,
                                static_cast<const T*>(dy), static_cast<const T*>(x), alpha, static_cast<T*>(dx), dalpha, dbeta, N);
@@ -256,9 +256,8 @@ static int run_twelve(Op op, Args& a) {
     if constexpr (M == 6) {
         // What is neither few elements nor up to four tokens, and fits one workgroup of 256 threads, runs there: it saves the second
         // launch, and the workspace of so few tokens has no rows for groups of four.
-        const bool in_place = a.dx && (a.dx == a.dy || a.dx == a.x), over_alpha = a.dalpha == a.alpha || a.dbeta == a.alpha;
         constexpr Rows rows = rows_of<SmallBackwardCfg>();
-        const bool few = takes_few_backward(rows, a.N, SmallBackwardCfg::G, in_place, over_alpha);
+        const bool few = takes_few_backward(rows, a.N, a.dalpha == a.alpha || a.dbeta == a.alpha);
         if (a.N <= kSmallBackwardTokens &&
             (!a.dalpha || few || a.N <= SmallBackwardCfg::G || a.N > one_workgroup_groups(rows) * TwelveCfg<M>::G))
             return launch_backward<SmallBackwardCfg>(a.dy, a.x, a.alpha, a.dx, a.dalpha, a.dbeta, a.N, a.workspace, a.stream);

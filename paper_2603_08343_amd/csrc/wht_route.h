@@ -169,17 +169,12 @@ constexpr int64_t one_workgroup_groups(Rows rows) {
     return row >= 12288 ? 1 : row <= 1024 && rows.sched != Sched::Twelve ? 3 : rows.sched != Sched::Wave ? 2 : 1;
 }
 
-// Whether a backward call with parameter gradients runs on backward_few_kernel; group: tokens of a workgroup of the other kernels.
-// With dalpha or dbeta over alpha it cannot.  With dx over dy or x (in_place), dx is a launch of its own behind the sums, which pays
-// for wide rows only, beyond what one workgroup does and while the sums are short.  us per call, in place, other kernels / few and dx:
-// 4 x 1024 3.4 / 5.0, 64 x 1024 5.6 / 6.7, 96 x 512 6.0 / 8.1, 2 x 4096 4.3 / 5.8, 8 x 4096 6.8 / 6.2, 24 x 4096 6.9 / 7.4, 12 x 2048 6.9 / 6.1, 48 x
-// 2048 7.0 / 8.2, 2 x 16384 10.8 / 8.9, 12 x 16384 11.3 / 11.9, 8 x 12288 11.7 / 10.0, 64 x 768 6.3 / 7.1; float32 8 x 1024 5.0 / 5.3, 16 x 2048 8.1 / 6.9,
-// 48 x 2048 8.2 / 9.4, 4 x 4096 7.9 / 6.2, 24 x 4096 8.1 / 8.9, 1 x 8192 6.2 / 7.1, 4 x 8192 8.5 / 7.6, 12 x 8192 8.7 / 9.6.
-constexpr bool takes_few_backward(Rows rows, int64_t N, int64_t group, bool in_place, bool over_alpha) {
-    const int row = row_length(rows);
-    const int64_t elements = N * row;
-    if (over_alpha || elements > few_backward_elements(rows)) return false;
-    return !in_place || (row >= 2048 && N > one_workgroup_groups(rows) * group && elements <= (row >= 12288 ? 3 << 15 : 1 << 15));
+// Whether a backward call with parameter gradients runs on backward_few_kernel.  With dalpha or dbeta over alpha it cannot.  With dx
+// over dy or x, dx is a launch of its own behind the sums, although one workgroup would be faster for the first token groups (us per call,
+// one workgroup / sums and dx: 4 x 1024 3.4 / 5.0, 8 x 512 3.8 / 5.2, 2 x 4096 4.3 / 5.8, 4 x 768 4.0 / 5.9; faster from 8 x 4096, 12 x 2048 and 2 x 16384 on):
+// dalpha and dbeta are then added in the order of a call on buffers of its own, and in place or not the results are the same bits.
+constexpr bool takes_few_backward(Rows rows, int64_t N, bool over_alpha) {
+    return !over_alpha && N * row_length(rows) <= few_backward_elements(rows);
 }
 
 // Rows of 768: a backward call of up to this many tokens has workgroups of 128 threads (four tokens), so that twice as many share it.

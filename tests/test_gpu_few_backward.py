@@ -151,38 +151,34 @@ def _launches(call):
 @pytest.mark.parametrize("dtype,d,group,groups", [("bf16", 512, 8, 3), ("bf16", 1024, 4, 3), ("bf16", 2048, 4, 2), ("bf16", 4096, 2, 2),
                                                   ("bf16", 8192, 1, 2), ("bf16", 768, 8, 2), ("bf16", 1536, 4, 2), ("bf16", 12288, 1, 1),
                                                   ("f32", 256, 16, 3), ("f32", 512, 8, 3), ("f32", 1024, 4, 3), ("f32", 8192, 1, 1)])
-def test_few_groups_are_one_launch_in_place_too(dtype, d, group, groups):
-    """dx over dy or x, dalpha or dbeta over alpha: up to as many groups as one workgroup takes in a single launch, with the sums and
-    the dx of a call on buffers of its own."""
+def test_few_groups_over_alpha_are_one_launch(dtype, d, group, groups):
+    """dalpha or dbeta over alpha: up to as many token groups as one workgroup takes in a single launch, as on buffers of its own."""
     code = wht.DTYPE_BF16 if dtype == "bf16" else wht.DTYPE_F32
     for N in (1, group, group * groups):
-        print(f"[few] in place d={d} {dtype} N={N}", flush=True)
+        print(f"[few] over alpha, one launch, d={d} {dtype} N={N}", flush=True)
         inp = synth.make_inputs(N, d, dtype, seed=5 * d + N)
+        x, dy = to_gpu(inp.x, dtype), to_gpu(inp.dy, dtype)
         rdx, rda, rdb = oracle.backward(inp.dy, inp.x, inp.alpha, "fast")
         ws = torch.empty(max(16, wht.wht_affine_backward_workspace_bytes(N, d, code)), dtype=torch.uint8, device="cuda")
-        for over in ("dy", "x", "dalpha", "dbeta", None):
-            x, dy, a = to_gpu(inp.x, dtype), to_gpu(inp.dy, dtype), torch.from_numpy(inp.alpha).cuda()
-            dx, da, db = torch.empty_like(x), torch.empty_like(a), torch.empty_like(a)
-            out = {"dx": {"dy": dy, "x": x}.get(over, dx), "dalpha": a if over == "dalpha" else da, "dbeta": a if over == "dbeta" else db}
+        for over in ("dalpha", "dbeta", None):
+            a = torch.from_numpy(inp.alpha).cuda()
+            out = {"dx": torch.empty_like(x), "dalpha": torch.empty_like(a), "dbeta": torch.empty_like(a), **({over: a} if over else {})}
             assert _launches(lambda: wht.wht_affine_backward(dy, x, a, workspace=ws, **out)) == 1, over     # captured, not run
             wht.wht_affine_backward(dy, x, a, workspace=ws, **out)
-            assert_io_close(out["dx"], rdx, dtype, f"dx over {over}")
-            assert_grad_close(out["dalpha"], rda, f"dalpha over {over}")
-            assert_grad_close(out["dbeta"], rdb, f"dbeta over {over}")
+            assert_io_close(out["dx"], rdx, dtype, f"dx, {over} over alpha")
+            assert_grad_close(out["dalpha"], rda, f"dalpha, {over} over alpha")
+            assert_grad_close(out["dbeta"], rdb, f"dbeta, {over} over alpha")
 
 
 @pytest.mark.parametrize("dtype,d", list(LIMITS))
-def test_in_place_calls_around_their_limits(dtype, d):
-    """dx over dy at sizes on both sides of every change of kernel that takes_few_backward makes for it."""
-    sizes = {1, 2, 3, 4, 5, 8, 9, 12, 13, 16, 17, 24, 25, (1 << 15) // d, (1 << 15) // d + 1, (3 << 15) // d, (3 << 15) // d + 1}
-    for N in sorted(n for n in sizes if 0 < n * d <= 3 << 16):
-        print(f"[few] limits in place d={d} {dtype} N={N}", flush=True)
+def test_in_place_or_not_is_the_same_bits(dtype, d):
+    """dx over dy or x: dx, dalpha and dbeta bit for bit those of a call on buffers of its own, up to behind the limit of the kernel."""
+    top = LIMITS[dtype, d] // d
+    for N in sorted({1, 2, 3, 4, 5, 8, 9, 12, 13, 16, 17, 24, 25, 48, top, top + 1} & set(range(1, top + 2))):
+        print(f"[few] in place d={d} {dtype} N={N}", flush=True)
         inp = synth.make_inputs(N, d, dtype, seed=7 * d + N)
         x, dy, a = to_gpu(inp.x, dtype), to_gpu(inp.dy, dtype), torch.from_numpy(inp.alpha).cuda()
-        dx = wht.wht_affine_backward(dy, x, a)[0]
-        _, da, db = wht.wht_affine_backward(dy, x, a, dx=dy)
-        rdx, rda, rdb = oracle.backward(inp.dy, inp.x, inp.alpha, "fast")
-        assert torch.equal(dy, dx)
-        assert_io_close(dx, rdx, dtype, "dx")
-        assert_grad_close(da, rda, "dalpha")
-        assert_grad_close(db, rdb, "dbeta")
+        apart = wht.wht_affine_backward(dy, x, a)
+        onto_dy, onto_x = dy.clone(), x.clone()
+        assert all(torch.equal(p, q) for p, q in zip(apart, wht.wht_affine_backward(onto_dy, x, a, dx=onto_dy)))
+        assert all(torch.equal(p, q) for p, q in zip(apart, wht.wht_affine_backward(dy, onto_x, a, dx=onto_x)))
