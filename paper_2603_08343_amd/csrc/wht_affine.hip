@@ -146,18 +146,23 @@ static int launch_backward(const void* dy, const void* x, const float* alpha, vo
         hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), 0, stream, static_cast<const T*>(dy), static_cast<const T*>(x),
                            alpha, static_cast<T*>(dx), sums, N);
     };
-    with_bool(dx_through(rows_of<C>(), grads, bytes_of<C>(N)), [&](auto b) {
-        constexpr bool THROUGH = (C::kTwelve && C::kKeep) || decltype(b)::value;
-        if constexpr (C::kWave) {
-            if (grads && dx) launch(backward_wave_kernel<C, true, true, THROUGH>, C::BT);
-            else if (!grads) launch(backward_wave_kernel<C, false, true, THROUGH>, C::BT);
-            else launch(backward_wave_kernel<C, true, false, false>, C::BT);
-        } else if (grads && dx) {
-            if constexpr (C::kBwdTeams) launch(backward_teams_kernel<C, THROUGH>, 3 * C::BT);
-            else launch(backward_kernel<C, true, true, THROUGH>, C::BT);
-        } else if (!grads) launch(backward_kernel<C, false, true, THROUGH>, C::BT);
+    const bool through = dx_through(rows_of<C>(), grads, bytes_of<C>(N));
+    if (grads && !dx) {
+        if constexpr (C::kWave) launch(backward_wave_kernel<C, true, false, false>, C::BT);
         else launch(backward_kernel<C, true, false, false>, C::BT);
-    });
+    } else if (grads) {
+        with_bool(through, [&](auto b) {
+            constexpr bool THROUGH = (C::kTwelve && C::kKeep) || decltype(b)::value;      // always where x and dy are kept
+            if constexpr (C::kWave) launch(backward_wave_kernel<C, true, true, THROUGH>, C::BT);
+            else if constexpr (C::kBwdTeams) launch(backward_teams_kernel<C, THROUGH>, 3 * C::BT);
+            else launch(backward_kernel<C, true, true, THROUGH>, C::BT);
+        });
+    } else {
+        with_bool(through, [&](auto b) {
+            if constexpr (C::kWave) launch(backward_wave_kernel<C, false, true, decltype(b)::value>, C::BT);
+            else launch(backward_kernel<C, false, true, decltype(b)::value>, C::BT);
+        });
+    }
     if (hipGetLastError() != hipSuccess) return WHT_ERR_LAUNCH;
     if (!grads || direct) return WHT_OK;
     constexpr int CG = reduce_columns(C::kRow);

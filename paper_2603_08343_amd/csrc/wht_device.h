@@ -1693,6 +1693,21 @@ __device__ __forceinline__ void wave_issue(unsigned char* wave_slot, const typen
     });
 }
 
+// Registers in the first layout -> the rows, streamed.  With global_put's 64-bit address of a row per lane the kernels for dx take 4
+// to 8 registers more, and are up to 6 % slower (float32 2048 wide, 24 to 50 MiB).
+template <class C>
+__device__ __forceinline__ void wave_put(const float (&r)[C::E], typename C::io::elem_t* tensor, const WaveRows<C>& rows,
+                                         unsigned thread_elem) {
+    unsigned char* base = reinterpret_cast<unsigned char*>(tensor + rows.base);
+    const unsigned off = (rows.rel + thread_elem) * (unsigned)sizeof(typename C::io::elem_t);
+    if (rows.active)
+        static_for<0, C::NV>([&](auto c) {
+            constexpr int Cc = decltype(c)::value;
+            constexpr unsigned elem = reg_elem_offset(C::plan.ph[0], C::e, Cc * C::V);
+            stream_store16(base + elem * sizeof(typename C::io::elem_t) + off, C::io::pack(&r[Cc * C::V]));
+        });
+}
+
 // Zeros for this lane's vectors of a wave's stage slot.
 template <class C>
 __device__ __forceinline__ void zero_stage(const unsigned char* wave_slot) {
@@ -1825,7 +1840,8 @@ void backward_wave_kernel(const typename C::io::elem_t* dy, const typename C::io
         if constexpr (C::w > 0 && GRADS != DX) exchange_barrier();
         if (more) wait_vmem<0>();
         if constexpr (DX) {
-            put_output<C, 0, THROUGH>(r, dx, threadIdx.x / C::TPT, N, grp, tm);
+            if constexpr (THROUGH) global_put_through<C, 0>(r, dx, threadIdx.x / C::TPT, N, grp, tm);
+            else wave_put<C>(r, dx, rows, tm.first_elem);
         }
     }
     if constexpr (GRADS) {

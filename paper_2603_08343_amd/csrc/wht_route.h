@@ -15,6 +15,7 @@ enum class Sched { Matrix, Wave, Twelve };
 
 // n: log2 d, or m for rows of 12 * 2^m; bytes: of an element.
 struct Rows { Sched sched; int n; int bytes; };
+constexpr int row_length(Rows rows) { return rows.sched == Sched::Twelve ? 12 << rows.n : 1 << rows.n; }
 
 // ---- forward -------------------------------------------------------------------------------------------------------------------
 
@@ -113,7 +114,7 @@ constexpr bool forward_keeps(int m, bool resid, int64_t bytes) {
 // ---- backward ------------------------------------------------------------------------------------------------------------------
 
 // Rows of 12 * 2^m: x and dy of a backward call up to 32 MiB are read with the default cache policy, dy where dx is made alone
-// up to 128.  The 32 MiB: backward, default policy / streamed, three sets of buffers in turn and inputs from memory (rows padded to
+// up to 84 (dx_through).  The 32 MiB: backward, default policy / streamed, three sets of buffers in turn and inputs from memory (rows padded to
 // 16 * 2^m, before: always default):
 //     10923 x 768    16.0 / 17.9   18.1 / 18.4   (16.9, 18.0)        1365 x 6144    18.5 / 22.0   20.3 / 22.3   (19.4, 21.3)
 //     21845 x 768    22.6 / 25.5   27.1 / 26.1   (24.9, 27.3)        2731 x 6144    27.0 / 29.4   28.9 / 30.1   (27.9, 29.2)
@@ -122,25 +123,44 @@ constexpr bool forward_keeps(int m, bool resid, int64_t bytes) {
 //     32768 x 768    36.2 / 33.2   37.1 / 33.2   (38.7, 39.7)        4096 x 6144    41.0 / 36.8   41.3 / 36.8   (43.7, 44.0)
 // So the default policy costs up to 5 % from memory at 768 and 3072 and gains more elsewhere; streamed, calls of 6144 and
 // 768 would be slower than before.  The power-of-two rows have always been streamed and lose by a change.
-constexpr bool backward_keeps(bool grads, int64_t bytes) { return bytes <= (int64_t(grads ? 32 : 128) << 20); }
+constexpr bool backward_keeps(bool grads, int64_t bytes) { return bytes <= (int64_t(grads ? 32 : 84) << 20); }
 
 // Whether dx goes through L2 (and y, in the table above) rather than being streamed past the caches ("nt").  Written through,
-// results stay in the Infinity Cache: the next kernel finds them there, and a
-// program that gets the same output buffers back overwrites them there.  us per call, streamed / through, everything from
-// memory: 32768 x 1024 forward 24.5 / 24.1, backward 39.4 / 38.6; forward, forward on its result with the residual and backward, 32 MiB
-// each, 47.5 / 43.1, 128 MiB each 182 / 172; with two sets of outputs in turn forward 32768 x 2048 44.1 / 40.6, a step of
-// 32768 x 1024 64.4 / 59.3.  Above 136 MiB the three kinds of stream no longer fit together and streaming is ahead
-// (backward of 32768 x 8192 276 / 281, a step of 16384 x 4096 float32 231 / 236).  dx alone of 16 MiB of 2048 wide 7.6 / 8.5.
-// Rows of 12 * 2^m: where x or dy is read with the default policy always; above, up to 136 MiB but for 56 to 80 MiB, where x, y, dy
-// and dx of a step just fill the Infinity Cache, and for m = 10: streamed / through, backward and a step: 48 MiB of 768 32.6 / 31.4 and
+// results stay in the Infinity Cache: the next kernel finds them there, and a program that gets the same output buffers back
+// overwrites them there.  But a kernel ends when memory has its results, and a workgroup's next round waits for the stores of the
+// one before: short calls lose, and rows whose rounds are short.  Through against streamed, again / memory / inputs (a size is written through where
+// the three together gain, or lose nothing):
+//   backward: 32 to 256 wide rows 1 to 24 MiB +0..+7 % / +1..+7 / -1..+7, 36 to 136 -7..+1 / +0..+3 / -7..+1; float32 512 wide 2 to 8 MiB -6..-4 / -3..+2 / -3..+2, 8 to
+//     18 +2..+3 / 0..+1 / +1..+3; other rows below 1 MiB +2 / +6 / +3 (4096 wide and more -2 / +2 / 0), from 1 or 2 MiB on -14..+1 / -6..+2 / -8..+1;
+//   dx alone: below 2 MiB -3 / +7 / +4, 2 to 4 -5 / +5 / +2; rows of up to 128 bytes 4 to 8 MiB -20..-6 / +11..+18 / +8..+14, 12 on -12..-1 / +1 / -12..-4; 128 to 512 wide 4 to 8 -10 / +4 / +1, 8 to 12
+//     -18..+4 / +11 / +13, 12 to 16 +6..+9 / +7..+9 / +8..+12, 24 on -11..+2 / +0..+4 / -12..-2; 1024 wide 5 MiB -7 / +19 / +13, 6 on -13..-3 / 0..+6 / -13..+3;
+//     2048 to 8192 wide 4 to 10 MiB -9..-6 / +2 / 0, 10 to 24 -3..+2 / +1..+7 / -1..+7; bfloat16 4096 and 8192 wide 34 MiB +5..+7 / +7..+9 / +1..+2, 40 on -11..-1 /
+//     0..+6 / -10..-3; float32 2048 and 8192 wide 24 to 40 MiB +1..+11 / +3..+11 / 0..+10; 16384 wide -6..+4 / -1..+4 / -2..+2, never together ahead;
+//   above 136 MiB 0..+2 / 0..+4 / -8..-18 (dx alone, 150 to 256 MiB), a step of 16384 x 4096 float32 231 / 236 us, backward of 32768 x 8192 276 / 281: streamed.
+// Rows of 12 * 2^m: with the sums, where x and dy are kept always; above, up to 136 MiB but for 56 to 80 MiB, where x, y, dy
+// and dx of a step just fill the Infinity Cache, and for m = 10: streamed / through, us, backward and a step: 48 MiB of 768 32.6 / 31.4 and
 // 48.6 / 48.7 (from memory 50.2 / 49.4), 64 41.6 / 39.4 and 62.9 / 63.5, 128 73.8 / 67.9 and 112.2 / 110.6; 48 of 6144 36.2 / 34.8 and 54.7 / 53.9,
-// 128 of 1536 75.0 / 68.5 and 121.6 / 111.3; 48 of 12288 47.1 / 44.1 and 67.5 / 69.6.
+// 128 of 1536 75.0 / 68.5 and 121.6 / 111.3; 48 of 12288 47.1 / 44.1 and 67.5 / 69.6.  dx alone on a dy that is kept: 1 to 46 MiB -7..0 / -3..+11 / -8..+3, above
+// +5..+18 / +0..+6 / -9..-3 (75 MiB of 768 24.0 / 28.1 us); on a streamed one, 84 to 128 MiB, against kept and streamed -14..0 / -3..+1 / -14..-5.
 constexpr bool dx_through(Rows rows, bool grads, int64_t bytes) {
     constexpr int64_t MiB = 1 << 20;
-    if (rows.sched == Sched::Twelve)
-        return backward_keeps(grads, bytes) || (bytes <= 136 * MiB && rows.n < 10 && (bytes < 56 * MiB || bytes >= 80 * MiB));
-    if (!grads && (rows.n == 14 ? bytes < 56 * MiB : bytes >= 12 * MiB && bytes < 24 * MiB)) return false;
-    return bytes <= 136 * MiB;
+    const int row = row_length(rows);
+    if (bytes > 136 * MiB) return false;
+    if (rows.sched == Sched::Twelve) {
+        if (grads) return backward_keeps(true, bytes) || (rows.n < 10 && (bytes < 56 * MiB || bytes >= 80 * MiB));
+        return bytes < 46 * MiB || !backward_keeps(false, bytes);
+    }
+    if (grads) {
+        if (row <= 256) return bytes >= 36 * MiB;
+        if (rows.bytes == 4 && row == 512) return bytes >= 2 * MiB && (bytes < 8 * MiB || bytes >= 18 * MiB);
+        return row >= 4096 || bytes >= (rows.bytes == 4 && row == 1024 ? 2 : 1) * MiB;
+    }
+    if (row == 16384) return false;
+    if (row * rows.bytes <= 128) return bytes >= 12 * MiB;
+    if (rows.sched == Sched::Matrix && row == 1024) return bytes >= 2 * MiB && (bytes < 4 * MiB || bytes >= 6 * MiB);
+    if (row <= (rows.bytes == 4 ? 1024 : 512)) return bytes >= 2 * MiB && (bytes < 8 * MiB || bytes >= 24 * MiB);
+    const int64_t again = rows.bytes == 4 ? (row == 2048 ? 56 : row == 4096 ? 24 : 46) : row == 2048 ? 24 : 40;
+    return (bytes >= 2 * MiB && bytes < (rows.bytes == 4 && row == 4096 ? 12 : 10) * MiB) || bytes >= again * MiB;
 }
 
 // A call of few elements runs on backward_few_kernel: no partial rows and no second launch, which cost the stream 2.5 us and
@@ -150,7 +170,6 @@ constexpr bool dx_through(Rows rows, bool grads, int64_t bytes) {
 // 5.9), 60 x 1536 7.5 / 4.6 (85: 7.6 / 7.1), 16 x 4096 6.3 / 3.1, 32 6.3 / 4.3 (45: 6.4 / 5.5, from memory 6.9 / 7.2), 16 x 8192 6.7 / 4.4 (23: 6.8 / 5.3,
 // from memory 7.2 / 6.8), 12 x 16384 12.0 / 9.4 (16: 12.1 / 10.5), 64 x 768 6.5 / 3.9 (121: 6.5 / 6.0), 16 x 12288 12.2 / 5.8; float32
 // 64 x 512 6.3 / 3.7 (128: 6.4 / 5.6), 64 x 1024 6.1 / 4.5, 32 x 2048 8.0 / 4.0 (64: 8.0 / 6.1), 12 x 8192 8.9 / 5.1 (16: 9.0 / 6.0).
-constexpr int row_length(Rows rows) { return rows.sched == Sched::Twelve ? 12 << rows.n : 1 << rows.n; }
 constexpr bool has_few_backward(Rows rows) { return row_length(rows) % 64 == 0 && row_length(rows) / 64 >= 16 / rows.bytes; }
 constexpr int64_t few_backward_elements(Rows rows) {
     const int row = row_length(rows);
