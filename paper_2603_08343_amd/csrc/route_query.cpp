@@ -42,6 +42,10 @@ int wht_query_dx_through(int32_t dtype, int32_t d, int32_t grads, int64_t N) {
     if (!rows_for(dtype, d, 0, &rows)) return -1;
     return dx_through(rows, grads != 0, N * d * rows.bytes);
 }
+int wht_query_sums_store(int32_t dtype, int32_t d, int32_t dx) {
+    Rows rows{};
+    return rows_for(dtype, d, 0, &rows) ? static_cast<int>(sums_store(rows, dx != 0)) : -1;
+}
 int wht_query_takes_few(int32_t dtype, int32_t d, int64_t N, int32_t over_alpha) {
     Rows rows{};
     if (!rows_for(dtype, d, 0, &rows)) return -1;

@@ -10,7 +10,6 @@
 
 #include "../../include/wht_affine.h"
 #include "wht_device.h"
-#include "wht_route.h"
 #include "wht_validate.h"
 
 namespace wht {
@@ -62,11 +61,6 @@ static int forward_cluster(int64_t N, int grid, bool resid) {
     return grid;
 }
 
-template <class C>
-constexpr Rows rows_of() {
-    if constexpr (C::kTwelve) return {Sched::Twelve, C::m, 2};
-    else return {C::kWave ? Sched::Wave : Sched::Matrix, C::n, (int)sizeof(typename C::io::elem_t)};
-}
 template <class C>
 static int64_t bytes_of(int64_t N) { return N * C::kRow * (int64_t)sizeof(typename C::io::elem_t); }
 

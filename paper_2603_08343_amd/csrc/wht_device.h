@@ -17,6 +17,7 @@
 #include <type_traits>
 
 #include "wht_plan.h"
+#include "wht_route.h"
 
 namespace wht {
 
@@ -233,6 +234,13 @@ struct WaveCfg {
     static constexpr unsigned kStageBytes = BT * NV * 16u;          // one tensor's token group, as stored
     static_assert(G == 1 || 2u * kStageBytes >= G * kTokenWords * 4u, "the token sums reuse the stage buffers");
 };
+
+// What the rules of dispatch call a configuration's rows.
+template <class C>
+constexpr Rows rows_of() {
+    if constexpr (C::kTwelve) return {Sched::Twelve, C::m, 2};
+    else return {C::kWave ? Sched::Wave : Sched::Matrix, C::n, (int)sizeof(typename C::io::elem_t)};
+}
 
 // Workgroup barrier for the LDS exchange.  __syncthreads() carries a release/acquire fence that
 // makes the wave wait for *all* its outstanding memory operations -- including the prefetches in
@@ -1141,13 +1149,16 @@ __device__ __forceinline__ void transform_back(float (&r)[C::E], float* lds, con
 // computed.  In a ragged last group a slot without a token re-reads the last token (clamped row), or reads
 // nothing where dx could be stored over that row meanwhile; its stores and its sums are left out.
 
-// Four sums of a partial row.  Every workgroup writes its row at the end of the kernel, and rows that lie
-// dirty in L2 are written back before the next kernel adds them up; written through L2 they are on their way at once and
-// wait in the Infinity Cache.  us per call under graph replay, before (plain stores, from 2048 to 4096 columns streamed) /
-// through: dalpha and dbeta of 8192 x 1024 12.3 / 11.4, backward of 2000 x 2048 11.4 / 10.8; over all widths the call for the
-// parameters alone gains 5 to 8 % from 1 to 16 MiB, the whole backward pass 1 to 3 %.
+// Four sums of a partial row; with which policy: sums_store (wht_route.h).
+template <class C, bool DX>
+constexpr int sums_policy() {
+    constexpr Store store = sums_store(rows_of<C>(), DX);
+    return store == Store::Plain ? 0 : store == Store::Stream ? kStreamPolicy : kThroughPolicy;
+}
+template <int POLICY>
 __device__ __forceinline__ void put_sums(rsrc_t row, unsigned column, const float4& q) {
-    store16_through(row, column * 4u, make_uint4(__float_as_uint(q.x), __float_as_uint(q.y), __float_as_uint(q.z), __float_as_uint(q.w)));
+    const u32x4 v = {__float_as_uint(q.x), __float_as_uint(q.y), __float_as_uint(q.z), __float_as_uint(q.w)};
+    __builtin_amdgcn_raw_buffer_store_b128(v, row, column * 4u, 0, POLICY);
 }
 
 __device__ __forceinline__ float4 add4(const float4& a, const float4& b) {
@@ -1436,7 +1447,7 @@ __global__ __launch_bounds__(C::BT) void forward_once_kernel(const typename C::i
 // slots in up to eight chains that are combined by a fixed tree (short chains: less rounding, LDS reads in
 // flight).  Four columns against one, and 16-byte stores against 4-byte ones, at 32768 x 1536: 63.4 against
 // 68.7 us for the call.
-template <class C>
+template <class C, bool DX>
 __device__ __forceinline__ void add_token_slots(rsrc_t out, const float* slots, unsigned tid, float scale) {
     constexpr int SLOTS = C::G / C::kPair, CHAINS = SLOTS < 8 ? SLOTS : 8;
     if constexpr (C::D >= 4 * C::BT || C::kTwelve) {
@@ -1456,7 +1467,7 @@ __device__ __forceinline__ void add_token_slots(rsrc_t out, const float* slots, 
             for (int half = CHAINS / 2; half >= 1; half /= 2)
 #pragma unroll
                 for (int c = 0; c < half; ++c) acc[c] = add4(acc[c], acc[c + half]);
-            put_sums(out, j, make_float4(acc[0].x * scale, acc[0].y * scale, acc[0].z * scale, acc[0].w * scale));
+            put_sums<sums_policy<C, DX>()>(out, j, make_float4(acc[0].x * scale, acc[0].y * scale, acc[0].z * scale, acc[0].w * scale));
         }
     } else {
         for (unsigned j = tid; j < (unsigned)C::D; j += C::BT) {
@@ -1470,7 +1481,7 @@ __device__ __forceinline__ void add_token_slots(rsrc_t out, const float* slots, 
             for (int half = CHAINS / 2; half >= 1; half /= 2)
 #pragma unroll
                 for (int c = 0; c < half; ++c) acc[c] += acc[c + half];
-            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc[0] * scale), out, j * 4u, 0, kThroughPolicy);
+            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc[0] * scale), out, j * 4u, 0, sums_policy<C, DX>());
         }
     }
 }
@@ -1502,11 +1513,11 @@ __device__ __forceinline__ void sums_to_slot(const float (&acc)[C::kSums], float
 }
 
 // A thread's sums (last layout) times `scale` straight to the row, where the workgroup has one token.
-template <class C>
+template <class C, bool DX>
 __device__ __forceinline__ void put_thread_sums(const float (&acc)[C::E], rsrc_t out, float scale, const ThreadMap<C>& tm) {
     static_for<0, C::E / 4>([&](auto i) {
         constexpr int I = decltype(i)::value * 4;
-        put_sums(out, vector_offset<C, C::P - 1, I / C::V>(tm, 0u) + I % C::V,
+        put_sums<sums_policy<C, DX>()>(out, vector_offset<C, C::P - 1, I / C::V>(tm, 0u) + I % C::V,
                           make_float4(acc[I] * scale, acc[I + 1] * scale, acc[I + 2] * scale, acc[I + 3] * scale));
     });
 }
@@ -1621,7 +1632,7 @@ __global__ __launch_bounds__(C::BT, C::kBwdWavesPerSimd) void backward_kernel(co
         __syncthreads();                          // the last exchange, or the first sums, have been read everywhere
         sums_to_slot<C>(which == 0 ? da : db, lds, tm);
         __syncthreads();
-        add_token_slots<C>(sums.row<C>(which), lds, threadIdx.x, which == 0 ? s : 1.0f);
+        add_token_slots<C, DX>(sums.row<C>(which), lds, threadIdx.x, which == 0 ? s : 1.0f);
     }
     }   // GRADS
 }
@@ -1853,13 +1864,13 @@ void backward_wave_kernel(const typename C::io::elem_t* dy, const typename C::io
             const rsrc_t row = sums.row<C>(which);
             if (which == 0) unsign_sums<C>(da, tm);
             if constexpr (C::G == 1) {                         // one token per workgroup: straight to the row
-                put_thread_sums<C>(which == 0 ? da : db, row, which == 0 ? s : 1.0f, tm);
+                put_thread_sums<C, DX>(which == 0 ? da : db, row, which == 0 ? s : 1.0f, tm);
                 continue;
             }
             __syncthreads();
             sums_to_slot<C>(which == 0 ? da : db, slots, tm);
             __syncthreads();
-            add_token_slots<C>(row, slots, threadIdx.x, which == 0 ? s : 1.0f);
+            add_token_slots<C, DX>(row, slots, threadIdx.x, which == 0 ? s : 1.0f);
         }
     }
 }
@@ -1871,7 +1882,7 @@ __device__ __forceinline__ void write_partial_row(const float (&acc)[C::E], floa
                                                   float scale, unsigned tid, const ThreadMap<C>& tm) {
     sums_to_slot<C>(acc, slots, tm);
     __syncthreads();
-    add_token_slots<C>(out, slots, tid, scale);
+    add_token_slots<C, true>(out, slots, tid, scale);
 }
 
 // backward (all three outputs) on three teams of waves per workgroup, 3 * C::BT threads, for the

@@ -163,6 +163,19 @@ constexpr bool dx_through(Rows rows, bool grads, int64_t bytes) {
     return (bytes >= 2 * MiB && bytes < (rows.bytes == 4 && row == 4096 ? 12 : 10) * MiB) || bytes >= again * MiB;
 }
 
+// How the rows of partial sums are written.  Every workgroup writes its row at the end of the kernel, and rows that lie
+// dirty in L2 are written back before the next kernel adds them up; written through L2 they are on their way at once and
+// wait in the Infinity Cache.  Short rows gain nothing by that, and where dx is streamed beside them they lose; 512 workgroups with rows of
+// 32 KiB (float32 4096 wide) are fastest when nothing is kept.  Parameters alone, plain or (2048 to 4096 columns) streamed / through, 1 to 16 MiB:
+// 128 columns -1 %, 256 -2..-5, 512 -5..-12, 1024 -4..-12, 1536 -5..-15, 2048 -4..-12, 4096 of bfloat16 0..-12, 6144 -7..-11, 16384 -2..-11; float32
+// 4096 0..-6 up to 8 MiB, +2..+3 from 12 on (20 MiB 20.1 / 22.2 us).  With dx, 32 to 128 columns +1..+4 %, 256 +0..+3, 512 and more -1..-9.
+enum class Store { Plain, Stream, Through };
+constexpr Store sums_store(Rows rows, bool dx) {
+    const int row = row_length(rows);
+    if (row <= 128 || (dx && row <= 256)) return Store::Plain;
+    return rows.bytes == 4 && row == 4096 && !dx ? Store::Stream : Store::Through;
+}
+
 // A call of few elements runs on backward_few_kernel: no partial rows and no second launch, which cost the stream 2.5 us and
 // the host 3.3, and a workgroup for every 64 columns where a launch of one workgroup has a single one.  Rows must have 8 slices of 64
 // columns (float32: 4).  Its workgroups read x, dy and alpha while others write dx, dalpha and dbeta: takes_few_backward.

@@ -17,6 +17,7 @@ def _lib():
     lib.wht_query_forward_steps.argtypes = [i32, i32, i32, i32, ctypes.POINTER(ctypes.c_double), ctypes.POINTER(i32)]
     lib.wht_query_forward.argtypes = [i32, i32, i32, i32, i64]
     lib.wht_query_dx_through.argtypes = [i32, i32, i32, i64]
+    lib.wht_query_sums_store.argtypes = [i32, i32, i32]
     lib.wht_query_few_elements.argtypes = [i32, i32]
     lib.wht_query_few_elements.restype = i64
     return lib
@@ -56,6 +57,11 @@ def persistent_from(dtype, d, out="y", butterfly=False):
 
 def dx_through(dtype, d, N, grads=True):
     return bool(_lib().wht_query_dx_through(_code(dtype), d, int(grads), N))
+
+
+def sums_store(dtype, d, dx=True):
+    """How the partial rows of dalpha and dbeta are written."""
+    return ("plain", "stream", "through")[_lib().wht_query_sums_store(_code(dtype), d, int(dx))]
 
 
 def few_elements(dtype, d):

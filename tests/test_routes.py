@@ -34,3 +34,10 @@ def test_every_size_has_a_way(dtype, d):
     ("bf16", 2048, 0.5, True, False), ("bf16", 2048, 0.5, False, False), ("bf16", 1024, 160, True, False), ("bf16", 6144, 20, True, True)])
 def test_dx_goes_where_it_was_faster(dtype, d, mib, grads, through):
     assert routes.dx_through(dtype, d, routes.tokens(dtype, d, mib), grads) is through
+
+
+@pytest.mark.parametrize("dtype,d,dx,store", [("bf16", 64, True, "plain"), ("f32", 128, False, "plain"), ("f32", 256, True, "plain"),
+                                              ("f32", 256, False, "through"), ("bf16", 512, True, "through"), ("f32", 4096, False, "stream"),
+                                              ("f32", 4096, True, "through"), ("bf16", 4096, False, "through"), ("bf16", 12288, True, "through")])
+def test_partial_rows_are_written_as_was_faster(dtype, d, dx, store):
+    assert routes.sums_store(dtype, d, dx) == store
