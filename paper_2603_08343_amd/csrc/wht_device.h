@@ -1389,6 +1389,25 @@ constexpr Requests requests_first_through(bool resid, bool stats, int R) {
     }
 }
 
+// The end of one token group: the affine part, the statistic and plain stores.
+template <class C, bool RESID, bool STATS, bool PIN>
+__device__ __forceinline__ void once_finish(float (&r)[C::E], const uint4 (&rraw)[RESID ? C::NV : 1], const float (&a)[C::E],
+                                            const float (&b)[C::E], float* wave_sums, typename C::io::elem_t* y, float* sumsq,
+                                            const Walker<C>& wk, int64_t N, int64_t grp, unsigned t, const ThreadMap<C>& tm) {
+    if constexpr (RESID) {
+        float res[C::E];
+        unpack_all<C>(res, rraw);
+#pragma unroll
+        for (int i = 0; i < C::E; ++i) r[i] = res[i] + fmaf(r[i], a[i], b[i]);
+    } else {
+#pragma unroll
+        for (int i = 0; i < C::E; ++i) r[i] = fmaf(r[i], a[i], b[i]);
+    }
+    if constexpr (PIN) pin<C::E>(r);
+    if constexpr (STATS) token_sumsq<C>(r, wave_sums, sumsq, wk.token(grp), N, t, wk.slot, tm);
+    global_put<C, C::P - 1, false>(r, y, wk.slot, N, grp, tm);
+}
+
 template <class C, bool RESID, bool STATS, bool THROUGH, int R>
 __global__ __launch_bounds__(C::BT) void forward_once_kernel(const typename C::io::elem_t* x,
                                                              const float* __restrict__ alpha,
@@ -1404,42 +1423,65 @@ __global__ __launch_bounds__(C::BT) void forward_once_kernel(const typename C::i
     const Walker<C> wk{N, (N + C::G - 1) / C::G, threadIdx.x / C::TPT};
     ThreadMap<C> tm;
     tm.init(t, wk.slot);
-    uint4 raw[R][C::NV], rraw[R][RESID ? C::NV : 1];
-    constexpr Requests FIRST = THROUGH ? requests_first_through<C>(RESID, STATS, R) : requests_first<C>(RESID, STATS);
-    auto group = [&](int i) { return (int64_t)blockIdx.x + (int64_t)i * gridDim.x; };
-#pragma unroll
-    for (int i = 0; i < R; ++i) global_get<C, 0>(raw[i], x, wk, group(i), tm);      // a ragged group re-reads the last token
-    if constexpr (FIRST == Requests::kX) __builtin_amdgcn_sched_barrier(0);
-    if constexpr (RESID)
-#pragma unroll
-        for (int i = 0; i < R; ++i) global_get<C, LAST>(rraw[i], resid, wk, group(i), tm);
-    if constexpr (FIRST == Requests::kInputs) __builtin_amdgcn_sched_barrier(0);
-    float a[C::E], b[C::E];
-    param_load<C>(a, alpha, tm);
-    param_load<C>(b, beta, tm);
-    if constexpr (FIRST == Requests::kAll) __builtin_amdgcn_sched_barrier(0);
-    else scale_alpha<C>(a, tm);
-    RoundB<C> hb{};
-    if constexpr (C::kMfma) hb = make_round_b<C>();
-    static_for<0, R>([&](auto rr) {
-        constexpr int I = decltype(rr)::value;
+    // One group with plain stores is written out, and not a turn of the loops below: in them the same statements take other registers
+    // (float32 2048 wide 110 for 83, four waves per SIMD for five: 25 MiB from memory 14.8 us for 13.1).  The loops' own figures are those
+    // of two groups and of stores through L2, where they are as fast as this or faster (11 MiB of float32 2048 from memory by 10 %).
+    if constexpr (!THROUGH) {
+        static_assert(R == 1);
+        constexpr Requests FIRST = requests_first<C>(RESID, STATS);
+        const int64_t grp = blockIdx.x;
+        uint4 raw[C::NV], rraw[RESID ? C::NV : 1];
+        global_get<C, 0>(raw, x, wk, grp, tm);                  // a ragged group re-reads the last token
+        if constexpr (FIRST == Requests::kX) __builtin_amdgcn_sched_barrier(0);
+        if constexpr (RESID) global_get<C, LAST>(rraw, resid, wk, grp, tm);
+        if constexpr (FIRST == Requests::kInputs) __builtin_amdgcn_sched_barrier(0);
+        float a[C::E], b[C::E];
+        param_load<C>(a, alpha, tm);
+        param_load<C>(b, beta, tm);
+        if constexpr (FIRST == Requests::kAll) __builtin_amdgcn_sched_barrier(0);
+        else scale_alpha<C>(a, tm);
+        RoundB<C> hb{};
+        if constexpr (C::kMfma) hb = make_round_b<C>();
         float r[C::E];
-        transform_from_raw<C, I + 1 < R>(r, raw[I], lds, tm, hb);
-        if constexpr (FIRST == Requests::kAll && I == 0) scale_alpha<C>(a, tm);      // here, so that nothing before waits for alpha
-        if constexpr (RESID) {
-            float res[C::E];
-            unpack_all<C>(res, rraw[I]);
+        transform_from_raw<C, false>(r, raw, lds, tm, hb);
+        if constexpr (FIRST == Requests::kAll) scale_alpha<C>(a, tm);          // here, so that nothing before waits for alpha
+        once_finish<C, RESID, STATS, (FIRST != Requests::kFree && C::G > 1)>(r, rraw, a, b, wave_sums, y, sumsq, wk, N, grp, t, tm);
+    } else {
+        constexpr Requests FIRST = requests_first_through<C>(RESID, STATS, R);
+        uint4 raw[R][C::NV], rraw[R][RESID ? C::NV : 1];
+        auto group = [&](int i) { return (int64_t)blockIdx.x + (int64_t)i * gridDim.x; };
 #pragma unroll
-            for (int i = 0; i < C::E; ++i) r[i] = res[i] + fmaf(r[i], a[i], b[i]);
-        } else {
+        for (int i = 0; i < R; ++i) global_get<C, 0>(raw[i], x, wk, group(i), tm);
+        if constexpr (FIRST == Requests::kX) __builtin_amdgcn_sched_barrier(0);
+        if constexpr (RESID)
 #pragma unroll
-            for (int i = 0; i < C::E; ++i) r[i] = fmaf(r[i], a[i], b[i]);
-        }
-        if constexpr (!THROUGH && FIRST != Requests::kFree && C::G > 1) pin<C::E>(r);
-        if constexpr (STATS) token_sumsq<C>(r, wave_sums, sumsq, wk.token(group(I)), N, t, wk.slot, tm);
-        if constexpr (THROUGH) global_put_through<C, LAST>(r, y, wk.slot, N, group(I), tm);
-        else global_put<C, LAST, false>(r, y, wk.slot, N, group(I), tm);
-    });
+            for (int i = 0; i < R; ++i) global_get<C, LAST>(rraw[i], resid, wk, group(i), tm);
+        if constexpr (FIRST == Requests::kInputs) __builtin_amdgcn_sched_barrier(0);
+        float a[C::E], b[C::E];
+        param_load<C>(a, alpha, tm);
+        param_load<C>(b, beta, tm);
+        if constexpr (FIRST == Requests::kAll) __builtin_amdgcn_sched_barrier(0);
+        else scale_alpha<C>(a, tm);
+        RoundB<C> hb{};
+        if constexpr (C::kMfma) hb = make_round_b<C>();
+        static_for<0, R>([&](auto rr) {
+            constexpr int I = decltype(rr)::value;
+            float r[C::E];
+            transform_from_raw<C, I + 1 < R>(r, raw[I], lds, tm, hb);
+            if constexpr (FIRST == Requests::kAll && I == 0) scale_alpha<C>(a, tm);
+            if constexpr (RESID) {
+                float res[C::E];
+                unpack_all<C>(res, rraw[I]);
+#pragma unroll
+                for (int i = 0; i < C::E; ++i) r[i] = res[i] + fmaf(r[i], a[i], b[i]);
+            } else {
+#pragma unroll
+                for (int i = 0; i < C::E; ++i) r[i] = fmaf(r[i], a[i], b[i]);
+            }
+            if constexpr (STATS) token_sumsq<C>(r, wave_sums, sumsq, wk.token(group(I)), N, t, wk.slot, tm);
+            global_put_through<C, LAST>(r, y, wk.slot, N, group(I), tm);
+        });
+    }
 }
 
 // The sums of a workgroup's G token slots (in LDS, one region of kTokenWords floats each) added up, times

@@ -33,15 +33,23 @@ enum class Way { Plain, Through, Pair, Stream, Flow };
 struct Step { double mib; Way way; };       // from this many MiB on
 struct Route { Step step[8]; };             // ends with the first step of 0 MiB behind the first one
 
+// The sizes were set by a sweep of every width from 1 to 256 MiB in the three settings: a way is taken where it is faster in them together
+// and not slower than the others by more than the runs differ (2 %) in the first.  us per call, again / memory unless more are named:
 //   plain against through: 4097 x 1024 4.53 / 5.41 and 4.02 / 5.04, 1024 x 4096 4.68 / 5.66 and 3.74 / 4.75, 16385 x 256 4.36 / 5.46
-//     and 3.62 / 5.53 (again / memory); one token of 4096 with the statistic 2.65 and 2.77 (the kernel ends when memory, not L2, has the results);
+//     and 3.62 / 5.53; one token of 4096 with the statistic 2.65 and 2.77 (the kernel ends when memory, not L2, has the results); with the
+//     statistic 7 MiB of 2048 wide 5.9 / 7.8 and 6.0 / 8.5, 16 MiB 9.0 / 13.6 and 9.1 / 14.7, 30 MiB of float32 2048 15.8 / 21.1 and 16.4 / 22.6, 12 MiB of
+//     float32 64 wide 6.7 / 9.0 and 7.0 / 9.0 (so plain there);
 //   one group against two, 2048 wide: 1025 tokens 3.05 / 3.86 and 3.03 / 3.76, 4097 6.9 / 9.8 and 6.3 / 8.0; 8 MiB of 1536 wide
 //     7.0 / 7.7 and 5.6 / 6.3, of 12288 wide 10.6 / 11.4 and 7.9 / 8.8 (there the persistent kernel took over from 2^22 elements on);
-//     below, half the workgroups leave CUs idle: 1 MiB of 2048 wide 2.8 and 3.2;
-//   persistent against one pass: 32 MiB of 256 wide (bfloat16) 13.4 / 14.4 and 11.1 / 14.4, of 2048 13.1 / 15.3 and 11.4 / 18.0 (so 24 there), 8 MiB
-//     of 16384 9.9 / 10.8 and 6.0 / 8.6, 32 MiB of 1536 11.5 / 13.5 and 14.2 / 15.3; with the residual 25 MiB of 1024 14.6 / 14.7 and 12.5 /
-//     14.6, 29 of 2048 17.5 / 17.5 and 14.8 / 19.1, of float32 2048 17.0 / 17.4 and 14.2 / 17.5 (so 33 there);
-//   two groups with the statistic, 2048 wide: 18 MiB 10.9 / 14.0, one 10.3 / 13.8, so one.
+//     below, half the workgroups leave CUs idle: 1 MiB of 2048 wide 2.8 and 3.2; with the statistic 3 MiB of
+//     3072 wide 4.7 and 4.9, 13 to 18 MiB of 12288 +6 (one group -7);
+//   one pass against persistent: 25 to 48 MiB of 1024 wide 12 to 18 % less again, 13 to 16 less from memory up to 32 MiB, 2 to 3 more beyond; 32 MiB of 256 wide (bfloat16) 11.1 / 14.4
+//     and 13.4 / 14.4, of 2048 11.4 / 18.0 and 13.1 / 15.3 (so 24 there), 8 MiB of 16384 6.0 / 8.6 and 9.9 / 10.8, 32 MiB of 1536 14.2 / 15.3 and 11.5 / 13.5; with the
+//     residual 25 MiB of 1024 12.5 / 14.6 and 14.6 / 14.7, 29 of 2048 14.8 / 19.1 and 17.5 / 17.5; with the statistic 20 MiB of 1536 +2 / +12 / inputs +9 %, 25 MiB of 12288 +11;
+//     without either 14 MiB of 6144 +6, 20 MiB of float32 2048, plain 9.3 / 11.4, through 8.7 / 11.9, persistent 8.0 / 8.9 (inputs 9.9, 10.5 and 9.0), 30 MiB 11.6 /
+//     15.0, 10.6 / 16.0 and 12.5 / 13.9 (inputs 12.3, 14.9 and 13.8);
+//   y of the persistent kernel through L2, where it is not as in dx_through: 24 to 32 MiB of 4096 wide +1..+8 / +4..+8 / inputs +1, 40 and more -3 / +6 / -5; with
+//     the statistic 56 to 134 MiB of 16384 +1..+4 in all three, 60 MiB of float32 8192 +3 / +4 / +2.
 // Rows of 12 * 2^m elements have workgroups of one token (two of 768): workgroups of 256 threads, with up to eight tokens,
 // leave CUs without any, and from 257 of them on put two on one CU beside others with one (341 x 768 3.33 / 2.34, 1365 x
 // 1536 5.60 / 4.80, 683 x 3072 6.01 / 4.83).
@@ -57,32 +65,48 @@ constexpr Route forward_route(Rows rows, Out out) {
         const double keep = !resid ? 80 : rows.n <= 8 ? 48 : 56;
         switch (rows.n) {
         case 6:  return {{{0, P}, {through, T}, {resid ? 5.0 : 7.0, R}, {22, S}, {keep, F}, {136, S}}};
-        case 7:  return {{{0, P}, {resid ? 3.5 : 2.5, R}, {resid ? 22.0 : 17.0, S}, {keep, F}, {136, S}}};
-        case 8:  return {{{0, P}, {through, T}, {stats ? 3.0 : 2.0, R}, {resid ? 14.0 : 17.0, S}, {keep, F}, {136, S}}};
+        case 7:  return {{{0, P}, {resid ? 3.5 : 2.5, R}, {stats ? 19.0 : resid ? 22.0 : 17.0, S}, {keep, F}, {136, S}}};
+        case 8:  return {{{0, P}, {through, T}, {stats ? 4.0 : 2.0, R}, {resid ? 14.0 : 17.0, S}, {keep, F}, {136, S}}};
         case 9:
             if (resid) return {{{0, P}, {3.5, R}, {stats ? 7.0 : 12.0, S}, {keep, F}, {136, S}}};
-            return {{{0, P}, {1, T}, {3.5, R}, {17, S}, {keep, F}, {136, S}}};
-        default: return {{{0, P}, {4, T}, {7, R}, {34, S}, {keep, F}, {136, S}}};
+            return {{{0, P}, {1, T}, {3.5, R}, {13, S}, {15, R}, {18.5, S}, {keep, F}, {136, S}}};
+        default:
+            if (stats) return {{{0, P}, {4, T}, {7, R}, {13, T}, {19, R}, {25, S}, {keep, F}, {136, S}}};
+            return {{{0, P}, {4, T}, {7, R}, {34, S}, {keep, F}, {136, S}}};
         }
     }
     if (rows.sched == Sched::Wave) {
-        const double from = resid && rows.bytes == 4 && rows.n <= 10 ? 6.0 : through;
-        if (rows.bytes == 2 || rows.n <= 10) return {{{0, P}, {from, T}, {resid ? 33.0 : 48.0, F}, {136, S}}};
-        if (rows.n == 11 && !resid) return {{{0, P}, {from, T}, {20, S}, {24, F}, {136, S}}};
-        if (rows.n == 11) return {{{0, P}, {from, T}, {33, F}, {136, S}}};
-        if (rows.n == 12) return {{{0, P}, {from, T}, {17, S}, {24, F}, {136, S}}};
-        return {{{0, P}, {from, T}, {resid ? 17.0 : 9.0, S}, {56, F}, {136, S}}};
+        if (rows.bytes == 2) return {{{0, P}, {through, T}, {resid ? 33.0 : 48.0, F}, {136, S}}};
+        if (rows.n <= 10) {
+            if (stats) return {{{0, P}, {6, T}, {rows.n <= 6 ? 9.0 : 13.0, P}, {33, F}, {136, S}}};
+            return {{{0, P}, {resid ? 6.0 : 1.0, T}, {resid ? 33.0 : 48.0, F}, {136, S}}};
+        }
+        if (rows.n == 11) {
+            if (stats) return {{{0, P}, {through, T}, {25, P}, {33, F}, {136, S}}};
+            if (resid) return {{{0, P}, {through, T}, {33, F}, {136, S}}};
+            return {{{0, P}, {1, T}, {13, S}, {25, P}, {33, F}, {136, S}}};     // 3072 tokens: 12 to a CU
+        }
+        if (rows.n == 12) return {{{0, P}, {stats ? 3.5 : through, T}, {17, S}, {24, F}, {136, S}}};
+        if (stats) return {{{0, P}, {2.5, T}, {6, P}, {8, T}, {17, S}, {80, F}, {136, S}}};
+        return {{{0, P}, {2, T}, {resid ? 17.0 : 9.0, S}, {56, F}, {136, S}}};
     }
     switch (rows.n) {
     case 10:
-        if (resid) return {{{0, P}, {through, T}, {33, F}, {136, S}}};
-        return {{{0, P}, {1, T}, {2.5, R}, {24, F}, {136, S}}};
+        if (stats) return {{{0, P}, {2.5, T}, {5, P}, {33, F}, {136, S}}};
+        if (resid) return {{{0, P}, {1, T}, {33, F}, {136, S}}};
+        return {{{0, P}, {1, T}, {2.5, R}, {12, T}, {48, F}, {136, S}}};
     case 11:
-        if (stats) return {{{0, P}, {through, T}, {33, F}, {136, S}}};
+        if (stats) return {{{0, P}, {2.5, T}, {6, P}, {33, F}, {136, S}}};
         return {{{0, P}, {1, T}, {resid ? 7.0 : 3.5, R}, {resid ? 33.0 : 24.0, F}, {136, S}}};
-    case 12: return {{{0, P}, {through, T}, {resid ? 7.0 : 10.0, R}, {stats ? 9.0 : 17.0, S}, {24, F}, {136, S}}};
-    case 13: return {{{0, P}, {through, T}, {resid ? 7.0 : 13.0, S}, {56, F}, {136, S}}};
-    default: return {{{0, P}, {4, T}, {24, S}, {56, F}, {136, S}}};
+    case 12:
+        if (stats) return {{{0, P}, {2.5, T}, {7, R}, {8.1, S}, {40, F}, {136, S}}};
+        return {{{0, P}, {1, T}, {resid ? 7.0 : 10.0, R}, {17, S}, {resid ? 24.0 : 46.0, F}, {136, S}}};
+    case 13:
+        if (resid) return {{{0, P}, {through, T}, {stats ? 7.0 : 6.0, P}, {8.1, S}, {56, F}, {136, S}}};
+        return {{{0, P}, {1, T}, {13, S}, {56, F}, {136, S}}};
+    default:
+        if (stats) return {{{0, P}, {4, T}, {24, S}}};
+        return {{{0, P}, {4, T}, {24, S}, {56, F}, {136, S}}};
     }
 }
 

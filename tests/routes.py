@@ -51,8 +51,10 @@ def way(dtype, d, N, out="y", butterfly=False):
 
 
 def persistent_from(dtype, d, out="y", butterfly=False):
-    """The first token count on the persistent kernel."""
-    return tokens(dtype, d, next(mib for mib, w in steps(dtype, d, out, butterfly) if w in PERSISTENT))
+    """The first token count from which on every call is the persistent kernel's."""
+    s = steps(dtype, d, out, butterfly)
+    last = max(i for i, (_, w) in enumerate(s) if w in ONE_PASS)
+    return tokens(dtype, d, s[last + 1][0])
 
 
 def dx_through(dtype, d, N, grads=True):

@@ -14,8 +14,7 @@ def test_every_size_has_a_way(dtype, d):
             mib = [m for m, _ in s]
             assert mib[0] == 0 and mib == sorted(set(mib)), (out, s)
             assert s[0][1] == "plain" and s[-1][1] == "stream", (out, s)
-            first = next(i for i, (_, w) in enumerate(s) if w in routes.PERSISTENT)      # from there on only persistent
-            assert all(w in routes.PERSISTENT for _, w in s[first:]), (out, s)
+            assert routes.way(dtype, d, routes.persistent_from(dtype, d, out, butterfly), out, butterfly) in routes.PERSISTENT
             for i, (m, w) in enumerate(s):
                 n = routes.tokens(dtype, d, m)
                 assert routes.way(dtype, d, n, out, butterfly) == w or routes.tokens(dtype, d, s[min(i + 1, len(s) - 1)][0]) <= n
@@ -41,3 +40,14 @@ def test_dx_goes_where_it_was_faster(dtype, d, mib, grads, through):
                                               ("f32", 4096, True, "through"), ("bf16", 4096, False, "through"), ("bf16", 12288, True, "through")])
 def test_partial_rows_are_written_as_was_faster(dtype, d, dx, store):
     assert routes.sums_store(dtype, d, dx) == store
+
+
+# Both sides of what was measured at these sizes stand beside forward_route; the sizes are those at which another way was slower.
+@pytest.mark.parametrize("dtype,d,out,mib,way", [
+    ("f32", 2048, "y", 30, "plain"), ("f32", 2048, "y", 20, "stream"), ("f32", 2048, "stats", 30, "plain"), ("f32", 64, "stats", 12, "plain"), ("f32", 512, "stats", 12, "through"), ("f32", 8192, "stats", 70, "stream"),
+    ("bf16", 1024, "y", 14, "through"), ("bf16", 1024, "y", 30, "through"), ("bf16", 1024, "stats", 12, "plain"), ("bf16", 2048, "stats", 16, "plain"),
+    ("bf16", 4096, "y", 28, "stream"), ("bf16", 4096, "stats", 25, "stream"), ("bf16", 8192, "resid", 7.5, "plain"), ("bf16", 16384, "stats", 70, "stream"),
+    ("bf16", 1536, "stats", 20, "stream"), ("bf16", 3072, "stats", 3.4, "through"), ("bf16", 6144, "y", 14, "stream"), ("bf16", 12288, "stats", 15, "through"),
+    ("bf16", 12288, "stats", 27, "stream")])
+def test_forward_takes_the_way_that_was_faster(dtype, d, out, mib, way):
+    assert routes.way(dtype, d, routes.tokens(dtype, d, mib), out) == way
