@@ -10,15 +10,15 @@ import torch
 
 import oracle
 import paper_2603_08343_amd as wht
+import routes
 from paper_2603_08343_amd import synth
 from parity import assert_grad_close, assert_io_close, nan_filled, to_gpu
 
 pytestmark = pytest.mark.gpu
 
-LIMITS = {("bf16", 512): 1 << 16, ("bf16", 1024): 1 << 16, ("bf16", 2048): 1 << 17, ("bf16", 4096): 1 << 17, ("bf16", 8192): 1 << 17,
-          ("bf16", 16384): 3 << 16, ("bf16", 768): 1 << 16, ("bf16", 1536): 3 << 15, ("bf16", 3072): 1 << 17, ("bf16", 6144): 1 << 17,
-          ("bf16", 12288): 3 << 16, ("f32", 256): 3 << 14, ("f32", 512): 3 << 14, ("f32", 1024): 1 << 16, ("f32", 2048): 3 << 15,
-          ("f32", 4096): 3 << 15, ("f32", 8192): 3 << 15}
+LIMITS = {(t, d): routes.few_elements(t, d) for t, widths in (("bf16", [1 << n for n in range(5, 15)] + [12 << m for m in range(6, 11)]),
+                                                              ("f32", [1 << n for n in range(5, 14)])) for d in widths
+          if routes.few_elements(t, d)}
 
 
 @pytest.mark.parametrize("dtype,d", list(LIMITS))

@@ -250,3 +250,24 @@ def test_module_and_threads():
 
     with concurrent.futures.ThreadPoolExecutor(4) as pool:
         assert all(pool.map(one, range(8)))
+
+
+def test_compiled_autograd_of_a_graph_built_eagerly():
+    """The backward pass under torch's compiled autograd: it breaks its graph at the node, as it does inside the Python Function,
+    and gets the gradients of the eager backward pass, bit for bit, on either path."""
+    compiled_autograd = pytest.importorskip("torch._dynamo.compiled_autograd")
+    x, _, dy, a, b = _tensors((7, 1024))
+
+    def grads(call, compiled):
+        leaves = [t.clone().requires_grad_(True) for t in (x, a, b)]
+        y = call(leaves[0] * 2, leaves[1], leaves[2], None)
+        if compiled:
+            with compiled_autograd._enable(torch.compile(backend="eager")):
+                y.backward(dy)
+        else:
+            y.backward(dy)
+        return [t.grad for t in leaves]
+
+    for name, call in (("node", wht_affine), ("Function", WhtAffineFunction.apply)):
+        print(f"[autograd] compiled autograd, {name}", flush=True)
+        assert all(torch.equal(p, q) for p, q in zip(grads(call, True), grads(call, False))), name

@@ -11,6 +11,7 @@ import torch
 
 import oracle
 import paper_2603_08343_amd as wht
+import routes
 from paper_2603_08343_amd import synth
 from parity import assert_grad_close, assert_io_close, nan_filled, to_gpu
 
@@ -26,7 +27,7 @@ MATRIX = [(768, "bf16", 8, 2), (1024, "bf16", 4, 1), (1536, "bf16", 4, 1), (2048
 
 def _counts(G, W, d):
     workgroups = 1024 if d <= 64 else 512
-    few = (19, 33) if d == 768 else ()                # the backward pass on workgroups of four tokens
+    few = (19, 33, 91, 509) if d == 768 else ()       # few elements; from 86 on workgroups of four tokens with partial rows
     return (G + W + 1, 2 * workgroups * G + W + 1, *few)
 
 
@@ -88,10 +89,13 @@ def test_infinite_input_in_the_last_row(d, dtype, G, W):
         assert_grad_close(db, rdb, f"dbeta d={d} N={N}")
 
 
-# the last count of each runs the persistent forward kernel
 @pytest.mark.parametrize("d,dtype,N", [(256, "f32", 19), (2048, "f32", 7), (8192, "f32", 5), (64, "bf16", 67), (512, "bf16", 11),
-                                       (1024, "f32", 8195), (4096, "f32", 1029), (512, "bf16", 32775)])
+                                       (1024, "f32", 8195), (4096, "f32", 1029), (512, "bf16", 32775),
+                                       (1024, "f32", "persistent"), (4096, "f32", "persistent"), (512, "bf16", "persistent")])
 def test_forward_rows_with_infinity_and_nan(d, dtype, N):
+    if N == "persistent":
+        N = max(routes.persistent_from(dtype, d, out) for out in ("y", "stats")) + 3
+        assert all(routes.way(dtype, d, N, out) in routes.PERSISTENT for out in ("y", "stats"))
     print(f"[nonfinite] forward d={d} {dtype} N={N}", flush=True)
     inp = synth.make_inputs(N, d, dtype, seed=7 * d + N)              # dy doubles as the residual stream
     x, resid = to_gpu(inp.x, dtype), to_gpu(inp.dy, dtype)

@@ -8,6 +8,7 @@ import torch
 
 import oracle
 import paper_2603_08343_amd as wht
+import routes
 from paper_2603_08343_amd import binding, synth
 from parity import assert_grad_close, assert_io_close, nan_filled, to_f64, to_gpu
 
@@ -212,15 +213,11 @@ def test_many_passes_per_workgroup():
 # the hand-over to the persistent kernel and that kernel just above the limit, where it has the fewest
 # passes per workgroup.
 
-def _few_token_limit(d, dtype="bf16", resid=False):
-    """Largest N that runs the one-pass kernel (the library's rule, restated)."""
-    if d % 3 == 0:
-        log_elems = 21
-    elif dtype == "bf16":
-        log_elems = 24 if d <= 2048 else 22
-    else:
-        log_elems = 23 if d <= 2048 else (22 if resid else 21)
-    return (1 << log_elems) // d
+def _few_token_limit(d, dtype="bf16", out="y"):
+    """Largest N in front of the sizes that are all the persistent kernel's."""
+    lim = routes.persistent_from(dtype, d, out) - 1
+    assert routes.way(dtype, d, lim, out) in routes.ONE_PASS and routes.way(dtype, d, lim + 37, out) in routes.PERSISTENT
+    return lim
 
 
 @pytest.mark.parametrize("N", [1, 16, 64, 256])
@@ -272,7 +269,8 @@ def test_forward_on_both_sides_of_the_few_token_limit(d, dtype):
                          [(d, "f32") for d in ALL_D[:-1]])
 def test_forward_residual_stats_above_the_few_token_limit(d, dtype):
     # the persistent kernel's residual and residual + statistic variants, ragged last group, every width class
-    N = _few_token_limit(d, dtype, resid=True) + 37
+    N = max(_few_token_limit(d, dtype, "resid"), _few_token_limit(d, dtype, "stats")) + 37
+    assert all(routes.way(dtype, d, N, out) in routes.PERSISTENT for out in ("resid", "stats"))
     _announce(f"forward+residual+stats above the few-token limit d={d} {dtype} N={N}")
     inp = synth.make_inputs(N, d, dtype, seed=d + 13)
     x, resid = to_gpu(inp.x, dtype), to_gpu(inp.dy, dtype)

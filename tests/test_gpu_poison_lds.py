@@ -7,10 +7,12 @@ failure.  Widths in this build: bf16 4096 and 8192 (matrix-core schedule, one ex
 backward), 16384 (two exchanges in the backward), 768 (two tokens to a wave, a missing one's zeros in the stage),
 3072, 6144, 12288 (single-team backward with an exchange), 512 (wave schedule, no
 exchange), and float32 512, 4096 and 8192 (wave schedule with a token on part of one wave, on two and
-on four).  Token counts: past the few-token limit of the residual forward (2^24, 2^23, 2^22 or 2^21
-elements), and more token groups than any backward kernel has workgroups, so that every kernel refills
-its stages and re-uses its exchange region; 300 tokens of 512 run the one-pass forward kernel, as do the smaller counts
-of 768, 3072 and 12288.  Odd counts of 768 leave half a wave without a token."""
+on four).  Token counts: at every width one behind the sizes from which the plain, the residual and the statistic's forward calls
+run the persistent kernel, and more token groups than any backward kernel has workgroups, so that those kernels refill
+their stages and re-use their exchange regions; one on which two token groups of a workgroup follow each other in the one-pass
+forward kernel, where a width has that; and small ones for the one-pass kernel, the backward kernel of few elements (300 tokens of
+512, 9 and 19 of 768 and the like) and the backward workgroups of four tokens of 768 (91 and 509).  Odd counts of 768 leave half a wave
+without a token."""
 import ctypes
 
 import numpy as np
@@ -19,6 +21,7 @@ import torch
 
 import oracle
 import paper_2603_08343_amd as wht
+import routes
 from paper_2603_08343_amd import synth
 from paper_2603_08343_amd.build import POISON_LIB
 from parity import assert_grad_close, assert_io_close, nan_filled, to_gpu
@@ -42,11 +45,36 @@ def poison_lib():
     return _lib
 
 
-@pytest.mark.parametrize("d,dtype,N", [(512, "bf16", 300), (512, "f32", 300), (4096, "bf16", 1031), (4096, "f32", 70),
-                                       (8192, "bf16", 700), (8192, "f32", 300), (16384, "bf16", 600), (6144, "bf16", 600),
-                                       (768, "bf16", 9), (768, "bf16", 19), (768, "bf16", 8197), (3072, "bf16", 301), (3072, "bf16", 701), (3072, "bf16", 1031),
-                                       (12288, "bf16", 259), (12288, "bf16", 701), (512, "bf16", 32805), (512, "f32", 16421), (4096, "f32", 1061), (8192, "f32", 1061)])
+WIDTHS = [(512, "bf16"), (4096, "bf16"), (8192, "bf16"), (16384, "bf16"), (768, "bf16"), (3072, "bf16"), (6144, "bf16"), (12288, "bf16"),
+          (512, "f32"), (4096, "f32"), (8192, "f32")]
+
+
+def _behind_the_persistent_sizes(d, dtype):
+    N = max(routes.persistent_from(dtype, d, out) for out in routes.OUTS) + 37
+    assert all(routes.way(dtype, d, N, out) in routes.PERSISTENT for out in routes.OUTS)
+    return N
+
+
+def _two_groups(d, dtype):
+    """A count at which two groups follow each other, the last one ragged, with the most outputs that any size has; or None."""
+    sizes = {routes.tokens(dtype, d, mib) + 5 for out in routes.OUTS for mib, w in routes.steps(dtype, d, out) if w == "pair"}
+    return max(sizes, key=lambda n: sum(routes.way(dtype, d, n, out) == "pair" for out in routes.OUTS), default=None)
+
+
+COUNTS = [(512, "bf16", 300), (512, "f32", 300), (4096, "bf16", 1031), (4096, "f32", 70), (8192, "bf16", 700), (8192, "f32", 300),
+          (16384, "bf16", 600), (6144, "bf16", 600), (768, "bf16", 9), (768, "bf16", 19), (768, "bf16", 91), (768, "bf16", 509),
+          (768, "bf16", 8197), (3072, "bf16", 301), (3072, "bf16", 701), (3072, "bf16", 1031), (12288, "bf16", 259), (12288, "bf16", 701),
+          (512, "bf16", 32805), (512, "f32", 16421), (4096, "f32", 1061), (8192, "f32", 1061)]
+
+
+@pytest.mark.parametrize("d,dtype,N", COUNTS + [(d, t, "persistent") for d, t in WIDTHS] +
+                         [(d, t, "two groups") for d, t in WIDTHS if _two_groups(d, t)])
 def test_poisoned_lds_build_matches_the_oracle(d, dtype, N):
+    if N == "persistent":
+        N = _behind_the_persistent_sizes(d, dtype)
+    elif N == "two groups":
+        N = _two_groups(d, dtype)
+        assert any(routes.way(dtype, d, N, out) == "pair" for out in routes.OUTS)
     print(f"[poison] d={d} {dtype} N={N}", flush=True)
     lib = poison_lib()
     inp = synth.make_inputs(N, d, dtype, seed=d + N)

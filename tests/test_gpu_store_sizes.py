@@ -6,16 +6,26 @@ import pytest
 import torch
 
 import paper_2603_08343_amd as wht
+import routes
 
 pytestmark = pytest.mark.gpu
 
 MIB = 1 << 20
 CASES = [(d, "bf16") for d in (32, 64, 128, 256, 512, 1024, 2048, 4096, 8192, 16384, 768, 1536, 3072, 6144, 12288)] + \
         [(d, "f32") for d in (32, 64, 256, 1024, 2048, 4096, 8192)]
-# MiB of x at which some width changes its forward route
-ONCE = (1, 2, 2.5, 3, 3.5, 4, 5, 6, 7, 9, 10, 12, 13, 14, 17, 20, 22, 24, 28, 33, 34, 48)
-# MiB at which the persistent forward and the backward kernels do
-PERSISTENT = (12, 24, 32, 56, 80, 128, 136)
+# MiB at which how dx is written, or how rows of 12 * 2^m are read, changes at some width
+BACKWARD = (1, 2, 4, 6, 8, 10, 12, 18, 24, 32, 36, 40, 46, 56, 80, 84, 136)
+
+
+def _once(d, dtype):
+    """MiB of x at which this width changes its forward route, up to where y goes through L2 or not on the persistent kernel."""
+    return sorted({mib for out in routes.OUTS for mib, _ in routes.steps(dtype, d, out) if 0 < mib <= 48})
+
+
+def _large(d, dtype):
+    """MiB at which the persistent forward kernel and the backward kernels change how they write, and what is read."""
+    steps = {mib for mib, w in routes.steps(dtype, d) if w in routes.PERSISTENT}
+    return sorted(steps | set(BACKWARD))
 
 
 def _inputs(N, d, dtype):
@@ -45,13 +55,14 @@ def _pieces(N, row):
 @pytest.mark.parametrize("d,dtype", CASES)
 def test_forward_rows_on_both_sides_of_every_size(d, dtype):
     row = d * (2 if dtype == "bf16" else 4)
-    top = max(_around(ONCE[-1], row, 16))
+    sizes = _once(d, dtype)
+    top = max(_around(sizes[-1], row, 16))
     x, r, a, b = _inputs(top, d, dtype)
     ref, ref_r, ref_s = torch.empty_like(x), torch.empty_like(x), torch.empty(top, device="cuda")
     for part in _pieces(top, row):
         ref[part] = wht.wht_affine_forward(x[part], a, b)
         ref_r[part], ref_s[part] = wht.wht_affine_forward_residual_stats(x[part], a, b, r[part])
-    for mib in ONCE:
+    for mib in sizes:
         for N in _around(mib, row, 16):
             print(f"[sizes] d={d} {dtype} N={N} ({N * row / MIB:.2f} MiB)", flush=True)
             for resid, stats, want in ((None, False, ref), (r, False, ref_r), (r, True, ref_r)):
@@ -74,13 +85,14 @@ def test_forward_rows_on_both_sides_of_every_size(d, dtype):
 @pytest.mark.parametrize("d,dtype", CASES)
 def test_large_rows_on_both_sides_of_every_size(d, dtype):
     row = d * (2 if dtype == "bf16" else 4)
-    top = max(_around(PERSISTENT[-1], row, 16))
+    sizes = _large(d, dtype)
+    top = max(_around(sizes[-1], row, 16))
     x, g, a, b = _inputs(top, d, dtype)
     ref, ref_dx = torch.empty_like(x), torch.empty_like(x)
     for part in _pieces(top, row):
         ref[part] = wht.wht_affine_forward(x[part], a, b)
         ref_dx[part] = wht.wht_affine_backward(g[part], None, a, want_param_grads=False)[0]
-    for mib in PERSISTENT:
+    for mib in sizes:
         for N in _around(mib, row, 16)[1::2]:
             print(f"[sizes] d={d} {dtype} N={N} ({N * row / MIB:.2f} MiB)", flush=True)
             buf, out = _guarded(x, N)

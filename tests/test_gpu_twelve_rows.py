@@ -8,14 +8,11 @@ import torch
 
 import oracle
 import paper_2603_08343_amd as wht
+import routes
 from paper_2603_08343_amd import synth
 from parity import assert_grad_close, assert_io_close, nan_filled, to_gpu
 
 pytestmark = pytest.mark.gpu
-
-# elements per call up to which the one-pass forward kernel runs
-FEW = {768: 3 << 20, 1536: 3 << 20, 3072: 3 << 20, 6144: 3 << 20, 12288: 1 << 23}
-
 
 @pytest.mark.parametrize("d,N", [(768, n) for n in (1, 2, 3, 4, 5, 8, 9, 23, 24, 25, 47, 4099)] +
                          [(1536, 5), (1536, 2053), (3072, 3), (3072, 1025), (6144, 2), (6144, 517), (12288, 2), (12288, 259)])
@@ -43,8 +40,10 @@ def test_every_output_at_partial_waves(d, N):
 
 @pytest.mark.parametrize("d", [768, 1536, 3072, 6144, 12288])
 def test_rows_are_the_same_on_both_sides_of_every_limit(d):
-    # few-token limits; 32 MiB (backward) and 128 MiB (forward, dx alone) a tensor
-    for N, back in ((FEW[d] // d, False), ((32 << 20) // (2 * d), True), ((128 << 20) // (2 * d), False)):
+    # where the persistent forward kernel takes over, and the MiB of a tensor at which a cache policy changes: backward 32, dx alone
+    # 46 and 84, forward 80 (with the residual 48 or 56), all 136
+    few = {routes.persistent_from("bf16", d, out) - 1 for out in routes.OUTS}
+    for N, back in [(n, False) for n in sorted(few)] + [((mib << 20) // (2 * d), mib == 32) for mib in (32, 46, 48, 56, 80, 84, 136)]:
         print(f"[twelve] d={d} N={N}", flush=True)
         gen = torch.Generator(device="cuda").manual_seed(N)
         x = torch.empty(N + 1, d, dtype=torch.bfloat16, device="cuda").normal_(generator=gen)

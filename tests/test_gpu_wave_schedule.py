@@ -9,6 +9,7 @@ import torch
 
 import oracle
 import paper_2603_08343_amd as wht
+import routes
 from paper_2603_08343_amd import synth
 from parity import assert_grad_close, assert_io_close, nan_filled, to_gpu
 
@@ -62,8 +63,8 @@ def test_backward_where_the_grid_changes(N):
 
 @pytest.mark.parametrize("d,dtype", F32 + BF16)
 def test_forward_kernels_agree_across_the_size_limit(d, dtype):
-    limit = 1 << (24 if dtype == "bf16" else (23 if d <= 2048 else 21))
-    lim = limit // d
+    lim = routes.persistent_from(dtype, d) - 1
+    assert routes.way(dtype, d, lim) in routes.ONE_PASS and routes.way(dtype, d, lim + 37) in routes.PERSISTENT
     N = lim + 37
     print(f"[wave] forward limit d={d} {dtype} N={lim} and N={N}", flush=True)
     gen = torch.Generator(device="cuda").manual_seed(d)
