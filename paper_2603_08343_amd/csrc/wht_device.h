@@ -1384,7 +1384,7 @@ constexpr Requests requests_first_through(bool resid, bool stats, int R) {
         if (C::n == 11 && !resid) return Requests::kAll;
         return C::n >= 11 && resid ? Requests::kInputs : Requests::kX;
     } else {
-        if (C::n == 10 && (R == 1 || !resid)) return Requests::kAll;
+        if (C::n == 10) return Requests::kAll;
         return R == 1 && resid ? Requests::kInputs : Requests::kX;
     }
 }

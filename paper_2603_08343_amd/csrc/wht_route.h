@@ -92,7 +92,7 @@ constexpr Route forward_route(Rows rows, Out out) {
     }
     switch (rows.n) {
     case 10:
-        if (stats) return {{{0, P}, {2.5, T}, {5, P}, {33, F}, {136, S}}};
+        if (stats) return {{{0, P}, {2.5, T}, {5.8, P}, {33, F}, {136, S}}};
         if (resid) return {{{0, P}, {1, T}, {33, F}, {136, S}}};
         return {{{0, P}, {1, T}, {2.5, R}, {12, T}, {48, F}, {136, S}}};
     case 11:
@@ -156,10 +156,13 @@ constexpr bool backward_keeps(bool grads, int64_t bytes) { return bytes <= (int6
 // the three together gain, or lose nothing):
 //   backward: 32 to 256 wide rows 1 to 24 MiB +0..+7 % / +1..+7 / -1..+7, 36 to 136 -7..+1 / +0..+3 / -7..+1; float32 512 wide 2 to 8 MiB -6..-4 / -3..+2 / -3..+2, 8 to
 //     18 +2..+3 / 0..+1 / +1..+3; other rows below 1 MiB +2 / +6 / +3 (4096 wide and more -2 / +2 / 0), from 1 or 2 MiB on -14..+1 / -6..+2 / -8..+1;
-//   dx alone: below 2 MiB -3 / +7 / +4, 2 to 4 -5 / +5 / +2; rows of up to 128 bytes 4 to 8 MiB -20..-6 / +11..+18 / +8..+14, 12 on -12..-1 / +1 / -12..-4; 128 to 512 wide 4 to 8 -10 / +4 / +1, 8 to 12
-//     -18..+4 / +11 / +13, 12 to 16 +6..+9 / +7..+9 / +8..+12, 24 on -11..+2 / +0..+4 / -12..-2; 1024 wide 5 MiB -7 / +19 / +13, 6 on -13..-3 / 0..+6 / -13..+3;
-//     2048 to 8192 wide 4 to 10 MiB -9..-6 / +2 / 0, 10 to 24 -3..+2 / +1..+7 / -1..+7; bfloat16 4096 and 8192 wide 34 MiB +5..+7 / +7..+9 / +1..+2, 40 on -11..-1 /
-//     0..+6 / -10..-3; float32 2048 and 8192 wide 24 to 40 MiB +1..+11 / +3..+11 / 0..+10; 16384 wide -6..+4 / -1..+4 / -2..+2, never together ahead;
+//   dx alone: below 2 MiB -3 / +7 / +4; rows of up to 128 bytes 3 and 4 MiB -8 / +5 / +2, 5 to 7 -10..-5 / +14..+20 / +10..+14, 8 and 9 -34..-20 / +2..+13 / -1..+13, 10 and
+//     11 +1 / +4 / 0, 13 on -12..-1 / +1 / -12..-4; 128 to 512 wide bfloat16 3 to 8 MiB -13..-4 / +5 / +2, 9 -20 / +14 / +14, 10
+//     and 11 -5..+18 / +8..+16 / +6..+19, float32 (64 to 512 wide) 2 to 8
+//     -4 / +6 / +4, 9 and 10 -25 / +1..+10 / +3..+14, 10.6 and 11 +3 / +5 / +11, both 12 to 16 +6..+9 / +7..+9 / +8..+12, 24 on -11..+2 / +0..+4 / -12..-2; 1024 wide
+//     bfloat16 2 to 4 MiB -7 / +3 / +1, 5 and 6 -7 / +20 / +13, 7 on -28..-3 / 0..+7 / -13..+5, float32 -8 / +12 / +14 at 9; 2048 to 8192 wide 3 to 10 MiB -13..-3 / +2..+6 / 0..+5,
+//     11 to 24 -3..+6 / +1..+8 / -1..+7; bfloat16 4096 and 8192 wide 34 MiB +5..+7 / +7..+9 / +1..+2, 40 on -11..-1 / 0..+6 / -10..-3; float32 2048 and 8192 wide 24 to
+//     40 MiB +1..+11 / +3..+11 / 0..+10; 16384 wide -6..+4 / -1..+4 / -2..+2, never together ahead;
 //   above 136 MiB 0..+2 / 0..+4 / -8..-18 (dx alone, 150 to 256 MiB), a step of 16384 x 4096 float32 231 / 236 us, backward of 32768 x 8192 276 / 281: streamed.
 // Rows of 12 * 2^m: with the sums, where x and dy are kept always; above, up to 136 MiB but for 56 to 80 MiB, where x, y, dy
 // and dx of a step just fill the Infinity Cache, and for m = 10: streamed / through, us, backward and a step: 48 MiB of 768 32.6 / 31.4 and
@@ -179,12 +182,15 @@ constexpr bool dx_through(Rows rows, bool grads, int64_t bytes) {
         if (rows.bytes == 4 && row == 512) return bytes >= 2 * MiB && (bytes < 8 * MiB || bytes >= 18 * MiB);
         return row >= 4096 || bytes >= (rows.bytes == 4 && row == 1024 ? 2 : 1) * MiB;
     }
+    const double mib = (double)bytes / MiB;
     if (row == 16384) return false;
-    if (row * rows.bytes <= 128) return bytes >= 12 * MiB;
-    if (rows.sched == Sched::Matrix && row == 1024) return bytes >= 2 * MiB && (bytes < 4 * MiB || bytes >= 6 * MiB);
-    if (row <= (rows.bytes == 4 ? 1024 : 512)) return bytes >= 2 * MiB && (bytes < 8 * MiB || bytes >= 24 * MiB);
-    const int64_t again = rows.bytes == 4 ? (row == 2048 ? 56 : row == 4096 ? 24 : 46) : row == 2048 ? 24 : 40;
-    return (bytes >= 2 * MiB && bytes < (rows.bytes == 4 && row == 4096 ? 12 : 10) * MiB) || bytes >= again * MiB;
+    if (row * rows.bytes <= 128) return (mib >= 2.5 && mib < 4.2) || mib >= 7.9;
+    if (rows.sched == Sched::Matrix && row == 1024) return (mib >= 2 && mib < 4.2) || mib >= 6.3;
+    if (rows.bytes == 4 && row <= 1024) return (row < 1024 && mib >= 8.3 && mib < 10.3) || mib >= 24;
+    if (row <= 512) return (mib >= 2.5 && mib < 9.5) || mib >= 24;
+    const double again = rows.bytes == 4 ? (row == 2048 ? 56 : row == 4096 ? 24 : 46) : row == 2048 ? 24 : 40;
+    const bool wide_f32 = rows.bytes == 4 && row != 4096;
+    return (mib >= (wide_f32 ? 4 : 2.5) && mib < (rows.bytes == 4 && row == 4096 ? 12 : 10.4)) || mib >= again;
 }
 
 // How the rows of partial sums are written.  Every workgroup writes its row at the end of the kernel, and rows that lie

@@ -14,7 +14,7 @@ MIB = 1 << 20
 CASES = [(d, "bf16") for d in (32, 64, 128, 256, 512, 1024, 2048, 4096, 8192, 16384, 768, 1536, 3072, 6144, 12288)] + \
         [(d, "f32") for d in (32, 64, 256, 1024, 2048, 4096, 8192)]
 # MiB at which how dx is written, or how rows of 12 * 2^m are read, changes at some width
-BACKWARD = (1, 2, 4, 6, 8, 10, 12, 18, 24, 32, 36, 40, 46, 56, 80, 84, 136)
+BACKWARD = (1, 2, 2.5, 4, 4.2, 6.3, 7.9, 8, 8.3, 9.5, 10.3, 10.4, 12, 18, 24, 32, 36, 40, 46, 56, 80, 84, 136)
 
 
 def _once(d, dtype):

@@ -26,7 +26,7 @@ def test_every_size_has_a_way(dtype, d):
 @pytest.mark.parametrize("dtype,d,mib,grads,through", [
     ("f32", 8192, 30, False, False), ("f32", 8192, 60, False, True), ("f32", 2048, 36, False, False), ("bf16", 512, 11, False, False),
     ("bf16", 4096, 34, False, False), ("bf16", 1024, 36, False, True), ("bf16", 1024, 5, False, False), ("f32", 4096, 30, False, True),
-    ("bf16", 16384, 100, False, False), ("bf16", 64, 6, False, False), ("bf16", 64, 15, False, True), ("bf16", 2048, 1.5, False, False),
+    ("bf16", 16384, 100, False, False), ("bf16", 64, 6, False, False), ("bf16", 64, 9, False, True), ("bf16", 2048, 1.5, False, False), ("f32", 128, 9, False, True), ("f32", 1024, 9, False, False),
     ("bf16", 768, 40, False, True), ("bf16", 768, 75, False, False), ("bf16", 12288, 75, False, False), ("bf16", 3072, 100, False, True),
     ("f32", 256, 10, True, False), ("bf16", 64, 7, True, False), ("bf16", 32, 30, True, False), ("bf16", 128, 100, True, True),
     ("f32", 512, 12, True, False), ("f32", 512, 20, True, True), ("f32", 1024, 1.5, True, False), ("bf16", 4096, 5, True, True),
