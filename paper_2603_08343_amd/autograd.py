@@ -51,7 +51,8 @@ class WhtAffineFunction(torch.autograd.Function):
 def wht_affine(x, alpha, beta, resid=None):
     """Differentiable y = [resid +] alpha (.) (H x) + beta; x: [..., d] bfloat16|float32 on the GPU.
     Plain calls go to the extension module's node of torch's C++ autograd (csrc/torch_marshal.cpp), which does what
-    WhtAffineFunction does; the others, and everything under a compiler's trace, to WhtAffineFunction."""
+    WhtAffineFunction does; the others, and everything under a compiler's trace, to WhtAffineFunction.  The node's grad_fn has
+    a name, next_functions and hooks; saved_tensors and needs_input_grad are the Python Function's alone (WhtAffineFunction.apply)."""
     if not torch.compiler.is_compiling():
         y = binding._native().layer(x, alpha, beta, resid)
         if y is not None:
