@@ -1,5 +1,5 @@
 // Which kernel a call runs on, by the schedule and width of its rows, what it asks for and its size -- never by what is in
-// the tensors or where they lie.  No GPU call and no HIP header: wht_affine.hip takes its launches from here, and
+// the tensors or where they lie (but for outputs that lie over inputs: takes_few_backward).  No GPU call and no HIP header: wht_affine.hip takes its launches from here, and
 // route_query.cpp, which a host compiler builds, tells the tests which kernel a size reaches.
 //
 // Sizes are bytes of one [N, d] tensor.  The figures beside the rules are us per call under graph replay, in three settings:
